@@ -9,47 +9,71 @@ namespace {
 // ---------------------------------------------------------------------------
 // Why: with one row (or one row per team) on a wave at a time, every row costs
 // a fixed number of instructions and memory round trips, and a wave whose rows
-// differ in length idles the lanes of the short ones.  Short rows -- sampled
-// rows with W of 16..64, the eighth-of-a-row pieces of the column-partitioned
-// product, the rows of a column slice -- then run at the instruction rate, not
-// at the memory rate.  Here a wave takes NR = E or 2E consecutive rows (E =
-// 64 / G edge slots), lays their kept entries end to end (each row padded to a
-// multiple of E with zero-valued repeats of its first entry), stages that run
-// tile by tile into LDS (stage 1 of Algorithm 1; the sample index of a slot is
-// evaluated from its definition, Equation 2, since consecutive slots of a lane
-// no longer belong to one row) and lets the E edge slots walk it E entries per
-// step (stage 2).  Because of the padding a step never straddles two rows, so
-// "a new row starts here" is a wave-uniform bit per step (scalar test): at such
-// a step the slots' partial sums for the finished row are added across the wave
-// with lane swaps (LDS float atomics run about a lane per cycle here: far too
-// slow), written to that row's place in LDS, and the slots start over.  The
-// rows' sums leave LDS once, at the end: E rows per pass, coalesced (plain
-// stores, or load-add-store in the later phases of the column-partitioned
-// product).
+// differ in length idles the lanes of the short ones.  Here a workgroup takes up
+// to 64 consecutive rows (or the pieces of one column range of those rows), lays
+// their kept entries end to end -- each row padded to a multiple of a block of
+// max(8, E) entries, E = 64 / G edge slots, with zero-valued repeats of its last
+// one -- and stages that run into LDS in bursts of 1536 or 2048 entries (stage 1
+// of Algorithm 1): a table of the burst's blocks first (a binary search per block
+// for its row), then every entry of the burst requested before the first is
+// awaited.  Stage 2: each of the four waves multiplies an equal share of the
+// run, whatever rows it holds, E entries per step, 8 steps' rows of X in flight
+// together.  Because of the padding a step never straddles two rows, so "a row
+// ends here" is a wave-uniform bit (scalar test); there the slots' sums are added
+// across the wave with lane swaps and written to the row's place in LDS.  A row
+// that crosses into the next wave's share (or the next burst) leaves the second
+// part in that wave's own place; the parts are added in a fixed order, so the
+// sums are bit-reproducible.  Row sums leave LDS once, coalesced (plain stores, or
+// load-add-store in the later phases of the column-partitioned product).
+//
+// What bounds it, measured on this chip with gathers of 128-byte rows: a compute
+// unit takes 31-33 TB/s (all units together) of rows of X as long as every one hits
+// its L2, but its vector cache returns data in order, so one line that misses holds
+// back the hits behind it: a stream of CSR entries of 1/16 of the gathered bytes
+// brings the rate down to 19 TB/s when every wave reads its part as it goes, 22 TB/s
+// when a wave reads 512 entries at a time, and 27 TB/s when a workgroup reads 2048 at a
+// time (and 10 % of gathers that miss bring it down to 17 TB/s).  Hence the bursts,
+// and hence no wave-private prefetch.  Dense social-like graph (233 k rows, 113 M
+// entries, F = 64), exact product in column ranges: 2.59 -> 2.11 ms against the
+// former form (256 entries per wave, requested one tile ahead, a row search per
+// entry); co-purchase-like graph (2.45 M rows, 120 M entries, F = 128): exact product
+// 5.93 -> 5.86 ms, FastRand W = 64 2.84 -> 2.76 ms (bound by L2 misses, 7 TB/s).
+// Tried and slower: entries copied into LDS by the load itself (dword copies: 2.9
+// ms), a pass of 64 entries per row streamed two passes ahead (2.6 ms), 16 column
+// ranges (3.2 ms), two batches of gathers in flight per wave (spills or 12 waves).
 // ---------------------------------------------------------------------------
-constexpr int kFlatTile = 256;                        // staged entries per tile
+constexpr int kFlatMaxRows = 64;                      // rows of a workgroup's run at most: one per lane
+constexpr int kFlatBlockMin = 8;                      // smallest unit a row is padded to
 constexpr int kFlatLongRow = 8192;                    // kept entries above which a row goes to the long-row part (at most)
-constexpr int kFlatPartRps = 2;                       // rows per edge slot in the column-partitioned product
-constexpr int kFlatAccFloats = 512;                   // NR rows x 4G columns at most
-constexpr int kFlatMaxRows = 32;                      // NR at most
+constexpr int kFlatLongSeg = 2048;                    // slots per segment of such a row
 
-struct FlatLds {                                      // one per wave
-    uint2 tile[kFlatTile];                            // (row key, value)
-    float rowacc[kFlatAccFloats];                     // [NR][4G] sums of the chunk's non-empty rows, in order
-    int32_t start[kFlatMaxRows + 1];                  // padded start of each row in the run
-    int32_t kept[kFlatMaxRows];                       // entries the row really keeps
-    int32_t src[kFlatMaxRows];                        // CSR position of the row's (piece's) entry 0, < 2^31
-    uint32_t len[kFlatMaxRows];                       // FastRand on a longer row: its length n; else 0
-    uint32_t mul[kFlatMaxRows];                       //   multiplier P
-    uint32_t rot[kFlatMaxRows];                       //   rotation off
+// Rows of a run with G column lanes: `rps` rows per edge slot of each wave.
+constexpr int flat_rows(int G, int rps) { return rps * 256 / G < kFlatMaxRows ? rps * 256 / G : kFlatMaxRows; }
+
+template <int G_, int RPS>
+struct FlatLds {
+    static constexpr int G = G_;                      // lanes across the feature columns
+    static constexpr int FB = 4 * G;                  // feature columns per block
+    static constexpr int ROWS = flat_rows(G, RPS);    // rows of the run
+    static constexpr int CAP = RPS == 1 ? 1536 : 2048;   // entries staged in one burst: about the run's mean, six or four workgroups per compute unit
+    int32_t col[CAP];                            // staged column ids, in the order the slots read them
+    float val[CAP];
+    float rowsum[ROWS * FB];                     // [row][FB]
+    float head[kWavesPerBlock * FB];                  // per wave: partial sum of a row that began in an earlier wave's share
+    int32_t head_row[kWavesPerBlock];
+    uint2 block[CAP / kFlatBlockMin];                      // staged block: CSR position (or slot) of its first entry; entries | row << 8
+    uint64_t ends[CAP / kFlatBlockMin / kWaveSize];        // bit b: staged block b is the last of its row
+    int32_t first[kFlatMaxRows];                         // the rows: first block of the run,
+    int32_t src[kFlatMaxRows];                           // CSR position of the row's (piece's) entry 0, < 2^31
+    int32_t kept[kFlatMaxRows];                          // entries the row really keeps
+    uint32_t len[kFlatMaxRows];                          // FastRand on a longer row: its length n; else 0
+    uint32_t mul[kFlatMaxRows];                          //   multiplier P
+    uint32_t rot[kFlatMaxRows];                          //   rotation off
 };
 
-// What the chunk's rows are: whole sampled rows (forward kernel) or the pieces
-// of one column range (a phase of the column-partitioned product).
-struct FlatJob {
-    int part;          // column range, or -1: whole rows
-    bool accumulate;   // add to Y instead of overwriting it (phases after the first)
-};
+// What a lane reads when it has no entry to stage (an absent entry's value), and
+// the value of every entry of an unweighted graph.
+__device__ const float kFlatConst[2] = {0.0f, 1.0f};
 
 // Lanes whose bit BIT (4 or 5) is clear get a + a', the others b + b', where a',
 // b' are the values of the lane that differs in that bit alone: the row and
@@ -80,278 +104,361 @@ __device__ __forceinline__ float all_add(float v)
     return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kRowRor, 0xf, 0xf, true));
 }
 
-// RPS: rows per edge slot on a wave (NR = RPS * E rows per wave).  Fewer rows per
-// wave cost more set-up per row and even the waves out: 1 for the exact product
-// (its rows differ most in length), 2 for sampled rows.
-template <int G, bool ALIGNED, bool WIDE, bool STRIDED, int RPS>
-__device__ __forceinline__ void flat_block(const Args& a, uint32_t vb, const FlatJob job, FlatLds* lds_all)
+
+// x mod n for n < 2^31 and any x < 2^24: quotient from a float reciprocal (off by
+// one at most: x and the quotient's error bound stay below 2^24).
+__device__ __forceinline__ uint32_t small_mod(uint32_t x, uint32_t n)
 {
+    const uint32_t q = (uint32_t)((float)x * __builtin_amdgcn_rcpf((float)n));
+    int32_t r = (int32_t)(x - q * n);
+    if (r < 0) r += (int32_t)n;
+    if (r >= (int32_t)n) r -= (int32_t)n;
+    return (uint32_t)r;
+}
+
+__device__ __forceinline__ int32_t lane_of(int32_t v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
+
+
+// One row (piece) per lane: the workgroup's run, held alike by all of its waves.
+struct FlatRow {
+    int32_t src;               // CSR position of entry 0 of the row (piece)
+    int32_t k;                 // entries to multiply, 0 for lanes past the run
+    uint32_t len, mul, rot;    // FastRand on a longer row: slot i reads entry (rot + i * mul) mod len; len == 0: entry i
+};
+
+// Multiplies the workgroup's run: row j's sum goes to s.rowsum[j][FB] (rows
+// without entries: zeros).  Ends with a barrier.
+template <bool ALIGNED, bool WIDE, bool STRIDED, class Lds>
+__device__ __forceinline__ void flat_run(const Args& a, const FlatRow& row, int colblk, Lds& s)
+{
+    constexpr int G = Lds::G;
     constexpr int LOG_G = ilog2(G);
     constexpr int LOG_E = 6 - LOG_G;
     constexpr int E = kWaveSize / G;                  // edge slots
-    constexpr int NR = RPS * E;                       // rows per wave
     constexpr int FB = 4 * G;                         // feature columns per block
-    constexpr int U = E <= 8 ? 8 : kWaveSize / E;     // steps per batch = loads in flight per lane; U*E <= 64
-    static_assert(NR * FB <= kFlatAccFloats && NR <= kFlatMaxRows, "row accumulators fit their LDS array");
-    static_assert(U * E <= kWaveSize && kWaveSize % (U * E) == 0, "a batch lies inside 64 slots");
+    constexpr int BE = E < kFlatBlockMin ? kFlatBlockMin : E;   // entries per block
+    constexpr int LOG_BE = ilog2(BE);
+    constexpr int CAPB = Lds::CAP / BE;               // blocks per burst
+    constexpr int BPC = kWaveSize / BE;               // blocks per chunk of 64 entries
+    constexpr int U = 8;                              // steps per batch = gathers in flight per lane
+    constexpr int BPB = U * E / BE;                   // blocks per batch (1, 2, 4 or 8)
     using P = Pack<4, ALIGNED>;
-    using K = RowKey<ALIGNED, WIDE>;
 
     const int lane = threadIdx.x & (kWaveSize - 1);
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int e = lane >> LOG_G;
     const int l = lane & (G - 1);
-    FlatLds& s = lds_all[wave];
-
     LaneCols<G, 1, 4, ALIGNED> cols;
-    cols.init(blockIdx.y * FB, l, a.F);
+    cols.init(colblk, l, a.F);
 
-    // ---- the chunk's rows: lane j describes row r0 + j -------------------------
-    const int64_t r0 = ((int64_t)vb * kWavesPerBlock + wave) * NR;
+    // ---- the run in blocks --------------------------------------------------------
+    const int32_t nb = (row.k + BE - 1) >> LOG_BE;
+    int32_t incl = nb;                                // inclusive scan over the 64 rows
+#pragma unroll
+    for (int d = 1; d < kWaveSize; d <<= 1) {
+        const int32_t up = __shfl_up(incl, d, kWaveSize);
+        if (lane >= d) incl += up;
+    }
+    const int32_t total = lane_of(incl, kWaveSize - 1);
+    const uint64_t nonempty = __ballot(row.k > 0);
+    if (wave == 0) {
+        s.first[lane] = incl - nb;
+        s.src[lane] = row.src;
+        s.kept[lane] = row.k;
+        if constexpr (STRIDED) {
+            s.len[lane] = row.len;
+            s.mul[lane] = row.mul;
+            s.rot[lane] = row.rot;
+        }
+    }
+    for (int i = threadIdx.x * 4; i < Lds::ROWS * FB; i += kBlockThreads * 4)
+        *reinterpret_cast<float4*>(&s.rowsum[i]) = make_float4(0.f, 0.f, 0.f, 0.f);
+    __syncthreads();
+
+    // chunk position -> entry of the chunk, in the order the slots read: a slot's four
+    // consecutive steps lie side by side (one 128-bit LDS read)
+    const int c_entry = (((lane >> (LOG_E + 2)) * 4 + (lane & 3)) << LOG_E) + ((lane & (4 * E - 1)) >> 2);
+    const int c_block = c_entry >> LOG_BE;
+    const int c_in = c_entry & (BE - 1);
+    const int32_t* get_col = s.col + e * 4;
+    const float* get_val = s.val + e * 4;
+    const uint32_t stride = (uint32_t)a.ldx * 4u;
+    const uint32_t load_at = (uint32_t)cols.off[0] * 4u;
+    const char* X = reinterpret_cast<const char*>(a.X);
+
+    struct Batch { P x[U]; };
+    auto gather = [&](int s0, Batch& bt) {
+#pragma unroll
+        for (int q = 0; q < U / 4; ++q) {
+            const int4 col = *reinterpret_cast<const int4*>(get_col + (s0 + 4 * q) * E);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t c = (uint32_t)(&col.x)[u];
+                if constexpr (WIDE)
+                    bt.x[4 * q + u].load(reinterpret_cast<const float*>(X + (uint64_t)c * stride + load_at));
+                else
+                    bt.x[4 * q + u].load(reinterpret_cast<const float*>(X + (uint32_t)(__umul24(c, stride) + load_at)));
+            }
+        }
+    };
+
+    for (int b0 = 0; b0 < total; b0 += CAPB) {
+        const int nblk = min(total - b0, CAPB);
+        const int batches = (nblk + BPB - 1) / BPB;
+        // ---- the burst's blocks: which row, where, how many entries --------------------
+        const int chunks = (batches * U * E + kWaveSize - 1) / kWaveSize;
+#pragma unroll 1
+        for (int i = threadIdx.x; i < CAPB; i += kBlockThreads) {
+            const int b = b0 + i;
+            const int bc = min(b, total - 1);
+            int r = 0;                                        // last row that starts at or before block bc and is not empty
+#pragma unroll
+            for (int d = kFlatMaxRows / 2; d >= 1; d >>= 1) r += s.first[r + d] <= bc ? d : 0;
+            const int32_t i0 = (bc - s.first[r]) << LOG_BE;
+            const int32_t left = s.kept[r] - i0;
+            bool strided = false;
+            if constexpr (STRIDED) strided = s.len[r] != 0;
+            s.block[i] = make_uint2((uint32_t)(strided ? i0 : s.src[r] + i0),
+                                    (uint32_t)(b < total ? min(left, BE) : 0) | ((uint32_t)r << 8));
+            const uint64_t ends = __ballot(b < total && left <= BE);
+            if (lane == 0) s.ends[i / kWaveSize] = ends;
+        }
+        __syncthreads();
+        // ---- stage 1: the burst's entries, all requested before the first is awaited ----
+        constexpr int M = 4;
+#pragma unroll 1
+        for (int q0 = wave; q0 < chunks; q0 += M * kWavesPerBlock) {
+            int32_t col[M];
+            float val[M];
+#pragma unroll
+            for (int i = 0; i < M; ++i) {
+                const int q = min(q0 + i * kWavesPerBlock, chunks - 1);
+                const uint2 blk = s.block[q * BPC + c_block];
+                const int32_t cnt = (int32_t)(blk.y & 0xFFu);
+                uint32_t pos = blk.x + (uint32_t)max(min(c_in, cnt - 1), 0);   // absent entries repeat one of the row's
+                if constexpr (STRIDED) {
+                    const uint32_t r = blk.y >> 8;
+                    const uint32_t n = s.len[r];
+                    if (n) {
+                        uint32_t step;
+                        if (a.W < 28000) step = small_mod(pos * s.mul[r], n);          // pos < W: below 2^24
+                        else step = (uint32_t)(((uint64_t)pos * s.mul[r]) % n);
+                        uint32_t entry = s.rot[r] + step;         // both < n < 2^31
+                        if (entry >= n) entry -= n;
+                        pos = (uint32_t)s.src[r] + entry;
+                    }
+                }
+                const float* v = a.vals ? a.vals + pos : kFlatConst + 1;
+                v = c_in < cnt ? v : kFlatConst;                  // absent entries: zero
+                col[i] = __builtin_nontemporal_load(a.colidx + pos);
+                val[i] = __builtin_nontemporal_load(v);
+            }
+#pragma unroll
+            for (int i = 0; i < M; ++i) {
+                const int q = min(q0 + i * kWavesPerBlock, chunks - 1);
+                s.col[q * kWaveSize + lane] = col[i];
+                s.val[q * kWaveSize + lane] = val[i];
+            }
+        }
+        __syncthreads();
+        // ---- stage 2: every wave an equal share of the batches ------------------------
+        const int first_batch = batches * wave / kWavesPerBlock;
+        const int last_batch = batches * (wave + 1) / kWavesPerBlock;
+        int32_t head = -1;
+        if (first_batch < last_batch) {
+            const int blk0 = first_batch * BPB;
+            int r = __builtin_amdgcn_readfirstlane((int)(s.block[blk0].y >> 8));
+            // a row that began before this wave's share leaves its sum in the wave's own place
+            if (__builtin_amdgcn_readfirstlane(s.first[r]) < b0 + blk0) head = r;
+            uint64_t pending = nonempty & ~((2ull << r) - 1ull);  // rows behind r
+            bool at_head = head >= 0;
+            P acc;
+            acc.zero();
+            auto flush = [&]() {
+                float* dst = (at_head ? s.head + wave * FB : s.rowsum + r * FB) + l * 4;
+                if constexpr (E == 1) {
+                    *reinterpret_cast<float4*>(dst) = acc.v;
+                } else if constexpr (E == 2) {
+                    const float s0 = halve_add<5>(acc.v.x, acc.v.z);
+                    const float s1 = halve_add<5>(acc.v.y, acc.v.w);
+                    *reinterpret_cast<float2*>(dst + 2 * e) = make_float2(s0, s1);
+                } else {
+                    const float s0 = halve_add<4>(acc.v.x, acc.v.z);    // bit 4 clear: x, set: z
+                    const float s1 = halve_add<4>(acc.v.y, acc.v.w);    //              y       w
+                    float v = halve_add<5>(s0, s1);                     // bit 5 clear: s0, set: s1
+                    if constexpr (LOG_E > 2) v = all_add<3>(v);
+                    if constexpr (LOG_E > 3) v = all_add<2>(v);
+                    const int top = e >> (LOG_E - 2);                   // lane bits 4, 5
+                    dst[2 * (top & 1) + (top >> 1)] = v;                // slots that differ in lower bits hold the same sum
+                }
+                acc.zero();
+                at_head = false;
+                r = pending ? __builtin_ctzll(pending) : kFlatMaxRows;  // kFlatMaxRows: nothing left
+                pending &= pending - 1;
+            };
+            auto multiply = [&](int batch, const Batch& bt) {
+                const uint32_t end = (uint32_t)__builtin_amdgcn_readfirstlane(
+                    (int)(reinterpret_cast<const uint32_t*>(s.ends)[batch * BPB / 32] >> (batch * BPB % 32)));
+                float4 val[U / 4];
+#pragma unroll
+                for (int q = 0; q < U / 4; ++q)
+                    val[q] = *reinterpret_cast<const float4*>(get_val + (batch * U + 4 * q) * E);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    acc.fma((&val[u / 4].x)[u & 3], bt.x[u]);
+                    if (((u + 1) * E) % BE == 0 && (end & (1u << ((u * E) / BE)))) flush();
+                }
+            };
+            Batch xa;
+#pragma unroll 1
+            for (int b = first_batch; b < last_batch; ++b) { gather(b * U, xa); multiply(b, xa); }
+            // the share's last row may go on in the next one
+            const int blk1 = last_batch * BPB - 1;
+            const uint32_t ended = reinterpret_cast<const uint32_t*>(s.ends)[blk1 / 32] >> (blk1 % 32);
+            if (!(__builtin_amdgcn_readfirstlane((int)ended) & 1) && r < kFlatMaxRows) flush();
+        }
+        if (lane == 0) s.head_row[wave] = head;
+        __syncthreads();
+        if (threadIdx.x < FB) {
+#pragma unroll
+            for (int w = 0; w < kWavesPerBlock; ++w) {
+                const int32_t hr = s.head_row[w];
+                if (hr >= 0) s.rowsum[hr * FB + threadIdx.x] += s.head[w * FB + threadIdx.x];
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// The run of workgroup `vb`: whole sampled rows, or with PART the pieces of
+// column range `part` (ACC: add to Y instead of overwriting it).
+template <bool ALIGNED, bool WIDE, bool STRIDED, bool PART, bool ACC, class Lds>
+__device__ __forceinline__ void flat_block(const Args& a, uint32_t vb, int part, Lds& s)
+{
+    constexpr int G = Lds::G;
+    constexpr int ROWS = Lds::ROWS;
+    constexpr int FB = 4 * G;
+    constexpr int RPP = kBlockThreads / G;            // rows out per pass
+    constexpr int PASSES = (ROWS + RPP - 1) / RPP;
+    using P = Pack<4, ALIGNED>;
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    const int l = threadIdx.x & (G - 1);
+    const int jr = threadIdx.x / G;
+    const int colblk = blockIdx.y * FB;
+    LaneCols<G, 1, 4, ALIGNED> cols;
+    cols.init(colblk, l, a.F);
+    const int64_t r0 = (int64_t)vb * ROWS;
+    FlatRow row{0, 0, 0, 0, 0};
     int32_t my_n = 0, my_k = 0;
     bool my_store = false;                            // this launch writes the row's Y
-    uint64_t nonempty;                                // bit j: row j has entries in this run
-    {
-        int32_t base = 0, lo = 0, hi = 0, kj = 0;
-        bool strided = false;
-        const int64_t r = r0 + lane;
-        if (lane < NR && r < a.N) {
-            base = a.rowptr[r];
-            my_n = a.rowptr[r + 1] - base;
-            my_k = kept_count(a.mode, my_n, a.W);
-            if (job.part < 0) {
-                hi = my_k;
-                my_store = my_k <= a.long_k;          // longer rows belong to the long-row part
-                if (!my_store) hi = 0;
-                strided = STRIDED && my_n > a.W;
-            } else {
-                const int32_t* cr = a.cuts + r * kParts;
-                lo = __builtin_nontemporal_load(&cr[job.part]);
-                hi = (job.part + 1 < kParts) ? __builtin_nontemporal_load(&cr[job.part + 1]) : my_n;
-                my_store = !job.accumulate || hi > lo;
-            }
-            kj = hi - lo;
-        }
-        nonempty = __ballot(kj > 0);
-        const int32_t padded = (kj + E - 1) & ~(E - 1);
-        int32_t incl = padded;                        // inclusive scan over the wave
-#pragma unroll
-        for (int d = 1; d < kWaveSize; d <<= 1) {
-            const int32_t up = __shfl_up(incl, d, kWaveSize);
-            if (lane >= d) incl += up;
-        }
-        if (lane < NR) {
-            s.start[lane + 1] = incl;
-            s.kept[lane] = kj;
-            s.src[lane] = base + lo;
-            if constexpr (STRIDED) {
-                s.len[lane] = strided ? (uint32_t)my_n : 0u;
-                s.mul[lane] = strided ? fastrand_multiplier((uint32_t)my_n) : 0u;
-                s.rot[lane] = strided ? fastrand_offset(a.seed, r, (uint32_t)my_n) : 0u;
-            }
-        }
-        if (lane == 0) s.start[0] = 0;
-    }
-    wave_lds_fence();
-    const int total = __builtin_amdgcn_readfirstlane(s.start[NR]);
-
-    // ---- the run, tile by tile -----------------------------------------------------
-    P acc;
-    acc.zero();
-    int cur = -1;                                     // rank of the row being summed among the non-empty ones
-    int jrow = 0;                                     // row of this lane's next slot (never decreases)
-    // A row ends once.  Its sum over the slots is taken so that the two steps over
-    // the highest slot bits (lane bits 4 and 5: plain swaps) also halve what a lane
-    // carries: after them a lane holds one of the four columns; the lower slot bits
-    // are summed by rotations inside a row of 16 lanes.  The lanes of the slots
-    // whose low bits are zero write the four columns side by side.
-    auto flush = [&]() {
-        float* dst = &s.rowacc[cur * FB + l * 4];
-        if constexpr (E == 1) {
-            *reinterpret_cast<float4*>(dst) = acc.v;
-        } else if constexpr (E == 2) {
-            const float s0 = halve_add<5>(acc.v.x, acc.v.z);
-            const float s1 = halve_add<5>(acc.v.y, acc.v.w);
-            *reinterpret_cast<float2*>(dst + 2 * e) = make_float2(s0, s1);
+    const int64_t r = r0 + lane;
+    if (lane < ROWS && r < a.N) {
+        const int32_t base = a.rowptr[r];
+        my_n = a.rowptr[r + 1] - base;
+        my_k = kept_count(a.mode, my_n, a.W);
+        if constexpr (PART) {
+            const int32_t* cr = a.cuts + r * kParts;
+            const int32_t lo = cr[part];
+            const int32_t hi = (part + 1 < kParts) ? cr[part + 1] : my_n;
+            row.src = base + lo;
+            row.k = hi - lo;
+            my_store = !ACC || hi > lo;
         } else {
-            const float s0 = halve_add<4>(acc.v.x, acc.v.z);    // bit 4 clear: x, set: z
-            const float s1 = halve_add<4>(acc.v.y, acc.v.w);    //              y       w
-            float v = halve_add<5>(s0, s1);                     // bit 5 clear: s0, set: s1
-            if constexpr (LOG_E > 2) v = all_add<3>(v);
-            if constexpr (LOG_E > 3) v = all_add<2>(v);
-            const int top = e >> (LOG_E - 2);                         // lane bits 4, 5
-            if ((e & (E / 4 - 1)) == 0) dst[2 * (top & 1) + (top >> 1)] = v;
-        }
-    };
-    // Stage 1 for one tile, up to the loads: slot -> (row, slot in row) -> sample
-    // index -> CSR position, then the entry's column and value requested.  No
-    // branch encloses a global load (lanes past the tile's end redo its last
-    // slot; past the run's end, the run's last slot), so that all of a lane's
-    // loads are in flight together, and the next tile's are in flight while this
-    // tile is consumed.
-    constexpr int M = kFlatTile / kWaveSize;
-    struct Staged {
-        int32_t col[M];
-        float val[M];
-        bool real[M];
-        uint64_t firsts[M];                                       // bit i: slot 64m + i is the first of its row
-    };
-    auto request = [&](int t0, Staged& st) {
-        const int count = min(total - t0, kFlatTile);             // a multiple of E; <= 0 past the run
-        int64_t pos[M];
-#pragma unroll
-        for (int m = 0; m < M; ++m) {
-            const int at = min(m * kWaveSize + lane, count - 1);
-            const int sl = t0 + at;                               // t0 - 1 at least: a slot of the run
-            while (sl >= s.start[jrow + 1]) ++jrow;               // sl < total = start[NR]: stops at NR-1
-            const int i = sl - s.start[jrow];
-            st.real[m] = i < s.kept[jrow];
-            st.firsts[m] = __ballot(i == 0 && m * kWaveSize + lane < count);
-            const uint32_t slot = st.real[m] ? (uint32_t)i : 0u;  // padding repeats the row's first entry
-            uint32_t entry = slot;
-            if constexpr (STRIDED) {
-                const uint32_t n = s.len[jrow];
-                if (n) {
-                    const uint32_t step = a.W < (1 << 22) ? (slot * s.mul[jrow]) % n
-                                                          : (uint32_t)(((uint64_t)slot * s.mul[jrow]) % n);
-                    entry = s.rot[jrow] + step;                   // both < n < 2^31
-                    if (entry >= n) entry -= n;
-                }
-            }
-            pos[m] = (int64_t)s.src[jrow] + entry;
-        }
-#pragma unroll
-        for (int m = 0; m < M; ++m) {
-            st.col[m] = __builtin_nontemporal_load(&a.colidx[pos[m]]);
-            st.val[m] = a.vals ? __builtin_nontemporal_load(&a.vals[pos[m]]) : 1.0f;
-        }
-    };
-    Staged st;
-    if (total > 0) request(0, st);                                // an empty run has no slot to stand in for
-    for (int t0 = 0; t0 < total; t0 += kFlatTile) {
-        const int count = min(total - t0, kFlatTile);
-        // the tile is filled up to whole batches with zero-valued repeats of its last
-        // entry (what the lanes past its end requested), so stage 2 needs no bounds
-        const int filled = (count + U * E - 1) & ~(U * E - 1);
-        uint64_t firsts[M];
-#pragma unroll
-        for (int m = 0; m < M; ++m) {
-            firsts[m] = st.firsts[m];
-            const int at = m * kWaveSize + lane;
-            if (at < filled)
-                s.tile[at] = make_uint2(K::make(st.col[m], a.stride_units),
-                                        __float_as_uint(at < count && st.real[m] ? st.val[m] : 0.0f));
-        }
-        wave_lds_fence();
-        request(t0 + kFlatTile, st);
-        // stage 2: E entries per step, U steps per batch, a batch's rows of X in
-        // flight together.  Rows start at multiples of E, so "step b0 + u starts a
-        // row" is bit (b0 + u) * E of the tile's first-slot bits: a scalar test.
-        const int steps = count >> LOG_E;
-        for (int b0 = 0; b0 < steps; b0 += U) {
-            const int slot0 = b0 << LOG_E;
-            uint64_t word = firsts[0];
-#pragma unroll
-            for (int m = 1; m < M; ++m)
-                if ((slot0 >> 6) == m) word = firsts[m];
-            const uint64_t starts = word >> (slot0 & 63);
-            uint2 ed[U];
-            P x[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) ed[u] = s.tile[(b0 + u) * E + e];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-#if defined(ES_PROBE_NO_GATHER)        // measurement builds only (wrong results): the kernel without stage 2's loads
-                x[u].v = make_float4(__uint_as_float(ed[u].x), 1.f, 2.f, 3.f);
-#elif defined(ES_PROBE_NEAR_GATHER)    // measurement builds only: every gather inside the first 64 KB of X
-                x[u].load(K::row(a.X, ed[u].x & 0xFFFu, a.ldx) + cols.off[0]);
-#else
-                x[u].load(K::row(a.X, ed[u].x, a.ldx) + cols.off[0]);
-#endif
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const float v = __uint_as_float(ed[u].y);
-                if ((starts >> (u * E)) & 1) {                     // wave-uniform; never set past the last step
-                    if (cur >= 0) flush();
-                    ++cur;
-                    acc.mul(v, x[u]);                              // the row's first step
-                } else {
-                    acc.fma(v, x[u]);
-                }
+            my_store = my_k <= a.long_k;              // longer rows belong to the long-row part
+            row.src = base;
+            row.k = my_store ? my_k : 0;
+            if (STRIDED && my_n > a.W) {
+                row.len = (uint32_t)my_n;
+                row.mul = fastrand_multiplier(row.len);
+                row.rot = fastrand_offset(a.seed, r, row.len);
             }
         }
-        wave_lds_fence();
     }
-    if (cur >= 0) flush();
-    wave_lds_fence();
-
-    // ---- rows out: E rows per pass (earlier partial sums requested for all passes first) ----
-    constexpr int PASSES = NR / E;
     P prev[PASSES];
-    if (job.accumulate) {
+    if constexpr (ACC) {                              // earlier partial sums, requested ahead of the entries
 #pragma unroll
         for (int pass = 0; pass < PASSES; ++pass) {
-            const int64_t r = min(r0 + pass * E + e, a.N - 1);     // past the end: any valid row, unused
-            prev[pass].load_streaming(a.Y + r * (int64_t)a.ldy + cols.off[0]);
+            const int64_t ry = min(r0 + min(pass * RPP + jr, ROWS - 1), a.N - 1);
+            prev[pass].load_streaming(a.Y + ry * (int64_t)a.ldy + cols.off[0]);
         }
     }
+    flat_run<ALIGNED, WIDE, STRIDED>(a, row, colblk, s);
 #pragma unroll
     for (int pass = 0; pass < PASSES; ++pass) {
-        const int j = pass * E + e;
-        const int64_t r = r0 + j;
-        const int32_t n = __shfl(my_n, j, kWaveSize);
-        const int32_t k = __shfl(my_k, j, kWaveSize);
+        const int j = pass * RPP + jr;
         const bool store = __shfl((int)my_store, j, kWaveSize) != 0;
-        const int rank = __popcll(nonempty & ((1ull << j) - 1ull));
         P out;
-        out.zero();
-        if ((nonempty >> j) & 1) out.v = *reinterpret_cast<const float4*>(&s.rowacc[rank * FB + l * 4]);
-        if (a.norm != ES_NORM_NONE) out.scale(row_factor(a.norm, n, k));
-        if (job.accumulate) out.add(prev[pass]);
-        if (store && cols.ok[0]) {
-            float* y = a.Y + r * (int64_t)a.ldy + cols.off[0];
-            out.store_streaming(y, cols.first[0]);                 // not read again by this launch
+        out.v = *reinterpret_cast<const float4*>(&s.rowsum[j * FB + l * 4]);
+        if (a.norm != ES_NORM_NONE)
+            out.scale(row_factor(a.norm, __shfl(my_n, j, kWaveSize), __shfl(my_k, j, kWaveSize)));
+        if constexpr (ACC) out.add(prev[pass]);
+        if (store && cols.ok[0]) out.store_streaming(a.Y + (r0 + j) * (int64_t)a.ldy + cols.off[0], cols.first[0]);
+    }
+}
+
+// Long-row part, as long_block in es_fused_kernel.h: the workgroup's share of the
+// segments of the long rows among its 1024, added to Y with fp32 atomics.
+template <bool ALIGNED, bool WIDE, bool STRIDED, class Lds>
+__device__ __forceinline__ void flat_long_block(const Args& a, uint32_t bx, uint32_t by, Lds& s, LongScratch& sc)
+{
+    constexpr int G = Lds::G;
+    constexpr int FB = 4 * G;
+    const int total = long_segments<kFlatLongSeg>(a, bx, sc);
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    LaneCols<G, 1, 4, ALIGNED> cols;
+    cols.init(blockIdx.y * FB, threadIdx.x & (G - 1), a.F);
+    for (int task = by; task < total; task += kLongSplit) {
+        const LongSegment sg = long_segment<kFlatLongSeg>(a, bx, task, sc);
+        FlatRow row{sg.base, lane == 0 ? sg.count : 0, 0, 0, 0};
+        if (STRIDED && sg.n > a.W) {
+            row.len = (uint32_t)sg.n;
+            row.mul = fastrand_multiplier(row.len);
+            row.rot = (uint32_t)(((uint64_t)sg.t0 * row.mul + fastrand_offset(a.seed, sg.r, row.len)) % row.len);
+        } else {
+            row.src += sg.t0;
         }
+        flat_run<ALIGNED, WIDE, STRIDED>(a, row, blockIdx.y * FB, s);
+        if (threadIdx.x < G) {
+            Pack<4, ALIGNED> out;
+            out.v = *reinterpret_cast<const float4*>(&s.rowsum[threadIdx.x * 4]);
+            if (a.norm != ES_NORM_NONE) out.scale(row_factor(a.norm, sg.n, sg.k));
+            if (cols.ok[0]) out.atomic_add(a.Y + sg.r * (int64_t)a.ldy + cols.off[0], cols.first[0]);
+        }
+        __syncthreads();
     }
 }
 
 // The forward kernel on flattened rows: as es_spmm_kernel, the leading
 // a.long_blocks workgroups split the rows that keep more than a.long_k entries
-// (those rows are left out of the flattened runs), the rest serve 4 * NR rows
-// each, remapped so that every XCD walks one contiguous range of rows.
+// (those rows are left out of the flattened runs), the rest serve
+// flat_rows(G, RPS) rows each, remapped so that every XCD walks one contiguous range of rows.
 template <int G, bool ALIGNED, bool WIDE, bool STRIDED, int RPS>
 __global__ void __launch_bounds__(kBlockThreads) es_spmm_flat_kernel(const Args a)
 {
-    constexpr size_t kLongBytes = kWavesPerBlock * kWaveTileStride * sizeof(uint2) + sizeof(LongScratch);
-    constexpr size_t kBytes = sizeof(FlatLds) * kWavesPerBlock > kLongBytes ? sizeof(FlatLds) * kWavesPerBlock
-                                                                            : kLongBytes;
-    __shared__ __align__(16) unsigned char raw[kBytes];
+    __shared__ __align__(16) FlatLds<G, RPS> lds;
+    __shared__ LongScratch sc;
     if (blockIdx.x < a.long_blocks) {
-        uint2* tiles = reinterpret_cast<uint2*>(raw);
-        LongScratch& sc = *reinterpret_cast<LongScratch*>(raw + kWavesPerBlock * kWaveTileStride * sizeof(uint2));
-        long_block<G, 1, 4, ALIGNED, false, WIDE>(a, blockIdx.x / kLongSplit, blockIdx.x % kLongSplit, tiles, sc);
+        flat_long_block<ALIGNED, WIDE, STRIDED>(a, blockIdx.x / kLongSplit, blockIdx.x % kLongSplit, lds, sc);
         return;
     }
     const uint32_t b = blockIdx.x - a.long_blocks;
     const uint32_t vb = (b % kNumXcd) * a.blocks_per_xcd + b / kNumXcd;
     if (vb >= a.nblocks) return;
-    flat_block<G, ALIGNED, WIDE, STRIDED, RPS>(a, vb, FlatJob{-1, false}, reinterpret_cast<FlatLds*>(raw));
+    flat_block<ALIGNED, WIDE, STRIDED, false, false>(a, vb, 0, lds);
 }
 
 // One phase of the column-partitioned exact product on flattened pieces (see
 // es_part_kernel.h for the phases): XCD p = b % 8 serves column range p of the
 // rows of row range (p + phase) % 8.
-template <int G, bool ALIGNED, bool WIDE>
+template <int G, bool ALIGNED, bool WIDE, bool ACC>
 __global__ void __launch_bounds__(kBlockThreads) es_spmm_part_flat_kernel(const Args a)
 {
-    __shared__ FlatLds lds[kWavesPerBlock];
+    __shared__ __align__(16) FlatLds<G, 2> lds;
     const uint32_t p = blockIdx.x % kNumXcd;
     const uint32_t q = blockIdx.x / kNumXcd;
-    const uint32_t sblock = (p + (uint32_t)a.phase) % kNumXcd;
-    const uint32_t vb = sblock * a.blocks_per_xcd + q;
+    const uint32_t vb = ((p + (uint32_t)a.phase) % kNumXcd) * a.blocks_per_xcd + q;
     if (vb >= a.nblocks) return;
-    flat_block<G, ALIGNED, WIDE, false, kFlatPartRps>(a, vb, FlatJob{(int)p, a.phase != 0}, lds);
+    flat_block<ALIGNED, WIDE, false, true, ACC>(a, vb, (int)p, lds);
 }
 
 }  // namespace

@@ -105,14 +105,12 @@ struct LongScratch {
     int wave_total[kWavesPerBlock];
 };
 
-template <int G, int CH, int VEC, bool ALIGNED, bool BACKWARD, bool WIDE>
-__device__ __forceinline__ void long_block(const Args& a, uint32_t bx, uint32_t by, uint2* lds,
-                                           LongScratch& sc)
+// Number of segments of the long rows among the workgroup's 1024 rows; leaves
+// their prefix sums in `sc`.
+template <int SEG>
+__device__ __forceinline__ int long_segments(const Args& a, uint32_t bx, LongScratch& sc)
 {
-    constexpr int LOG_G = ilog2(G);
     constexpr int kRowsPerThread = kLongScanRows / kBlockThreads;
-    using P = Pack<VEC, ALIGNED>;
-
     const int tid = threadIdx.x;
     const int lane = tid & (kWaveSize - 1);
     const int wave = tid >> 6;
@@ -129,11 +127,11 @@ __device__ __forceinline__ void long_block(const Args& a, uint32_t bx, uint32_t 
         if (r < a.N) {
             const int n = a.rowptr[r + 1] - a.rowptr[r];
             const int k = kept_count(a.mode, n, a.W);
-            if (k > a.long_k) nseg[i] = (k + kLongSeg - 1) / kLongSeg;
+            if (k > a.long_k) nseg[i] = (k + SEG - 1) / SEG;
         }
         mine += nseg[i];
     }
-    if (__syncthreads_or(mine) == 0) return;     // no long row among these 1024: the common case
+    if (__syncthreads_or(mine) == 0) return 0;   // no long row among these 1024: the common case
     int incl = mine;                             // inclusive scan inside the wave
 #pragma unroll
     for (int d = 1; d < kWaveSize; d <<= 1) {
@@ -150,9 +148,46 @@ __device__ __forceinline__ void long_block(const Args& a, uint32_t bx, uint32_t 
         sc.seg_end[tid * kRowsPerThread + i] = before;
     }
     __syncthreads();
-    const int total = sc.seg_end[kLongScanRows - 1];
+    return sc.seg_end[kLongScanRows - 1];
+}
+
+// Segment number `task` of the workgroup's long rows.
+struct LongSegment {
+    int64_t r;
+    int32_t base, n, k;                          // the row: first CSR position, stored and kept entries
+    int t0, count;                               // the segment's slots
+};
+
+template <int SEG>
+__device__ __forceinline__ LongSegment long_segment(const Args& a, uint32_t bx, int task, const LongScratch& sc)
+{
+    int lo = 0, hi = kLongScanRows - 1;          // first row whose prefix exceeds task
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (sc.seg_end[mid] > task) hi = mid; else lo = mid + 1;
+    }
+    LongSegment s;
+    s.r = (int64_t)bx * kLongScanRows + lo;
+    s.base = a.rowptr[s.r];
+    s.n = a.rowptr[s.r + 1] - s.base;
+    s.k = kept_count(a.mode, s.n, a.W);
+    s.t0 = (task - (lo ? sc.seg_end[lo - 1] : 0)) * SEG;
+    s.count = min(s.k - s.t0, SEG);
+    return s;
+}
+
+template <int G, int CH, int VEC, bool ALIGNED, bool BACKWARD, bool WIDE>
+__device__ __forceinline__ void long_block(const Args& a, uint32_t bx, uint32_t by, uint2* lds,
+                                           LongScratch& sc)
+{
+    constexpr int LOG_G = ilog2(G);
+    using P = Pack<VEC, ALIGNED>;
+
+    const int total = long_segments<kLongSeg>(a, bx, sc);
     if (total == 0) return;
 
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    const int wave = threadIdx.x >> 6;
     const int e = lane >> LOG_G;
     const int l = lane & (G - 1);
     constexpr int E = kWaveSize / G;
@@ -162,18 +197,10 @@ __device__ __forceinline__ void long_block(const Args& a, uint32_t bx, uint32_t 
 
     const int gw = by * kWavesPerBlock + wave;
     for (int task = gw; task < total; task += kLongSplit * kWavesPerBlock) {
-        int lo = 0, hi = kLongScanRows - 1;      // first row whose prefix exceeds task
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (sc.seg_end[mid] > task) hi = mid; else lo = mid + 1;
-        }
-        const int seg = task - (lo ? sc.seg_end[lo - 1] : 0);
-        const int64_t r = row0 + lo;
-        const int32_t base = a.rowptr[r];
-        const int n = a.rowptr[r + 1] - base;
-        const int k = kept_count(a.mode, n, a.W);
-        const int t0 = seg * kLongSeg;
-        const int count = min(k - t0, kLongSeg);
+        const LongSegment sg = long_segment<kLongSeg>(a, bx, task, sc);
+        const int64_t r = sg.r;
+        const int32_t base = sg.base;
+        const int n = sg.n, k = sg.k, t0 = sg.t0, count = sg.count;
 
         RowSampler sampler;
         sampler.init(a.mode, a.seed, r, (uint32_t)n, (uint32_t)a.W, (uint32_t)(t0 + lane), kWaveSize);

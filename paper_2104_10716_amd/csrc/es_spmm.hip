@@ -159,7 +159,10 @@ hipError_t launch_flat(Args a, dim3 grid, bool partition, int32_t* cuts, hipStre
     if (err != hipSuccess) return err;
     for (int phase = 0; phase < kParts; ++phase) {
         a.phase = phase;
-        hipLaunchKernelGGL((es_spmm_part_flat_kernel<G, ALIGNED, WIDE>), grid, dim3(kBlockThreads), 0, st, a);
+        if (phase == 0)
+            hipLaunchKernelGGL((es_spmm_part_flat_kernel<G, ALIGNED, WIDE, false>), grid, dim3(kBlockThreads), 0, st, a);
+        else
+            hipLaunchKernelGGL((es_spmm_part_flat_kernel<G, ALIGNED, WIDE, true>), grid, dim3(kBlockThreads), 0, st, a);
         err = hipGetLastError();
         if (err != hipSuccess) return err;
     }
@@ -374,13 +377,14 @@ int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool a
     }
     p->logR = logR;
 
+    int rps = 0;
     if (p->flat) {                                         // a wave lays 1 or 2 rows per edge slot end to end
-        const int rps = p->partition ? kFlatPartRps : mode == ES_FULL ? 1 : 2;
+        rps = mode == ES_FULL && !p->partition ? 1 : 2;
         logR = 0;
         while ((1 << logR) < rps * 64 / s.G) ++logR;
         p->logR = logR;
     }
-    const int64_t rows_per_block = (int64_t)kWavesPerBlock << logR;
+    const int64_t rows_per_block = p->flat ? flat_rows(s.G, rps) : (int64_t)kWavesPerBlock << logR;
     p->nblocks = (N + rows_per_block - 1) / rows_per_block;
     p->per_xcd = (p->nblocks + kNumXcd - 1) / kNumXcd;
     const int cols_per_block = s.G * s.CH * s.vec;
@@ -507,10 +511,13 @@ int es_run(const int32_t* rowptr, const int32_t* colidx, const float* vals, cons
     if (backward && s.G == G_ && s.CH == CH_)   \
         err = wide ? launch_backward<G_, CH_, true>(a, grid, st) : launch_backward<G_, CH_, false>(a, grid, st);
     ES_BWD(4, 1) ES_BWD(8, 1) ES_BWD(16, 1) ES_BWD(32, 1) ES_BWD(64, 1) ES_BWD(64, 2) ES_BWD(64, 4)
+    // the run kernel's 32-bit form: byte offsets from one 24-bit multiply
+    const uint64_t stride_bytes = (uint64_t)ldx * 4u;
+    const bool flat_wide = N > (1 << 24) || stride_bytes >= (1u << 24) || (uint64_t)N * stride_bytes > 0x100000000ull;
 #define ES_FLAT(G_, A_)                                                                         \
     if (p.flat && s.G == G_ && s.aligned == A_)                                                 \
-        err = wide ? launch_flat<G_, A_, true>(a, grid, p.partition, static_cast<int32_t*>(workspace), st)  \
-                   : launch_flat<G_, A_, false>(a, grid, p.partition, static_cast<int32_t*>(workspace), st);
+        err = flat_wide ? launch_flat<G_, A_, true>(a, grid, p.partition, static_cast<int32_t*>(workspace), st)  \
+                       : launch_flat<G_, A_, false>(a, grid, p.partition, static_cast<int32_t*>(workspace), st);
     ES_FLAT(4, true) ES_FLAT(8, true) ES_FLAT(16, true) ES_FLAT(32, true) ES_FLAT(64, true)
     ES_FLAT(4, false) ES_FLAT(8, false) ES_FLAT(16, false) ES_FLAT(32, false) ES_FLAT(64, false)
 #undef ES_FLAT

@@ -365,6 +365,47 @@ def test_flattened_kernel_rows_at_tile_boundaries(es, F, lanes):
                                              opts=opts)
 
 
+@pytest.mark.parametrize("F,lanes", [(16, 0), (64, 8), (64, 0), (128, 0), (256, 0), (41, 0)])
+def test_flattened_kernel_bursts_and_shares(es, F, lanes):
+    """The flattened kernel around the sizes a workgroup counts in: bursts of 1536
+    and 2048 entries, quarter shares of a burst (a row that ends on, before and
+    behind a share's border, one that spans several shares or bursts), runs of
+    empty rows longer than a workgroup's 64, and FastRand beyond the width up to
+    which its index fits a 24-bit product (28000)."""
+    from gpu_util import DeviceCSR, check_against_oracle
+    n = 6200
+    rng = np.random.default_rng(77 + F + lanes)
+    runs = [[384] * 9 + [383, 385, 7, 1], [512] * 9 + [511, 513, 520], [1536, 1535, 1537, 8, 2048, 2047, 2049],
+            [5000, 1, 0, 6144, 3], [0] * 130 + [1], [4096] + [0] * 62 + [9], [8] * 192 + [1] * 64]
+    lengths = [L for run in runs for L in run]
+    cols = [np.sort(rng.choice(n, size=int(L), replace=False)) for L in lengths]
+    rowptr = np.zeros(n + 1, dtype=np.int32)
+    rowptr[1:len(lengths) + 1] = np.cumsum([len(c) for c in cols])
+    rowptr[len(lengths) + 1:] = rowptr[len(lengths)]
+    colidx = np.concatenate(cols).astype(np.int32)
+    vals = rng.standard_normal(colidx.size).astype(np.float32)
+    X = rng.uniform(-1, 1, (n, F)).astype(np.float32)
+    d = DeviceCSR(rowptr, colidx, vals, X).with_workspace()
+    base = dict(kernel=2, workspace=d.default_ws)
+    if lanes:
+        base["lanes_per_row"] = lanes
+    _say(f"bursts and shares F={F} lanes={lanes}")
+    for extra in (dict(long_row_threshold=100000), dict(long_row_threshold=1500), dict(column_partition=1)):
+        opts = dict(base, **extra)
+        check_against_oracle(d, 0, "full", what=f"full F={F} {extra}", opts=opts)
+        for mode, W in (("bucket", 384), ("bucket", 3000), ("fastrand", 384), ("fastrand", 3000)):
+            check_against_oracle(d, W, mode, 5, norm="mean", what=f"{mode} W={W} F={F} {extra}", opts=opts)
+    m = 29_600                                # two rows beyond the 24-bit width, on both sides of it
+    rowptr = np.zeros(m + 1, dtype=np.int32)
+    rowptr[1], rowptr[2:] = m, 2 * m - 100
+    colidx = np.concatenate([np.arange(m), np.arange(m - 100)]).astype(np.int32)
+    d = DeviceCSR(rowptr, colidx, None, rng.uniform(-1, 1, (m, F)).astype(np.float32))
+    for W in (27_999, 28_000, 29_500, 29_550):
+        for thr in (100000, 1500):
+            check_against_oracle(d, W, "fastrand", 3, what=f"wide fastrand W={W} F={F} long rows above {thr}",
+                                 opts=dict(kernel=2, long_row_threshold=thr))
+
+
 def test_degenerate_inputs(es):
     import torch
     from gpu_util import DeviceCSR, check_against_oracle
