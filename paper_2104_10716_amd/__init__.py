@@ -1,7 +1,7 @@
 """MI355X-native edge-sampled SpMM (ES-SpMM).
 
 Thin binding over the C-ABI library ``libes_spmm.so`` (see ``include/es_spmm.h``):
-argument marshalling only -- every step of the computation runs in the HIP
+argument marshalling only (natively for the products) -- every step of the computation runs in the HIP
 kernels.  PyTorch supplies device memory and streams.
 """
 from .binding import (  # noqa: F401
@@ -33,4 +33,5 @@ from .binding import (  # noqa: F401
     es_spmm_ws,
     library_path,
     load_library,
+    load_marshal,
 )

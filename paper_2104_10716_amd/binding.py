@@ -1,5 +1,7 @@
-"""ctypes binding of libes_spmm.so: same names as the C ABI, tensors in, status
-checked.  No arithmetic happens here."""
+"""Binding of libes_spmm.so: same names as the C ABI, tensors in, status checked.  No
+arithmetic happens here.  The products go through a native marshalling module
+(csrc/es_marshal.cpp); it hands back (None) whatever is not the plain case, and the
+checks below then name the fault or convert the argument."""
 from __future__ import annotations
 
 import ctypes
@@ -111,6 +113,29 @@ def load_library():
     return lib
 
 
+_marshal = None
+
+
+def load_marshal():
+    """Load the native marshalling module (csrc/es_marshal.cpp) and give it the
+    library's entry points; raises if it has not been built."""
+    global _marshal
+    if _marshal is not None:
+        return _marshal
+    import torch  # noqa: F401  (the module links against torch's libraries)
+    try:
+        from . import _es_marshal
+    except ImportError as e:
+        raise ImportError(
+            f"{os.path.join(_PKG, '_es_marshal.so')} is missing or does not load ({e}): build it with "
+            "`python -m paper_2104_10716_amd.build` (or __graft_entry__.build())") from e
+    lib = load_library()
+    _es_marshal.bind(*(ctypes.cast(f, ctypes.c_void_p).value
+                       for f in (lib.es_spmm_ws, lib.es_spmm_backward, lib.es_spmm_backward_pull)))
+    _marshal = _es_marshal
+    return _marshal
+
+
 def _mode(mode) -> int:
     return MODES[mode] if isinstance(mode, str) else int(mode)
 
@@ -187,6 +212,11 @@ def es_spmm(rowptr, colidx, vals, X, Y, W: int, mode, seed: int = 0, F: Optional
     stride (row stride = leading dimension).  Enqueued on `stream` (default:
     torch's current stream); not synchronised.  `nnz` (default: len(colidx)) is
     only the launch-shape hint of the C ABI."""
+    rc = (_marshal or load_marshal()).spmm(rowptr, colidx, vals, X, Y, W, mode, seed, "none", None, F, stream, nnz)
+    if rc == 0:
+        return Y
+    if rc is not None:
+        raise EsSpmmError(rc, "es_spmm")
     lib = load_library()
     args = _spmm_args(rowptr, colidx, vals, X, Y, F, nnz)
     rc = lib.es_spmm(*args, int(W), _mode(mode), int(seed) & 0xFFFFFFFFFFFFFFFF, _stream_ptr(stream))
@@ -198,6 +228,11 @@ def es_spmm(rowptr, colidx, vals, X, Y, W: int, mode, seed: int = 0, F: Optional
 def es_spmm_norm(rowptr, colidx, vals, X, Y, W: int, mode, seed: int = 0, norm="none",
                  F: Optional[int] = None, stream=None, nnz: Optional[int] = None):
     """es_spmm with a row factor ("none", "mean", "rsqrt", "rescale") applied in the kernel."""
+    rc = (_marshal or load_marshal()).spmm(rowptr, colidx, vals, X, Y, W, mode, seed, norm, None, F, stream, nnz)
+    if rc == 0:
+        return Y
+    if rc is not None:
+        raise EsSpmmError(rc, "es_spmm_norm")
     lib = load_library()
     args = _spmm_args(rowptr, colidx, vals, X, Y, F, nnz)
     nm = NORMS[norm] if isinstance(norm, str) else int(norm)
@@ -229,6 +264,12 @@ def es_spmm_ws(rowptr, colidx, vals, X, Y, W: int, mode, seed: int = 0, norm="no
                workspace=None, F: Optional[int] = None, stream=None, nnz: Optional[int] = None):
     """es_spmm_ex with a caller-owned workspace (a device tensor of at least
     es_spmm_workspace_bytes(N) bytes, any dtype), which enables the column-partitioned product."""
+    if opts is None:
+        rc = (_marshal or load_marshal()).spmm(rowptr, colidx, vals, X, Y, W, mode, seed, norm, workspace, F, stream, nnz)
+        if rc == 0:
+            return Y
+        if rc is not None:
+            raise EsSpmmError(rc, "es_spmm_ws")
     lib = load_library()
     args = _spmm_args(rowptr, colidx, vals, X, Y, F, nnz)
     nm = NORMS[norm] if isinstance(norm, str) else int(norm)
@@ -277,6 +318,11 @@ def es_spmm_backward_ex(rowptr, colidx, vals, dY, dX, W: int, mode, seed: int = 
 def es_spmm_backward(rowptr, colidx, vals, dY, dX, W: int, mode, seed: int = 0, norm="none",
                      F: Optional[int] = None, stream=None, nnz: Optional[int] = None):
     """dX[:, :F] = sample_W(A)^T @ dY[:, :F] (dX is overwritten); returns dX."""
+    rc = (_marshal or load_marshal()).backward(rowptr, colidx, vals, dY, dX, W, mode, seed, norm, F, stream, nnz)
+    if rc == 0:
+        return dX
+    if rc is not None:
+        raise EsSpmmError(rc, "es_spmm_backward")
     lib = load_library()
     args = _spmm_args(rowptr, colidx, vals, dY, dX, F, nnz)
     nm = NORMS[norm] if isinstance(norm, str) else int(norm)
@@ -419,6 +465,11 @@ def es_spmm_backward_pull(rowptr, t, dY, dX, W: int, mode, seed: int = 0, norm="
                           F: Optional[int] = None, stream=None):
     """dX[:, :F] = sample_W(A)^T @ dY[:, :F] as a gather over `t`, the dict
     es_spmm_transpose_graph returned for the same graph; returns dX."""
+    rc = (_marshal or load_marshal()).pull(rowptr, t, dY, dX, W, mode, seed, norm, F, stream)
+    if rc == 0:
+        return dX
+    if rc is not None:
+        raise EsSpmmError(rc, "es_spmm_backward_pull")
     import torch
     lib = load_library()
     if dY.dim() != 2 or dX.dim() != 2 or dY.stride(1) != 1 or dX.stride(1) != 1:

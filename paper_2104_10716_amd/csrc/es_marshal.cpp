@@ -1,0 +1,201 @@
+// es_marshal.cpp -- native argument marshalling for the hot entry points: torch tensors in, one C-ABI call out.
+//
+// A Python program calls es_spmm once per layer; on a graph of a few thousand
+// rows the kernel takes about 4 us, and reading fifteen tensor attributes,
+// finding the current stream and converting twenty ctypes arguments in Python
+// took another 8 (13 us per call in all; 5 with this module).  Nothing is
+// computed here.  Every function returns the C entry point's status, or None when
+// an argument is not the plain case (wrong type, shape, device or stride): the
+// caller then goes through the checks written in Python, which name the fault.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include "es_spmm.h"
+
+namespace {
+
+decltype(&es_spmm_ws) g_spmm_ws = nullptr;
+decltype(&es_spmm_backward) g_backward = nullptr;
+decltype(&es_spmm_backward_pull) g_pull = nullptr;
+
+bool as_tensor(PyObject* o, at::ScalarType type, const at::Tensor** out)
+{
+    if (!THPVariable_Check(o)) return false;
+    const at::Tensor& t = THPVariable_Unpack(o);
+    if (!t.is_cuda() || t.scalar_type() != type) return false;
+    *out = &t;
+    return true;
+}
+
+// One of `names`, or an int: its code.
+bool as_code(PyObject* o, const char* const* names, int n, int32_t* out)
+{
+    if (PyUnicode_Check(o)) {
+        for (int i = 0; i < n; ++i)
+            if (PyUnicode_CompareWithASCIIString(o, names[i]) == 0) { *out = i; return true; }
+        return false;
+    }
+    if (!PyLong_Check(o)) return false;
+    int overflow = 0;
+    const long v = PyLong_AsLongAndOverflow(o, &overflow);
+    if (overflow || v < INT32_MIN || v > INT32_MAX) return false;
+    *out = (int32_t)v;
+    return true;
+}
+
+const char* const kModes[] = {"full", "bucket", "fastrand"};
+const char* const kNorms[] = {"none", "mean", "rsqrt", "rescale", "inv_degree"};
+
+bool as_stream(PyObject* o, void** out)
+{
+    if (o != Py_None) return false;
+    *out = c10::hip::getCurrentHIPStream().stream();
+    return true;
+}
+
+// What every product has in common: X (gathered) and Y (written), [N x F] with
+// unit column stride, and the sampler's arguments.
+struct Product {
+    const at::Tensor *X, *Y;
+    int64_t N;
+    int32_t F, ldx, ldy, W, mode, norm;
+    uint64_t seed;
+    void* stream;
+
+    bool parse(int64_t n, PyObject* x, PyObject* y, PyObject* w, PyObject* m, PyObject* sd, PyObject* nm,
+               PyObject* f, PyObject* st)
+    {
+        N = n;
+        if (!as_tensor(x, at::kFloat, &X) || !as_tensor(y, at::kFloat, &Y)) return false;
+        if (X->dim() != 2 || Y->dim() != 2 || X->stride(1) != 1 || Y->stride(1) != 1) return false;
+        if (X->size(0) != N || Y->size(0) != N) return false;
+        int32_t cols = 0;
+        if (f != Py_None) {
+            if (!as_code(f, nullptr, 0, &cols)) return false;
+        } else if (X->size(1) <= INT32_MAX) {
+            cols = (int32_t)X->size(1);
+        } else {
+            return false;
+        }
+        if (cols > X->size(1) || cols > Y->size(1)) return false;
+        const int64_t lx = N > 1 ? X->stride(0) : std::max<int64_t>(X->size(1), 1);
+        const int64_t ly = N > 1 ? Y->stride(0) : std::max<int64_t>(Y->size(1), 1);
+        if (lx > INT32_MAX || ly > INT32_MAX || lx < 0 || ly < 0) return false;
+        F = cols; ldx = (int32_t)lx; ldy = (int32_t)ly;
+        if (!as_code(w, nullptr, 0, &W) || !as_code(m, kModes, 3, &mode) || !as_code(nm, kNorms, 5, &norm)) return false;
+        if (!PyLong_Check(sd)) return false;
+        seed = PyLong_AsUnsignedLongLongMask(sd);
+        return as_stream(st, &stream);
+    }
+};
+
+struct Csr {
+    const int32_t *rowptr, *colidx;
+    const float* vals;
+    int64_t N, nnz;
+
+    bool parse(PyObject* rp, PyObject* ci, PyObject* va, PyObject* nz)
+    {
+        const at::Tensor *r, *c, *v;
+        if (!as_tensor(rp, at::kInt, &r) || !as_tensor(ci, at::kInt, &c)) return false;
+        N = r->numel() - 1;
+        nnz = c->numel();
+        vals = nullptr;
+        if (va != Py_None) {
+            if (!as_tensor(va, at::kFloat, &v) || v->numel() != nnz) return false;
+            vals = static_cast<const float*>(v->data_ptr());
+        }
+        rowptr = static_cast<const int32_t*>(r->data_ptr());
+        colidx = static_cast<const int32_t*>(c->data_ptr());
+        if (nz != Py_None) {
+            int32_t hint;
+            if (!as_code(nz, nullptr, 0, &hint)) return false;
+            nnz = hint;
+        }
+        return true;
+    }
+};
+
+// bind(es_spmm_ws, es_spmm_backward, es_spmm_backward_pull): addresses of the C entry points
+PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    if (n != 3) { PyErr_SetString(PyExc_TypeError, "bind takes three addresses"); return nullptr; }
+    void* p[3];
+    for (int i = 0; i < 3; ++i) {
+        p[i] = PyLong_AsVoidPtr(a[i]);
+        if (!p[i]) {
+            if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "null entry point");
+            return nullptr;
+        }
+    }
+    g_spmm_ws = reinterpret_cast<decltype(g_spmm_ws)>(p[0]);
+    g_backward = reinterpret_cast<decltype(g_backward)>(p[1]);
+    g_pull = reinterpret_cast<decltype(g_pull)>(p[2]);
+    Py_RETURN_NONE;
+}
+
+// spmm(rowptr, colidx, vals, X, Y, W, mode, seed, norm, workspace, F, stream, nnz)
+PyObject* spmm(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    Csr g;
+    Product p;
+    if (n != 13 || !g_spmm_ws || !g.parse(a[0], a[1], a[2], a[12]) ||
+        !p.parse(g.N, a[3], a[4], a[5], a[6], a[7], a[8], a[10], a[11]))
+        Py_RETURN_NONE;
+    void* ws = nullptr;
+    size_t ws_bytes = 0;
+    if (a[9] != Py_None) {
+        if (!THPVariable_Check(a[9])) Py_RETURN_NONE;
+        const at::Tensor& t = THPVariable_Unpack(a[9]);
+        if (!t.is_cuda() || !t.is_contiguous()) Py_RETURN_NONE;
+        ws = t.data_ptr();
+        ws_bytes = t.nbytes();
+    }
+    return PyLong_FromLong(g_spmm_ws(g.rowptr, g.colidx, g.vals, static_cast<const float*>(p.X->data_ptr()),
+                                     static_cast<float*>(p.Y->data_ptr()), g.N, g.nnz, p.F, p.ldx, p.ldy, p.W,
+                                     p.mode, p.seed, p.norm, nullptr, ws, ws_bytes, p.stream));
+}
+
+// backward(rowptr, colidx, vals, dY, dX, W, mode, seed, norm, F, stream, nnz)
+PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    Csr g;
+    Product p;
+    if (n != 12 || !g_backward || !g.parse(a[0], a[1], a[2], a[11]) ||
+        !p.parse(g.N, a[3], a[4], a[5], a[6], a[7], a[8], a[9], a[10]))
+        Py_RETURN_NONE;
+    return PyLong_FromLong(g_backward(g.rowptr, g.colidx, g.vals, static_cast<const float*>(p.X->data_ptr()),
+                                      static_cast<float*>(p.Y->data_ptr()), g.N, g.nnz, p.F, p.ldx, p.ldy, p.W,
+                                      p.mode, p.seed, p.norm, p.stream));
+}
+
+// pull(rowptr, t, dY, dX, W, mode, seed, norm, F, stream); t: the dict of es_spmm_transpose_graph
+PyObject* pull(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    static const char* const names[] = {"t_ptr", "t_row", "t_idx", "t_slot", "t_vals", "t_pinv", "t_rows"};
+    const at::Tensor *rp, *t[7];
+    Product p;
+    if (n != 10 || !g_pull || !as_tensor(a[0], at::kInt, &rp) || !PyDict_Check(a[1])) Py_RETURN_NONE;
+    for (int i = 0; i < 7; ++i) {
+        PyObject* o = PyDict_GetItemString(a[1], names[i]);
+        if (!o || !as_tensor(o, i == 4 ? at::kFloat : at::kInt, &t[i])) Py_RETURN_NONE;
+    }
+    const int64_t N = rp->numel() - 1;
+    if (!p.parse(N, a[2], a[3], a[4], a[5], a[6], a[7], a[8], a[9])) Py_RETURN_NONE;
+    auto ints = [](const at::Tensor* x) { return static_cast<int32_t*>(x->data_ptr()); };
+    return PyLong_FromLong(g_pull(ints(rp), ints(t[0]), ints(t[1]), ints(t[2]), ints(t[3]),
+                                  static_cast<const float*>(t[4]->data_ptr()), ints(t[5]), ints(t[6]),
+                                  static_cast<const float*>(p.X->data_ptr()), static_cast<float*>(p.Y->data_ptr()), N,
+                                  t[1]->numel(), p.F, p.ldx, p.ldy, p.W, p.mode, p.seed, p.norm, p.stream));
+}
+
+#define ES_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {ES_METHOD(bind), ES_METHOD(spmm), ES_METHOD(backward), ES_METHOD(pull), {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_es_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__es_marshal() { return PyModule_Create(&module); }
