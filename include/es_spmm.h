@@ -218,8 +218,8 @@ int es_spmm_transpose_graph(const int32_t* rowptr, const int32_t* colidx, const 
  *   rowptr            the ORIGINAL graph's row pointers [N+1]
  *   t_ptr .. t_pinv   as written by es_spmm_transpose_graph for that graph (t_end
  *                     is not needed)
- *   t_rows            [2 * N] int32, 8-byte aligned, scratch: every call
- *                     overwrites it with each row's (length, rotation) for this
+ *   t_rows            [2 * N] int32, 8-byte aligned, scratch: a call may
+ *                     overwrite it with each row's (length, rotation) for this
  *                     seed; calls that share it must be ordered (same stream)
  *   dY  N rows of F fp32, row stride ldy (input); dX likewise, stride ldx (output,
  *       fully overwritten); they must not overlap

@@ -127,7 +127,7 @@ __device__ __forceinline__ int long_segments(const Args& a, uint32_t bx, LongScr
         if (r < a.N) {
             const int n = a.rowptr[r + 1] - a.rowptr[r];
             const int k = kept_count(a.mode, n, a.W);
-            if (k > a.long_k) nseg[i] = (k + SEG - 1) / SEG;
+            if (k > a.long_k) nseg[i] = (k - 1) / SEG + 1;
         }
         mine += nseg[i];
     }
@@ -174,6 +174,67 @@ __device__ __forceinline__ LongSegment long_segment(const Args& a, uint32_t bx, 
     s.t0 = (task - (lo ? sc.seg_end[lo - 1] : 0)) * SEG;
     s.count = min(s.k - s.t0, SEG);
     return s;
+}
+
+// Long rows of a small product: each is summed by one workgroup, its waves
+// taking 256-slot segments in turn and adding their partial sums through LDS, so
+// that nothing has to be zeroed beforehand (a launch of its own, as long as the
+// whole product at this size).
+template <int G, int CH, int VEC, bool ALIGNED, bool WIDE>
+__device__ __forceinline__ void long_rows_alone(const Args& a, uint32_t bx, uint32_t by, uint2* lds, LongScratch& sc)
+{
+    constexpr int LOG_G = ilog2(G);
+    constexpr int E = kWaveSize / G;
+    constexpr int FB = G * CH * VEC;
+    using P = Pack<VEC, ALIGNED>;
+    static_assert(FB * sizeof(float) <= kWaveTileStride * sizeof(uint2), "a wave's partial row fits its tile");
+    const int total = long_segments<(1 << 30)>(a, bx, sc);   // rows of up to 2^30 entries: one segment each
+    if (total == 0) return;
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    const int wave = threadIdx.x >> 6;
+    const int e = lane >> LOG_G;
+    const int l = lane & (G - 1);
+    uint2* tile = lds + wave * kWaveTileStride;
+    LaneCols<G, CH, VEC, ALIGNED> cols;
+    cols.init(blockIdx.y * FB, l, a.F);
+    for (int task = by; task < total; task += kLongSplit) {
+        const LongSegment sg = long_segment<(1 << 30)>(a, bx, task, sc);
+        P acc[CH];
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) acc[ch].zero();
+        for (int t0 = wave * kLongSeg; t0 < sg.count; t0 += kWavesPerBlock * kLongSeg) {
+            const int count = min(sg.count - t0, kLongSeg);
+            RowSampler sampler;
+            sampler.init(a.mode, a.seed, sg.r, (uint32_t)sg.n, (uint32_t)a.W, (uint32_t)(t0 + lane), kWaveSize);
+            stage_tile<ALIGNED, WIDE>(sampler, lane, kWaveSize, count, sg.base, a.colidx, a.vals, a.stride_units, tile);
+            wave_lds_fence();
+            consume_tile<G, CH, VEC, ALIGNED, WIDE>(tile, count, e, E, a.X, a.ldx, cols, acc);
+            wave_lds_fence();
+        }
+#pragma unroll
+        for (int m = G; m < kWaveSize; m <<= 1) {
+#pragma unroll
+            for (int ch = 0; ch < CH; ++ch) acc[ch].add_xor(m);
+        }
+        P* part = reinterpret_cast<P*>(tile) + l;
+        if (e == 0) {
+#pragma unroll
+            for (int ch = 0; ch < CH; ++ch) part[ch * G] = acc[ch];
+        }
+        __syncthreads();
+        if (wave == 0 && e == 0) {
+            const float f = row_factor(a.norm, sg.n, sg.k);
+            float* y = a.Y + sg.r * (int64_t)a.ldy;
+#pragma unroll
+            for (int ch = 0; ch < CH; ++ch) {
+                for (int w = 1; w < kWavesPerBlock; ++w)
+                    acc[ch].add(*(reinterpret_cast<P*>(lds + w * kWaveTileStride) + ch * G + l));
+                acc[ch].scale(f);
+                if (cols.ok[ch]) acc[ch].store(y + cols.off[ch], cols.first[ch]);
+            }
+        }
+        __syncthreads();
+    }
 }
 
 template <int G, int CH, int VEC, bool ALIGNED, bool BACKWARD, bool WIDE>
@@ -251,6 +312,12 @@ __global__ void __launch_bounds__(kBlockThreads) es_spmm_kernel(const Args a)
     __shared__ LongScratch long_scratch;
 
     if (blockIdx.x < a.long_blocks) {
+        if constexpr (!BACKWARD) {
+            if (a.long_alone) {
+                long_rows_alone<G, CH, VEC, ALIGNED, WIDE>(a, blockIdx.x / kLongSplit, blockIdx.x % kLongSplit, lds, long_scratch);
+                return;
+            }
+        }
         long_block<G, CH, VEC, ALIGNED, BACKWARD, WIDE>(a, blockIdx.x / kLongSplit, blockIdx.x % kLongSplit,
                                                   lds, long_scratch);
         return;

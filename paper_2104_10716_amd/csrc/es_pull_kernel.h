@@ -97,6 +97,14 @@ es_pull_rows_kernel(const int32_t* __restrict__ rowptr, const int32_t* __restric
     rows[r] = make_int2((int)n, (int)shift);
 }
 
+// A row's length and rotation are only needed for a rotated FastRand (seed != 0)
+// and for the row factor: without rotation the stored slot (or entry number) is
+// below n, so "n <= W or slot < W" is just "slot < W".
+__host__ __device__ __forceinline__ bool pull_needs_rows(int32_t mode, uint64_t seed, int32_t norm)
+{
+    return (mode == ES_FASTRAND && seed != 0) || norm != ES_NORM_NONE;
+}
+
 // One wave per output row c, E = 64 / G edge slots.  Stage 1 reads the row's
 // transposed entries 64 at a time, tests them, and packs the kept ones
 // (row of dY as its key, value times the forward row factor) into the LDS tile;
@@ -139,7 +147,7 @@ es_pull_kernel(const Args a, const int32_t* __restrict__ t_ptr, const int32_t* _
     // kPullChunks * 64 entries per pass: all their loads are issued before the
     // first test, so that one pass costs two memory round trips, not sixteen
     constexpr int kPullChunks = 8;
-    const bool need_rows = (a.mode == ES_FASTRAND && a.seed != 0) || a.norm != ES_NORM_NONE;
+    const bool need_rows = pull_needs_rows(a.mode, a.seed, a.norm);
     int fill = 0;
     for (int j0 = 0; j0 < count; j0 += kPullChunks * kWaveSize) {
         int32_t r[kPullChunks], pick[kPullChunks];
@@ -154,9 +162,6 @@ es_pull_kernel(const Args a, const int32_t* __restrict__ t_ptr, const int32_t* _
             v[q] = t_vals[j];
             pick[q] = a.mode == ES_BUCKET ? t_idx[j] : a.mode == ES_FASTRAND ? t_slot[j] : 0;
         }
-        // A row's length and rotation are only needed for a rotated FastRand
-        // (seed != 0) and for the row factor: without rotation the stored slot
-        // (or entry number) is below n, so "n <= W or slot < W" is just "slot < W".
         int2 info[kPullChunks];
 #pragma unroll
         for (int q = 0; q < kPullChunks; ++q) info[q] = need_rows ? rows[r[q]] : make_int2(INT32_MAX, 0);

@@ -122,7 +122,7 @@ int pick_logR(const Shape& s, double mean_kept)
 template <int G, int CH, int VEC, bool ALIGNED, bool WIDE>
 hipError_t launch_forward(const Args& a, dim3 grid, hipStream_t st)
 {
-    if (a.long_blocks > 0) {
+    if (a.long_blocks > 0 && !a.long_alone) {
         const uint32_t zb = (uint32_t)((a.N + kBlockThreads - 1) / kBlockThreads);
         hipLaunchKernelGGL(es_zero_long_rows_kernel, dim3(zb), dim3(kBlockThreads), 0, st, a);
         const hipError_t err = hipGetLastError();
@@ -255,6 +255,7 @@ struct Plan {
     int64_t per_xcd;           // row workgroups per XCD
     int64_t grid_x, grid_y;    // launch grid (long-row workgroups included in grid_x)
     int64_t long_blocks;       // leading long-row workgroups
+    bool long_alone;           // ... each long row in one of them
     bool partition;            // column-partitioned product (kParts phases, needs a workspace)
     bool flat;                 // flattened kernel (es_flat_kernel.h) instead of the row kernel
 };
@@ -413,6 +414,10 @@ int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool a
     const bool may_be_long = mode == ES_FULL || W > p->long_k;
     p->long_blocks = may_be_long ? ((N + kLongScanRows - 1) / kLongScanRows) * kLongSplit : 0;
     p->grid_x = p->per_xcd * kNumXcd + p->long_blocks;
+    // A long row in one workgroup saves the launch that zeroes such rows (2.5 us on
+    // the host, 0.5 us on the GPU) and costs at worst -- one row holding all the
+    // entries -- about 4 F bytes per entry at 27 GB/s: 40 us at this bound.
+    p->long_alone = !backward && !p->flat && entries * F <= 262144.0;
     if (p->partition && p->flat) {                         // one sweep per launch, no long-piece handling
         p->long_k = INT32_MAX;
         p->long_blocks = 0;
@@ -484,6 +489,7 @@ int es_run(const int32_t* rowptr, const int32_t* colidx, const float* vals, cons
     a.mode = mode; a.logR = p.logR; a.norm = norm; a.long_k = p.long_k;
     a.nblocks = (uint32_t)p.nblocks; a.blocks_per_xcd = (uint32_t)p.per_xcd;
     a.long_blocks = (uint32_t)p.long_blocks;
+    a.long_alone = p.long_alone ? 1 : 0;
     a.cuts = nullptr; a.part_cols = 0; a.phase = 0;
 
     const dim3 grid((uint32_t)p.grid_x, (uint32_t)p.grid_y);
@@ -753,7 +759,7 @@ int es_spmm_backward_pull(const int32_t* rowptr, const int32_t* t_ptr, const int
     a.mode = mode; a.logR = 0; a.norm = norm; a.long_k = INT32_MAX;
     const int64_t nblocks = (N + kWavesPerBlock - 1) / kWavesPerBlock;
     const int64_t per_xcd = (nblocks + kNumXcd - 1) / kNumXcd;
-    a.nblocks = (uint32_t)nblocks; a.blocks_per_xcd = (uint32_t)per_xcd; a.long_blocks = 0;
+    a.nblocks = (uint32_t)nblocks; a.blocks_per_xcd = (uint32_t)per_xcd; a.long_blocks = 0; a.long_alone = 0;
     a.cuts = nullptr; a.part_cols = 0; a.phase = 0;
     const int cols_per_block = s.G * s.CH * s.vec;
     const int64_t grid_y = ((int64_t)F + cols_per_block - 1) / cols_per_block;
@@ -767,9 +773,11 @@ int es_spmm_backward_pull(const int32_t* rowptr, const int32_t* t_ptr, const int
     int2* rows = reinterpret_cast<int2*>(t_rows);
     const int64_t rb = (N + kBlockThreads - 1) / kBlockThreads;
     if (rb > INT32_MAX) return ES_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(es_pull_rows_kernel, dim3((uint32_t)rb), dim3(kBlockThreads), 0, st, rowptr, t_pinv, N,
-                       mode, seed, a.W, rows);
-    if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
+    if (pull_needs_rows(mode, seed, norm)) {
+        hipLaunchKernelGGL(es_pull_rows_kernel, dim3((uint32_t)rb), dim3(kBlockThreads), 0, st, rowptr, t_pinv, N,
+                           mode, seed, a.W, rows);
+        if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
+    }
     bool launched = false;
 #define ES_PULL(G_, CH_, V_, A_)                                                                     \
     if (s.G == G_ && s.CH == CH_ && s.vec == V_ && s.aligned == A_) {                                \

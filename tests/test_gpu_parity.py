@@ -406,6 +406,38 @@ def test_flattened_kernel_bursts_and_shares(es, F, lanes):
                                  opts=dict(kernel=2, long_row_threshold=thr))
 
 
+@pytest.mark.parametrize("F,lengths", [
+    (3, [5000, 1025, 1024, 1023, 257, 256, 255, 65, 64, 0, 1]), (16, [5000, 1025, 1024, 1023, 257, 256, 0, 65, 64, 1]),
+    (41, [1300, 1024, 257, 256, 65]), (64, [1100, 257, 256, 65, 0]), (130, [1040, 300, 65]), (602, [300, 70])])
+def test_long_rows_of_a_small_product(es, F, lengths):
+    """Entries * F below 2^18: a long row is one workgroup's (segments of 256 dealt
+    to four waves, partial sums added through LDS), and nothing is zeroed first;
+    the same rows through the split-and-atomics form (a larger nnz hint)."""
+    import torch
+    from gpu_util import DeviceCSR, check_against_oracle, check_Y
+    import oracle
+    n = 6000
+    rng = np.random.default_rng(F)
+    cols = [np.sort(rng.choice(n, size=L, replace=False)) for L in lengths]
+    rowptr = np.zeros(n + 1, dtype=np.int32)
+    at = rng.permutation(n)[:len(lengths)]
+    counts = np.zeros(n, dtype=np.int64)
+    counts[at] = [len(c) for c in cols]
+    rowptr[1:] = np.cumsum(counts)
+    colidx = np.concatenate([c for _, c in sorted(zip(at, cols), key=lambda t: t[0])]).astype(np.int32)
+    assert colidx.size * F <= 262144
+    d = DeviceCSR(rowptr, colidx, rng.standard_normal(colidx.size).astype(np.float32),
+                  rng.uniform(-1, 1, (n, F)).astype(np.float32))
+    for mode, W in (("full", 0), ("bucket", 1100), ("fastrand", 290)):
+        for norm in ("none", "mean"):
+            check_against_oracle(d, W, mode, 5, norm=norm, what=f"{mode} W={W} F={F} {norm}", opts=dict(long_row_threshold=64))
+            Y = torch.full((n, F), float("nan"), device=d.X.device)
+            es.es_spmm_ex(d.rowptr, d.colidx, d.vals, d.X, Y, W, mode, 5, norm, dict(long_row_threshold=64), nnz=10_000_000)
+            torch.cuda.synchronize()
+            ref, den = oracle.spmm(d.h_rowptr, d.h_colidx, d.h_vals, d.h_X, F, W, mode, 5, norm=norm)
+            check_Y(Y.cpu().numpy(), ref, den, f"split {mode} W={W} F={F} {norm}")
+
+
 def test_degenerate_inputs(es):
     import torch
     from gpu_util import DeviceCSR, check_against_oracle
