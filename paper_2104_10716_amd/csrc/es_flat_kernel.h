@@ -438,7 +438,7 @@ __global__ void __launch_bounds__(kBlockThreads) es_spmm_flat_kernel(const Args 
     __shared__ __align__(16) FlatLds<G, RPS> lds;
     __shared__ LongScratch sc;
     if (blockIdx.x < a.long_blocks) {
-        flat_long_block<ALIGNED, WIDE, STRIDED>(a, blockIdx.x / kLongSplit, blockIdx.x % kLongSplit, lds, sc);
+        flat_long_block<ALIGNED, WIDE, STRIDED>(a, blockIdx.x / kLongSplit, long_share(blockIdx.x), lds, sc);
         return;
     }
     const uint32_t b = blockIdx.x - a.long_blocks;

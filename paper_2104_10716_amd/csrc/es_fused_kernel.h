@@ -314,11 +314,11 @@ __global__ void __launch_bounds__(kBlockThreads) es_spmm_kernel(const Args a)
     if (blockIdx.x < a.long_blocks) {
         if constexpr (!BACKWARD) {
             if (a.long_alone) {
-                long_rows_alone<G, CH, VEC, ALIGNED, WIDE>(a, blockIdx.x / kLongSplit, blockIdx.x % kLongSplit, lds, long_scratch);
+                long_rows_alone<G, CH, VEC, ALIGNED, WIDE>(a, blockIdx.x / kLongSplit, long_share(blockIdx.x), lds, long_scratch);
                 return;
             }
         }
-        long_block<G, CH, VEC, ALIGNED, BACKWARD, WIDE>(a, blockIdx.x / kLongSplit, blockIdx.x % kLongSplit,
+        long_block<G, CH, VEC, ALIGNED, BACKWARD, WIDE>(a, blockIdx.x / kLongSplit, long_share(blockIdx.x),
                                                   lds, long_scratch);
         return;
     }
