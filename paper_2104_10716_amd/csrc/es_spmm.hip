@@ -189,12 +189,16 @@ hipError_t launch_backward(const Args& a, dim3 grid, hipStream_t st)
 
 // Longest row one wave may own.  A wave retires about E*U entries per memory
 // round trip (~2 us under load) while the whole launch moves entries*(4F+8)
-// bytes at a few TB/s; the bound keeps one wave's row near 5 % of the launch.
-int32_t pick_long_k(const Shape& s, int logR, double entries, int F)
+// bytes at a few TB/s; the bound keeps one wave's row near 5 % of the launch.  Rows
+// up to four times the mean are never split: on a small dense graph the bound alone
+// would send nearly every row through the atomics (10 k rows, mean 300, F = 32:
+// 63.8 us at a threshold of 64).
+int32_t pick_long_k(const Shape& s, int logR, double entries, int F, double mean)
 {
     const int U = 8 / s.CH;
     const int E = (64 >> logR) / s.G;
-    const double k = (double)E * U * entries * (4.0 * F + 8.0) / 2.4e8;
+    double k = (double)E * U * entries * (4.0 * F + 8.0) / 2.4e8;
+    if (k < 4.0 * mean) k = 4.0 * mean;
     if (k >= (double)(INT32_MAX - kLongMin)) return INT32_MAX;
     const int32_t v = ((int32_t)k / kLongMin) * kLongMin;
     return v < kLongMin ? kLongMin : v;
@@ -395,7 +399,7 @@ int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool a
     // for W above the bound (nnz is a hint, so it does not gate the launch)
     double entries = (double)nnz;
     if (mode != ES_FULL && entries > (double)N * W) entries = (double)N * W;
-    p->long_k = pick_long_k(s, logR, entries, F);
+    p->long_k = pick_long_k(s, logR, entries, F, mean);
     // the long-row part costs a second small launch and a scan of the row
     // pointers; below one tile per row that is more than the tail it removes
     if (mode != ES_FULL && p->long_k < kTileSlots) p->long_k = kTileSlots;
