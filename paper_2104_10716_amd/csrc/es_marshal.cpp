@@ -5,8 +5,11 @@
 // finding the current stream and converting twenty ctypes arguments in Python
 // took another 8 (13 us per call in all; 5 with this module).  Nothing is
 // computed here.  Every function returns the C entry point's status, or None when
-// an argument is not the plain case (wrong type, shape, device or stride): the
-// caller then goes through the checks written in Python, which name the fault.
+// an argument is not the plain case (wrong type, shape, device or stride, or a
+// tensor that throws when asked for its sizes, strides or address: sparse, fake):
+// the caller then goes through the checks written in Python, which name the fault.
+// No exception leaves a function, and the C call runs without the interpreter lock,
+// as a ctypes call does: a launch that waits for room in a queue stops no other thread.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -56,20 +59,33 @@ bool as_stream(PyObject* o, void** out)
     return true;
 }
 
+// `call` (noexcept: every address is read before) without the interpreter lock
+template <class Call>
+PyObject* unlocked(Call&& call)
+{
+    int rc;
+    Py_BEGIN_ALLOW_THREADS
+    rc = call();
+    Py_END_ALLOW_THREADS
+    return PyLong_FromLong(rc);
+}
+
 // What every product has in common: X (gathered) and Y (written), [N x F] with
 // unit column stride, and the sampler's arguments.
 struct Product {
-    const at::Tensor *X, *Y;
+    const float* x;
+    float* y;
     int64_t N;
     int32_t F, ldx, ldy, W, mode, norm;
     uint64_t seed;
     void* stream;
 
-    bool parse(int64_t n, PyObject* x, PyObject* y, PyObject* w, PyObject* m, PyObject* sd, PyObject* nm,
+    bool parse(int64_t n, PyObject* xt, PyObject* yt, PyObject* w, PyObject* m, PyObject* sd, PyObject* nm,
                PyObject* f, PyObject* st)
     {
         N = n;
-        if (!as_tensor(x, at::kFloat, &X) || !as_tensor(y, at::kFloat, &Y)) return false;
+        const at::Tensor *X, *Y;
+        if (!as_tensor(xt, at::kFloat, &X) || !as_tensor(yt, at::kFloat, &Y)) return false;
         if (X->dim() != 2 || Y->dim() != 2 || X->stride(1) != 1 || Y->stride(1) != 1) return false;
         if (X->size(0) != N || Y->size(0) != N) return false;
         int32_t cols = 0;
@@ -84,6 +100,8 @@ struct Product {
         const int64_t lx = N > 1 ? X->stride(0) : std::max<int64_t>(X->size(1), 1);
         const int64_t ly = N > 1 ? Y->stride(0) : std::max<int64_t>(Y->size(1), 1);
         if (lx > INT32_MAX || ly > INT32_MAX || lx < 0 || ly < 0) return false;
+        x = static_cast<const float*>(X->data_ptr());
+        y = static_cast<float*>(Y->data_ptr());
         F = cols; ldx = (int32_t)lx; ldy = (int32_t)ly;
         if (!as_code(w, nullptr, 0, &W) || !as_code(m, kModes, 3, &mode) || !as_code(nm, kNorms, 5, &norm)) return false;
         if (!PyLong_Check(sd)) return false;
@@ -154,9 +172,10 @@ PyObject* spmm(PyObject*, PyObject* const* a, Py_ssize_t n)
         ws = t.data_ptr();
         ws_bytes = t.nbytes();
     }
-    return PyLong_FromLong(g_spmm_ws(g.rowptr, g.colidx, g.vals, static_cast<const float*>(p.X->data_ptr()),
-                                     static_cast<float*>(p.Y->data_ptr()), g.N, g.nnz, p.F, p.ldx, p.ldy, p.W,
-                                     p.mode, p.seed, p.norm, nullptr, ws, ws_bytes, p.stream));
+    return unlocked([&] {
+        return g_spmm_ws(g.rowptr, g.colidx, g.vals, p.x, p.y, g.N, g.nnz, p.F, p.ldx, p.ldy, p.W, p.mode, p.seed,
+                         p.norm, nullptr, ws, ws_bytes, p.stream);
+    });
 }
 
 // backward(rowptr, colidx, vals, dY, dX, W, mode, seed, norm, F, stream, nnz)
@@ -167,9 +186,10 @@ PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (n != 12 || !g_backward || !g.parse(a[0], a[1], a[2], a[11]) ||
         !p.parse(g.N, a[3], a[4], a[5], a[6], a[7], a[8], a[9], a[10]))
         Py_RETURN_NONE;
-    return PyLong_FromLong(g_backward(g.rowptr, g.colidx, g.vals, static_cast<const float*>(p.X->data_ptr()),
-                                      static_cast<float*>(p.Y->data_ptr()), g.N, g.nnz, p.F, p.ldx, p.ldy, p.W,
-                                      p.mode, p.seed, p.norm, p.stream));
+    return unlocked([&] {
+        return g_backward(g.rowptr, g.colidx, g.vals, p.x, p.y, g.N, g.nnz, p.F, p.ldx, p.ldy, p.W, p.mode, p.seed,
+                          p.norm, p.stream);
+    });
 }
 
 // pull(rowptr, t, dY, dX, W, mode, seed, norm, F, stream); t: the dict of es_spmm_transpose_graph
@@ -185,14 +205,30 @@ PyObject* pull(PyObject*, PyObject* const* a, Py_ssize_t n)
     }
     const int64_t N = rp->numel() - 1;
     if (!p.parse(N, a[2], a[3], a[4], a[5], a[6], a[7], a[8], a[9])) Py_RETURN_NONE;
-    auto ints = [](const at::Tensor* x) { return static_cast<int32_t*>(x->data_ptr()); };
-    return PyLong_FromLong(g_pull(ints(rp), ints(t[0]), ints(t[1]), ints(t[2]), ints(t[3]),
-                                  static_cast<const float*>(t[4]->data_ptr()), ints(t[5]), ints(t[6]),
-                                  static_cast<const float*>(p.X->data_ptr()), static_cast<float*>(p.Y->data_ptr()), N,
-                                  t[1]->numel(), p.F, p.ldx, p.ldy, p.W, p.mode, p.seed, p.norm, p.stream));
+    int32_t* q[7];
+    for (int i = 0; i < 7; ++i) q[i] = i == 4 ? nullptr : static_cast<int32_t*>(t[i]->data_ptr());
+    const float* t_vals = static_cast<const float*>(t[4]->data_ptr());
+    const int32_t* rowptr = static_cast<const int32_t*>(rp->data_ptr());
+    const int64_t nnz = t[1]->numel();
+    return unlocked([&] {
+        return g_pull(rowptr, q[0], q[1], q[2], q[3], t_vals, q[5], q[6], p.x, p.y, N, nnz, p.F, p.ldx, p.ldy, p.W,
+                      p.mode, p.seed, p.norm, p.stream);
+    });
 }
 
-#define ES_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL, nullptr}
+// `f`, with anything its tensors throw turned into None
+template <PyObject* (*f)(PyObject*, PyObject* const*, Py_ssize_t)>
+PyObject* guarded(PyObject* self, PyObject* const* a, Py_ssize_t n)
+{
+    try {
+        return f(self, a, n);
+    } catch (...) {
+        PyErr_Clear();
+        Py_RETURN_NONE;
+    }
+}
+
+#define ES_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(guarded<f>)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {ES_METHOD(bind), ES_METHOD(spmm), ES_METHOD(backward), ES_METHOD(pull), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_es_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

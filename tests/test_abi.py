@@ -127,3 +127,26 @@ def test_no_process_wide_settings_are_exported(lib):
     for name in ("es_spmm_set_rows_per_wave", "es_spmm_set_lanes_per_row", "es_spmm_set_long_row_threshold"):
         assert not hasattr(lib, name), name
     assert not [n for n in _declared_functions() if "_set_" in n]
+
+
+def test_native_marshalling_hands_back_what_it_cannot_read():
+    """Tensors that throw when asked for an address or a stride (fake, sparse) and
+    arguments of other types come back as None, not as an exception or an abort.
+    Fake tensors call themselves device tensors without a GPU."""
+    import torch
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    import paper_2104_10716_amd as es
+    m = es.load_marshal()
+    with FakeTensorMode():
+        i32 = dict(dtype=torch.int32, device="cuda")
+        rowptr, colidx = torch.empty(5, **i32), torch.empty(8, **i32)
+        X, Y = torch.empty(4, 16, device="cuda"), torch.empty(4, 16, device="cuda")
+        t = {k: torch.empty(8, **i32) for k in ("t_ptr", "t_row", "t_idx", "t_slot", "t_pinv", "t_rows")}
+        t["t_vals"] = torch.empty(8, device="cuda")
+        assert m.spmm(rowptr, colidx, None, X, Y, 4, "full", 0, "none", None, None, None, None) is None
+        assert m.backward(rowptr, colidx, None, X, Y, 4, "full", 0, "none", None, None, None) is None
+        assert m.pull(rowptr, t, X, Y, 4, "full", 0, "none", None, None) is None
+    sparse = torch.eye(4).to_sparse()
+    assert m.spmm(rowptr, colidx, None, sparse, sparse, 4, "full", 0, "none", None, None, None, None) is None
+    for bad in (None, 3, "x", [1]):
+        assert m.spmm(bad, colidx, None, X, Y, 4, "full", 0, "none", None, None, None, None) is None
