@@ -2,6 +2,8 @@
 #ifndef ES_SPMM_FLAT_KERNEL_H
 #define ES_SPMM_FLAT_KERNEL_H
 
+#include <type_traits>
+
 #include "es_fused_kernel.h"
 
 namespace {
@@ -182,7 +184,8 @@ __device__ __forceinline__ void flat_run(const Args& a, const FlatRow& row, int 
     const int c_in = c_entry & (BE - 1);
     const int32_t* get_col = s.col + e * 4;
     const float* get_val = s.val + e * 4;
-    const uint32_t stride = (uint32_t)a.ldx * 4u;
+    using Stride = std::conditional_t<WIDE, uint64_t, uint32_t>;   // bytes from one row of X to the next: up to 33 bits
+    const Stride stride = (Stride)a.ldx * 4u;
     const uint32_t load_at = (uint32_t)cols.off[0] * 4u;
     const char* X = reinterpret_cast<const char*>(a.X);
 
@@ -195,7 +198,7 @@ __device__ __forceinline__ void flat_run(const Args& a, const FlatRow& row, int 
             for (int u = 0; u < 4; ++u) {
                 const uint32_t c = (uint32_t)(&col.x)[u];
                 if constexpr (WIDE)
-                    bt.x[4 * q + u].load(reinterpret_cast<const float*>(X + (uint64_t)c * stride + load_at));
+                    bt.x[4 * q + u].load(reinterpret_cast<const float*>(X + (c * stride + load_at)));
                 else
                     bt.x[4 * q + u].load(reinterpret_cast<const float*>(X + (uint32_t)(__umul24(c, stride) + load_at)));
             }

@@ -278,6 +278,37 @@ def test_row_offsets_beyond_32_bits(es, ld):
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("ld", [1 << 30, (1 << 30) + 1, (1 << 30) + 1024])
+def test_row_strides_whose_bytes_exceed_32_bits(es, ld):
+    """Row strides of 4 GiB and a little more (the C ABI takes any 31-bit ldx):
+    the bytes from one row of X to the next do not fit 32 bits either.  Three
+    rows, 8.6 GB touched sparsely, every forward kernel."""
+    import torch
+    import oracle
+    from gpu_util import check_Y
+    n, F = 3, 16
+    rowptr = np.array([0, 3, 4, 6], dtype=np.int32)
+    colidx = np.array([0, 1, 2, 1, 0, 2], dtype=np.int32)
+    rng = np.random.default_rng(ld % 97)
+    vals = rng.standard_normal(6).astype(np.float32)
+    Xh = rng.uniform(-1, 1, (n, F)).astype(np.float32)
+    dev = "cuda:0"
+    X = torch.empty((n - 1) * ld + F, dtype=torch.float32, device=dev).as_strided((n, F), (ld, 1))
+    X.copy_(torch.from_numpy(Xh))
+    rp, ci, va = (torch.from_numpy(a).to(dev) for a in (rowptr, colidx, vals))
+    for kernel in (0, 1, 2):
+        for mode, W, thr in (("full", 0, 0), ("full", 0, 2), ("bucket", 2, 0), ("fastrand", 2, 0), ("fastrand", 2, 1)):
+            what = f"ld={ld} kernel={kernel} {mode} W={W} long rows above {thr}"
+            _say(what)
+            Y = torch.full((n, F), float("nan"), device=dev)
+            es.es_spmm_ex(rp, ci, va, X, Y, W, mode, 3, "none", dict(kernel=kernel, long_row_threshold=thr))
+            torch.cuda.synchronize()
+            Yref, den = oracle.spmm(rowptr, colidx, vals, Xh, F, W, mode, 3)
+            check_Y(Y.cpu().numpy(), Yref, den, what)
+    del X
+    torch.cuda.empty_cache()
+
+
 def test_long_rows_span_several_tiles(es):
     """Rows far longer than one LDS tile (full mode and W above the tile),
     including lengths that are multiples of 577 where the multiplier changes."""
