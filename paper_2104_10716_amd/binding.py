@@ -156,7 +156,10 @@ def _dev_ptr(t, dtype, name):
         raise ValueError(f"{name} must be a device tensor")
     if t.dtype != dtype:
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
-    return t.data_ptr() or None
+    ptr = t.data_ptr()
+    if not ptr and name == "vals" and t.numel():        # null there means an unweighted graph
+        raise ValueError("vals has no device memory (a fake tensor, or a freed storage)")
+    return ptr or None
 
 
 def es_spmm_status_string(status: int) -> str:

@@ -6,8 +6,8 @@
 // took another 8 (13 us per call in all; 5 with this module).  Nothing is
 // computed here.  Every function returns the C entry point's status, or None when
 // an argument is not the plain case (wrong type, shape, device or stride, or a
-// tensor that throws when asked for its sizes, strides or address: sparse, fake):
-// the caller then goes through the checks written in Python, which name the fault.
+// tensor without memory of its own: sparse, fake, a wrapper): the caller then goes
+// through the checks written in Python, which name the fault.
 // No exception leaves a function, and the C call runs without the interpreter lock,
 // as a ctypes call does: a launch that waits for room in a queue stops no other thread.
 #define PY_SSIZE_T_CLEAN
@@ -24,11 +24,20 @@ decltype(&es_spmm_ws) g_spmm_ws = nullptr;
 decltype(&es_spmm_backward) g_backward = nullptr;
 decltype(&es_spmm_backward_pull) g_pull = nullptr;
 
+// Strided, with a storage that holds its elements, and not a Python-dispatched
+// wrapper.  A fake tensor calls itself a device tensor and answers with a null
+// address, which as `vals` would mean an unweighted graph.
+bool has_memory(const at::Tensor& t)
+{
+    return t.defined() && t.layout() == at::kStrided && !t.unsafeGetTensorImpl()->is_python_dispatch() &&
+           t.has_storage() && (t.data_ptr() || t.numel() == 0);
+}
+
 bool as_tensor(PyObject* o, at::ScalarType type, const at::Tensor** out)
 {
     if (!THPVariable_Check(o)) return false;
     const at::Tensor& t = THPVariable_Unpack(o);
-    if (!t.is_cuda() || t.scalar_type() != type) return false;
+    if (!t.is_cuda() || t.scalar_type() != type || !has_memory(t)) return false;
     *out = &t;
     return true;
 }
@@ -168,7 +177,7 @@ PyObject* spmm(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (a[9] != Py_None) {
         if (!THPVariable_Check(a[9])) Py_RETURN_NONE;
         const at::Tensor& t = THPVariable_Unpack(a[9]);
-        if (!t.is_cuda() || !t.is_contiguous()) Py_RETURN_NONE;
+        if (!t.is_cuda() || !has_memory(t) || !t.is_contiguous()) Py_RETURN_NONE;
         ws = t.data_ptr();
         ws_bytes = t.nbytes();
     }
@@ -216,6 +225,13 @@ PyObject* pull(PyObject*, PyObject* const* a, Py_ssize_t n)
     });
 }
 
+// readable(tensor): whether has_memory holds
+PyObject* readable(PyObject*, PyObject* const* a, Py_ssize_t n)
+{
+    if (n != 1 || !THPVariable_Check(a[0])) Py_RETURN_FALSE;
+    return PyBool_FromLong(has_memory(THPVariable_Unpack(a[0])));
+}
+
 // `f`, with anything its tensors throw turned into None
 template <PyObject* (*f)(PyObject*, PyObject* const*, Py_ssize_t)>
 PyObject* guarded(PyObject* self, PyObject* const* a, Py_ssize_t n)
@@ -229,7 +245,8 @@ PyObject* guarded(PyObject* self, PyObject* const* a, Py_ssize_t n)
 }
 
 #define ES_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(guarded<f>)), METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {ES_METHOD(bind), ES_METHOD(spmm), ES_METHOD(backward), ES_METHOD(pull), {nullptr, nullptr, 0, nullptr}};
+PyMethodDef methods[] = {ES_METHOD(bind), ES_METHOD(spmm), ES_METHOD(backward), ES_METHOD(pull), ES_METHOD(readable),
+                         {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_es_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

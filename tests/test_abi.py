@@ -130,9 +130,10 @@ def test_no_process_wide_settings_are_exported(lib):
 
 
 def test_native_marshalling_hands_back_what_it_cannot_read():
-    """Tensors that throw when asked for an address or a stride (fake, sparse) and
-    arguments of other types come back as None, not as an exception or an abort.
-    Fake tensors call themselves device tensors without a GPU."""
+    """Tensors without memory of their own (fake, sparse, wrapped by a transform, a
+    freed storage) are recognised before an address is taken from them, and the
+    calls come back as None, not as an exception or an abort.  Fake tensors call
+    themselves device tensors without a GPU and answer with a null address."""
     import torch
     from torch._subclasses.fake_tensor import FakeTensorMode
     import paper_2104_10716_amd as es
@@ -140,13 +141,29 @@ def test_native_marshalling_hands_back_what_it_cannot_read():
     with FakeTensorMode():
         i32 = dict(dtype=torch.int32, device="cuda")
         rowptr, colidx = torch.empty(5, **i32), torch.empty(8, **i32)
+        vals, none = torch.empty(8, device="cuda"), torch.empty(0, device="cuda")
         X, Y = torch.empty(4, 16, device="cuda"), torch.empty(4, 16, device="cuda")
         t = {k: torch.empty(8, **i32) for k in ("t_ptr", "t_row", "t_idx", "t_slot", "t_pinv", "t_rows")}
         t["t_vals"] = torch.empty(8, device="cuda")
-        assert m.spmm(rowptr, colidx, None, X, Y, 4, "full", 0, "none", None, None, None, None) is None
+        coo = torch.sparse_coo_tensor(torch.zeros(2, 1, dtype=torch.long), torch.ones(1), (4, 16), device="cuda")
+        for x in (rowptr, vals, none, X, coo):
+            assert x.is_cuda and not m.readable(x)
+        assert m.spmm(rowptr, colidx, vals, X, Y, 4, "full", 0, "none", None, None, None, None) is None
+        assert m.spmm(rowptr, colidx, None, coo, coo, 4, "full", 0, "none", None, None, None, None) is None
         assert m.backward(rowptr, colidx, None, X, Y, 4, "full", 0, "none", None, None, None) is None
         assert m.pull(rowptr, t, X, Y, 4, "full", 0, "none", None, None) is None
-    sparse = torch.eye(4).to_sparse()
-    assert m.spmm(rowptr, colidx, None, sparse, sparse, 4, "full", 0, "none", None, None, None, None) is None
+        # a null `vals` means an unweighted graph: the checks in Python refuse it too
+        with pytest.raises(ValueError, match="vals"):
+            es.binding._dev_ptr(vals, torch.float32, "vals")
+    freed = torch.ones(4)
+    freed.untyped_storage().resize_(0)
+    for x in (torch.eye(4).to_sparse(), torch.empty(3, device="meta"), freed, None, 3):
+        assert not m.readable(x)
+    for x in (torch.eye(4), torch.eye(4)[1:, 2:], torch.empty(0), torch.nn.Parameter(torch.eye(2))):
+        assert m.readable(x)
+    seen = []
+    torch.vmap(lambda a: (seen.append(m.readable(a)), a * 1)[1])(torch.ones(3, 2))
+    torch.func.grad(lambda a: (seen.append(m.readable(a)), a.sum())[1])(torch.ones(3))
+    assert seen == [False, False]
     for bad in (None, 3, "x", [1]):
         assert m.spmm(bad, colidx, None, X, Y, 4, "full", 0, "none", None, None, None, None) is None
