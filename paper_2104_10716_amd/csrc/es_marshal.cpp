@@ -42,7 +42,25 @@ bool as_tensor(PyObject* o, at::ScalarType type, const at::Tensor** out)
     return true;
 }
 
-// One of `names`, or an int: its code.
+// A reference that is dropped at the end of the scope.
+struct Owned {
+    PyObject* p;
+    ~Owned() { Py_XDECREF(p); }
+};
+
+// An int, or what converts to one without loss (a NumPy integer); false, with no
+// error left behind, for anything else.
+bool as_long(PyObject* o, long long* out)
+{
+    Owned index{PyNumber_Index(o)};
+    int overflow = 0;
+    if (index.p) *out = PyLong_AsLongLongAndOverflow(index.p, &overflow);
+    if (index.p && !overflow) return true;
+    PyErr_Clear();
+    return false;
+}
+
+// One of `names`, or an integer: its code.
 bool as_code(PyObject* o, const char* const* names, int n, int32_t* out)
 {
     if (PyUnicode_Check(o)) {
@@ -50,22 +68,39 @@ bool as_code(PyObject* o, const char* const* names, int n, int32_t* out)
             if (PyUnicode_CompareWithASCIIString(o, names[i]) == 0) { *out = i; return true; }
         return false;
     }
-    if (!PyLong_Check(o)) return false;
-    int overflow = 0;
-    const long v = PyLong_AsLongAndOverflow(o, &overflow);
-    if (overflow || v < INT32_MIN || v > INT32_MAX) return false;
+    long long v;
+    if (!as_long(o, &v) || v < INT32_MIN || v > INT32_MAX) return false;
     *out = (int32_t)v;
     return true;
+}
+
+// The low 64 bits of an integer.
+bool as_seed(PyObject* o, uint64_t* out)
+{
+    Owned index{PyNumber_Index(o)};
+    if (index.p) *out = PyLong_AsUnsignedLongLongMask(index.p);
+    if (index.p && !PyErr_Occurred()) return true;
+    PyErr_Clear();
+    return false;
 }
 
 const char* const kModes[] = {"full", "bucket", "fastrand"};
 const char* const kNorms[] = {"none", "mean", "rsqrt", "rescale", "inv_degree"};
 
+// None: torch's current stream; an int: the address; else a stream object of torch.
 bool as_stream(PyObject* o, void** out)
 {
-    if (o != Py_None) return false;
-    *out = c10::hip::getCurrentHIPStream().stream();
-    return true;
+    if (o == Py_None) {
+        *out = c10::hip::getCurrentHIPStream().stream();
+        return true;
+    }
+    Owned address{PyLong_Check(o) ? (Py_INCREF(o), o) : PyObject_GetAttrString(o, "cuda_stream")};
+    if (address.p && PyLong_Check(address.p)) {
+        *out = PyLong_AsVoidPtr(address.p);
+        if (*out || !PyErr_Occurred()) return true;
+    }
+    PyErr_Clear();
+    return false;
 }
 
 // `call` (noexcept: every address is read before) without the interpreter lock
@@ -89,33 +124,34 @@ struct Product {
     uint64_t seed;
     void* stream;
 
-    bool parse(int64_t n, PyObject* xt, PyObject* yt, PyObject* w, PyObject* m, PyObject* sd, PyObject* nm,
-               PyObject* f, PyObject* st)
+    // the scalars first: what they may run (an object's __index__) comes before any address is read
+    bool scalars(PyObject* w, PyObject* m, PyObject* sd, PyObject* nm, PyObject* f, PyObject* st)
+    {
+        F = -1;
+        return as_code(w, nullptr, 0, &W) && as_code(m, kModes, 3, &mode) && as_seed(sd, &seed) &&
+               as_code(nm, kNorms, 5, &norm) && (f == Py_None || (as_code(f, nullptr, 0, &F) && F >= 0)) &&
+               as_stream(st, &stream);
+    }
+
+    bool matrices(int64_t n, PyObject* xt, PyObject* yt)
     {
         N = n;
         const at::Tensor *X, *Y;
         if (!as_tensor(xt, at::kFloat, &X) || !as_tensor(yt, at::kFloat, &Y)) return false;
         if (X->dim() != 2 || Y->dim() != 2 || X->stride(1) != 1 || Y->stride(1) != 1) return false;
         if (X->size(0) != N || Y->size(0) != N) return false;
-        int32_t cols = 0;
-        if (f != Py_None) {
-            if (!as_code(f, nullptr, 0, &cols)) return false;
-        } else if (X->size(1) <= INT32_MAX) {
-            cols = (int32_t)X->size(1);
-        } else {
-            return false;
+        if (F < 0) {
+            if (X->size(1) > INT32_MAX) return false;
+            F = (int32_t)X->size(1);
         }
-        if (cols > X->size(1) || cols > Y->size(1)) return false;
+        if (F > X->size(1) || F > Y->size(1)) return false;
         const int64_t lx = N > 1 ? X->stride(0) : std::max<int64_t>(X->size(1), 1);
         const int64_t ly = N > 1 ? Y->stride(0) : std::max<int64_t>(Y->size(1), 1);
         if (lx > INT32_MAX || ly > INT32_MAX || lx < 0 || ly < 0) return false;
         x = static_cast<const float*>(X->data_ptr());
         y = static_cast<float*>(Y->data_ptr());
-        F = cols; ldx = (int32_t)lx; ldy = (int32_t)ly;
-        if (!as_code(w, nullptr, 0, &W) || !as_code(m, kModes, 3, &mode) || !as_code(nm, kNorms, 5, &norm)) return false;
-        if (!PyLong_Check(sd)) return false;
-        seed = PyLong_AsUnsignedLongLongMask(sd);
-        return as_stream(st, &stream);
+        ldx = (int32_t)lx; ldy = (int32_t)ly;
+        return true;
     }
 };
 
@@ -126,6 +162,8 @@ struct Csr {
 
     bool parse(PyObject* rp, PyObject* ci, PyObject* va, PyObject* nz)
     {
+        int32_t hint = 0;
+        if (nz != Py_None && !as_code(nz, nullptr, 0, &hint)) return false;
         const at::Tensor *r, *c, *v;
         if (!as_tensor(rp, at::kInt, &r) || !as_tensor(ci, at::kInt, &c)) return false;
         N = r->numel() - 1;
@@ -137,11 +175,7 @@ struct Csr {
         }
         rowptr = static_cast<const int32_t*>(r->data_ptr());
         colidx = static_cast<const int32_t*>(c->data_ptr());
-        if (nz != Py_None) {
-            int32_t hint;
-            if (!as_code(nz, nullptr, 0, &hint)) return false;
-            nnz = hint;
-        }
+        if (nz != Py_None) nnz = hint;
         return true;
     }
 };
@@ -169,8 +203,8 @@ PyObject* spmm(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     Csr g;
     Product p;
-    if (n != 13 || !g_spmm_ws || !g.parse(a[0], a[1], a[2], a[12]) ||
-        !p.parse(g.N, a[3], a[4], a[5], a[6], a[7], a[8], a[10], a[11]))
+    if (n != 13 || !g_spmm_ws || !p.scalars(a[5], a[6], a[7], a[8], a[10], a[11]) ||
+        !g.parse(a[0], a[1], a[2], a[12]) || !p.matrices(g.N, a[3], a[4]))
         Py_RETURN_NONE;
     void* ws = nullptr;
     size_t ws_bytes = 0;
@@ -192,8 +226,8 @@ PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     Csr g;
     Product p;
-    if (n != 12 || !g_backward || !g.parse(a[0], a[1], a[2], a[11]) ||
-        !p.parse(g.N, a[3], a[4], a[5], a[6], a[7], a[8], a[9], a[10]))
+    if (n != 12 || !g_backward || !p.scalars(a[5], a[6], a[7], a[8], a[9], a[10]) ||
+        !g.parse(a[0], a[1], a[2], a[11]) || !p.matrices(g.N, a[3], a[4]))
         Py_RETURN_NONE;
     return unlocked([&] {
         return g_backward(g.rowptr, g.colidx, g.vals, p.x, p.y, g.N, g.nnz, p.F, p.ldx, p.ldy, p.W, p.mode, p.seed,
@@ -207,13 +241,15 @@ PyObject* pull(PyObject*, PyObject* const* a, Py_ssize_t n)
     static const char* const names[] = {"t_ptr", "t_row", "t_idx", "t_slot", "t_vals", "t_pinv", "t_rows"};
     const at::Tensor *rp, *t[7];
     Product p;
-    if (n != 10 || !g_pull || !as_tensor(a[0], at::kInt, &rp) || !PyDict_Check(a[1])) Py_RETURN_NONE;
+    if (n != 10 || !g_pull || !p.scalars(a[4], a[5], a[6], a[7], a[8], a[9]) || !as_tensor(a[0], at::kInt, &rp) ||
+        !PyDict_Check(a[1]))
+        Py_RETURN_NONE;
     for (int i = 0; i < 7; ++i) {
         PyObject* o = PyDict_GetItemString(a[1], names[i]);
         if (!o || !as_tensor(o, i == 4 ? at::kFloat : at::kInt, &t[i])) Py_RETURN_NONE;
     }
     const int64_t N = rp->numel() - 1;
-    if (!p.parse(N, a[2], a[3], a[4], a[5], a[6], a[7], a[8], a[9])) Py_RETURN_NONE;
+    if (!p.matrices(N, a[2], a[3])) Py_RETURN_NONE;
     int32_t* q[7];
     for (int i = 0; i < 7; ++i) q[i] = i == 4 ? nullptr : static_cast<int32_t*>(t[i]->data_ptr());
     const float* t_vals = static_cast<const float*>(t[4]->data_ptr());

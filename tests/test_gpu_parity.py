@@ -1,6 +1,7 @@
 """GPU parity: the HIP path (through the C ABI) against the CPU oracle on the
 same seeded inputs -- sampled edge lists bit-exact, Y within the normalised
 1e-5 bound.  Needs an MI355X; run with -m gpu."""
+import ctypes
 import functools
 import sys
 
@@ -467,6 +468,48 @@ def test_long_rows_of_a_small_product(es, F, lengths):
             torch.cuda.synchronize()
             ref, den = oracle.spmm(d.h_rowptr, d.h_colidx, d.h_vals, d.h_X, F, W, mode, 5, norm=norm)
             check_Y(Y.cpu().numpy(), ref, den, f"split {mode} W={W} F={F} {norm}")
+
+
+def test_native_marshalling_of_streams_and_integers(es):
+    """Explicit streams (torch streams, raw addresses) and NumPy integers are
+    marshalled natively and mean what they mean in the Python checks: the native
+    call answers 0 and writes the product; what those checks refuse stays refused."""
+    import torch
+    import oracle
+    from gpu_util import check_Y
+    n, F = 500, 16
+    rowptr, colidx, vals, Xh = _random_graph(n, 9.0, seed=3, F=F)
+    rp, ci, va, X = (torch.from_numpy(a).cuda() for a in (rowptr, colidx, vals, Xh))
+    t = es.es_spmm_transpose_graph(rp, ci, va)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    m = es.load_marshal()
+    Yref, den = oracle.spmm(rowptr, colidx, vals, Xh, F, 4, "fastrand", 9)
+    Bref, bden = oracle.spmm_backward(rowptr, colidx, vals, Xh, F, 4, "fastrand", 9)
+    for stream in (None, 0, side, side.cuda_stream, torch.cuda.default_stream()):
+        for W, seed, f, nnz in ((4, 9, None, None), (np.int64(4), np.uint64(9), np.int32(F), np.int64(colidx.size))):
+            what = f"stream {stream!r} {type(W).__name__}"
+            Y = torch.full((n, F), float("nan"), device="cuda")
+            torch.cuda.synchronize()
+            assert m.spmm(rp, ci, va, X, Y, W, "fastrand", seed, np.int8(0), None, f, stream, nnz) == 0, what
+            torch.cuda.synchronize()
+            check_Y(Y.cpu().numpy(), Yref, den, what)
+            assert m.backward(rp, ci, va, X, Y, W, np.int64(2), seed, "none", f, stream, nnz) == 0, what
+            torch.cuda.synchronize()
+            check_Y(Y.cpu().numpy(), Bref, bden, "backward " + what)
+            assert m.pull(rp, t, X, Y, W, "fastrand", seed, "none", f, stream) == 0, what
+            torch.cuda.synchronize()
+            check_Y(Y.cpu().numpy(), Bref, bden, "pull " + what)
+    Y = torch.empty((n, F), device="cuda")
+    for bad in (dict(stream="x"), dict(F=16.5), dict(F=F + 1), dict(F=np.int64(F + 1)), dict(nnz=3.0), dict(stream=1.5)):
+        args = dict(dict(F=None, stream=None, nnz=None), **bad)
+        assert m.spmm(rp, ci, va, X, Y, 4, "bucket", 0, "none", None, args["F"], args["stream"], args["nnz"]) is None, bad
+        with pytest.raises((TypeError, ValueError, AttributeError, ctypes.ArgumentError)):
+            es.es_spmm(rp, ci, va, X, Y, 4, "bucket", **bad)
+    for odd in (dict(W=4.0), dict(W="4"), dict(seed=9.0)):           # what int() takes is still taken
+        es.es_spmm(rp, ci, va, X, Y, odd.get("W", 4), "fastrand", odd.get("seed", 9))
+        torch.cuda.synchronize()
+        check_Y(Y.cpu().numpy(), Yref, den, f"{odd}")
 
 
 def test_degenerate_inputs(es):
