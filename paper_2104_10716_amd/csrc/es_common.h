@@ -47,7 +47,6 @@ struct Args {
     uint32_t nblocks;          // workgroups that carry rows
     uint32_t blocks_per_xcd;   // ceil(nblocks / 8)
     uint32_t long_blocks;      // leading workgroups that run the long-row part
-    int32_t long_alone;        // a long row is one workgroup's: no atomics, Y not zeroed beforehand (row kernel)
     // column-partitioned product only
     const int32_t* cuts;       // [N x kParts]: row r's piece of column range j starts at entry cuts[r][j]
     int32_t part_cols;         // columns per range, ceil(N / kParts)

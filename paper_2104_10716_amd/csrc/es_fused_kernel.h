@@ -105,10 +105,10 @@ struct LongScratch {
     int wave_total[kWavesPerBlock];
 };
 
-// Number of segments of the long rows among the workgroup's 1024 rows; leaves
-// their prefix sums in `sc`.
-template <int SEG>
-__device__ __forceinline__ int long_segments(const Args& a, uint32_t bx, LongScratch& sc)
+// Sum of count(kept entries) over the long rows among the workgroup's 1024 rows;
+// leaves the prefix sums in `sc`.
+template <class Count>
+__device__ __forceinline__ int long_scan(const Args& a, uint32_t bx, LongScratch& sc, Count&& count)
 {
     constexpr int kRowsPerThread = kLongScanRows / kBlockThreads;
     const int tid = threadIdx.x;
@@ -127,7 +127,7 @@ __device__ __forceinline__ int long_segments(const Args& a, uint32_t bx, LongScr
         if (r < a.N) {
             const int n = a.rowptr[r + 1] - a.rowptr[r];
             const int k = kept_count(a.mode, n, a.W);
-            if (k > a.long_k) nseg[i] = (k - 1) / SEG + 1;
+            if (k > a.long_k) nseg[i] = count(k);
         }
         mine += nseg[i];
     }
@@ -151,6 +151,27 @@ __device__ __forceinline__ int long_segments(const Args& a, uint32_t bx, LongScr
     return sc.seg_end[kLongScanRows - 1];
 }
 
+// Number of segments of those rows.
+template <int SEG>
+__device__ __forceinline__ int long_segments(const Args& a, uint32_t bx, LongScratch& sc)
+{
+    return long_scan(a, bx, sc, [](int k) { return (k - 1) / SEG + 1; });
+}
+
+// First of the 1024 rows whose prefix exceeds `task`, in the 16-bit half HALF of
+// the prefix sums or (-1) all of them.
+template <int HALF>
+__device__ __forceinline__ int long_row_of(const LongScratch& sc, int task)
+{
+    int lo = 0, hi = kLongScanRows - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        const int end = HALF < 0 ? sc.seg_end[mid] : (sc.seg_end[mid] >> (16 * HALF)) & 0xFFFF;
+        if (end > task) hi = mid; else lo = mid + 1;
+    }
+    return lo;
+}
+
 // Segment number `task` of the workgroup's long rows.
 struct LongSegment {
     int64_t r;
@@ -161,11 +182,7 @@ struct LongSegment {
 template <int SEG>
 __device__ __forceinline__ LongSegment long_segment(const Args& a, uint32_t bx, int task, const LongScratch& sc)
 {
-    int lo = 0, hi = kLongScanRows - 1;          // first row whose prefix exceeds task
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (sc.seg_end[mid] > task) hi = mid; else lo = mid + 1;
-    }
+    const int lo = long_row_of<-1>(sc, task);
     LongSegment s;
     s.r = (int64_t)bx * kLongScanRows + lo;
     s.base = a.rowptr[s.r];
@@ -176,19 +193,31 @@ __device__ __forceinline__ LongSegment long_segment(const Args& a, uint32_t bx, 
     return s;
 }
 
-// Long rows of a small product: each is summed by one workgroup, its waves
-// taking 256-slot segments in turn and adding their partial sums through LDS, so
-// that nothing has to be zeroed beforehand (a launch of its own, as long as the
-// whole product at this size).
-template <int G, int CH, int VEC, bool ALIGNED, bool WIDE>
+// Long rows of a small product: each is summed by one wave or, above
+// alone_wave_row entries, by one workgroup whose waves take 256-slot segments in
+// turn and add their partial sums through LDS, so that nothing has to be zeroed
+// beforehand (a launch of its own, as long as the whole product at this size).
+// What bounds a row then is the chain of memory round trips of one wave: a
+// segment's entries are all requested at once, and the next segment's before the
+// rows of X of this one (a row of 3999 entries, F = 16: 8.9 us without, 7.3 with).
+// One wave on two segments instead leaves the other three to other rows and costs
+// the row 0.6 us at F = 16, 1.6 at F = 64, 3 at F = 128, so wide rows of more than one
+// segment go to the workgroup.  Many long rows in 1024: 250 of 66 entries, F = 4: 10.8
+// us, split with atomics 17.4; 24 of 257, F = 128: 12.6 and 12.3.
+constexpr int alone_wave_row(int G) { return G < 16 ? 2 * kLongSeg : kLongSeg; }
+
+template <int G, int CH, int VEC, bool ALIGNED>
 __device__ __forceinline__ void long_rows_alone(const Args& a, uint32_t bx, uint32_t by, uint2* lds, LongScratch& sc)
 {
     constexpr int LOG_G = ilog2(G);
     constexpr int E = kWaveSize / G;
     constexpr int FB = G * CH * VEC;
+    constexpr int M = kLongSeg / kWaveSize;
     using P = Pack<VEC, ALIGNED>;
+    using K = RowKey<ALIGNED, false>;
     static_assert(FB * sizeof(float) <= kWaveTileStride * sizeof(uint2), "a wave's partial row fits its tile");
-    const int total = long_segments<(1 << 30)>(a, bx, sc);   // rows of up to 2^30 entries: one segment each
+    // low half: rows of one wave, high half: rows of the workgroup (at most 1024 each)
+    const int total = long_scan(a, bx, sc, [](int k) { return k <= alone_wave_row(G) ? 1 : 1 << 16; });
     if (total == 0) return;
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wave = threadIdx.x >> 6;
@@ -197,18 +226,40 @@ __device__ __forceinline__ void long_rows_alone(const Args& a, uint32_t bx, uint
     uint2* tile = lds + wave * kWaveTileStride;
     LaneCols<G, CH, VEC, ALIGNED> cols;
     cols.init(blockIdx.y * FB, l, a.F);
-    for (int task = by; task < total; task += kLongSplit) {
-        const LongSegment sg = long_segment<(1 << 30)>(a, bx, task, sc);
-        P acc[CH];
+
+    P acc[CH];
+    int n, k;
+    int64_t r;
+    // this wave's part of row `row` of the 1024: segments from slot t0 on, `step` slots apart
+    auto sum_row = [&](int row, uint32_t t0, uint32_t step) {
+        r = (int64_t)bx * kLongScanRows + row;
+        const int64_t base = a.rowptr[r];
+        n = a.rowptr[r + 1] - (int32_t)base;
+        k = kept_count(a.mode, n, a.W);
+        int32_t col[M];
+        float val[M];
+        auto request = [&](uint32_t at) {
+            RowSampler sampler;
+            sampler.init(a.mode, a.seed, r, (uint32_t)n, (uint32_t)a.W, at + lane, kWaveSize);
+            uint32_t entry[M];
+#pragma unroll
+            for (int i = 0; i < M; ++i) entry[i] = min(sampler.next(), (uint32_t)n - 1u);   // past the row: its last
+#pragma unroll
+            for (int i = 0; i < M; ++i) {
+                col[i] = a.colidx[base + entry[i]];
+                val[i] = a.vals ? a.vals[base + entry[i]] : 1.0f;
+            }
+        };
 #pragma unroll
         for (int ch = 0; ch < CH; ++ch) acc[ch].zero();
-        for (int t0 = wave * kLongSeg; t0 < sg.count; t0 += kWavesPerBlock * kLongSeg) {
-            const int count = min(sg.count - t0, kLongSeg);
-            RowSampler sampler;
-            sampler.init(a.mode, a.seed, sg.r, (uint32_t)sg.n, (uint32_t)a.W, (uint32_t)(t0 + lane), kWaveSize);
-            stage_tile<ALIGNED, WIDE>(sampler, lane, kWaveSize, count, sg.base, a.colidx, a.vals, a.stride_units, tile);
+        if (t0 < (uint32_t)k) request(t0);
+        for (; t0 < (uint32_t)k; t0 += step) {
+#pragma unroll
+            for (int i = 0; i < M; ++i)
+                tile[i * kWaveSize + lane] = make_uint2(K::make(col[i], a.stride_units), __float_as_uint(val[i]));
             wave_lds_fence();
-            consume_tile<G, CH, VEC, ALIGNED, WIDE>(tile, count, e, E, a.X, a.ldx, cols, acc);
+            if (t0 + step < (uint32_t)k) request(t0 + step);
+            consume_tile<G, CH, VEC, ALIGNED, false>(tile, min((int)((uint32_t)k - t0), kLongSeg), e, E, a.X, a.ldx, cols, acc);
             wave_lds_fence();
         }
 #pragma unroll
@@ -216,6 +267,23 @@ __device__ __forceinline__ void long_rows_alone(const Args& a, uint32_t bx, uint
 #pragma unroll
             for (int ch = 0; ch < CH; ++ch) acc[ch].add_xor(m);
         }
+    };
+    auto store_row = [&]() {
+        const float f = row_factor(a.norm, n, k);
+        float* y = a.Y + r * (int64_t)a.ldy;
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) {
+            acc[ch].scale(f);
+            if (cols.ok[ch]) acc[ch].store(y + cols.off[ch], cols.first[ch]);
+        }
+    };
+
+    for (int task = by * kWavesPerBlock + wave; task < (total & 0xFFFF); task += kLongSplit * kWavesPerBlock) {
+        sum_row(long_row_of<0>(sc, task), 0, kLongSeg);
+        if (e == 0) store_row();
+    }
+    for (int task = by; task < (total >> 16); task += kLongSplit) {
+        sum_row(long_row_of<1>(sc, task), wave * kLongSeg, kWavesPerBlock * kLongSeg);
         P* part = reinterpret_cast<P*>(tile) + l;
         if (e == 0) {
 #pragma unroll
@@ -223,15 +291,11 @@ __device__ __forceinline__ void long_rows_alone(const Args& a, uint32_t bx, uint
         }
         __syncthreads();
         if (wave == 0 && e == 0) {
-            const float f = row_factor(a.norm, sg.n, sg.k);
-            float* y = a.Y + sg.r * (int64_t)a.ldy;
+            for (int w = 1; w < kWavesPerBlock; ++w)
 #pragma unroll
-            for (int ch = 0; ch < CH; ++ch) {
-                for (int w = 1; w < kWavesPerBlock; ++w)
+                for (int ch = 0; ch < CH; ++ch)
                     acc[ch].add(*(reinterpret_cast<P*>(lds + w * kWaveTileStride) + ch * G + l));
-                acc[ch].scale(f);
-                if (cols.ok[ch]) acc[ch].store(y + cols.off[ch], cols.first[ch]);
-            }
+            store_row();
         }
         __syncthreads();
     }
@@ -312,12 +376,6 @@ __global__ void __launch_bounds__(kBlockThreads) es_spmm_kernel(const Args a)
     __shared__ LongScratch long_scratch;
 
     if (blockIdx.x < a.long_blocks) {
-        if constexpr (!BACKWARD) {
-            if (a.long_alone) {
-                long_rows_alone<G, CH, VEC, ALIGNED, WIDE>(a, blockIdx.x / kLongSplit, long_share(blockIdx.x), lds, long_scratch);
-                return;
-            }
-        }
         long_block<G, CH, VEC, ALIGNED, BACKWARD, WIDE>(a, blockIdx.x / kLongSplit, long_share(blockIdx.x),
                                                   lds, long_scratch);
         return;
@@ -326,6 +384,23 @@ __global__ void __launch_bounds__(kBlockThreads) es_spmm_kernel(const Args a)
     const uint32_t vb = (b % kNumXcd) * a.blocks_per_xcd + b / kNumXcd;
     if (vb >= a.nblocks) return;
     row_block<G, CH, VEC, ALIGNED, BACKWARD, WIDE>(a, vb, lds);
+}
+
+// The same for a small product: a long row is one workgroup's.  A kernel of its
+// own, so that the general one keeps its registers.
+template <int G, int CH, int VEC, bool ALIGNED>
+__global__ void __launch_bounds__(kBlockThreads) es_spmm_small_kernel(const Args a)
+{
+    __shared__ __align__(16) uint2 lds[kWavesPerBlock * kWaveTileStride];   // also holds partial rows, as Packs
+    __shared__ LongScratch long_scratch;
+    if (blockIdx.x < a.long_blocks) {
+        long_rows_alone<G, CH, VEC, ALIGNED>(a, blockIdx.x / kLongSplit, long_share(blockIdx.x), lds, long_scratch);
+        return;
+    }
+    const uint32_t b = blockIdx.x - a.long_blocks;
+    const uint32_t vb = (b % kNumXcd) * a.blocks_per_xcd + b / kNumXcd;
+    if (vb >= a.nblocks) return;
+    row_block<G, CH, VEC, ALIGNED, false, false>(a, vb, lds);
 }
 
 // Zero-fills an [N x F] matrix with row stride ld (the transposed product

@@ -120,9 +120,15 @@ int pick_logR(const Shape& s, double mean_kept)
 }
 
 template <int G, int CH, int VEC, bool ALIGNED, bool WIDE>
-hipError_t launch_forward(const Args& a, dim3 grid, hipStream_t st)
+hipError_t launch_forward(const Args& a, dim3 grid, bool long_alone, hipStream_t st)
 {
-    if (a.long_blocks > 0 && !a.long_alone) {
+    if constexpr (!WIDE) {
+        if (long_alone) {
+            hipLaunchKernelGGL((es_spmm_small_kernel<G, CH, VEC, ALIGNED>), grid, dim3(kBlockThreads), 0, st, a);
+            return hipGetLastError();
+        }
+    }
+    if (a.long_blocks > 0) {
         const uint32_t zb = (uint32_t)((a.N + kBlockThreads - 1) / kBlockThreads);
         hipLaunchKernelGGL(es_zero_long_rows_kernel, dim3(zb), dim3(kBlockThreads), 0, st, a);
         const hipError_t err = hipGetLastError();
@@ -418,10 +424,16 @@ int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool a
     const bool may_be_long = mode == ES_FULL || W > p->long_k;
     p->long_blocks = may_be_long ? ((N + kLongScanRows - 1) / kLongScanRows) * kLongSplit : 0;
     p->grid_x = p->per_xcd * kNumXcd + p->long_blocks;
-    // A long row in one workgroup saves the launch that zeroes such rows (2.5 us on
-    // the host, 0.5 us on the GPU) and costs at worst -- one row holding all the
-    // entries -- about 4 F bytes per entry at 27 GB/s: 40 us at this bound.
-    p->long_alone = !backward && !p->flat && entries * F <= 262144.0;
+    // Long rows without atomics (es_spmm_small_kernel) save the launch that zeroes
+    // such rows (2.5 us on the host, 1.5 us on the GPU) and cost a chain of round
+    // trips per row, so the rule bounds the longest row there can be -- all columns of
+    // a row are different, so min(entries, N) -- and how many there can be.  One row
+    // of n entries, us on the GPU, this form / split with atomics: F = 16: n = 300: 4.8 /
+    // 6.9, 3000: 6.6 / 7.2, 4000: 7.3 / 7.4, 6000: 8.6 / 7.8; F = 64: 1000: 6.4 / 8.8,
+    // 2000: 8.4 / 8.8, 3000: 10.4 / 9.0; no long row at all: 2.8 / 4.3.
+    const double longest = entries < (double)N ? entries : (double)N;
+    p->long_alone = !backward && !p->flat && !p->partition && p->long_blocks > 0 &&
+                    longest * (F + 64.0) <= 262144.0 && entries * (F + 64.0) <= 5.0 * 262144.0;
     if (p->partition && p->flat) {                         // one sweep per launch, no long-piece handling
         p->long_k = INT32_MAX;
         p->long_blocks = 0;
@@ -493,7 +505,6 @@ int es_run(const int32_t* rowptr, const int32_t* colidx, const float* vals, cons
     a.mode = mode; a.logR = p.logR; a.norm = norm; a.long_k = p.long_k;
     a.nblocks = (uint32_t)p.nblocks; a.blocks_per_xcd = (uint32_t)p.per_xcd;
     a.long_blocks = (uint32_t)p.long_blocks;
-    a.long_alone = p.long_alone ? 1 : 0;
     a.cuts = nullptr; a.part_cols = 0; a.phase = 0;
 
     const dim3 grid((uint32_t)p.grid_x, (uint32_t)p.grid_y);
@@ -508,7 +519,7 @@ int es_run(const int32_t* rowptr, const int32_t* colidx, const float* vals, cons
     a.stride_units = wide ? 0u : (uint32_t)stride_units;
 #define ES_LAUNCH(G_, CH_, V_, A_, W_)                                                              \
     (p.partition ? launch_partitioned<G_, CH_, V_, A_, W_>(a, grid, static_cast<int32_t*>(workspace), st) \
-                 : launch_forward<G_, CH_, V_, A_, W_>(a, grid, st))
+                 : launch_forward<G_, CH_, V_, A_, W_>(a, grid, p.long_alone, st))
 #define ES_CASE(G_, CH_, V_, A_)                                                          \
     if (!backward && !p.flat && s.G == G_ && s.CH == CH_ && s.vec == V_ && s.aligned == A_) \
         err = wide ? ES_LAUNCH(G_, CH_, V_, A_, true) : ES_LAUNCH(G_, CH_, V_, A_, false);
@@ -763,7 +774,7 @@ int es_spmm_backward_pull(const int32_t* rowptr, const int32_t* t_ptr, const int
     a.mode = mode; a.logR = 0; a.norm = norm; a.long_k = INT32_MAX;
     const int64_t nblocks = (N + kWavesPerBlock - 1) / kWavesPerBlock;
     const int64_t per_xcd = (nblocks + kNumXcd - 1) / kNumXcd;
-    a.nblocks = (uint32_t)nblocks; a.blocks_per_xcd = (uint32_t)per_xcd; a.long_blocks = 0; a.long_alone = 0;
+    a.nblocks = (uint32_t)nblocks; a.blocks_per_xcd = (uint32_t)per_xcd; a.long_blocks = 0;
     a.cuts = nullptr; a.part_cols = 0; a.phase = 0;
     const int cols_per_block = s.G * s.CH * s.vec;
     const int64_t grid_y = ((int64_t)F + cols_per_block - 1) / cols_per_block;

@@ -439,25 +439,30 @@ def test_flattened_kernel_bursts_and_shares(es, F, lanes):
 
 
 @pytest.mark.parametrize("F,lengths", [
-    (3, [5000, 1025, 1024, 1023, 257, 256, 255, 65, 64, 0, 1]), (16, [5000, 1025, 1024, 1023, 257, 256, 0, 65, 64, 1]),
-    (41, [1300, 1024, 257, 256, 65]), (64, [1100, 257, 256, 65, 0]), (130, [1040, 300, 65]), (602, [300, 70])])
+    (3, [3900, 1025, 1024, 1023, 513, 512, 511, 257, 256, 255, 65, 64, 0, 1]),
+    (16, [3270, 1025, 1024, 1023, 513, 512, 511, 257, 256, 255, 65, 64, 0, 1]), (16, [520] * 20 + [70] * 70),
+    (41, [2490, 1300, 1024, 513, 512, 257, 256, 65]), (64, [2048, 1100, 1025, 513, 512, 257, 256, 65, 0]),
+    (130, [1340, 1040, 513, 512, 300, 257, 256, 65]), (256, [819, 513, 512, 257, 256, 65]),
+    (602, [393, 300, 257, 256, 70, 65])])
 def test_long_rows_of_a_small_product(es, F, lengths):
-    """Entries * F below 2^18: a long row is one workgroup's (segments of 256 dealt
-    to four waves, partial sums added through LDS), and nothing is zeroed first;
-    the same rows through the split-and-atomics form (a larger nnz hint)."""
+    """Within the bounds on the longest row and on the entries a long row is one
+    wave's or one workgroup's (segments of 256 dealt to four waves, partial sums
+    added through LDS) and nothing is zeroed first: row lengths around a segment,
+    two and four, more rows than waves and workgroups share; the same rows through
+    the split-and-atomics form (a larger nnz hint)."""
     import torch
     from gpu_util import DeviceCSR, check_against_oracle, check_Y
     import oracle
-    n = 6000
+    n = 262144 // (F + 64)
     rng = np.random.default_rng(F)
     cols = [np.sort(rng.choice(n, size=L, replace=False)) for L in lengths]
     rowptr = np.zeros(n + 1, dtype=np.int32)
-    at = rng.permutation(n)[:len(lengths)]
+    at = rng.permutation(min(n, 1000))[:len(lengths)]
     counts = np.zeros(n, dtype=np.int64)
     counts[at] = [len(c) for c in cols]
     rowptr[1:] = np.cumsum(counts)
     colidx = np.concatenate([c for _, c in sorted(zip(at, cols), key=lambda t: t[0])]).astype(np.int32)
-    assert colidx.size * F <= 262144
+    assert colidx.size * (F + 64) <= 5 * 262144
     d = DeviceCSR(rowptr, colidx, rng.standard_normal(colidx.size).astype(np.float32),
                   rng.uniform(-1, 1, (n, F)).astype(np.float32))
     for mode, W in (("full", 0), ("bucket", 1100), ("fastrand", 290)):
@@ -468,6 +473,28 @@ def test_long_rows_of_a_small_product(es, F, lengths):
             torch.cuda.synchronize()
             ref, den = oracle.spmm(d.h_rowptr, d.h_colidx, d.h_vals, d.h_X, F, W, mode, 5, norm=norm)
             check_Y(Y.cpu().numpy(), ref, den, f"split {mode} W={W} F={F} {norm}")
+
+
+def test_a_hint_far_below_the_truth_changes_no_result(es):
+    """nnz is a hint: with one of 1000 for a row of 2^30 + 1000 entries the library
+    takes the small-product form, in which such a row is still one task.  Sixteen
+    entries pick the row of ones (on both sides of entry 2^30), the others a row of
+    zeros, so the sum is exact."""
+    import torch
+    n = (1 << 30) + 1000
+    rowptr = torch.tensor([0, n, n], dtype=torch.int32, device="cuda")
+    colidx = torch.zeros(n, dtype=torch.int32, device="cuda")
+    colidx[torch.tensor([0, 63, 255, 256, 1023, 1024, 99_999, (1 << 30) - 1, 1 << 30, (1 << 30) + 1, n - 257, n - 256,
+                         n - 3, n - 2, n - 1, 12_345_678], device="cuda")] = 1
+    X = torch.tensor([[0.0] * 4, [1.0, 2.0, 3.0, 4.0]], device="cuda")
+    for hint in (1000, n):
+        _say(f"row of {n} entries, hint {hint}")
+        Y = torch.full((2, 4), float("nan"), device="cuda")
+        es.es_spmm(rowptr, colidx, None, X, Y, 0, "full", nnz=hint)
+        torch.cuda.synchronize()
+        assert Y.tolist() == [[16.0, 32.0, 48.0, 64.0], [0.0] * 4], hint
+    del colidx
+    torch.cuda.empty_cache()
 
 
 def test_native_marshalling_of_streams_and_integers(es):
