@@ -195,10 +195,14 @@ hipError_t launch_backward(const Args& a, dim3 grid, hipStream_t st)
 
 // Longest row one wave may own.  A wave retires about E*U entries per memory
 // round trip (~2 us under load) while the whole launch moves entries*(4F+8)
-// bytes at a few TB/s; the bound keeps one wave's row near 5 % of the launch.  Rows
-// up to four times the mean are never split: on a small dense graph the bound alone
-// would send nearly every row through the atomics (10 k rows, mean 300, F = 32:
-// 63.8 us at a threshold of 64).
+// bytes at a few TB/s; the bound keeps one wave's row near 5 % of the launch.  Below
+// four times the mean (rounded down to a multiple of kLongMin) a row is never split,
+// whatever the bound: on a small dense graph that would send nearly every row through
+// the splitting and its atomics (exact product, 10 k rows of mean 300, F = 64: 159
+// us at a threshold of 64, 33 now; the transposed one, whose rows are atomic either
+// way: 641 and 598, 1000 rows of mean 400: 305 and 104).  Rounding up instead takes
+// rows of 65 to 128 entries on one wave where the mean is 16 to 31: 40 k rows, F = 16:
+// 14.7 us, 13.5 this way.
 int32_t pick_long_k(const Shape& s, int logR, double entries, int F, double mean)
 {
     const int U = 8 / s.CH;

@@ -68,6 +68,17 @@ def test_long_rows_are_only_possible_when_the_long_part_is_launched():
         assert (big["long_row_workgroups"] > 0) == (2304 > big["long_row_threshold"])
 
 
+def test_rows_up_to_about_four_times_the_mean_are_not_split():
+    """Exact product and its transpose: the threshold is at least 64 and at least
+    four times the mean, rounded down to a multiple of 64."""
+    for N, mean, F, backward in itertools.product((300, 3000, 40_000, 2_450_000), (1, 15, 16, 20, 31, 32, 300, 1000),
+                                                  (16, 41, 64, 128, 602), (False, True)):
+        if N * mean >= 2 ** 31 or mean > N:
+            continue
+        info = es.es_spmm_launch_info(N, N * mean, F, 0, "full", backward=backward, opts=dict(column_partition=-1))
+        assert info["long_row_threshold"] >= max(64, 4 * mean // 64 * 64), (N, mean, F, backward)
+
+
 def test_options_are_honoured_and_clamped():
     base = es.es_spmm_launch_info(1000, 5000, 64, 8, "bucket")
     info = es.es_spmm_launch_info(1000, 5000, 64, 8, "bucket", opts=dict(rows_per_wave=64))
