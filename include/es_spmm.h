@@ -273,18 +273,19 @@ typedef struct {
                                     of X per sweep; the sampler runs once per slice).
                                     -1 = never slice.  Ignored by the backward pass */
     int32_t long_row_threshold;  /* a row keeping more entries than this is cut into
-                                    256-entry segments that several workgroups sum
-                                    with atomic adds (load balance for skewed degree
-                                    distributions); any positive value             */
+                                    segments that several workgroups sum with atomic
+                                    adds, or in a small product given to one of them
+                                    (load balance for skewed degree distributions);
+                                    any positive value                              */
     int32_t column_partition;    /* es_spmm_ws only: 1 = run the column-partitioned
                                     product whenever it applies (a workspace is given,
                                     mode is not ES_BUCKET, N >= 512), -1 = never, 0 =
                                     the library decides from N, F, W and nnz / N      */
     int32_t kernel;              /* 1 = the row kernel (a row, or a row per team of
                                     lanes, on a wave at a time); 2 = the flattened
-                                    kernel (a wave lays 64 or 128 / lanes_per_row rows
-                                    end to end and deals their entries to its edge
-                                    slots: for short rows and narrow column slices;
+                                    kernel (a workgroup lays up to 64 rows end to end
+                                    and deals their entries to the edge slots of its
+                                    waves: for short rows and narrow column slices;
                                     the library picks it by itself where that
                                     measured faster); falls back to 1 where 2 does not
                                     apply (F < 4, the backward pass, FastRand in the
@@ -384,8 +385,10 @@ typedef struct {
     int32_t long_row_threshold;  /* rows keeping more entries are split             */
     int64_t long_row_workgroups; /* leading workgroups that serve such rows (or 0)  */
     int64_t grid_x, grid_y;      /* launch grid, 256 threads per workgroup          */
-    int32_t flattened;           /* 1: the flattened kernel would run (rows_per_wave then
-                                    is the number of rows a wave lays end to end)     */
+    int32_t flattened;           /* 1: the flattened kernel would run: a workgroup's run
+                                    then is 4 * rows_per_wave rows, edge_slots are 64 / G,
+                                    and its LDS holds 1536 or 2048 entries of the run
+                                    at a time, not tile_slots_per_row of each row     */
     int32_t column_ranges;       /* 8: es_spmm_ws with a sufficient workspace would run
                                     the column-partitioned product (grid_x then is the
                                     grid of each of its 8 launches); 1: it would not  */

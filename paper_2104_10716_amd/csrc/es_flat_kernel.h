@@ -46,7 +46,7 @@ namespace {
 // ---------------------------------------------------------------------------
 constexpr int kFlatMaxRows = 64;                      // rows of a workgroup's run at most: one per lane
 constexpr int kFlatBlockMin = 8;                      // smallest unit a row is padded to
-constexpr int kFlatLongRow = 8192;                    // kept entries above which a row goes to the long-row part (at most)
+constexpr int kFlatLongRow = 8192;                    // kept entries above which a row goes to the long-row part (unless the mean is near)
 constexpr int kFlatLongSeg = 2048;                    // slots per segment of such a row
 
 // Rows of a run with G column lanes: `rps` rows per edge slot of each wave.

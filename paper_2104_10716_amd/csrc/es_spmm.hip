@@ -214,6 +214,21 @@ int32_t pick_long_k(const Shape& s, int logR, double entries, int F, double mean
     return v < kLongMin ? kLongMin : v;
 }
 
+// The same for the flattened kernel, whose four waves share a row at no extra cost
+// per entry: only rows that alone would keep their workgroup busy for a good part of
+// the launch are split, above min(8192, 3e-4 * entries) entries, and none below four
+// times the mean.  F = 128, exact product, thresholds 512 / 2048 / 8192 / 16384 / never:
+// 118 M entries in 2.45 M rows (rule: 8192): 6054 / 5826 / 5677 / 5647 / 5674 us; 25 M in
+// 1.3 M (7466): 1941 / 1950 / 1953 / 1993 / 2030; 6.9 M in 1.3 M (2064): 875 / 853 / 846 /
+// 865 / 864; 8.7 M in 0.7 M (2610): 577 / 567 / 575 / 586 / 586.
+int32_t pick_flat_long_k(double entries, double mean)
+{
+    double k = entries * 3.0e-4 < (double)kFlatLongRow ? entries * 3.0e-4 : (double)kFlatLongRow;
+    const double whole = 4.0 * mean < (double)INT32_MAX ? 4.0 * mean : (double)INT32_MAX;
+    if (k < whole) k = (double)((int32_t)whole / kLongMin * kLongMin);
+    return k < (double)kLongMin ? kLongMin : (int32_t)k;
+}
+
 // Per-call overrides, parsed from an es_launch_opts_t (absent = the heuristic).
 struct Overrides {
     int logR = -1;             // rows_per_wave as a power of two, -1 = heuristic
@@ -392,14 +407,13 @@ int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool a
     }
     p->logR = logR;
 
-    int rps = 0;
-    if (p->flat) {                                         // a wave lays 1 or 2 rows per edge slot end to end
-        rps = mode == ES_FULL && !p->partition ? 1 : 2;
+    int64_t rows_per_block = (int64_t)kWavesPerBlock << logR;
+    if (p->flat) {                                         // a workgroup's run: 1 or 2 rows per edge slot of its waves
+        rows_per_block = flat_rows(s.G, mode == ES_FULL && !p->partition ? 1 : 2);
         logR = 0;
-        while ((1 << logR) < rps * 64 / s.G) ++logR;
+        while (((int64_t)kWavesPerBlock << logR) < rows_per_block) ++logR;
         p->logR = logR;
     }
-    const int64_t rows_per_block = p->flat ? flat_rows(s.G, rps) : (int64_t)kWavesPerBlock << logR;
     p->nblocks = (N + rows_per_block - 1) / rows_per_block;
     p->per_xcd = (p->nblocks + kNumXcd - 1) / kNumXcd;
     const int cols_per_block = s.G * s.CH * s.vec;
@@ -409,21 +423,10 @@ int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool a
     // for W above the bound (nnz is a hint, so it does not gate the launch)
     double entries = (double)nnz;
     if (mode != ES_FULL && entries > (double)N * W) entries = (double)N * W;
-    p->long_k = pick_long_k(s, logR, entries, F, mean);
+    p->long_k = p->flat ? pick_flat_long_k(entries, mean) : pick_long_k(s, logR, entries, F, mean);
     // the long-row part costs a second small launch and a scan of the row
     // pointers; below one tile per row that is more than the tail it removes
     if (mode != ES_FULL && p->long_k < kTileSlots) p->long_k = kTileSlots;
-    // the flattened kernel walks a long row tile by tile on one wave at no extra
-    // cost per entry, so only rows that would make a tail are split: a row of k
-    // entries keeps its wave busy for about k * 16 ns, the whole launch takes about
-    // entries * 50 ps, and the tail should stay below a tenth of that (co-purchase
-    // graph, exact product: 8192 measured 6 % faster than 2048; citation graph,
-    // 2.4 M entries: 8192 would leave one 12 k row running alone for half the launch)
-    if (p->flat) {
-        const double tail_free = entries * 3.0e-4;
-        const int32_t k = tail_free >= (double)kFlatLongRow ? kFlatLongRow : (int32_t)tail_free;
-        if (p->long_k < k) p->long_k = k;
-    }
     if (ov.long_k > 0) p->long_k = ov.long_k;
     const bool may_be_long = mode == ES_FULL || W > p->long_k;
     p->long_blocks = may_be_long ? ((N + kLongScanRows - 1) / kLongScanRows) * kLongSplit : 0;

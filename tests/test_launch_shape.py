@@ -17,7 +17,8 @@ def _check(info, N, F, backward):
     R, E = info["rows_per_wave"], info["edge_slots"]
     assert V in (1, 4) and CH in (1, 2, 4) and G in (4, 8, 16, 32, 64)
     if info["flattened"]:
-        assert R * G in (64, 128) and E * G == 64         # a wave lays E or 2E rows end to end for its E slots
+        assert R * G in (64, 128) and E * G == 64         # E or 2E rows per wave in the workgroup's run ...
+        assert 4 * R <= 64                                # ... of which a lane of a wave describes one
     else:
         assert R * G * E == 64 and E >= 1                 # a wave is R rows x E slots x G lanes
     assert info["loads_in_flight"] * CH == 8
@@ -31,6 +32,7 @@ def _check(info, N, F, backward):
         assert info["long_row_workgroups"] == row_groups
     assert row_groups % 8 == 0                            # one equal share per XCD
     assert row_groups * rows_per_workgroup >= N
+    assert (row_groups - 8) * rows_per_workgroup < N      # no more workgroups than needed, up to one per XCD
     assert info["long_row_workgroups"] % 8 == 0
     assert info["long_row_threshold"] >= 64
     if backward:
@@ -175,7 +177,7 @@ def test_flattened_kernel_option():
         info = es.es_spmm_launch_info(100_000, 1_000_000, F, 16, "fastrand", aligned16=(F % 4 == 0),
                                       opts=dict(kernel=2, lanes_per_row=-1))
         assert info["flattened"] == 1 and info["lanes_per_row"] == G and info["chunks_per_lane"] == 1
-        assert info["rows_per_wave"] == 128 // G and info["edge_slots"] == 64 // G   # sampled: two rows per slot
+        assert info["rows_per_wave"] == min(128 // G, 16) and info["edge_slots"] == 64 // G   # sampled: two rows per slot
         assert info["grid_y"] == -(-F // (4 * G))
         _check(info, 100_000, F, False)
     assert es.es_spmm_launch_info(1000, 5000, 3, 2, "bucket", opts=dict(kernel=2))["flattened"] == 0    # F < 4
