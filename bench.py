@@ -40,9 +40,9 @@ HBM_PEAK_GBPS = 8000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
 CONFIG_TEXT = {
-    2: "configs[1] mid-size citation-like graph: N=170k, power-law degree mean 14, F=128",
-    3: "configs[2] dense social-like graph: N=233k, power-law degree mean 490, F=64",
-    4: "configs[3] large co-purchase-like graph: N=2.45M, mean degree 50, F=128 (100 padded)",
+    2: "mid-size citation-like graph: N=170k, power-law degree mean 14, F=128",
+    3: "dense social-like graph: N=233k, power-law degree mean 490, F=64",
+    4: "large co-purchase-like graph: N=2.45M, mean degree 50, F=128 (100 padded)",
 }
 
 
@@ -66,7 +66,10 @@ def compulsory_bytes(N: int, nnz_kept: int, F: int, distinct_cols: int) -> int:
 def sector_adjusted_bytes(N: int, nnz_kept: int, nnz_kept_strided: int, F: int, L: int) -> int:
     """B_eff with the 8 bytes per sampled entry replaced by two fetch units of L
     bytes (one of colidx, one of vals) for the entries FastRand reads at stride
-    577 (rows longer than W); contiguous reads keep their 8 bytes."""
+    577 (rows longer than W); contiguous reads keep their 8 bytes.  What a sampled
+    call moves at most: picks of one row share fetch units as soon as the row has
+    fewer units than picks (dense social-like graph, W = 64: 28 bytes of CSR per kept
+    entry by the counters, not 256)."""
     return (4 * (N + 1) + 8 * (nnz_kept - nnz_kept_strided) + 2 * L * nnz_kept_strided
             + 4 * F * nnz_kept + 4 * F * N)
 
@@ -246,6 +249,19 @@ def per_call_table(dw, calls, reps, flush, cold_reps, traffic_calls=None, L=None
     for r in rows:
         r["speedup_vs_full"] = round(t_full / r["ms"], 2) if t_full else None
     return rows
+
+
+def brief(table):
+    """A table as the result line carries it: per call [ms, B_eff GB/s, B_min GB/s, speed-up
+    over the exact product] (the whole rows go to stderr), other rows as they are."""
+    if not isinstance(table, dict):
+        return table
+    short = {k: v for k, v in table.items() if k not in ("calls", "stages", "traffic_source")}
+    for key in ("calls", "stages"):
+        if key in table:
+            short[key] = {(f"F={r['F']} " if "F" in r else "") + call_label(r["mode"], r["W"]):
+                          [r["ms"], r["eff_GBps"], r["min_GBps"], r.get("speedup_vs_full")] for r in table[key]}
+    return short
 
 
 def log_rows(tag, rows):
@@ -430,7 +446,7 @@ def main() -> int:
     if args.config == 5:
         dw = gcn_stage_workload(w, dev, args.feature_width)
         calls = dw.calls((64,))
-        workload_text = (f"configs[4] 2-layer GCN forward on the config-3 graph, SpMM stage at "
+        workload_text = (f"2-layer GCN forward on the dense social-like graph, SpMM stage at "
                          f"F={args.feature_width} (row stride {args.feature_width})")
         traffic_key = f"config5:F{args.feature_width}"
     else:
@@ -581,14 +597,17 @@ def main() -> int:
                 extra.append(backward_table(dw, dev, ((("fastrand", 16), ("fastrand", 64), ("bucket", 64),
                                                        ("fastrand", 256)))))
                 extra.append(gcn_feature_sweep(dw, dev, flush))
-        result["extra"] = extra
+        log("detail " + json.dumps({"calls": result["calls"], "extra": extra}))
+        result["calls"] = brief({"calls": result["calls"]})["calls"]
+        result["calls_columns"] = ["ms", "B_eff GB/s", "B_min GB/s", "speed-up over full"]
+        result["extra"] = [brief(t) for t in extra]
 
     print(json.dumps(result), flush=True)
     return 0
 
 
 def tiny_config1(dev):
-    """configs[0]: ~1 MB moved per call, so a call is launch-bound; report the
+    """Tiny GCN aggregation: ~1 MB moved per call, so a call is launch-bound; report the
     per-call time and the time of the whole sweep replayed as one HIP graph."""
     import torch
     from workloads import make_workload
@@ -608,7 +627,7 @@ def tiny_config1(dev):
         for mode, W in calls:
             dw.launch(mode, W)
     t_graph = _time_fn(g.replay, reps=50)
-    out = {"workload": "configs[0] tiny GCN aggregation: N=2708, F=16 (launch-bound)", "N": dw.N,
+    out = {"workload": "tiny GCN aggregation: N=2708, F=16 (launch-bound)", "N": dw.N,
            "nnz": dw.nnz, "F": dw.F, "calls": rows,
            "sweep_as_hip_graph_ms": round(t_graph, 4), "calls_in_graph": len(calls)}
     log(f"  cfg1: per-call {min(r['ms'] for r in rows):.4f}-{max(r['ms'] for r in rows):.4f} ms; "
@@ -732,7 +751,7 @@ def backward_table(dw, dev, cases):
 
 
 def gcn_stage_workload(w3, dev, F):
-    """DeviceWorkload for one SpMM stage of configs[4]: X = X0 W1 (F=256) or
+    """DeviceWorkload for one SpMM stage of the 2-layer GCN: X = X0 W1 (F=256) or
     X = relu(ES-SpMM(A, X0 W1)) W2 (F=41; first stage run with FastRand, W=64)."""
     import torch
     from workloads import gcn_operands
@@ -747,7 +766,7 @@ def gcn_stage_workload(w3, dev, F):
 
 
 def gcn_feature_sweep(dw3, dev, flush):
-    """configs[4]: the SpMM stages of a 2-layer GCN forward on the config-3
+    """The SpMM stages of a 2-layer GCN forward on the config-3
     graph, H1 = relu(A (X0 W1)) at F = 256 and out = A (H1 W2) at F = 41; the
     dense products are torch GEMMs and are not timed."""
     import torch
@@ -758,7 +777,7 @@ def gcn_feature_sweep(dw3, dev, flush):
     W2 = torch.from_numpy(W2h).to(dev)
     Z1 = X0 @ W1
     del X0
-    out = {"workload": "configs[4] 2-layer GCN forward on the config-3 graph, SpMM stages only",
+    out = {"workload": "2-layer GCN forward on the dense social-like graph, SpMM stages only",
            "N": dw3.N, "nnz": dw3.nnz, "stages": []}
     t256, _ = load_traffic("config5:F256")
     t41, _ = load_traffic("config5:F41")
