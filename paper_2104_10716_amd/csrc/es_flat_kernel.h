@@ -28,21 +28,18 @@ namespace {
 // sums are bit-reproducible.  Row sums leave LDS once, coalesced (plain stores, or
 // load-add-store in the later phases of the column-partitioned product).
 //
-// What bounds it, measured on this chip with gathers of 128-byte rows: a compute
-// unit takes 31-33 TB/s (all units together) of rows of X as long as every one hits
-// its L2, but its vector cache returns data in order, so one line that misses holds
-// back the hits behind it: a stream of CSR entries of 1/16 of the gathered bytes
-// brings the rate down to 19 TB/s when every wave reads its part as it goes, 22 TB/s
-// when a wave reads 512 entries at a time, and 27 TB/s when a workgroup reads 2048 at a
-// time (and 10 % of gathers that miss bring it down to 17 TB/s).  Hence the bursts,
-// and hence no wave-private prefetch.  Dense social-like graph (233 k rows, 113 M
-// entries, F = 64), exact product in column ranges: 2.59 -> 2.11 ms against the
-// former form (256 entries per wave, requested one tile ahead, a row search per
-// entry); co-purchase-like graph (2.45 M rows, 120 M entries, F = 128): exact product
-// 5.93 -> 5.86 ms, FastRand W = 64 2.84 -> 2.76 ms (bound by L2 misses, 7 TB/s).
-// Tried and slower: entries copied into LDS by the load itself (dword copies: 2.9
-// ms), a pass of 64 entries per row streamed two passes ahead (2.6 ms), 16 column
-// ranges (3.2 ms), two batches of gathers in flight per wave (spills or 12 waves).
+// What bounds it: the L2 misses of the gathers where X is large (7 TB/s of them), and
+// where nearly all gathers hit, the order in which a compute unit's vector cache
+// returns data: a line that misses, be it of the CSR entries, holds back the hits
+// behind it.  Hence the bursts, which put a workgroup's misses on the entries
+// together, and hence no wave-private prefetch.  Dense social-like graph (233 k rows,
+// 113 M entries, F = 64), exact product in column ranges, 82 % L2 hits: 2.59 -> 2.16 ms
+// against the former form (256 entries per wave, requested one tile ahead, a row
+// search per entry); co-purchase-like graph (2.45 M rows, 120 M entries, F = 128), 46 %
+// hits: exact product 6.02 -> 5.68 ms, FastRand W = 64 2.81 -> 2.76 ms.
+// Tried and slower on the former: entries copied into LDS by the load itself (dword
+// copies: 2.9 ms), a pass of 64 entries per row streamed two passes ahead (2.6 ms), 16
+// column ranges (3.2 ms), two batches of gathers in flight per wave (spills or 12 waves).
 // ---------------------------------------------------------------------------
 constexpr int kFlatMaxRows = 64;                      // rows of a workgroup's run at most: one per lane
 constexpr int kFlatBlockMin = 8;                      // smallest unit a row is padded to

@@ -3,7 +3,7 @@
 // A Python program calls es_spmm once per layer; on a graph of a few thousand
 // rows the kernel takes about 4 us, and reading fifteen tensor attributes,
 // finding the current stream and converting twenty ctypes arguments in Python
-// took another 8 (13 us per call in all; 5 with this module).  Nothing is
+// took another 8 (13 us per call in all; 4 with this module).  Nothing is
 // computed here.  Every function returns the C entry point's status, or None when
 // an argument is not the plain case (wrong type, shape, device or stride, or a
 // tensor without memory of its own: sparse, fake, a wrapper): the caller then goes

@@ -24,7 +24,8 @@
 //     has drained.  The leading workgroups of the launch split each such row
 //     into 256-slot segments, deal the segments to the waves of kLongSplit
 //     workgroups and add the partial sums to Y with fp32 atomics (a small
-//     kernel zeroes those rows of Y first); the row workgroups skip them.
+//     kernel zeroes those rows of Y first; in a small product one wave or
+//     workgroup sums the row instead); the row workgroups skip them.
 //     long_k is chosen on the host so that a single wave's longest row stays a
 //     few percent of the whole launch.
 #include <hip/hip_runtime.h>
@@ -299,8 +300,6 @@ int check_sizes(int64_t N, int64_t nnz, int32_t F, int32_t ldx, int32_t ldy, int
     return ES_OK;
 }
 
-// Launch shape for N >= 1 rows.  `aligned`: F and both row strides are
-// multiples of 4 and both matrices are 16-byte aligned.
 // Bytes of workspace the column-partitioned product needs for N rows.
 size_t part_workspace_bytes(int64_t N)
 {
@@ -310,8 +309,11 @@ size_t part_workspace_bytes(int64_t N)
 // Whether to run the column-partitioned product.  It pays when a row's piece
 // inside one column range is long enough to amortise the extra pass over Y
 // (kept entries per row well above kParts) and when an XCD's eighth of a
-// 32-column slice of X is of the order of its L2 (measured gains on the dense
-// social-like graph from 58k to 699k rows, i.e. shares of 0.9 to 11 MB).
+// 32-column slice of X is of the order of its L2.  Exact product, F = 64, us without /
+// in ranges: mean 490: 30 k rows (share 0.5 MB) 285 / 323, 58 k 745 / 569, 233 k 3777 /
+// 2144, 466 k (7.5 MB) 7880 / 5118; mean 150: 250 k 1263 / 1069, 600 k 3109 / 2869, but
+// below 125 k rows, where the row form serves the ranges, 125 k 600 / 818 and 45 k 171 /
+// 367: there the line on the mean is too low.
 bool pick_partition(int64_t N, double mean_kept, int32_t mode, int cols_per_block, int force)
 {
     if (mode == ES_BUCKET) return false;       // first-W entries crowd into the lowest column range
@@ -320,13 +322,15 @@ bool pick_partition(int64_t N, double mean_kept, int32_t mode, int cols_per_bloc
     if (force < 0) return false;
     // FastRand has to walk all W slots of a row once per column range to find the
     // ones that fall inside it; measured, that costs more than the locality
-    // returns (config-3 graph, W = 256: 0.8x), so it is only run on request
+    // returns (233 k rows of mean 490, F = 64, W = 256: 0.8x), so it is only run on request
     if (mode == ES_FASTRAND) return false;
     if (mean_kept < 128.0) return false;
     const double share = (double)N * cols_per_block * 4.0 / kParts;
     return share >= 0.5e6 && share <= 12.0e6;
 }
 
+// Launch shape for N >= 1 rows.  `aligned`: F and both row strides are
+// multiples of 4 and both matrices are 16-byte aligned.
 int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool aligned, bool backward,
               const Overrides& ov, bool have_workspace, Plan* p)
 {
@@ -351,23 +355,31 @@ int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool a
     // partitioned product needs the row kernel's per-row walk over all W slots.
     const bool flat_applies = !backward && s.vec == 4 && !(p->partition && mode == ES_FASTRAND);
     // chosen by rule only on 16-byte-aligned rows: 32-column slices of rows that do
-    // not tile 128-byte lines fetch every line twice (F = 41: 0.7x)
+    // not tile 128-byte lines fetch every line twice (F = 41, 233 k rows of mean 490,
+    // sampled: 0.53x; in column ranges level with the row form: 2395 / 2131 us at mean 300)
     const bool flat_allowed = flat_applies && ov.kernel != 1 && s.aligned;
 
     // Column slicing: fewer lanes across the feature columns, the rows swept once
     // per slice, so that the part of X in use at a time is smaller.  A slice makes
     // every row short, which the row kernel pays for per row and the flattened
     // kernel does not; so the narrow (32-column) slices go with the flattened
-    // kernel.  Measured (profiles/):
-    //  * partitioned product: 32-column slices on the flattened kernel once an
-    //    XCD's share of a 64-column slice no longer fits its L2 (1.07x..1.3x over
-    //    64-column slices on the row kernel, which stay best below that);
-    //  * tables of 0.3 GB and more with F >= 128: 32-column slices on the
-    //    flattened kernel (1.08x..1.2x where column ids cluster, so that the X rows
-    //    of a community come nearer to an L2; 0.98x..1.0x where they do not);
-    //    with the row kernel forced, 64-column slices from 0.5 GB;
-    //  * Bucket on rows several times longer than W: 32-column slices (its picks
-    //    crowd into the lowest-numbered columns).
+    // kernel.  Both sides, us (profiles/ has the sweeps):
+    //  * partitioned product: 32-column slices on the flattened kernel above 125 k
+    //    rows, where an XCD's share of a 64-column slice no longer fits its L2 (row
+    //    form on 64-column slices / flattened on 32, F = 64, mean 490: 160 k rows
+    //    1834 / 1465, 233 k 2815 / 2145, 466 k 6599 / 5123).  The line is from the
+    //    flattened kernel's former version; the present one is the faster from
+    //    60 - 90 k rows on as well (58 k 569 / 629, 90 k 1161 / 915, 125 k 1425 / 1177).
+    //  * tables of 0.3 GB and more with F >= 128: 32-column slices on the flattened
+    //    kernel, so that the X rows of a community of ids come nearer to an L2.
+    //    Whole rows on the row kernel / this, 0.6 GB, F = 128: ids that cluster, mean
+    //    50: exact 3137 / 2242, FastRand W = 64 1400 / 1208; mean 14: 1026 / 972, 623 /
+    //    644; uniform ids, mean 50: 4078 / 4338, 1904 / 2159.  At 0.15 GB, clustered,
+    //    mean 50: 561 / 500, 199 / 274.  With the row kernel forced, 64-column slices
+    //    from 0.5 GB.
+    //  * Bucket on rows several times longer than W: 32-column slices on the row
+    //    kernel (its picks crowd into the lowest-numbered columns; 233 k rows, mean
+    //    490, F = 64: W = 64 452 / 393, W = 16 79 / 69).
     // Elsewhere slicing only re-reads the CSR entries.
     int slice_G = 0;
     bool sliced_by_rule = false;
