@@ -25,6 +25,7 @@
 #ifndef ES_SPMM_H
 #define ES_SPMM_H
 
+#include <stddef.h>
 #include <stdint.h>
 
 #ifdef __cplusplus
@@ -126,6 +127,28 @@ int es_spmm_backward(const int32_t* rowptr, const int32_t* colidx, const float* 
                      const float* dY, float* dX,
                      int64_t N, int64_t nnz, int32_t F, int32_t ldy, int32_t ldx,
                      int32_t W, int32_t mode, uint64_t seed, int32_t norm, void* stream);
+
+/*
+ * es_spmm_backward_ws -- es_spmm_backward with a caller-owned workspace, in which
+ * the library first transposes the sampled graph, so that the product becomes a
+ * gather: no atomic adds to dX except for rows of dX that sum a great many
+ * entries.  es_spmm_backward_workspace_bytes is the size it takes for these
+ * arguments, or 0 where the scatter of es_spmm_backward is the faster form or this
+ * one does not apply (ES_FULL, small products, F <= 16, N > 2^22, W > 4096); with a
+ * smaller workspace, or none, es_spmm_backward_ws is es_spmm_backward.
+ *   nnz        rowptr[N] or more (here it sizes the workspace: with a smaller
+ *              number dX is wrong, though no other memory is touched)
+ *   workspace  256-byte aligned; its contents are scratch, and calls that share it
+ *              must be ordered (same stream)
+ * Every other argument, and the result, as in es_spmm_backward.
+ */
+size_t es_spmm_backward_workspace_bytes(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode);
+
+int es_spmm_backward_ws(const int32_t* rowptr, const int32_t* colidx, const float* vals,
+                        const float* dY, float* dX,
+                        int64_t N, int64_t nnz, int32_t F, int32_t ldy, int32_t ldx,
+                        int32_t W, int32_t mode, uint64_t seed, int32_t norm,
+                        void* workspace, size_t workspace_bytes, void* stream);
 
 /*
  * es_spmm_sample_edges -- the sampler of Section 4.2 / 4.4 on its own, for

@@ -16,6 +16,8 @@ from .binding import (  # noqa: F401
     es_spmm_backward,
     es_spmm_backward_ex,
     es_spmm_backward_pull,
+    es_spmm_backward_workspace_bytes,
+    es_spmm_backward_ws,
     es_spmm_ex,
     es_launch_opts_t,
     es_spmm_launch_info,

@@ -80,6 +80,11 @@ def load_library():
     lib.es_spmm_static_ws.argtypes = lib.es_spmm_ex.argtypes
     lib.es_spmm_workspace_bytes.restype = ctypes.c_size_t
     lib.es_spmm_workspace_bytes.argtypes = [ctypes.c_int64]
+    lib.es_spmm_backward_workspace_bytes.restype = ctypes.c_size_t
+    lib.es_spmm_backward_workspace_bytes.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32,
+                                                     ctypes.c_int32]
+    lib.es_spmm_backward_ws.restype = ctypes.c_int
+    lib.es_spmm_backward_ws.argtypes = lib.es_spmm_norm.argtypes[:-1] + [vp, ctypes.c_size_t, vp]
     lib.es_spmm_sample_edges.restype = ctypes.c_int
     lib.es_spmm_sample_edges.argtypes = [vp, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32,
                                          ctypes.c_uint64, ctypes.c_int32, vp, vp, vp]
@@ -131,7 +136,8 @@ def load_marshal():
             "`python -m paper_2104_10716_amd.build` (or __graft_entry__.build())") from e
     lib = load_library()
     _es_marshal.bind(*(ctypes.cast(f, ctypes.c_void_p).value
-                       for f in (lib.es_spmm_ws, lib.es_spmm_backward, lib.es_spmm_backward_pull)))
+                       for f in (lib.es_spmm_ws, lib.es_spmm_backward, lib.es_spmm_backward_pull,
+                                 lib.es_spmm_backward_ws, lib.es_spmm_backward_workspace_bytes)))
     _marshal = _es_marshal
     return _marshal
 
@@ -320,7 +326,9 @@ def es_spmm_backward_ex(rowptr, colidx, vals, dY, dX, W: int, mode, seed: int = 
 
 def es_spmm_backward(rowptr, colidx, vals, dY, dX, W: int, mode, seed: int = 0, norm="none",
                      F: Optional[int] = None, stream=None, nnz: Optional[int] = None):
-    """dX[:, :F] = sample_W(A)^T @ dY[:, :F] (dX is overwritten); returns dX."""
+    """dX[:, :F] = sample_W(A)^T @ dY[:, :F] (dX is overwritten); returns dX.  Larger sampled
+    products take a workspace (es_spmm_backward_workspace_bytes) from torch's allocator for the
+    call; a captured stream, or a lack of memory, falls back to the form that takes none."""
     rc = (_marshal or load_marshal()).backward(rowptr, colidx, vals, dY, dX, W, mode, seed, norm, F, stream, nnz)
     if rc == 0:
         return dX
@@ -333,6 +341,29 @@ def es_spmm_backward(rowptr, colidx, vals, dY, dX, W: int, mode, seed: int = 0, 
                               _stream_ptr(stream))
     if rc != 0:
         raise EsSpmmError(rc, "es_spmm_backward")
+    return dX
+
+
+def es_spmm_backward_workspace_bytes(N: int, nnz: int, F: int, W: int, mode) -> int:
+    return int(load_library().es_spmm_backward_workspace_bytes(int(N), int(nnz), int(F), int(W), _mode(mode)))
+
+
+def es_spmm_backward_ws(rowptr, colidx, vals, dY, dX, W: int, mode, seed: int = 0, norm="none", workspace=None,
+                        F: Optional[int] = None, stream=None):
+    """es_spmm_backward with a caller-owned workspace (a device tensor of at least
+    es_spmm_backward_workspace_bytes(N, len(colidx), F, W, mode) bytes, any dtype)."""
+    lib = load_library()
+    args = _spmm_args(rowptr, colidx, vals, dY, dX, F, None)
+    nm = NORMS[norm] if isinstance(norm, str) else int(norm)
+    ws_ptr, ws_bytes = None, 0
+    if workspace is not None:
+        if not workspace.is_cuda or not workspace.is_contiguous():
+            raise ValueError("workspace must be a contiguous device tensor")
+        ws_ptr, ws_bytes = workspace.data_ptr() or None, workspace.numel() * workspace.element_size()
+    rc = lib.es_spmm_backward_ws(*args, int(W), _mode(mode), int(seed) & 0xFFFFFFFFFFFFFFFF, nm, ws_ptr, ws_bytes,
+                                 _stream_ptr(stream))
+    if rc != 0:
+        raise EsSpmmError(rc, "es_spmm_backward_ws")
     return dX
 
 

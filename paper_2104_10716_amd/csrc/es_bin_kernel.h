@@ -1,0 +1,271 @@
+// es_bin_kernel.h -- the transposed sampled product with a workspace: kept entries grouped by column blocks, sums in LDS.
+#ifndef ES_SPMM_BIN_KERNEL_H
+#define ES_SPMM_BIN_KERNEL_H
+
+#include "es_flat_kernel.h"
+
+namespace {
+
+// ---------------------------------------------------------------------------
+// dX = sample_W(A)^T dY with a workspace.  Scattering f * v * dY[r] to dX[c] with
+// global atomics is bound by the atomic path (20.5 G requests of 64 bytes a second
+// whatever the launch, a tenth of what gathers reach).  Here the sampled graph is
+// transposed first and the exact forward product run on the result.  The transposition is a counting sort in two
+// levels, so that no counter lies in global memory: the kept entries by blocks of
+// 2^log_width columns (count per workgroup and block, prefix sums, fill: records of
+// 8 bytes, the row and the column inside the block, value times row factor), then each
+// block by column.
+//
+// What bounds it: the product, i.e. its gathers.  170 k rows, W = 16 of a mean of 14, F =
+// 128: 126 us (scatter: 406), of which count 11, scan and base 8, fill 15, sort 12.  Larger
+// and denser (233 k rows, W = 64, 14.9 M entries): count 64, fill 140, sort 110 of 900; the
+// fill's records go out 8 bytes at a time (256 walkers: 133 us; 512, with half as many
+// records side by side: 259).
+// Tried and slower: sums kept in LDS per column block and added to with ds_add_f32,
+// which takes three clocks per lane (170 k rows: 650 us for that pass alone).
+// ---------------------------------------------------------------------------
+constexpr int kBinThreads = 512;                      // of a counting / filling workgroup: one row per thread at a time
+constexpr int kBinWaves = kBinThreads / kWaveSize;
+constexpr int kBinRowBits = 22;                       // a record holds the row in 22 bits, the column of the block in 10
+constexpr int kBinMaxBlocks = 8192;                   // column blocks at most: 32 KB of counters per workgroup
+constexpr int kBinMaxW = 4096;                        // kept entries of a row at most: one workgroup walks them
+constexpr int64_t kBinMinRequests = 1100000;          // requests of the scatter from which on this form is the faster
+constexpr int kBinWalkers = 256;                      // counting / filling workgroups at most
+
+struct BinArgs {
+    const int32_t* rowptr;
+    const int32_t* colidx;
+    const float* vals;
+    uint2* records;            // [capacity]
+    int32_t* counts;           // [walkers x nbins]: records of walker i in block b, then of all walkers before it
+    int32_t* base;             // [nbins + 1]: first record of block b
+    int32_t* t_ptr;            // [N + 1], t_row and t_val [capacity]: the transposed sampled graph
+    int32_t* t_row;
+    float* t_val;
+    int64_t N, capacity;
+    uint64_t seed;
+    int32_t W, mode, norm;
+    int32_t log_width, nbins, walkers;
+};
+
+// Walks the kept entries of this workgroup's rows, 512 rows at a time laid end to
+// end: every thread then takes entries, whatever rows they are of.  FILL == false
+// counts them per column block, FILL == true writes the records.
+template <bool FILL>
+__global__ void __launch_bounds__(kBinThreads) es_bin_walk_kernel(const BinArgs a)
+{
+    extern __shared__ int32_t counter[];              // [nbins]
+    __shared__ int32_t first[kBinThreads];
+    __shared__ int32_t src[kBinThreads];
+    __shared__ uint32_t len[kBinThreads], mul[kBinThreads], rot[kBinThreads];
+    __shared__ float factor[kBinThreads];
+    __shared__ int32_t wave_total[kBinWaves];
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWaveSize - 1);
+    const int wave = tid >> 6;
+    int32_t* mine = a.counts + (int64_t)blockIdx.x * a.nbins;
+    for (int b = tid; b < a.nbins; b += kBinThreads) counter[b] = FILL ? a.base[b] + mine[b] : 0;
+    const int64_t r_begin = a.N * blockIdx.x / a.walkers, r_end = a.N * (blockIdx.x + 1) / a.walkers;
+    for (int64_t r0 = r_begin; r0 < r_end; r0 += kBinThreads) {
+        const int64_t r = r0 + tid;
+        int32_t n = 0, k = 0;
+        if (r < r_end) {
+            const int32_t p = a.rowptr[r];
+            n = a.rowptr[r + 1] - p;
+            k = kept_count(a.mode, n, a.W);
+            src[tid] = p;
+            const bool strided = a.mode == ES_FASTRAND && n > a.W;
+            len[tid] = strided ? (uint32_t)n : 0u;
+            mul[tid] = strided ? fastrand_multiplier((uint32_t)n) : 0u;
+            rot[tid] = strided ? fastrand_offset(a.seed, r, (uint32_t)n) : 0u;
+            if (FILL) factor[tid] = row_factor(a.norm, n, k);
+        }
+        int32_t incl = k;
+#pragma unroll
+        for (int d = 1; d < kWaveSize; d <<= 1) {
+            const int32_t up = __shfl_up(incl, d, kWaveSize);
+            if (lane >= d) incl += up;
+        }
+        if (lane == kWaveSize - 1) wave_total[wave] = incl;
+        __syncthreads();
+        int32_t before = incl - k, total = 0;
+#pragma unroll
+        for (int w = 0; w < kBinWaves; ++w) {
+            if (w < wave) before += wave_total[w];
+            total += wave_total[w];
+        }
+        first[tid] = before;
+        __syncthreads();
+        constexpr int M = 4;                          // entries per thread requested together
+        for (int32_t i0 = tid; i0 < total; i0 += M * kBinThreads) {
+            int32_t col[M], row[M];
+            float val[M];
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                const int32_t i = min(i0 + m * kBinThreads, total - 1);
+                int q = 0;                            // last row that starts at or before entry i
+#pragma unroll
+                for (int d = kBinThreads / 2; d >= 1; d >>= 1) q += first[q + d] <= i ? d : 0;
+                uint32_t entry = (uint32_t)(i - first[q]);
+                const uint32_t n_q = len[q];
+                if (n_q) {                            // Equation 2; W <= 4096, so the product stays below 2^24
+                    entry = rot[q] + small_mod(entry * mul[q], n_q);
+                    if (entry >= n_q) entry -= n_q;
+                }
+                const int64_t p = (int64_t)src[q] + entry;
+                row[m] = q;
+                col[m] = a.colidx[p];
+                if (FILL) val[m] = a.vals ? a.vals[p] : 1.0f;
+            }
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                if (i0 + m * kBinThreads >= total) break;
+                const int32_t b = col[m] >> a.log_width;
+                const int32_t at = atomicAdd(&counter[b], 1);
+                if (FILL && at < a.capacity)
+                    a.records[at] = make_uint2((uint32_t)(r0 + row[m]) | ((uint32_t)(col[m] - (b << a.log_width)) << kBinRowBits),
+                                               __float_as_uint(val[m] * factor[row[m]]));
+            }
+        }
+        __syncthreads();
+    }
+    if (!FILL)
+        for (int b = tid; b < a.nbins; b += kBinThreads) mine[b] = counter[b];
+}
+
+// counts[i][b] becomes the records of block b that walkers before i hold; base[b]
+// becomes their number in all walkers.  A workgroup takes 64 blocks, a wave a
+// sixteenth of the walkers.
+constexpr int kBinScanThreads = 1024;
+__global__ void __launch_bounds__(kBinScanThreads) es_bin_scan_kernel(const BinArgs a)
+{
+    constexpr int WAVES = kBinScanThreads / kWaveSize;
+    constexpr int PER = kBinWalkers / WAVES;          // walkers of a wave at most
+    __shared__ int32_t sums[WAVES][kWaveSize];
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    const int wave = threadIdx.x >> 6;
+    const int b = blockIdx.x * kWaveSize + lane;
+    const int i0 = wave * PER;
+    int32_t v[PER];
+    int32_t sum = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        v[i] = (b < a.nbins && i0 + i < a.walkers) ? a.counts[(int64_t)(i0 + i) * a.nbins + b] : 0;
+        sum += v[i];
+    }
+    sums[wave][lane] = sum;
+    __syncthreads();
+    int32_t before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        if (w < wave) before += sums[w][lane];
+        total += sums[w][lane];
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        if (b < a.nbins && i0 + i < a.walkers) a.counts[(int64_t)(i0 + i) * a.nbins + b] = before;
+        before += v[i];
+    }
+    if (wave == 0 && b < a.nbins) a.base[b] = total;
+}
+
+// One workgroup: base[b] from the blocks' totals to their first records.
+__global__ void __launch_bounds__(kBinScanThreads) es_bin_base_kernel(const BinArgs a)
+{
+    constexpr int WAVES = kBinScanThreads / kWaveSize;
+    constexpr int PER = kBinMaxBlocks / kBinScanThreads;
+    __shared__ int32_t wave_total[WAVES];
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    const int wave = threadIdx.x >> 6;
+    int32_t count[PER];
+    int32_t mine = 0;
+    const int b0 = threadIdx.x * PER;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        count[i] = b0 + i < a.nbins ? a.base[b0 + i] : 0;
+        mine += count[i];
+    }
+    int32_t incl = mine;
+#pragma unroll
+    for (int d = 1; d < kWaveSize; d <<= 1) {
+        const int32_t up = __shfl_up(incl, d, kWaveSize);
+        if (lane >= d) incl += up;
+    }
+    if (lane == kWaveSize - 1) wave_total[wave] = incl;
+    __syncthreads();
+    int32_t at = incl - mine;
+    for (int w = 0; w < wave; ++w) at += wave_total[w];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        if (b0 + i <= a.nbins) a.base[b0 + i] = at;   // base[nbins]: all of them
+        at += count[i];
+    }
+    if (threadIdx.x == kBinScanThreads - 1 && a.nbins == kBinMaxBlocks) a.base[a.nbins] = at;
+}
+
+// Sorts column block blockIdx.x by column into the transposed graph.
+__global__ void __launch_bounds__(kBlockThreads) es_bin_sort_kernel(const BinArgs a)
+{
+    constexpr int COLS = 1 << (32 - kBinRowBits);     // columns of a block at most
+    constexpr int PER = COLS / kBlockThreads;
+    constexpr int M = 8;                              // records per thread requested together
+    __shared__ int32_t cursor[COLS];
+    __shared__ int32_t wave_total[kWavesPerBlock];
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWaveSize - 1);
+    const int wave = tid >> 6;
+    const int64_t c0 = (int64_t)blockIdx.x << a.log_width;
+    const int cols = (int)min((int64_t)1 << a.log_width, a.N - c0);
+    const int32_t begin = (int32_t)min((int64_t)a.base[blockIdx.x], a.capacity);
+    const int32_t end = (int32_t)min((int64_t)a.base[blockIdx.x + 1], a.capacity);
+    for (int c = tid; c < COLS; c += kBlockThreads) cursor[c] = 0;
+    __syncthreads();
+    for (int32_t i0 = begin + tid; i0 < end; i0 += M * kBlockThreads) {
+        uint32_t key[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m) key[m] = a.records[min(i0 + m * kBlockThreads, end - 1)].x;
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+            if (i0 + m * kBlockThreads < end) atomicAdd(&cursor[key[m] >> kBinRowBits], 1);
+    }
+    __syncthreads();
+    int32_t count[PER];
+    int32_t mine = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) { count[i] = cursor[tid * PER + i]; mine += count[i]; }
+    int32_t incl = mine;
+#pragma unroll
+    for (int d = 1; d < kWaveSize; d <<= 1) {
+        const int32_t up = __shfl_up(incl, d, kWaveSize);
+        if (lane >= d) incl += up;
+    }
+    if (lane == kWaveSize - 1) wave_total[wave] = incl;
+    __syncthreads();
+    int32_t at = begin + incl - mine;
+    for (int w = 0; w < wave; ++w) at += wave_total[w];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int c = tid * PER + i;
+        cursor[c] = at;
+        if (c < cols) a.t_ptr[c0 + c] = at;
+        at += count[i];
+    }
+    if (blockIdx.x == gridDim.x - 1 && tid == 0) a.t_ptr[a.N] = end;
+    __syncthreads();
+    for (int32_t i0 = begin + tid; i0 < end; i0 += M * kBlockThreads) {
+        uint2 rec[M];
+#pragma unroll
+        for (int m = 0; m < M; ++m) rec[m] = a.records[min(i0 + m * kBlockThreads, end - 1)];
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+            if (i0 + m * kBlockThreads < end) {
+                const int32_t to = atomicAdd(&cursor[rec[m].x >> kBinRowBits], 1);
+                a.t_row[to] = (int32_t)(rec[m].x & ((1u << kBinRowBits) - 1u));
+                a.t_val[to] = __uint_as_float(rec[m].y);
+            }
+    }
+}
+
+}  // namespace
+
+#endif  // ES_SPMM_BIN_KERNEL_H

@@ -367,7 +367,10 @@ __device__ __forceinline__ void long_block(const Args& a, uint32_t bx, uint32_t 
 // the splitting of long rows overlaps the bulk of the rows) run the long-row
 // part; the rest run the row part, remapped so that each XCD (hardware deals
 // workgroup b to XCD b % 8; long_blocks is a multiple of 8) walks one
-// contiguous range of rows.
+// contiguous range of rows, or with blocks_per_xcd == 0 not remapped: the rows of a
+// transposed Bucket sample get shorter from the first to the last, and as
+// contiguous ranges the first XCD would have most of the work (transposed product, 233 k
+// rows, W = 64 of a mean of 490, F = 64: 1.70 ms as ranges, 0.90 dealt round).
 // ---------------------------------------------------------------------------
 template <int G, int CH, int VEC, bool ALIGNED, bool BACKWARD, bool WIDE>
 __global__ void __launch_bounds__(kBlockThreads) es_spmm_kernel(const Args a)
@@ -381,7 +384,7 @@ __global__ void __launch_bounds__(kBlockThreads) es_spmm_kernel(const Args a)
         return;
     }
     const uint32_t b = blockIdx.x - a.long_blocks;
-    const uint32_t vb = (b % kNumXcd) * a.blocks_per_xcd + b / kNumXcd;
+    const uint32_t vb = a.blocks_per_xcd ? (b % kNumXcd) * a.blocks_per_xcd + b / kNumXcd : b;
     if (vb >= a.nblocks) return;
     row_block<G, CH, VEC, ALIGNED, BACKWARD, WIDE>(a, vb, lds);
 }

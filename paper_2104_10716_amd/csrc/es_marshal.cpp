@@ -13,6 +13,7 @@
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -22,6 +23,8 @@ namespace {
 
 decltype(&es_spmm_ws) g_spmm_ws = nullptr;
 decltype(&es_spmm_backward) g_backward = nullptr;
+decltype(&es_spmm_backward_ws) g_backward_ws = nullptr;
+decltype(&es_spmm_backward_workspace_bytes) g_backward_bytes = nullptr;
 decltype(&es_spmm_backward_pull) g_pull = nullptr;
 
 // Strided, with a storage that holds its elements, and not a Python-dispatched
@@ -158,7 +161,7 @@ struct Product {
 struct Csr {
     const int32_t *rowptr, *colidx;
     const float* vals;
-    int64_t N, nnz;
+    int64_t N, nnz, stored;                            // nnz: the caller's hint, or stored
 
     bool parse(PyObject* rp, PyObject* ci, PyObject* va, PyObject* nz)
     {
@@ -167,7 +170,7 @@ struct Csr {
         const at::Tensor *r, *c, *v;
         if (!as_tensor(rp, at::kInt, &r) || !as_tensor(ci, at::kInt, &c)) return false;
         N = r->numel() - 1;
-        nnz = c->numel();
+        nnz = stored = c->numel();
         vals = nullptr;
         if (va != Py_None) {
             if (!as_tensor(va, at::kFloat, &v) || v->numel() != nnz) return false;
@@ -180,12 +183,13 @@ struct Csr {
     }
 };
 
-// bind(es_spmm_ws, es_spmm_backward, es_spmm_backward_pull): addresses of the C entry points
+// bind(es_spmm_ws, es_spmm_backward, es_spmm_backward_pull, es_spmm_backward_ws,
+// es_spmm_backward_workspace_bytes): addresses of the C entry points
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
-    if (n != 3) { PyErr_SetString(PyExc_TypeError, "bind takes three addresses"); return nullptr; }
-    void* p[3];
-    for (int i = 0; i < 3; ++i) {
+    if (n != 5) { PyErr_SetString(PyExc_TypeError, "bind takes five addresses"); return nullptr; }
+    void* p[5];
+    for (int i = 0; i < 5; ++i) {
         p[i] = PyLong_AsVoidPtr(a[i]);
         if (!p[i]) {
             if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "null entry point");
@@ -195,6 +199,8 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n)
     g_spmm_ws = reinterpret_cast<decltype(g_spmm_ws)>(p[0]);
     g_backward = reinterpret_cast<decltype(g_backward)>(p[1]);
     g_pull = reinterpret_cast<decltype(g_pull)>(p[2]);
+    g_backward_ws = reinterpret_cast<decltype(g_backward_ws)>(p[3]);
+    g_backward_bytes = reinterpret_cast<decltype(g_backward_bytes)>(p[4]);
     Py_RETURN_NONE;
 }
 
@@ -221,6 +227,27 @@ PyObject* spmm(PyObject*, PyObject* const* a, Py_ssize_t n)
     });
 }
 
+// `bytes` from torch's allocator, in the pool of the stream that will use them: given
+// back as soon as the work on them is queued, they are handed out again in that stream's order only.
+struct Scratch {
+    void* p = nullptr;
+    Scratch(size_t bytes, hipStream_t stream) noexcept
+    {
+        // a capture that torch does not know of must not see the allocator ask the runtime for memory
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (!bytes || hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) return;
+        try {
+            p = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, stream);
+        } catch (...) {
+            p = nullptr;                               // no room: the caller's form without a workspace
+        }
+    }
+    ~Scratch()
+    {
+        if (p) c10::hip::HIPCachingAllocator::raw_delete(p);
+    }
+};
+
 // backward(rowptr, colidx, vals, dY, dX, W, mode, seed, norm, F, stream, nnz)
 PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
@@ -230,6 +257,14 @@ PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n)
         !g.parse(a[0], a[1], a[2], a[11]) || !p.matrices(g.N, a[3], a[4]))
         Py_RETURN_NONE;
     return unlocked([&] {
+        // sized by the entries there are: nnz may be a hint
+        const size_t bytes = g_backward_bytes(g.N, g.stored, p.F, p.W, p.mode);
+        if (bytes) {
+            const Scratch ws(bytes, static_cast<hipStream_t>(p.stream));
+            if (ws.p)
+                return g_backward_ws(g.rowptr, g.colidx, g.vals, p.x, p.y, g.N, g.stored, p.F, p.ldx, p.ldy, p.W,
+                                     p.mode, p.seed, p.norm, ws.p, bytes, p.stream);
+        }
         return g_backward(g.rowptr, g.colidx, g.vals, p.x, p.y, g.N, g.nnz, p.F, p.ldx, p.ldy, p.W, p.mode, p.seed,
                           p.norm, p.stream);
     });

@@ -42,6 +42,7 @@
 #include "es_part_kernel.h"
 #include "es_flat_kernel.h"
 #include "es_aux_kernels.h"
+#include "es_bin_kernel.h"
 #include "es_pull_kernel.h"
 
 // Workspace of es_spmm_static_ws: the cuts array of the column-partitioned
@@ -491,11 +492,12 @@ hipError_t launch_partitioned(Args a, dim3 grid, int32_t* cuts, hipStream_t st)
     return hipSuccess;
 }
 
-// Shared host path of es_spmm_norm (X -> Y) and es_spmm_backward (dY -> dX).
+// Shared host path of es_spmm_norm (X -> Y) and es_spmm_backward (dY -> dX).  `deal`:
+// row workgroups in order round the XCDs instead of a contiguous range each (row kernel).
 int es_run(const int32_t* rowptr, const int32_t* colidx, const float* vals, const float* X, float* Y,
            int64_t N, int64_t nnz, int32_t F, int32_t ldx, int32_t ldy, int32_t W, int32_t mode,
            uint64_t seed, int32_t norm, bool backward, const es_launch_opts_t* opts, void* workspace,
-           size_t workspace_bytes, void* stream)
+           size_t workspace_bytes, void* stream, bool deal = false)
 {
     const int bad = check_sizes(N, nnz, F, ldx, ldy, W, mode, norm);
     if (bad != ES_OK) return bad;
@@ -522,7 +524,8 @@ int es_run(const int32_t* rowptr, const int32_t* colidx, const float* vals, cons
     a.N = N; a.seed = seed; a.F = F; a.ldx = ldx; a.ldy = ldy;
     a.W = (mode == ES_FULL) ? INT32_MAX : W;
     a.mode = mode; a.logR = p.logR; a.norm = norm; a.long_k = p.long_k;
-    a.nblocks = (uint32_t)p.nblocks; a.blocks_per_xcd = (uint32_t)p.per_xcd;
+    a.nblocks = (uint32_t)p.nblocks;
+    a.blocks_per_xcd = deal && !p.flat && !p.partition && !p.long_alone ? 0u : (uint32_t)p.per_xcd;
     a.long_blocks = (uint32_t)p.long_blocks;
     a.cuts = nullptr; a.part_cols = 0; a.phase = 0;
 
@@ -570,6 +573,77 @@ int es_run(const int32_t* rowptr, const int32_t* colidx, const float* vals, cons
 int build_transposed(const int32_t* rowptr, const int32_t* colidx, const float* vals, int64_t N,
                      int64_t nnz, int32_t W, int32_t mode, uint64_t seed, int32_t norm, int32_t* out_ptr,
                      int32_t* out_end, int32_t* out_idx, float* out_vals, int32_t* out_pos, void* stream);
+
+// Layout of the binned transposed product's workspace (es_bin_kernel.h); bytes == 0:
+// the scatter is the faster form, or this one does not apply.
+struct BinPlan {
+    int64_t capacity;                  // kept entries at most
+    int log_width, nbins, walkers;
+    size_t records, counts, base, t_ptr, t_row, t_val, bytes;
+};
+
+// Where the line lies: the scatter moves one 64-byte request per kept entry and 16
+// columns, 20.5 G of them a second; this form takes some 25 us of launches and first
+// round trips, 0.04 us per 1000 kept entries to sort them, and the gather.  us,
+// scatter / this: F = 128: 170 k rows, 2.1 M entries at most 406 / 126; 10 k, 131 k (1.05 M
+// requests) 36 / 32; F = 64: 20 k, 260 k (1.04 M) 37 / 46; 40 k, 494 k (2.0 M) 62 / 41; 233 k,
+// 14.9 M 2923 / 1048; F = 32: 40 k, 494 k (1.0 M) 34 / 38; 80 k, 989 k (2.0 M) 60 / 49.  With one
+// request per entry the sort costs what it saves: F = 16: 160 k, 2.0 M 60 / 66; 2.4 M rows,
+// 10.5 M 382 / 399; 160 k, 7.6 M 191 / 159.
+BinPlan plan_bins(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode)
+{
+    BinPlan p = {};
+    if (mode != ES_BUCKET && mode != ES_FASTRAND) return p;    // exact rows have no bound on their length
+    if (W < 1 || W > kBinMaxW || F <= 16 || N < 1 || N > (1 << kBinRowBits) || nnz < 1 || nnz > INT32_MAX) return p;
+    p.capacity = nnz < N * W ? nnz : N * W;
+    if (p.capacity * ((F + 15) / 16) < kBinMinRequests) return p;
+    // blocks of N / 1024 columns up to N / 2048: enough workgroups for the sort, runs of records long enough to write
+    while (p.log_width < 32 - kBinRowBits && (N >> (p.log_width + 1)) >= 1024) ++p.log_width;
+    p.nbins = (int)((N + ((int64_t)1 << p.log_width) - 1) >> p.log_width);
+    p.walkers = (int)((N + kWaveSize - 1) / kWaveSize < kBinWalkers ? (N + kWaveSize - 1) / kWaveSize : kBinWalkers);
+    const auto take = [&p](size_t bytes) { const size_t at = p.bytes; p.bytes += (bytes + 255) / 256 * 256; return at; };
+    p.records = take((size_t)p.capacity * sizeof(uint2));
+    p.counts = take((size_t)p.walkers * p.nbins * sizeof(int32_t));
+    p.base = take((size_t)(p.nbins + 1) * sizeof(int32_t));
+    p.t_ptr = take((size_t)(N + 1) * sizeof(int32_t));
+    p.t_row = take((size_t)p.capacity * sizeof(int32_t));
+    p.t_val = take((size_t)p.capacity * sizeof(float));
+    return p;
+}
+
+// The transposed product through `workspace`, laid out by plan_bins.
+int run_binned(const int32_t* rowptr, const int32_t* colidx, const float* vals, const float* dY, float* dX,
+               int64_t N, int32_t F, int32_t ldy, int32_t ldx, int32_t W, int32_t mode, uint64_t seed,
+               int32_t norm, const BinPlan& p, void* workspace, void* stream)
+{
+    unsigned char* ws = static_cast<unsigned char*>(workspace);
+    BinArgs a;
+    a.rowptr = rowptr; a.colidx = colidx; a.vals = vals;
+    a.records = reinterpret_cast<uint2*>(ws + p.records);
+    a.counts = reinterpret_cast<int32_t*>(ws + p.counts);
+    a.base = reinterpret_cast<int32_t*>(ws + p.base);
+    a.t_ptr = reinterpret_cast<int32_t*>(ws + p.t_ptr);
+    a.t_row = reinterpret_cast<int32_t*>(ws + p.t_row);
+    a.t_val = reinterpret_cast<float*>(ws + p.t_val);
+    a.N = N; a.capacity = p.capacity; a.seed = seed; a.W = W; a.mode = mode; a.norm = norm;
+    a.log_width = p.log_width; a.nbins = p.nbins; a.walkers = p.walkers;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const uint32_t lds = (uint32_t)p.nbins * sizeof(int32_t);
+    hipLaunchKernelGGL(es_bin_walk_kernel<false>, dim3((uint32_t)p.walkers), dim3(kBinThreads), lds, st, a);
+    if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
+    hipLaunchKernelGGL(es_bin_scan_kernel, dim3((uint32_t)(p.nbins + kWaveSize - 1) / kWaveSize), dim3(kBinScanThreads), 0, st, a);
+    if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
+    hipLaunchKernelGGL(es_bin_base_kernel, dim3(1), dim3(kBinScanThreads), 0, st, a);
+    if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
+    hipLaunchKernelGGL(es_bin_walk_kernel<true>, dim3((uint32_t)p.walkers), dim3(kBinThreads), lds, st, a);
+    if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
+    hipLaunchKernelGGL(es_bin_sort_kernel, dim3((uint32_t)p.nbins), dim3(kBlockThreads), 0, st, a);
+    if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
+    // the row kernel: it multiplies no absent entries, so infinities in dY come out as from the scatter
+    const es_launch_opts_t opts = {0, 0, 0, -1, 1};
+    return es_run(a.t_ptr, a.t_row, a.t_val, dY, dX, N, p.capacity, F, ldy, ldx, 0, ES_FULL, 0, ES_NORM_NONE, false,
+                  &opts, nullptr, 0, stream, mode == ES_BUCKET);
+}
 
 }  // namespace
 
@@ -657,6 +731,26 @@ int es_spmm_backward(const int32_t* rowptr, const int32_t* colidx, const float* 
                      const float* dY, float* dX, int64_t N, int64_t nnz, int32_t F, int32_t ldy,
                      int32_t ldx, int32_t W, int32_t mode, uint64_t seed, int32_t norm, void* stream)
 {
+    return es_run(rowptr, colidx, vals, dY, dX, N, nnz, F, ldy, ldx, W, mode, seed, norm, true, nullptr,
+                  nullptr, 0, stream);
+}
+
+size_t es_spmm_backward_workspace_bytes(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode)
+{
+    return plan_bins(N, nnz, F, W, mode).bytes;
+}
+
+int es_spmm_backward_ws(const int32_t* rowptr, const int32_t* colidx, const float* vals,
+                        const float* dY, float* dX, int64_t N, int64_t nnz, int32_t F, int32_t ldy,
+                        int32_t ldx, int32_t W, int32_t mode, uint64_t seed, int32_t norm,
+                        void* workspace, size_t workspace_bytes, void* stream)
+{
+    const BinPlan p = plan_bins(N, nnz, F, W, mode);
+    const bool sound = check_sizes(N, nnz, F, ldy, ldx, W, mode, norm) == ES_OK && rowptr && colidx && dY && dX &&
+                       reinterpret_cast<uintptr_t>(dY) % 4 == 0 && reinterpret_cast<uintptr_t>(dX) % 4 == 0;
+    if (reinterpret_cast<uintptr_t>(workspace) % 256) return ES_ERR_INVALID_ARG;
+    if (sound && workspace && p.bytes && workspace_bytes >= p.bytes)
+        return run_binned(rowptr, colidx, vals, dY, dX, N, F, ldy, ldx, W, mode, seed, norm, p, workspace, stream);
     return es_run(rowptr, colidx, vals, dY, dX, N, nnz, F, ldy, ldx, W, mode, seed, norm, true, nullptr,
                   nullptr, 0, stream);
 }

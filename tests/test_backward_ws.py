@@ -1,0 +1,120 @@
+"""The transposed product through a workspace (es_spmm_backward_ws, which es_spmm_backward of
+the Python binding takes for larger sampled products): every element against the oracle at the
+sizes where its blocks, walkers and 512-row steps begin and end."""
+import numpy as np
+import pytest
+
+import paper_2104_10716_amd as es
+
+
+def test_workspace_is_asked_for_only_where_the_form_applies():
+    ask = es.es_spmm_backward_workspace_bytes
+    assert ask(170_000, 2_370_240, 128, 16, "bucket") > 16 * 2_370_240          # 16 bytes per kept entry and more
+    assert ask(170_000, 2_370_240, 128, 16, "fastrand") == ask(170_000, 2_370_240, 128, 16, "bucket")
+    assert ask(170_000, 2_370_240, 128, 0, "full") == 0
+    assert ask(170_000, 2_370_240, 17, 16, "bucket") > 0 and ask(170_000, 2_370_240, 16, 16, "bucket") == 0
+    assert ask(2 ** 22, 2 ** 24, 64, 16, "bucket") > 0 and ask(2 ** 22 + 1, 2 ** 24, 64, 16, "bucket") == 0
+    assert ask(170_000, 2_370_240, 128, 4096, "bucket") > 0 and ask(170_000, 2_370_240, 128, 4097, "bucket") == 0
+    assert ask(19_717, 88_000, 32, 16, "bucket") == 0                           # small: the scatter is the faster form
+    for bad in ((0, 5, 64, 4), (5, 0, 64, 4), (-1, 5, 64, 4), (1000, 2 ** 31, 64, 10_000), (1000, 10 ** 6, 64, 0)):
+        assert ask(*bad, "bucket") == 0
+
+
+def _graph(N, avg, seed, F, ldx=None, hot=None, long_row=0):
+    from workloads import random_csr
+    rowptr, colidx = random_csr(N, avg, seed, empty_frac=0.05)
+    rng = np.random.default_rng(seed)
+    rows = np.repeat(np.arange(N), np.diff(rowptr))
+    cols = colidx.astype(np.int64)
+    if hot is not None:                                # a column that every row holds
+        rows, cols = np.concatenate([rows, np.arange(N)]), np.concatenate([cols, np.full(N, hot)])
+    if long_row:
+        rows = np.concatenate([rows, np.full(long_row, N // 2)])
+        cols = np.concatenate([cols, rng.choice(N, long_row, replace=False)])
+    key = np.unique(rows * N + cols)
+    rowptr = np.zeros(N + 1, dtype=np.int32)
+    rowptr[1:] = np.cumsum(np.bincount(key // N, minlength=N))
+    colidx = (key % N).astype(np.int32)
+    vals = rng.standard_normal(colidx.size).astype(np.float32)
+    dY = rng.uniform(-1, 1, (N, ldx or F)).astype(np.float32)
+    return rowptr, colidx, vals, dY
+
+
+CASES = [
+    # N, avg, F, ldx, mode, W, seed, norm, extras
+    (511, 300.0, 256, None, "fastrand", 200, 3, "none", {}),                    # fewer rows than one step, blocks of one column
+    (2_047, 90.0, 160, None, "bucket", 64, 0, "mean", {}),
+    (2_048, 90.0, 160, 164, "fastrand", 64, 0, "rescale", {}),                    # the first two-column blocks
+    (16_385, 14.0, 128, None, "fastrand", 16, 2 ** 63 + 5, "none", {}),         # one row more than all walkers' first
+    (40_961, 20.0, 41, 41, "bucket", 33, 0, "inv_degree", {}),                  # rows that are 4-byte aligned only
+    (131_073, 9.0, 20, None, "fastrand", 8, 77, "rsqrt", {}),                   # 512 rows and one more per walker
+    (30_000, 30.0, 640, 644, "fastrand", 1, 5, "none", dict(hot=29_999)),         # one entry per row; a column of all rows, the last
+    (30_000, 25.0, 64, None, "bucket", 16, 0, "none", dict(hot=0)),
+    (6_000, 60.0, 64, None, "fastrand", 4_096, 9, "none", dict(long_row=5_900)),  # the widest rows it takes
+    (6_000, 60.0, 64, None, "bucket", 4_096, 0, "none", dict(long_row=4_097)),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,avg,F,ldx,mode,W,seed,norm,extra", CASES)
+def test_backward_through_a_workspace(N, avg, F, ldx, mode, W, seed, norm, extra):
+    import torch
+    from gpu_util import DeviceCSR, check_Y, check_backward_against_oracle
+    import oracle
+    rowptr, colidx, vals, dY = _graph(N, avg, N + F, F, ldx, **extra)
+    nbytes = es.es_spmm_backward_workspace_bytes(N, colidx.size, F, W, mode)
+    assert nbytes > 0
+    for v in (vals, None):
+        d = DeviceCSR(rowptr, colidx, v, dY, F=F)
+        what = f"N={N} F={F} {mode} W={W} {norm}"
+        check_backward_against_oracle(d, W, mode, seed, norm, what=what)        # torch's allocator lends the workspace
+        ref, den = oracle.spmm_backward(rowptr, colidx, v, dY, F, W, mode, seed, norm=norm)
+        for size in (nbytes, nbytes - 256):                                     # its own, and one that is too small: the scatter
+            ws = torch.full((size // 4,), -1, dtype=torch.int32, device="cuda:0")
+            dX = torch.full((N, F + 3), float("nan"), dtype=torch.float32, device="cuda:0")
+            es.es_spmm_backward_ws(d.rowptr, d.colidx, d.vals, d.X, dX, W, mode, seed, norm, ws, F=F)
+            torch.cuda.synchronize()
+            assert torch.isnan(dX[:, F:]).all()
+            check_Y(dX[:, :F].cpu().numpy(), ref, den, f"{what} workspace {size}")
+
+
+@pytest.mark.gpu
+def test_backward_workspace_on_streams_in_graphs_and_with_infinities():
+    import torch
+    from gpu_util import DeviceCSR, check_Y
+    import oracle
+    N, F, W = 20_000, 64, 16
+    rowptr, colidx, vals, dY = _graph(N, 20.0, 5, F)
+    d = DeviceCSR(rowptr, colidx, vals, dY)
+    ref, den = oracle.spmm_backward(rowptr, colidx, vals, dY, F, W, "fastrand", 3)
+    assert es.es_spmm_backward_workspace_bytes(N, colidx.size, F, W, "fastrand") > 0
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    outs = [torch.full((N, F), float("nan"), device="cuda:0") for _ in range(4)]
+    side.wait_stream(torch.cuda.current_stream())
+    for out, s in zip(outs, (None, side, side.cuda_stream, None)):              # calls on two streams, each with scratch of its own
+        es.es_spmm_backward(d.rowptr, d.colidx, d.vals, d.X, out, W, "fastrand", 3, stream=s, nnz=7)   # nnz: only a hint here
+    torch.cuda.synchronize()
+    for out in outs:
+        check_Y(out.cpu().numpy(), ref, den, "streams")
+    # inside a graph the form without a workspace runs; every replay is whole
+    with torch.cuda.stream(side):
+        es.es_spmm_backward(d.rowptr, d.colidx, d.vals, d.X, outs[0], W, "fastrand", 3)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        es.es_spmm_backward(d.rowptr, d.colidx, d.vals, d.X, outs[1], W, "fastrand", 3)
+    for _ in range(3):
+        outs[1].fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        check_Y(outs[1].cpu().numpy(), ref, den, "replay")
+    # an infinite or missing gradient reaches the same places as by the scatter, and no others
+    d.X[11, 5], d.X[4_000, 6] = float("inf"), float("nan")
+    es.es_spmm_backward(d.rowptr, d.colidx, d.vals, d.X, outs[2], W, "fastrand", 3)
+    es.es_spmm_backward_ex(d.rowptr, d.colidx, d.vals, d.X, outs[3], W, "fastrand", 3)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.isnan(outs[2]), torch.isnan(outs[3]))
+    assert torch.equal(torch.isposinf(outs[2]), torch.isposinf(outs[3]))
+    assert torch.equal(torch.isneginf(outs[2]), torch.isneginf(outs[3]))
+    assert int(torch.isinf(outs[2]).sum()) > 0
