@@ -229,7 +229,7 @@ __device__ __forceinline__ void part_row_block(const Args& a, uint32_t vb, int p
 #pragma unroll
         for (int ch = 0; ch < CH; ++ch) acc[ch].zero();
         bool touched = fill > 0;                 // wave-uniform: the piece holds a kept entry
-        consume_tile<G, CH, VEC, ALIGNED, WIDE>(tile, fill, e, E, a.X, a.ldx, cols, acc);
+        consume_tile<G, CH, VEC, ALIGNED, WIDE, false>(tile, fill, e, E, a.X, a.ldx, cols, acc);
         wave_lds_fence();
 
         // ---- further tiles of a long piece --------------------------------------
@@ -237,7 +237,7 @@ __device__ __forceinline__ void part_row_block(const Args& a, uint32_t vb, int p
             fill = stage_more(i, walk, 0, min(slots[i] - t0, T), 0);
             touched = touched || fill > 0;
             wave_lds_fence();
-            consume_tile<G, CH, VEC, ALIGNED, WIDE>(tile, fill, e, E, a.X, a.ldx, cols, acc);
+            consume_tile<G, CH, VEC, ALIGNED, WIDE, false>(tile, fill, e, E, a.X, a.ldx, cols, acc);
             wave_lds_fence();
         }
 

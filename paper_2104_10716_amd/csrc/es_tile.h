@@ -161,10 +161,49 @@ __device__ __forceinline__ void stage_tile(RowSampler& sampler, int t, int team,
     });
 }
 
+// One batch of N entries of a tile from slot j on, E apart, of which those below
+// `count` are there: N LDS broadcasts, then N*CH independent loads of X, then the FMAs.
+template <int N, int G, int CH, int VEC, bool ALIGNED, bool WIDE>
+__device__ __forceinline__ void consume_last(const uint2* tile, int j, int count, int E, const float* __restrict__ X,
+                                             int64_t ldx, const LaneCols<G, CH, VEC, ALIGNED>& cols,
+                                             Pack<VEC, ALIGNED> (&acc)[CH])
+{
+    using P = Pack<VEC, ALIGNED>;
+    using K = RowKey<ALIGNED, WIDE>;
+    uint2 ed[N];
+    bool ok[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const int jj = j + u * E;
+        ok[u] = jj < count;
+        ed[u] = tile[ok[u] ? jj : j];                        // absent slots re-read a present one
+    }
+    P x[N][CH];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const float* xr = K::row(X, ed[u].x, ldx);
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) x[u][ch].load(xr + cols.off[ch]);
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const float v = __uint_as_float(ed[u].y);
+        if (ok[u]) {
+#pragma unroll
+            for (int ch = 0; ch < CH; ++ch) acc[ch].fma(v, x[u][ch]);
+        }
+    }
+}
+
 // Stage 2 of Algorithm 1 for one tile: this lane's edge slot e (of E) walks
 // tile entries e, e+E, ... < count, U at a time: U LDS broadcasts, then U*CH
-// independent loads of X, then the FMAs.
-template <int G, int CH, int VEC, bool ALIGNED, bool WIDE>
+// independent loads of X, then the FMAs.  What is left behind the full batches is
+// loaded as a batch of U, U / 2 or U / 4, the smallest that holds every lane's rest:
+// an absent entry's load hits the vector cache, but takes as long there as a real one
+// (ids that cluster, 170 k rows of mean 40, F = 64: Bucket W = 32 85.3 -> 76.6 us, FastRand
+// W = 64 90.2 -> 82.0; uniform ids there, which wait for L2 misses: 103.5 -> 101.6, 120.0 ->
+// 119.3).  FINE == false: always U, for a kernel at the edge of its registers.
+template <int G, int CH, int VEC, bool ALIGNED, bool WIDE, bool FINE = true>
 __device__ __forceinline__ void consume_tile(const uint2* tile, int count, int e, int E,
                                              const float* __restrict__ X, int64_t ldx,
                                              const LaneCols<G, CH, VEC, ALIGNED>& cols,
@@ -192,30 +231,13 @@ __device__ __forceinline__ void consume_tile(const uint2* tile, int count, int e
             for (int ch = 0; ch < CH; ++ch) acc[ch].fma(v, x[u][ch]);
         }
     }
-    if (j < count) {                                         // last partial batch
-        uint2 ed[U];
-        bool ok[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int jj = j + u * E;
-            ok[u] = jj < count;
-            ed[u] = tile[ok[u] ? jj : j];                    // absent slots re-read a present one
-        }
-        P x[U][CH];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float* xr = K::row(X, ed[u].x, ldx);
-#pragma unroll
-            for (int ch = 0; ch < CH; ++ch) x[u][ch].load(xr + cols.off[ch]);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const float v = __uint_as_float(ed[u].y);
-            if (ok[u]) {
-#pragma unroll
-                for (int ch = 0; ch < CH; ++ch) acc[ch].fma(v, x[u][ch]);
-            }
-        }
+    constexpr int H = U / 2, Q = U >= 4 ? U / 4 : 1;
+    if (!FINE || __ballot(j + H * E < count)) {
+        if (j < count) consume_last<U, G, CH, VEC, ALIGNED, WIDE>(tile, j, count, E, X, ldx, cols, acc);
+    } else if (__ballot(j + Q * E < count)) {
+        if (j < count) consume_last<H, G, CH, VEC, ALIGNED, WIDE>(tile, j, count, E, X, ldx, cols, acc);
+    } else if (j < count) {
+        consume_last<Q, G, CH, VEC, ALIGNED, WIDE>(tile, j, count, E, X, ldx, cols, acc);
     }
 }
 
