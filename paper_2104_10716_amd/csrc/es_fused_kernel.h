@@ -374,8 +374,9 @@ __device__ __forceinline__ void long_block(const Args& a, uint32_t bx, uint32_t 
 // ---------------------------------------------------------------------------
 // Six waves per SIMD: the two registers more that the compiler takes otherwise cost a
 // sixth of the waves (170 k rows of mean 14, W = 16, F = 128: 83 us at five, 79 at six).
+// Four chunks per lane need 88 to 94 registers, which would spill at six.
 template <int G, int CH, int VEC, bool ALIGNED, bool BACKWARD, bool WIDE>
-__global__ void __launch_bounds__(kBlockThreads, 6) es_spmm_kernel(const Args a)
+__global__ void __launch_bounds__(kBlockThreads, CH == 4 ? 5 : 6) es_spmm_kernel(const Args a)
 {
     __shared__ uint2 lds[kWavesPerBlock * kWaveTileStride];
     __shared__ LongScratch long_scratch;

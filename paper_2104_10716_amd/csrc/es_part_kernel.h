@@ -267,8 +267,12 @@ __device__ __forceinline__ void part_row_block(const Args& a, uint32_t vb, int p
 // p = b % 8 (hardware deals workgroups round-robin; only the speed depends on
 // it, not the result) and serves column range p for the rows of row range
 // (p + phase) % 8.
+//
+// Four waves per SIMD where the variant fits 128 registers: at the 130 that the compiler
+// takes otherwise only three are resident (125 k rows of mean 300, F = 64: 1362 us, 1091 at
+// four; F = 41: 1320 and 1089).
 template <int G, int CH, int VEC, bool ALIGNED, bool WIDE>
-__global__ void __launch_bounds__(kBlockThreads) es_spmm_part_kernel(const Args a)
+__global__ void __launch_bounds__(kBlockThreads, VEC == 4 && G < 64 && !WIDE ? 4 : 1) es_spmm_part_kernel(const Args a)
 {
     __shared__ uint2 lds[kWavesPerBlock * kWaveTileStride];
     const bool long_sweep = blockIdx.x < a.long_blocks;          // a.long_blocks is a multiple of 8
