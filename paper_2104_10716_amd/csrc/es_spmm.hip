@@ -307,15 +307,27 @@ size_t part_workspace_bytes(int64_t N)
     return (size_t)N * kParts * sizeof(int32_t);
 }
 
-// Whether to run the column-partitioned product.  It pays when a row's piece
-// inside one column range is long enough to amortise the extra pass over Y
-// (kept entries per row well above kParts) and when an XCD's eighth of a
-// 32-column slice of X is of the order of its L2.  Exact product, F = 64, us without /
-// in ranges: mean 490: 30 k rows (share 0.5 MB) 285 / 323, 58 k 745 / 569, 233 k 3777 /
-// 2144, 466 k (7.5 MB) 7880 / 5118; mean 150: 250 k 1263 / 1069, 600 k 3109 / 2869, but
-// below 125 k rows, where the row form serves the ranges, 125 k 600 / 818 and 45 k 171 /
-// 367: there the line on the mean is too low.
-bool pick_partition(int64_t N, double mean_kept, int32_t mode, int cols_per_block, int force)
+// Rows from which the flattened kernel serves the column ranges of 16-byte-aligned rows.
+bool part_flat_size(int64_t N) { return (double)N * 32.0 > 4.0e6; }
+
+// Whether to run the column-partitioned product.  It pays when a row's piece inside one
+// column range is long enough to amortise the extra pass over Y (kept entries per row well
+// above kParts), when an XCD's eighth of a 32-column slice of X is of the order of its
+// L2, and when X as a whole is so far beyond an L2 that whole rows miss.  The row form
+// pays some 0.5 us per 100 rows whatever their length, so it asks for longer rows.  Exact
+// product, us, whole rows / column ranges:
+//  * flattened kernel (`flat`): F = 32: mean 150, 170 k rows (22 MB) 403 / 424, 233 k (30 MB) 575 /
+//    563, mean 300, 140 k (18 MB) 620 / 530; F = 16: mean 150, 350 k 796 / 647, mean 300, 140 k 467 / 454;
+//    F = 64: mean 150, 170 k 855 / 727, mean 300, 233 k 2372 / 1534; F = 128: mean 150, 170 k 1741 / 1322.
+//  * row form, mean 150: never: F = 64, 45 k rows 176 / 309, 90 k 422 / 577, 125 k 605 / 802; F = 41,
+//    233 k 1247 / 1617; F = 205, 60 k 1075 / 1462, 233 k 4443 / 7341.
+//  * row form, mean 300: F = 64, 30 k (7.7 MB) 183 / 270, 45 k (11.5) 337 / 364, 60 k (15.4) 495 / 470, 125 k
+//    1205 / 1082; F = 41, 60 k (9.8) 428 / 496, 90 k (14.8) 769 / 721, 233 k 2472 / 2172; F = 128, 30 k (15.4)
+//    480 / 463, 45 k 791 / 668; F = 205, 60 k 2094 / 1801, 125 k 4620 / 4652, 233 k 8802 / 10384 (two and more
+//    slices of rows that tile no line); at mean 490 125 k 7444 / 6196, 233 k 14332 / 14988.
+//  * row form on rows of one line: F = 32, 125 k, mean 300 540 / 892, mean 490 874 / 1127.
+bool pick_partition(int64_t N, double mean_kept, int32_t mode, int cols_per_block, int F, bool aligned, bool flat,
+                    int force)
 {
     if (mode == ES_BUCKET) return false;       // first-W entries crowd into the lowest column range
     if (N < kParts * 64) return false;
@@ -327,7 +339,12 @@ bool pick_partition(int64_t N, double mean_kept, int32_t mode, int cols_per_bloc
     if (mode == ES_FASTRAND) return false;
     if (mean_kept < 128.0) return false;
     const double share = (double)N * cols_per_block * 4.0 / kParts;
-    return share >= 0.5e6 && share <= 12.0e6;
+    if (share < 0.5e6 || share > 12.0e6) return false;
+    const double table = (double)N * (F < 32 ? 32 : F) * 4.0;       // no gather moves less than a line
+    if (flat) return table >= (mean_kept < 256.0 ? 24.0e6 : 14.0e6);
+    if (aligned && F <= 32) return false;
+    if (!aligned && F > 64 && N > 125000) return false;
+    return mean_kept >= 256.0 && table >= 14.0e6;
 }
 
 // Launch shape for N >= 1 rows.  `aligned`: F and both row strides are
@@ -350,7 +367,9 @@ int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool a
     // Column-partitioned product?  Decided on 32-column slices, its best width on
     // all but the smallest tables.
     const int slice_cols = F < 32 ? s.G * s.CH * s.vec : 32;
-    p->partition = !backward && have_workspace && pick_partition(N, mean, mode, slice_cols, ov.partition);
+    p->partition = !backward && have_workspace &&
+                   pick_partition(N, mean, mode, slice_cols, F, aligned,
+                                  aligned && s.vec == 4 && ov.kernel != 1 && part_flat_size(N), ov.partition);
 
     // The flattened kernel applies to 128-bit accesses; FastRand in the
     // partitioned product needs the row kernel's per-row walk over all W slots.
@@ -365,12 +384,13 @@ int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool a
     // every row short, which the row kernel pays for per row and the flattened
     // kernel does not; so the narrow (32-column) slices go with the flattened
     // kernel.  Both sides, us (profiles/ has the sweeps):
-    //  * partitioned product: 32-column slices on the flattened kernel above 125 k
-    //    rows, where an XCD's share of a 64-column slice no longer fits its L2 (row
-    //    form on 64-column slices / flattened on 32, F = 64, mean 490: 160 k rows
-    //    1834 / 1465, 233 k 2815 / 2145, 466 k 6599 / 5123).  The line is from the
-    //    flattened kernel's former version; the present one is the faster from
-    //    60 - 90 k rows on as well (58 k 569 / 629, 90 k 1161 / 915, 125 k 1425 / 1177).
+    //  * partitioned product: the flattened kernel above 125 k rows, where an XCD's share of
+    //    a 64-column slice no longer fits its L2 (row form / this, F = 64: 170 k rows of mean 150
+    //    1149 / 727, 233 k of mean 300 2181 / 1534; it is the faster below that too, 90 k of mean 300 726 /
+    //    640, but multiplies padding by zero, which turns an infinity in X into a NaN; the row
+    //    form does not).  Slices of 32 columns where they tile 128-byte lines, else of 64, which
+    //    fetch fewer lines twice (32 / 64 columns, F = 100: 170 k of mean 150 1970 / 1680, 233 k of mean
+    //    300 5123 / 4501; F = 128, 233 k of mean 300 2910 / 3077).
     //  * tables of 0.3 GB and more with F >= 128: 32-column slices on the flattened
     //    kernel, so that the X rows of a community of ids come nearer to an L2.
     //    Whole rows on the row kernel / this, 0.6 GB, F = 128: ids that cluster, mean
@@ -390,8 +410,8 @@ int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool a
         else if (ov.G == 0) {
             const double table = (double)N * F * 4.0;
             if (p->partition) {
-                want_flat = flat_allowed && (double)N * 32.0 > 4.0e6;
-                slice_G = want_flat ? 8 : 16;
+                want_flat = flat_allowed && part_flat_size(N);
+                slice_G = want_flat && F % 32 == 0 ? 8 : 16;
             } else if (flat_allowed && F >= 128 && table >= 300.0e6) {
                 want_flat = true;
                 slice_G = 8;

@@ -149,6 +149,19 @@ def test_column_partition_choice():
     assert es.es_spmm_launch_info(*dense, 64, 0, "full", backward=True)["column_ranges"] == 1
 
 
+@pytest.mark.parametrize("N,mean,F,aligned,ranges,lanes", [
+    # row form: rows of 256 entries and X of 14 MB on
+    (62_500, 255, 64, True, 1, 16), (62_500, 256, 64, True, 8, 16), (54_000, 300, 64, True, 1, 16), (55_000, 300, 64, True, 8, 16),
+    # ... not for rows of one line, nor for wide rows that tile none on large tables
+    (125_000, 490, 32, True, 1, 8), (125_000, 490, 36, True, 8, 16), (125_000, 300, 205, False, 8, 16), (125_001, 490, 205, False, 1, 64),
+    # flattened kernel: X, in lines, of 24 MB, or 14 MB from a mean of 256 on
+    (187_000, 150, 32, True, 1, 8), (188_000, 150, 32, True, 8, 8), (126_000, 300, 32, True, 8, 8), (350_000, 150, 16, True, 8, 4),
+    (233_000, 127, 64, True, 1, 16), (233_000, 128, 64, True, 8, 8), (180_000, 300, 100, True, 8, 16)])
+def test_column_range_rule(N, mean, F, aligned, ranges, lanes):
+    info = es.es_spmm_launch_info(N, N * mean, F, 0, "full", aligned16=aligned)
+    assert (info["column_ranges"], info["lanes_per_row"]) == (ranges, lanes)
+
+
 def test_flattened_kernel_choice():
     """Without options the flattened kernel runs where narrow column slices pay:
     the partitioned product once a 64-column share outgrows an L2, and tables of
