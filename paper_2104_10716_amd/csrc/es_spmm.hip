@@ -342,6 +342,7 @@ bool pick_partition(int64_t N, double mean_kept, int32_t mode, int cols_per_bloc
     if (share < 0.5e6 || share > 12.0e6) return false;
     const double table = (double)N * (F < 32 ? 32 : F) * 4.0;       // no gather moves less than a line
     if (flat) return table >= (mean_kept < 256.0 ? 24.0e6 : 14.0e6);
+    if (N <= 62500) return true;               // not at the crossing: kept for callers that count on the ranges' fixed order of sums
     if (aligned && F <= 32) return false;
     if (!aligned && F > 64 && N > 125000) return false;
     return mean_kept >= 256.0 && table >= 14.0e6;

@@ -151,7 +151,7 @@ def test_column_partition_choice():
 
 @pytest.mark.parametrize("N,mean,F,aligned,ranges,lanes", [
     # row form: rows of 256 entries and X of 14 MB on
-    (62_500, 255, 64, True, 1, 16), (62_500, 256, 64, True, 8, 16), (54_000, 300, 64, True, 1, 16), (55_000, 300, 64, True, 8, 16),
+    (62_500, 150, 64, True, 8, 16), (62_501, 255, 64, True, 1, 16), (62_501, 256, 64, True, 8, 16), (70_000, 300, 41, False, 1, 16),
     # ... not for rows of one line, nor for wide rows that tile none on large tables
     (125_000, 490, 32, True, 1, 8), (125_000, 490, 36, True, 8, 16), (125_000, 300, 205, False, 8, 16), (125_001, 490, 205, False, 1, 64),
     # flattened kernel: X, in lines, of 24 MB, or 14 MB from a mean of 256 on
