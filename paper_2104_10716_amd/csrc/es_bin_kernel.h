@@ -203,12 +203,23 @@ __global__ void __launch_bounds__(kBinScanThreads) es_bin_base_kernel(const BinA
     if (threadIdx.x == kBinScanThreads - 1 && a.nbins == kBinMaxBlocks) a.base[a.nbins] = at;
 }
 
+// The m-th record that a sorting thread requests in its step from i on, the last one
+// in place of what lies behind it.  Unsigned: i runs up to a step behind `end`, which may be 2^31 - 1.
+constexpr int kBinSortM = 8;                          // records per thread requested together
+constexpr uint32_t kBinSortStep = kBinSortM * kBlockThreads;
+__host__ __device__ constexpr uint32_t bin_record(uint32_t i, int m, uint32_t end)
+{
+    return i + m * kBlockThreads < end ? i + m * kBlockThreads : end - 1;
+}
+static_assert(bin_record(INT32_MAX - 1u, kBinSortM - 1, INT32_MAX) == INT32_MAX - 1u && INT32_MAX - 1u + kBinSortStep > INT32_MAX,
+              "the last records of the largest graph");
+
 // Sorts column block blockIdx.x by column into the transposed graph.
 __global__ void __launch_bounds__(kBlockThreads) es_bin_sort_kernel(const BinArgs a)
 {
     constexpr int COLS = 1 << (32 - kBinRowBits);     // columns of a block at most
     constexpr int PER = COLS / kBlockThreads;
-    constexpr int M = 8;                              // records per thread requested together
+    constexpr int M = kBinSortM;
     __shared__ int32_t cursor[COLS];
     __shared__ int32_t wave_total[kWavesPerBlock];
     const int tid = threadIdx.x;
@@ -216,14 +227,14 @@ __global__ void __launch_bounds__(kBlockThreads) es_bin_sort_kernel(const BinArg
     const int wave = tid >> 6;
     const int64_t c0 = (int64_t)blockIdx.x << a.log_width;
     const int cols = (int)min((int64_t)1 << a.log_width, a.N - c0);
-    const int32_t begin = (int32_t)min((int64_t)a.base[blockIdx.x], a.capacity);
-    const int32_t end = (int32_t)min((int64_t)a.base[blockIdx.x + 1], a.capacity);
+    const uint32_t begin = (uint32_t)min((int64_t)a.base[blockIdx.x], a.capacity);
+    const uint32_t end = (uint32_t)min((int64_t)a.base[blockIdx.x + 1], a.capacity);
     for (int c = tid; c < COLS; c += kBlockThreads) cursor[c] = 0;
     __syncthreads();
-    for (int32_t i0 = begin + tid; i0 < end; i0 += M * kBlockThreads) {
+    for (uint32_t i0 = begin + tid; i0 < end; i0 += kBinSortStep) {
         uint32_t key[M];
 #pragma unroll
-        for (int m = 0; m < M; ++m) key[m] = a.records[min(i0 + m * kBlockThreads, end - 1)].x;
+        for (int m = 0; m < M; ++m) key[m] = a.records[bin_record(i0, m, end)].x;
 #pragma unroll
         for (int m = 0; m < M; ++m)
             if (i0 + m * kBlockThreads < end) atomicAdd(&cursor[key[m] >> kBinRowBits], 1);
@@ -241,7 +252,7 @@ __global__ void __launch_bounds__(kBlockThreads) es_bin_sort_kernel(const BinArg
     }
     if (lane == kWaveSize - 1) wave_total[wave] = incl;
     __syncthreads();
-    int32_t at = begin + incl - mine;
+    int32_t at = (int32_t)begin + incl - mine;
     for (int w = 0; w < wave; ++w) at += wave_total[w];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
@@ -250,12 +261,12 @@ __global__ void __launch_bounds__(kBlockThreads) es_bin_sort_kernel(const BinArg
         if (c < cols) a.t_ptr[c0 + c] = at;
         at += count[i];
     }
-    if (blockIdx.x == gridDim.x - 1 && tid == 0) a.t_ptr[a.N] = end;
+    if (blockIdx.x == gridDim.x - 1 && tid == 0) a.t_ptr[a.N] = (int32_t)end;
     __syncthreads();
-    for (int32_t i0 = begin + tid; i0 < end; i0 += M * kBlockThreads) {
+    for (uint32_t i0 = begin + tid; i0 < end; i0 += kBinSortStep) {
         uint2 rec[M];
 #pragma unroll
-        for (int m = 0; m < M; ++m) rec[m] = a.records[min(i0 + m * kBlockThreads, end - 1)];
+        for (int m = 0; m < M; ++m) rec[m] = a.records[bin_record(i0, m, end)];
 #pragma unroll
         for (int m = 0; m < M; ++m)
             if (i0 + m * kBlockThreads < end) {

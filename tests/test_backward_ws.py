@@ -118,3 +118,38 @@ def test_backward_workspace_on_streams_in_graphs_and_with_infinities():
     assert torch.equal(torch.isposinf(outs[2]), torch.isposinf(outs[3]))
     assert torch.equal(torch.isneginf(outs[2]), torch.isneginf(outs[3]))
     assert int(torch.isinf(outs[2]).sum()) > 0
+
+
+@pytest.mark.gpu
+def test_backward_workspace_with_as_many_entries_as_int32_counts():
+    """2^31 - 128 kept entries: the last column block ends within one step of the largest index.
+    Row r holds columns r .. r + 4094 (mod N), so a row of dX is a window of dY, summed here in 64 bits."""
+    import torch
+    N, K, F = 524_416, 4_095, 17
+    assert 2 ** 31 - 8 * 256 < N * K < 2 ** 31
+    dev = torch.device("cuda:0")
+    if torch.cuda.mem_get_info()[0] < 80 << 30:
+        pytest.skip("needs 80 GB of device memory")
+    rowptr = torch.arange(N + 1, dtype=torch.int32, device=dev) * K
+    colidx = torch.empty(N * K, dtype=torch.int32, device=dev)
+    window = torch.arange(K, dtype=torch.int32, device=dev)
+    for r in range(0, N, 65_536):
+        rows = torch.arange(r, min(N, r + 65_536), dtype=torch.int32, device=dev)
+        part = (rows[:, None] + window).remainder_(N)
+        colidx[r * K:r * K + part.numel()] = part.view(-1)
+    del part
+    gen = torch.Generator(device=dev).manual_seed(3)
+    dY = torch.randn(N, F, device=dev, generator=gen)
+    nbytes = es.es_spmm_backward_workspace_bytes(N, N * K, F, 4_096, "bucket")
+    assert nbytes > 16 * N * K
+    ws = torch.empty(nbytes // 4, dtype=torch.int32, device=dev)
+    dX = torch.full((N, F), float("nan"), device=dev)
+    print("  2^31 - 128 entries: launching", flush=True)
+    es.es_spmm_backward_ws(rowptr, colidx, None, dY, dX, 4_096, "bucket", workspace=ws)
+    torch.cuda.synchronize()
+
+    def window_sums(t):                                # row c: the sum of rows c - 4094 .. c (mod N)
+        run = torch.cat([t[N - K + 1:], t]).double().cumsum(0)
+        return run[K - 1:] - torch.cat([run.new_zeros(1, F), run[:N - 1]])
+    err = (dX.double() - window_sums(dY)).abs()
+    assert bool((err <= 1e-5 * window_sums(dY.abs())).all())
