@@ -603,6 +603,10 @@ struct BinPlan {
     size_t records, counts, base, t_ptr, t_row, t_val, bytes;
 };
 
+// How the exact product runs on the transposed sample: the row kernel on whole rows.  It
+// multiplies no absent entries, so infinities in dY come out as from the scatter.
+constexpr es_launch_opts_t kBinProduct = {0, 0, 0, -1, 1};
+
 // Where the line lies: the scatter moves one 64-byte request per kept entry and 16
 // columns, 20.5 G of them a second; this form takes some 25 us of launches and first
 // round trips, 0.04 us per 1000 kept entries to sort them, and the gather.  us,
@@ -618,6 +622,13 @@ BinPlan plan_bins(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode)
     if (W < 1 || W > kBinMaxW || F <= 16 || N < 1 || N > (1 << kBinRowBits) || nnz < 1 || nnz > INT32_MAX) return p;
     p.capacity = nnz < N * W ? nnz : N * W;
     if (p.capacity * ((F + 15) / 16) < kBinMinRequests) return p;
+    // only where both the gather this form ends in (some million columns are more than its grid covers) and the
+    // scatter can run, so that a call is refused or accepted whatever workspace there is, and refused before a launch
+    Plan product;
+    Overrides ov;
+    if (parse_opts(&kBinProduct, &ov) != ES_OK ||
+        make_plan(N, p.capacity, F, 0, ES_FULL, false, false, ov, false, &product) != ES_OK ||
+        make_plan(N, nnz, F, W, mode, false, true, Overrides(), false, &product) != ES_OK) return p;
     // blocks of N / 1024 columns up to N / 2048: enough workgroups for the sort, runs of records long enough to write
     while (p.log_width < 32 - kBinRowBits && (N >> (p.log_width + 1)) >= 1024) ++p.log_width;
     p.nbins = (int)((N + ((int64_t)1 << p.log_width) - 1) >> p.log_width);
@@ -660,10 +671,8 @@ int run_binned(const int32_t* rowptr, const int32_t* colidx, const float* vals, 
     if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
     hipLaunchKernelGGL(es_bin_sort_kernel, dim3((uint32_t)p.nbins), dim3(kBlockThreads), 0, st, a);
     if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
-    // the row kernel: it multiplies no absent entries, so infinities in dY come out as from the scatter
-    const es_launch_opts_t opts = {0, 0, 0, -1, 1};
     return es_run(a.t_ptr, a.t_row, a.t_val, dY, dX, N, p.capacity, F, ldy, ldx, 0, ES_FULL, 0, ES_NORM_NONE, false,
-                  &opts, nullptr, 0, stream, mode == ES_BUCKET);
+                  &kBinProduct, nullptr, 0, stream, mode == ES_BUCKET);
 }
 
 }  // namespace

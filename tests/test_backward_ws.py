@@ -16,6 +16,9 @@ def test_workspace_is_asked_for_only_where_the_form_applies():
     assert ask(2 ** 22, 2 ** 24, 64, 16, "bucket") > 0 and ask(2 ** 22 + 1, 2 ** 24, 64, 16, "bucket") == 0
     assert ask(170_000, 2_370_240, 128, 4096, "bucket") > 0 and ask(170_000, 2_370_240, 128, 4097, "bucket") == 0
     assert ask(19_717, 88_000, 32, 16, "bucket") == 0                           # small: the scatter is the faster form
+    # columns beyond the grid of the gather it ends in (64 at a time on tables of 512 MB and more), or of the scatter
+    assert ask(100, 10_000, 65_535 * 64, 100, "bucket") > 0 and ask(100, 10_000, 65_535 * 64 + 1, 100, "bucket") == 0
+    assert ask(5, 25, 65_535 * 256, 5, "fastrand") > 0 and ask(5, 25, 65_535 * 256 + 1, 5, "fastrand") == 0
     for bad in ((0, 5, 64, 4), (5, 0, 64, 4), (-1, 5, 64, 4), (1000, 2 ** 31, 64, 10_000), (1000, 10 ** 6, 64, 0)):
         assert ask(*bad, "bucket") == 0
 
