@@ -257,8 +257,8 @@ PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n)
         !g.parse(a[0], a[1], a[2], a[11]) || !p.matrices(g.N, a[3], a[4]))
         Py_RETURN_NONE;
     return unlocked([&] {
-        // sized by the entries there are: nnz may be a hint
-        const size_t bytes = g_backward_bytes(g.N, g.stored, p.F, p.W, p.mode);
+        // sized by the entries there are: nnz may be a hint (a negative one is refused, by the form without a workspace)
+        const size_t bytes = g.nnz < 0 ? 0 : g_backward_bytes(g.N, g.stored, p.F, p.W, p.mode);
         if (bytes) {
             const Scratch ws(bytes, static_cast<hipStream_t>(p.stream));
             if (ws.p)

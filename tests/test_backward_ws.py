@@ -100,6 +100,8 @@ def test_backward_workspace_on_streams_in_graphs_and_with_infinities():
     torch.cuda.synchronize()
     for out in outs:
         check_Y(out.cpu().numpy(), ref, den, "streams")
+    with pytest.raises(es.EsSpmmError):                # a hint that the scatter refuses is refused here too
+        es.es_spmm_backward(d.rowptr, d.colidx, d.vals, d.X, outs[0], W, "fastrand", 3, nnz=-1)
     # inside a graph the form without a workspace runs; every replay is whole
     with torch.cuda.stream(side):
         es.es_spmm_backward(d.rowptr, d.colidx, d.vals, d.X, outs[0], W, "fastrand", 3)
