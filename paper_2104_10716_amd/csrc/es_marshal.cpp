@@ -233,14 +233,30 @@ struct Scratch {
     void* p = nullptr;
     Scratch(size_t bytes, hipStream_t stream) noexcept
     {
-        // a capture that torch does not know of must not see the allocator ask the runtime for memory
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        if (!bytes || hipStreamIsCapturing(stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) return;
+        if (!bytes || !lendable(stream)) return;
+        // The allocator may ask the runtime for memory.  In another thread's capture of a graph (of global
+        // mode) that is an error which ends the capture, unless this thread's mode is relaxed.
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) { (void)hipGetLastError(); return; }
         try {
             p = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, stream);
         } catch (...) {
             p = nullptr;                               // no room: the caller's form without a workspace
         }
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    // Not to a stream that is being captured (torch may not know of the capture, and a graph would
+    // outlive the memory), nor to one of another device: the allocator serves the current one.
+    static bool lendable(hipStream_t stream) noexcept
+    {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        hipDevice_t device = -1;
+        int current = -1;
+        if (hipStreamIsCapturing(stream, &capture) == hipSuccess && hipStreamGetDevice(stream, &device) == hipSuccess &&
+            hipGetDevice(&current) == hipSuccess)
+            return capture == hipStreamCaptureStatusNone && device == current;
+        (void)hipGetLastError();                       // the launches report their own errors
+        return false;
     }
     ~Scratch()
     {

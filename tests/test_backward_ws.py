@@ -126,6 +126,47 @@ def test_backward_workspace_on_streams_in_graphs_and_with_infinities():
 
 
 @pytest.mark.gpu
+def test_backward_workspace_beside_another_threads_capture():
+    """The first call in a thread takes its workspace while another thread captures a graph: the
+    capture and the call both come out whole."""
+    import threading
+    import torch
+    from gpu_util import DeviceCSR, check_Y
+    import oracle
+    N, F, W = 20_000, 64, 16
+    rowptr, colidx, vals, dY = _graph(N, 20.0, 5, F)
+    d = DeviceCSR(rowptr, colidx, vals, dY)
+    ref, den = oracle.spmm_backward(rowptr, colidx, vals, dY, F, W, "bucket")
+    assert es.es_spmm_backward_workspace_bytes(N, colidx.size, F, W, "bucket") > 0
+    side = torch.cuda.Stream()
+    out, captured = (torch.full((N, F), float("nan"), device="cuda:0") for _ in range(2))
+    es.es_spmm(d.rowptr, d.colidx, d.vals, d.X, captured, W, "bucket")
+    torch.cuda.synchronize()
+    expected = captured.clone()
+    failed = []
+
+    def call():
+        try:
+            es.es_spmm_backward(d.rowptr, d.colidx, d.vals, d.X, out, W, "bucket", stream=side)
+        except Exception as e:                         # noqa: BLE001 (reported below)
+            failed.append(e)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):                      # empties torch's cache of memory, then captures in global mode
+        es.es_spmm(d.rowptr, d.colidx, d.vals, d.X, captured, W, "bucket")
+        t = threading.Thread(target=call)
+        t.start()
+        t.join()
+    assert not failed, failed
+    torch.cuda.synchronize()
+    check_Y(out.cpu().numpy(), ref, den, "beside a capture")
+    for _ in range(3):
+        captured.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(captured, expected)
+
+
+@pytest.mark.gpu
 def test_backward_workspace_with_as_many_entries_as_int32_counts():
     """2^31 - 128 kept entries: the last column block ends within one step of the largest index.
     Row r holds columns r .. r + 4094 (mod N), so a row of dX is a window of dY, summed here in 64 bits."""
