@@ -57,6 +57,12 @@ def load_library():
         raise ImportError(
             f"{_LIB_PATH} is missing: build it with `python -m paper_2104_10716_amd.build` "
             "(or __graft_entry__.build()); there is no CPU fallback")
+    # torch first: its libraries bring a HIP runtime of their own, which this library then binds to.  Loaded
+    # before them it would bind to the system's, and the process would hold two that know nothing of each other.
+    try:
+        import torch  # noqa: F401
+    except ImportError:
+        pass
     lib = ctypes.CDLL(_LIB_PATH)
     vp = ctypes.c_void_p
     lib.es_spmm.restype = ctypes.c_int

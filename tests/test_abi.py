@@ -167,3 +167,14 @@ def test_native_marshalling_hands_back_what_it_cannot_read():
     assert seen == [False, False]
     for bad in (None, 3, "x", [1]):
         assert m.spmm(bad, colidx, None, X, Y, 4, "full", 0, "none", None, None, None, None) is None
+
+
+def test_one_hip_runtime_in_the_process():
+    """The library asked for something before torch is imported (a launch plan, say) and torch
+    used afterwards: both on the same HIP runtime.  On two, every launch on torch's memory is rejected."""
+    import subprocess
+    import sys
+    code = ("import paper_2104_10716_amd as es; es.es_spmm_max_W(4); import torch\n"
+            "print(len({l.split()[-1] for l in open('/proc/self/maps') if 'libamdhip64' in l}))")
+    out = subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True, capture_output=True, text=True, timeout=300)
+    assert out.stdout.split()[-1] == "1"
