@@ -349,9 +349,9 @@ bool pick_partition(int64_t N, double mean_kept, int32_t mode, int cols_per_bloc
 }
 
 // Launch shape for N >= 1 rows.  `aligned`: F and both row strides are
-// multiples of 4 and both matrices are 16-byte aligned.
+// multiples of 4 and both matrices are 16-byte aligned.  `crowded`: see es_run.
 int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool aligned, bool backward,
-              const Overrides& ov, bool have_workspace, Plan* p)
+              const Overrides& ov, bool have_workspace, Plan* p, int64_t crowded = 0)
 {
     Shape s = pick_shape(F, aligned);
     if (backward) {                                        // see launch_backward
@@ -457,7 +457,14 @@ int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool a
     // for W above the bound (nnz is a hint, so it does not gate the launch)
     double entries = (double)nnz;
     if (mode != ES_FULL && entries > (double)N * W) entries = (double)N * W;
-    p->long_k = p->flat ? pick_flat_long_k(entries, mean) : pick_long_k(s, logR, entries, F, mean);
+    // Crowded rows: those that are not empty are about as long as the stored graph's, whatever the mean of
+    // all, and four times that mean may be less than each of them; the threshold is at least twice the
+    // stored mean.  Transposed Bucket product, split from four times the kept mean / from there (scatter): 10 k
+    // rows of mean 390, W = 16, F = 128: 142 us / 43 (73); 30 k of mean 229, W = 22, F = 20: 103 / 52 (78); 233 k
+    // of mean 488, W = 16, F = 20: 335 / 251 (375).  From the whole stored mean's four times the longest rows of graphs
+    // with hubs hold the launch up (60 k of mean 279, W = 8, F = 64: 126 us, 85 from twice).
+    const double row_mean = (double)crowded / (2.0 * (double)N) > mean ? (double)crowded / (2.0 * (double)N) : mean;
+    p->long_k = p->flat ? pick_flat_long_k(entries, mean) : pick_long_k(s, logR, entries, F, row_mean);
     // the long-row part costs a second small launch and a scan of the row
     // pointers; below one tile per row that is more than the tail it removes
     if (mode != ES_FULL && p->long_k < kTileSlots) p->long_k = kTileSlots;
@@ -513,12 +520,15 @@ hipError_t launch_partitioned(Args a, dim3 grid, int32_t* cuts, hipStream_t st)
     return hipSuccess;
 }
 
-// Shared host path of es_spmm_norm (X -> Y) and es_spmm_backward (dY -> dX).  `deal`:
-// row workgroups in order round the XCDs instead of a contiguous range each (row kernel).
+// Shared host path of es_spmm_norm (X -> Y) and es_spmm_backward (dY -> dX).  `crowded`
+// > 0: the graph is the transpose of a Bucket sample of one of that many entries, whose
+// rows get shorter from the first to the last, most of them empty: row workgroups go
+// round the XCDs in order instead of a contiguous range each (row kernel), and the
+// long-row threshold follows the stored graph (make_plan).
 int es_run(const int32_t* rowptr, const int32_t* colidx, const float* vals, const float* X, float* Y,
            int64_t N, int64_t nnz, int32_t F, int32_t ldx, int32_t ldy, int32_t W, int32_t mode,
            uint64_t seed, int32_t norm, bool backward, const es_launch_opts_t* opts, void* workspace,
-           size_t workspace_bytes, void* stream, bool deal = false)
+           size_t workspace_bytes, void* stream, int64_t crowded = 0)
 {
     const int bad = check_sizes(N, nnz, F, ldx, ldy, W, mode, norm);
     if (bad != ES_OK) return bad;
@@ -536,7 +546,7 @@ int es_run(const int32_t* rowptr, const int32_t* colidx, const float* vals, cons
     if (workspace && reinterpret_cast<uintptr_t>(workspace) % 16) return ES_ERR_INVALID_ARG;
     const bool have_ws = workspace && workspace_bytes >= part_workspace_bytes(N);
     Plan p;
-    const int rc = make_plan(N, nnz, F, W, mode, aligned, backward, ov, have_ws, &p);
+    const int rc = make_plan(N, nnz, F, W, mode, aligned, backward, ov, have_ws, &p, crowded);
     if (rc != ES_OK) return rc;
     const Shape& s = p.s;
 
@@ -546,7 +556,7 @@ int es_run(const int32_t* rowptr, const int32_t* colidx, const float* vals, cons
     a.W = (mode == ES_FULL) ? INT32_MAX : W;
     a.mode = mode; a.logR = p.logR; a.norm = norm; a.long_k = p.long_k;
     a.nblocks = (uint32_t)p.nblocks;
-    a.blocks_per_xcd = deal && !p.flat && !p.partition && !p.long_alone ? 0u : (uint32_t)p.per_xcd;
+    a.blocks_per_xcd = crowded > 0 && !p.flat && !p.partition && !p.long_alone ? 0u : (uint32_t)p.per_xcd;
     a.long_blocks = (uint32_t)p.long_blocks;
     a.cuts = nullptr; a.part_cols = 0; a.phase = 0;
 
@@ -645,7 +655,7 @@ BinPlan plan_bins(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode)
 
 // The transposed product through `workspace`, laid out by plan_bins.
 int run_binned(const int32_t* rowptr, const int32_t* colidx, const float* vals, const float* dY, float* dX,
-               int64_t N, int32_t F, int32_t ldy, int32_t ldx, int32_t W, int32_t mode, uint64_t seed,
+               int64_t N, int64_t nnz, int32_t F, int32_t ldy, int32_t ldx, int32_t W, int32_t mode, uint64_t seed,
                int32_t norm, const BinPlan& p, void* workspace, void* stream)
 {
     unsigned char* ws = static_cast<unsigned char*>(workspace);
@@ -672,7 +682,7 @@ int run_binned(const int32_t* rowptr, const int32_t* colidx, const float* vals, 
     hipLaunchKernelGGL(es_bin_sort_kernel, dim3((uint32_t)p.nbins), dim3(kBlockThreads), 0, st, a);
     if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
     return es_run(a.t_ptr, a.t_row, a.t_val, dY, dX, N, p.capacity, F, ldy, ldx, 0, ES_FULL, 0, ES_NORM_NONE, false,
-                  &kBinProduct, nullptr, 0, stream, mode == ES_BUCKET);
+                  &kBinProduct, nullptr, 0, stream, mode == ES_BUCKET ? nnz : 0);
 }
 
 }  // namespace
@@ -780,7 +790,7 @@ int es_spmm_backward_ws(const int32_t* rowptr, const int32_t* colidx, const floa
                        reinterpret_cast<uintptr_t>(dY) % 4 == 0 && reinterpret_cast<uintptr_t>(dX) % 4 == 0;
     if (reinterpret_cast<uintptr_t>(workspace) % 256) return ES_ERR_INVALID_ARG;
     if (sound && workspace && p.bytes && workspace_bytes >= p.bytes)
-        return run_binned(rowptr, colidx, vals, dY, dX, N, F, ldy, ldx, W, mode, seed, norm, p, workspace, stream);
+        return run_binned(rowptr, colidx, vals, dY, dX, N, nnz, F, ldy, ldx, W, mode, seed, norm, p, workspace, stream);
     return es_run(rowptr, colidx, vals, dY, dX, N, nnz, F, ldy, ldx, W, mode, seed, norm, true, nullptr,
                   nullptr, 0, stream);
 }

@@ -55,6 +55,9 @@ CASES = [
     (30_000, 25.0, 64, None, "bucket", 16, 0, "none", dict(hot=0)),
     (6_000, 60.0, 64, None, "fastrand", 4_096, 9, "none", dict(long_row=5_900)),  # the widest rows it takes
     (6_000, 60.0, 64, None, "bucket", 4_096, 0, "none", dict(long_row=4_097)),
+    # rows far longer than W: every transposed row that is not empty is longer than four times their mean
+    (9_001, 390.0, 128, None, "bucket", 22, 0, "mean", {}),
+    (30_000, 230.0, 20, None, "bucket", 24, 0, "none", dict(hot=0)),
 ]
 
 
