@@ -617,14 +617,23 @@ struct BinPlan {
 // multiplies no absent entries, so infinities in dY come out as from the scatter.
 constexpr es_launch_opts_t kBinProduct = {0, 0, 0, -1, 1};
 
-// Where the line lies: the scatter moves one 64-byte request per kept entry and 16
+// Where the lines lie: the scatter moves one 64-byte request per kept entry and 16
 // columns, 20.5 G of them a second; this form takes some 25 us of launches and first
-// round trips, 0.04 us per 1000 kept entries to sort them, and the gather.  us,
-// scatter / this: F = 128: 170 k rows, 2.1 M entries at most 406 / 126; 10 k, 131 k (1.05 M
-// requests) 36 / 32; F = 64: 20 k, 260 k (1.04 M) 37 / 46; 40 k, 494 k (2.0 M) 62 / 41; 233 k,
-// 14.9 M 2923 / 1048; F = 32: 40 k, 494 k (1.0 M) 34 / 38; 80 k, 989 k (2.0 M) 60 / 49.  With one
-// request per entry the sort costs what it saves: F = 16: 160 k, 2.0 M 60 / 66; 2.4 M rows,
-// 10.5 M 382 / 399; 160 k, 7.6 M 191 / 159.
+// round trips, 0.04 us per 1000 kept entries to sort them, and the gather.  us, scatter / this:
+//  * kBinMinRequests, counted on min(nnz, N W) entries.  Rows of one length keep them all and
+//    cross near 0.65 M (F = 20, 14 entries a row: 0.7 M 39 / 37, 1.1 M 57 / 43), power-law rows keep about half
+//    and cross near 1.25 M (F = 20, mean 7, W = 8: 1.12 M 35.6 / 37.2, 1.3 M 39.9 / 39.4; F = 64, mean 13, W = 16:
+//    1.2 M 39 / 32); the line is between the two.  F = 128: 170 k rows, 2.1 M entries at most 406 / 126;
+//    F = 64: 233 k, 14.9 M 2923 / 1048; a column that all rows hold, 20 k to 1 M rows: always this.
+//  * F <= 16: with one request per entry the sort costs what it saves: 160 k, 2.0 M 60 / 66; 2.4 M rows,
+//    10.5 M 382 / 399; 160 k, 7.6 M 191 / 159.
+//  * rows longer than a line of 128 bytes of which few entries are kept: count and fill wait for
+//    a line each per row (Bucket) or per kept entry (FastRand), the scatter for one, with more waves to wait in.
+//    The more so the longer the rows, so the row has to be worth the more requests.  233 k rows of mean 488,
+//    F = 20 (2 requests an entry), Bucket and FastRand: W = 4 113 / 182 and 121 / 206, W = 8 202 / 209 and 212 / 260,
+//    W = 16 382 / 244 and 388 / 362; F = 64, W = 4: 209 / 181 and 210 / 234; mean 200, F = 20, W = 4: 106 / 117 and
+//    106 / 150, W = 8 196 / 141 and 196 / 192; 170 k of mean 99, W = 4: 77 / 77 and 76 / 92.  Ids that cluster
+//    cross earlier (mean 385, F = 64, FastRand W = 4: 0.77 of the scatter's time), hubs earlier still.
 BinPlan plan_bins(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode)
 {
     BinPlan p = {};
@@ -632,6 +641,8 @@ BinPlan plan_bins(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode)
     if (W < 1 || W > kBinMaxW || F <= 16 || N < 1 || N > (1 << kBinRowBits) || nnz < 1 || nnz > INT32_MAX) return p;
     p.capacity = nnz < N * W ? nnz : N * W;
     if (p.capacity * ((F + 15) / 16) < kBinMinRequests) return p;
+    const double mean = (double)nnz / (double)N, row_requests = (double)W * ((F + 15) / 16);
+    if (mean > 32.0 && mean > W && row_requests < (mode == ES_FASTRAND ? 5.0 + mean / 25.0 : 1.5 + mean / 46.0)) return p;
     // only where both the gather this form ends in (some million columns are more than its grid covers) and the
     // scatter can run, so that a call is refused or accepted whatever workspace there is, and refused before a launch
     Plan product;

@@ -16,6 +16,10 @@ def test_workspace_is_asked_for_only_where_the_form_applies():
     assert ask(2 ** 22, 2 ** 24, 64, 16, "bucket") > 0 and ask(2 ** 22 + 1, 2 ** 24, 64, 16, "bucket") == 0
     assert ask(170_000, 2_370_240, 128, 4096, "bucket") > 0 and ask(170_000, 2_370_240, 128, 4097, "bucket") == 0
     assert ask(19_717, 88_000, 32, 16, "bucket") == 0                           # small: the scatter is the faster form
+    # few entries kept of long rows: requests per row (W times 2 at F = 32) against the mean row
+    assert ask(233_000, 233_000 * 300, 32, 8, "fastrand") == 0 and ask(233_000, 233_000 * 300, 32, 9, "fastrand") > 0
+    assert ask(233_000, 233_000 * 300, 32, 4, "bucket") == 0 and ask(233_000, 233_000 * 300, 32, 5, "bucket") > 0
+    assert ask(600_000, 600_000 * 33, 32, 3, "fastrand") == 0 and ask(600_000, 600_000 * 32, 32, 3, "fastrand") > 0
     # columns beyond the grid of the gather it ends in (64 at a time on tables of 512 MB and more), or of the scatter
     assert ask(100, 10_000, 65_535 * 64, 100, "bucket") > 0 and ask(100, 10_000, 65_535 * 64 + 1, 100, "bucket") == 0
     assert ask(5, 25, 65_535 * 256, 5, "fastrand") > 0 and ask(5, 25, 65_535 * 256 + 1, 5, "fastrand") == 0
