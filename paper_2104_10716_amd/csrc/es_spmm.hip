@@ -313,19 +313,25 @@ bool part_flat_size(int64_t N) { return (double)N * 32.0 > 4.0e6; }
 // Whether to run the column-partitioned product.  It pays when a row's piece inside one
 // column range is long enough to amortise the extra pass over Y (kept entries per row well
 // above kParts), when an XCD's eighth of a 32-column slice of X is of the order of its
-// L2, and when X as a whole is so far beyond an L2 that whole rows miss.  The row form
-// pays some 0.5 us per 100 rows whatever their length, so it asks for longer rows.  Exact
-// product, us, whole rows / column ranges:
-//  * flattened kernel (`flat`): F = 32: mean 150, 170 k rows (22 MB) 403 / 424, 233 k (30 MB) 575 /
-//    563, mean 300, 140 k (18 MB) 620 / 530; F = 16: mean 150, 350 k 796 / 647, mean 300, 140 k 467 / 454;
-//    F = 64: mean 150, 170 k 855 / 727, mean 300, 233 k 2372 / 1534; F = 128: mean 150, 170 k 1741 / 1322.
-//  * row form, mean 150: never: F = 64, 45 k rows 176 / 309, 90 k 422 / 577, 125 k 605 / 802; F = 41,
-//    233 k 1247 / 1617; F = 205, 60 k 1075 / 1462, 233 k 4443 / 7341.
-//  * row form, mean 300: F = 64, 30 k (7.7 MB) 183 / 270, 45 k (11.5) 337 / 364, 60 k (15.4) 495 / 470, 125 k
-//    1205 / 1082; F = 41, 60 k (9.8) 428 / 496, 90 k (14.8) 769 / 721, 233 k 2472 / 2172; F = 128, 30 k (15.4)
-//    480 / 463, 45 k 791 / 668; F = 205, 60 k 2094 / 1801, 125 k 4620 / 4652, 233 k 8802 / 10384 (two and more
-//    slices of rows that tile no line); at mean 490 125 k 7444 / 6196, 233 k 14332 / 14988.
-//  * row form on rows of one line: F = 32, 125 k, mean 300 540 / 892, mean 490 874 / 1127.
+// L2, and when X as a whole is so far beyond an L2 that whole rows miss.  The larger X (the lines its rows
+// touch), the shorter the rows may be, so the lines are on the product of the two, `reach`.  The row form pays
+// some 0.5 us per 100 rows whatever their length, so it asks for longer rows; wide rows share that over
+// slices of full lines.  Time of whole rows over that of column ranges, exact product, uniform ids, `mean: ratio`:
+//  * flattened kernel (`flat`), F = 32: 130 k rows (16.6 MB) 179: 0.94, 219: 1.01, 249: 1.08, 180 k 129: 0.95, 149:
+//    1.00, 248: 1.20, 233 k 130: 1.02; rows that tile no line pay more for whole rows: F = 20, 130 k 130: 0.94,
+//    179: 1.04, 180 k 129: 1.13, F = 28, 130 k 130: 1.19, 180 k 248: 1.68, F = 36, 130 k 130: 1.13, F = 48 1.21;
+//    F = 64 1.09 (180 k 248: 1.45), F = 128, 170 k 150: 1.32; F = 16: 130 k 298: 0.97, 150 k 219: 0.98, 249: 1.02,
+//    180 k 149: 0.94, 178: 1.02.
+//  * row form, F = 64: 31 k (8.0 MB) 477: 0.92, 40 k 293: 0.83, 478: 1.12, 50 k 293: 0.93, 62 k (15.9 MB) 128: 0.59, 177:
+//    0.75, 245: 0.92, 294: 1.04, 90 k 246: 1.02, 120 k 179: 0.87, 248: 0.98, 297: 1.09; F = 41: 50 k 477: 0.96, 62 k
+//    294: 0.86, 478: 1.13, 120 k 248: 0.99, 297: 1.07; F = 205: 31 k 293: 1.03, 62 k 245: 1.02, 294: 1.14, 130 k 298:
+//    0.99, 233 k 300: 0.87 (and 490: 0.96; two and more slices of rows that tile no line).
+//  * row form, wide aligned rows: F = 128: 31 k (16 MB) 244: 0.93, 292: 1.05, 50 k 177: 0.87, 245: 1.06, 120 k 179: 0.91,
+//    248: 1.10; F = 192: 62 k 177: 0.94, 216: 1.08; F = 256: 31 k 176: 0.90, 244: 1.13, 70 k 180: 1.00, 120 k 179: 0.88,
+//    248: 1.08; F = 300: 62 k 216: 1.09, 120 k 241: 0.99.
+//  * row form on rows of one line: F = 32: 120 k 297: 0.59, 484: 0.76; F = 17: 484: 0.75, F = 31: 297: 0.98, 484: 1.24.
+// Ids that cluster hit on whole rows too and gain less: 0.7 - 0.86 on the flattened kernel, 0.4 - 0.7 on the
+// row form; sizes do not tell them apart.
 bool pick_partition(int64_t N, double mean_kept, int32_t mode, int cols_per_block, int F, bool aligned, bool flat,
                     int force)
 {
@@ -341,11 +347,12 @@ bool pick_partition(int64_t N, double mean_kept, int32_t mode, int cols_per_bloc
     const double share = (double)N * cols_per_block * 4.0 / kParts;
     if (share < 0.5e6 || share > 12.0e6) return false;
     const double table = (double)N * (F < 32 ? 32 : F) * 4.0;       // no gather moves less than a line
-    if (flat) return table >= (mean_kept < 256.0 ? 24.0e6 : 14.0e6);
-    if (N <= 62500) return true;               // not at the crossing: kept for callers that count on the ranges' fixed order of sums
-    if (aligned && F <= 32) return false;
+    const double reach = table * mean_kept;
+    if (flat) return F <= 16 ? table >= 19.0e6 && reach >= 4.1e9 : F % 32 != 0 || reach >= 3.6e9;
+    if (F <= (aligned ? 32 : 24)) return false;
     if (!aligned && F > 64 && N > 125000) return false;
-    return mean_kept >= 256.0 && table >= 14.0e6;
+    const bool wide = aligned && (F >= 256 || (F >= 128 && F % 64 == 0));
+    return mean_kept >= (wide ? 216.0 : 256.0) && reach >= (wide ? 4.5e9 : 4.0e9);
 }
 
 // Launch shape for N >= 1 rows.  `aligned`: F and both row strides are

@@ -150,12 +150,19 @@ def test_column_partition_choice():
 
 
 @pytest.mark.parametrize("N,mean,F,aligned,ranges,lanes", [
-    # row form: rows of 256 entries and X of 14 MB on
-    (62_500, 150, 64, True, 8, 16), (62_501, 255, 64, True, 1, 16), (62_501, 256, 64, True, 8, 16), (70_000, 300, 41, False, 1, 16),
+    # row form: rows of 256 entries on, and a product of mean and X of 4e9 bytes on
+    (62_500, 150, 64, True, 1, 16), (62_501, 255, 64, True, 1, 16), (62_501, 256, 64, True, 8, 16), (70_000, 300, 41, False, 1, 16),
+    (62_500, 255, 64, True, 1, 16), (32_000, 488, 64, True, 1, 16), (32_000, 489, 64, True, 8, 16), (70_000, 490, 41, False, 8, 16),
     # ... not for rows of one line, nor for wide rows that tile none on large tables
     (125_000, 490, 32, True, 1, 8), (125_000, 490, 36, True, 8, 16), (125_000, 300, 205, False, 8, 16), (125_001, 490, 205, False, 1, 64),
-    # flattened kernel: X, in lines, of 24 MB, or 14 MB from a mean of 256 on
+    (62_500, 490, 32, True, 1, 8), (125_000, 490, 24, False, 1, 8), (125_000, 490, 25, False, 8, 8),
+    # ... wide aligned rows: 216 entries and 4.5e9 bytes on
+    (70_000, 215, 128, True, 1, 32), (70_000, 216, 128, True, 8, 16), (40_000, 219, 128, True, 1, 32), (40_000, 220, 128, True, 8, 16),
+    (62_500, 255, 96, True, 1, 32), (62_500, 255, 160, True, 1, 64), (70_000, 216, 300, True, 8, 16), (70_000, 255, 301, False, 1, 64),
+    # flattened kernel: a product of 3.6e9 bytes on where rows tile lines, always where they do not, 4.1e9 and 19 MB up to F = 16
     (187_000, 150, 32, True, 1, 8), (188_000, 150, 32, True, 8, 8), (126_000, 300, 32, True, 8, 8), (350_000, 150, 16, True, 8, 4),
+    (140_000, 200, 32, True, 1, 8), (142_000, 200, 32, True, 8, 8), (126_000, 128, 28, True, 8, 8), (126_000, 128, 36, True, 8, 16),
+    (148_000, 300, 16, True, 1, 4), (149_000, 300, 16, True, 8, 4), (160_000, 200, 16, True, 1, 4), (161_000, 200, 16, True, 8, 4),
     (233_000, 127, 64, True, 1, 16), (233_000, 128, 64, True, 8, 8), (180_000, 300, 100, True, 8, 16)])
 def test_column_range_rule(N, mean, F, aligned, ranges, lanes):
     info = es.es_spmm_launch_info(N, N * mean, F, 0, "full", aligned16=aligned)

@@ -26,14 +26,15 @@ def test_static_workspace_matches_caller_workspace_on_two_calls_in_a_row():
     assert torch.cuda.is_available(), "GPU tests need a GPU"
     es.load_library()
     dev = "cuda:0"
-    big = DeviceCSR(*_graph(60_000, 150.0, 901, 64))           # dense enough that the library partitions by itself
+    big = DeviceCSR(*_graph(60_000, 150.0, 901, 64))           # dense enough that a piece in a column range has many entries
     small = DeviceCSR(*_graph(3_001, 40.0, 902, 41))           # smaller input right after, nothing cleared in between
-    info = es.es_spmm_launch_info(big.N, big.h_colidx.size, 64, 0, "full")
+    ranges = dict(column_partition=1)                          # the form that uses the workspace, and whose sums have a fixed order
+    info = es.es_spmm_launch_info(big.N, big.h_colidx.size, 64, 0, "full", opts=ranges)
     assert info["column_ranges"] == 8
-    cases = [(big, 0, "full", 0, None), (small, 0, "full", 0, dict(column_partition=1)),
+    cases = [(big, 0, "full", 0, ranges), (small, 0, "full", 0, dict(column_partition=1)),
              (big, 300, "fastrand", 7, dict(column_partition=1)), (small, 9, "fastrand", 7, dict(column_partition=1)),
              (big, 16, "bucket", 0, None), (small, 0, "full", 0, None),
-             (big, 0, "full", 0, dict(kernel=2, lanes_per_row=8)),          # flattened pieces of the column ranges
+             (big, 0, "full", 0, dict(ranges, kernel=2, lanes_per_row=8)),          # flattened pieces of the column ranges
              (small, 0, "full", 0, dict(kernel=2, column_partition=1))]
     for d, W, mode, seed, opts in cases:
         what = f"static workspace N={d.N} {mode} W={W} opts={opts}"
@@ -53,7 +54,7 @@ def test_static_workspace_matches_caller_workspace_on_two_calls_in_a_row():
     with torch.cuda.stream(s):
         Y1 = torch.empty((big.N, big.F), dtype=torch.float32, device=dev)
         Y2 = torch.empty((small.N, small.F), dtype=torch.float32, device=dev)
-        es.es_spmm_static_ws(big.rowptr, big.colidx, big.vals, big.X, Y1, 0, "full")
+        es.es_spmm_static_ws(big.rowptr, big.colidx, big.vals, big.X, Y1, 0, "full", 0, "none", ranges)
         es.es_spmm_static_ws(small.rowptr, small.colidx, small.vals, small.X, Y2, 0, "full", 0, "none",
                              dict(column_partition=1))
     s.synchronize()
