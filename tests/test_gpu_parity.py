@@ -745,6 +745,20 @@ def test_backward_full_size(es):
         del d, Xd, Y, dX
 
 
+def test_scatter_full_size(es):
+    """The atomic scatter, which captured streams, callers without memory and es_spmm_backward_ex
+    run where es_spmm_backward takes a workspace: configs 2 and 3 at full size, every element."""
+    from gpu_util import DeviceCSR, check_backward_against_oracle
+    for cfg, mode, W in ((2, "fastrand", 16), (3, "bucket", 16)):
+        w = _workload(cfg)
+        assert es.es_spmm_backward_workspace_bytes(w.N, w.nnz, w.F, W, mode) > 0
+        dY = np.random.default_rng(cfg).standard_normal((w.N, w.F)).astype(np.float32)
+        d = DeviceCSR(w.rowptr, w.colidx, w.vals, dY)
+        worst = check_backward_against_oracle(d, W, mode, 0, what=f"cfg{cfg} scatter {mode} W={W}", opts={})
+        _say(f"cfg{cfg} scatter {mode} W={W}: max normalised error {worst:.2e}")
+        del d
+
+
 def _oracle_transposed(rowptr, colidx, vals, W, mode, seed):
     """(column, row, value) of every kept entry, sorted by (column, row)."""
     import oracle
@@ -1222,6 +1236,21 @@ def test_row_kernel_forced_full_size(es, cfg):
         worst = check_every_element(d, W, mode, 0, what=f"cfg{cfg} row kernel {mode} W={W}",
                                     opts=dict(workspace=d.default_ws, kernel=1))
         _say(f"cfg{cfg} row kernel {mode} W={W}: max normalised error {worst:.2e}")
+
+
+def test_column_ranges_of_rows_that_tile_no_line(es):
+    """What the library chooses above 125 k rows where F is no multiple of 32: column ranges on the
+    flattened kernel, one slice (F = 20, 28), a second of few columns (68) and 64-column slices (100, 124)."""
+    from gpu_util import DeviceCSR, check_every_element
+    N = 126_001
+    rowptr, colidx, vals, X = _random_graph(N, 138.0, seed=3, F=124, empty_frac=0.02)
+    for F in (20, 28, 68, 100, 124):
+        info = es.es_spmm_launch_info(N, colidx.size, F, 0, "full", ldx=124)
+        assert info["column_ranges"] == 8 and info["flattened"] == 1 and info["lanes_per_row"] == (8 if F < 64 else 16), (F, info)
+        d = DeviceCSR(rowptr, colidx, vals, X, F=F).with_workspace()
+        worst = check_every_element(d, 0, "full", what=f"ranges F={F}", norm="mean")
+        _say(f"column ranges on the flattened kernel, F={F}: max normalised error {worst:.2e}")
+        del d
 
 
 def test_config3_column_partitioned(es):
