@@ -1,4 +1,4 @@
-// es_bin_kernel.h -- the transposed sampled product with a workspace: kept entries grouped by column blocks, sums in LDS.
+// es_bin_kernel.h -- the transposed sampled product with a workspace: kept entries sorted by column with counters in LDS.
 #ifndef ES_SPMM_BIN_KERNEL_H
 #define ES_SPMM_BIN_KERNEL_H
 
@@ -27,7 +27,8 @@ namespace {
 constexpr int kBinThreads = 512;                      // of a counting / filling workgroup: one row per thread at a time
 constexpr int kBinWaves = kBinThreads / kWaveSize;
 constexpr int kBinRowBits = 22;                       // a record holds the row in 22 bits, the column of the block in 10
-constexpr int kBinMaxBlocks = 8192;                   // column blocks at most: 32 KB of counters per workgroup
+constexpr int kBinMaxBlocks = 4096;                   // column blocks at most: 16 KB of counters per workgroup
+static_assert(kBinMaxBlocks == (1 << kBinRowBits) >> (32 - kBinRowBits), "the most rows, in blocks of the most columns");
 constexpr int kBinMaxW = 4096;                        // kept entries of a row at most: one workgroup walks them
 constexpr int64_t kBinMinRequests = 1100000;          // requests of the scatter from which on this form is the faster
 constexpr int kBinWalkers = 256;                      // counting / filling workgroups at most

@@ -45,7 +45,7 @@ struct Args {
     int32_t long_k;            // rows keeping more entries go to the long-row part  
     int32_t norm;              // es_norm_t: row factor applied before the store
     uint32_t nblocks;          // workgroups that carry rows
-    uint32_t blocks_per_xcd;   // ceil(nblocks / 8)
+    uint32_t blocks_per_xcd;   // ceil(nblocks / 8); 0: workgroups go round the XCDs in row order (row kernel)
     uint32_t long_blocks;      // leading workgroups that run the long-row part
     // column-partitioned product only
     const int32_t* cuts;       // [N x kParts]: row r's piece of column range j starts at entry cuts[r][j]

@@ -133,6 +133,27 @@ def test_backward_workspace_on_streams_in_graphs_and_with_infinities():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("N", [2 ** 22 - 1_024, 2 ** 22 - 1_023, 2 ** 22])
+def test_backward_workspace_with_the_most_column_blocks(N):
+    """4095 and 4096 blocks of 1024 columns, the last of them whole or of one column: one entry per row, any
+    column, against the same sum in 64 bits."""
+    import torch
+    F = 17
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev).manual_seed(N)
+    rowptr = torch.arange(N + 1, dtype=torch.int32, device=dev)
+    colidx = torch.randint(N, (N,), device=dev, generator=gen)
+    colidx[-1] = N - 1
+    vals = torch.randn(N, device=dev, generator=gen)
+    dY = torch.randn(N, F, device=dev, generator=gen)
+    assert es.es_spmm_backward_workspace_bytes(N, N, F, 1, "fastrand") > 0
+    dX = es.es_spmm_backward(rowptr, colidx.int(), vals, dY, torch.full_like(dY, float("nan")), 1, "fastrand", 3)
+    terms = vals.double()[:, None] * dY.double()
+    ref, den = (torch.zeros(N, F, dtype=torch.float64, device=dev).index_add_(0, colidx, t) for t in (terms, terms.abs()))
+    assert bool(((dX.double() - ref).abs() <= 1e-5 * den).all())
+
+
+@pytest.mark.gpu
 def test_backward_workspace_beside_another_threads_capture():
     """The first call in a thread takes its workspace while another thread captures a graph: the
     capture and the call both come out whole."""
