@@ -715,10 +715,11 @@ def unweighted_norm_table(dw, dev):
 
 
 def backward_table(dw, dev, cases):
-    """The transposed product dX = sample_W(A)^T dY two ways, beside the forward
-    call of the same (mode, W): es_spmm_backward (fp32 atomic scatter) and the
-    pull form (es_spmm_materialize_transposed once, then a full product on the
-    transposed structure, which can be reused while (W, mode, seed) stay)."""
+    """The transposed product dX = sample_W(A)^T dY, beside the forward call of the same
+    (mode, W): es_spmm_backward (here through a workspace: the sampled graph sorted by
+    column, then gathered), es_spmm_backward_ex (fp32 atomic scatter, what captured streams and
+    callers without memory run), the pull form over the transposed graph, and a full product on
+    es_spmm_materialize_transposed (which can be reused while (W, mode, seed) stay)."""
     import torch
     import paper_2104_10716_amd as es
     dX = torch.empty_like(dw.Y)
@@ -732,6 +733,8 @@ def backward_table(dw, dev, cases):
         t_fwd = _time_fn(lambda: dw.launch(mode, W))
         t_bwd = _time_fn(lambda: es.es_spmm_backward(dw.rowptr, dw.colidx, dw.vals, dw.X, dX, W, mode, 0,
                                                      F=dw.F))
+        t_atomic = _time_fn(lambda: es.es_spmm_backward_ex(dw.rowptr, dw.colidx, dw.vals, dw.X, dX, W, mode, 0,
+                                                           F=dw.F))
         bufs = es.es_spmm_materialize_transposed(dw.rowptr, dw.colidx, dw.vals, W, mode, 0)
         t_build = _time_fn(lambda: es.es_spmm_materialize_transposed(dw.rowptr, dw.colidx, dw.vals, W, mode,
                                                                      0, "none", *bufs))
@@ -741,10 +744,12 @@ def backward_table(dw, dev, cases):
         t_inv = _time_fn(lambda: es.es_spmm_backward_pull(dw.rowptr, tg, dw.X, dX, W, mode, 0, F=dw.F))
         out["rows"].append({"mode": mode, "W": W, "forward_ms": round(t_fwd, 4),
                             "backward_pull_ms": round(t_inv, 4),
-                            "backward_atomic_ms": round(t_bwd, 4), "sampled_transpose_build_ms": round(t_build, 4),
+                            "backward_ms": round(t_bwd, 4), "backward_atomic_ms": round(t_atomic, 4),
+                            "sampled_transpose_build_ms": round(t_build, 4),
                             "full_product_on_sampled_transpose_ms": round(t_pull, 4)})
-        log(f"  backward {mode:8s} W={W:3d}: pull over the transposed graph {t_inv:.3f} ms | atomic scatter "
-            f"{t_bwd:.3f} ms | sampled transpose build {t_build:.3f} ms + product on it {t_pull:.3f} ms | "
+        log(f"  backward {mode:8s} W={W:3d}: pull over the transposed graph {t_inv:.3f} ms | through a workspace "
+            f"{t_bwd:.3f} ms | atomic scatter {t_atomic:.3f} ms | sampled transpose build {t_build:.3f} ms + product on "
+            f"it {t_pull:.3f} ms | "
             f"forward {t_fwd:.3f} ms")
         del bufs, ptr, idx, val
     return out
