@@ -134,8 +134,9 @@ int es_spmm_backward(const int32_t* rowptr, const int32_t* colidx, const float* 
  * gather: no atomic adds to dX except for rows of dX that sum a great many
  * entries.  es_spmm_backward_workspace_bytes is the size it takes for these
  * arguments, or 0 where the scatter of es_spmm_backward is the faster form or this
- * one does not apply (ES_FULL, small products, F <= 16, N > 2^22, W > 4096); with a
- * smaller workspace, or none, es_spmm_backward_ws is es_spmm_backward.
+ * one does not apply (ES_FULL, small products, F <= 16, few kept entries of long
+ * rows, N > 2^22, W > 4096, more columns than its launches cover); with a smaller
+ * workspace, or none, es_spmm_backward_ws is es_spmm_backward.
  *   nnz        rowptr[N] or more (here it sizes the workspace: with a smaller
  *              number dX is wrong, though no other memory is touched)
  *   workspace  256-byte aligned; its contents are scratch, and calls that share it
@@ -339,8 +340,11 @@ int es_spmm_ex(const int32_t* rowptr, const int32_t* colidx, const float* vals,
  * column ids, so the locality is there for rows stored in increasing column
  * order (the usual CSR); for any other order the result is still the same
  * product -- the eight pieces always tile the row -- only the locality is lost.
- * Same sampled entries as es_spmm; Y differs only by fp32 summation order and
- * is bit-reproducible.
+ * Same sampled entries as es_spmm; Y differs only by fp32 summation order, and
+ * this form's is bit-reproducible.  Where it runs by itself is a question of
+ * speed and may change; on whole rows those above the long-row threshold are
+ * summed with atomics.  A caller who needs the same bits from call to call asks
+ * for it (column_partition = 1).
  *   workspace        device memory, 16-byte aligned, at least
  *                    es_spmm_workspace_bytes(N) bytes; contents on entry are
  *                    irrelevant, contents on return are unspecified.  NULL or

@@ -222,7 +222,7 @@ def _spmm_args(rowptr, colidx, vals, X, Y, F, nnz):
 
 def es_spmm(rowptr, colidx, vals, X, Y, W: int, mode, seed: int = 0, F: Optional[int] = None,
             stream=None, nnz: Optional[int] = None):
-    """Y[:, :F] = sample_W(A) @ X[:, :F] on the tensors' device; returns Y.
+    """Y[:, :F] = sample_W(A) @ X[:, :F] on the current device, which holds the tensors; returns Y.
     rowptr/colidx int32, vals float32 or None, X/Y 2-D float32 with unit column
     stride (row stride = leading dimension).  Enqueued on `stream` (default:
     torch's current stream); not synchronised.  `nnz` (default: len(colidx)) is
@@ -319,7 +319,7 @@ def es_spmm_static_ws(rowptr, colidx, vals, X, Y, W: int, mode, seed: int = 0, n
 
 def es_spmm_backward_ex(rowptr, colidx, vals, dY, dX, W: int, mode, seed: int = 0, norm="none", opts=None,
                         F: Optional[int] = None, stream=None, nnz: Optional[int] = None):
-    """es_spmm_backward with per-call launch options."""
+    """es_spmm_backward with per-call launch options, always by the scatter: it allocates nothing."""
     lib = load_library()
     args = _spmm_args(rowptr, colidx, vals, dY, dX, F, nnz)
     nm = NORMS[norm] if isinstance(norm, str) else int(norm)
@@ -333,8 +333,11 @@ def es_spmm_backward_ex(rowptr, colidx, vals, dY, dX, W: int, mode, seed: int = 
 def es_spmm_backward(rowptr, colidx, vals, dY, dX, W: int, mode, seed: int = 0, norm="none",
                      F: Optional[int] = None, stream=None, nnz: Optional[int] = None):
     """dX[:, :F] = sample_W(A)^T @ dY[:, :F] (dX is overwritten); returns dX.  Larger sampled
-    products take a workspace (es_spmm_backward_workspace_bytes) from torch's allocator for the
-    call; a captured stream, or a lack of memory, falls back to the form that takes none."""
+    products take a workspace (es_spmm_backward_workspace_bytes: some 16 bytes per kept entry) from
+    torch's allocator for the call; a captured stream, a stream of another device than the current
+    one, or a lack of memory falls back to the form that takes none.  Before it reports a lack of memory,
+    torch gives back the blocks it keeps, and waits for the device: a program that works at the
+    limit calls es_spmm_backward_ex, which never allocates."""
     rc = (_marshal or load_marshal()).backward(rowptr, colidx, vals, dY, dX, W, mode, seed, norm, F, stream, nnz)
     if rc == 0:
         return dX

@@ -373,8 +373,10 @@ __device__ __forceinline__ void long_block(const Args& a, uint32_t bx, uint32_t 
 // rows, W = 64 of a mean of 490, F = 64: 1.70 ms as ranges, 0.90 dealt round).
 // ---------------------------------------------------------------------------
 // Six waves per SIMD: the two registers more that the compiler takes otherwise cost a
-// sixth of the waves (170 k rows of mean 14, W = 16, F = 128: 83 us at five, 79 at six).
-// Four chunks per lane need 88 to 94 registers, which would spill at six.
+// sixth of the waves.  Ids that cluster, at five / at six: 170 k rows, Bucket W = 16, mean 14, F = 128: 59.2
+// us / 53.8, mean 40, F = 64: 57.2 / 51.2.  Uniform ids wait for L2 misses and are within 3 % either way (170 k of mean
+// 14, F = 128: 89.9 / 92.4, 40 k of mean 40, F = 128, exact: 95.1 / 95.3).  Four chunks per lane need 88 to 96
+// registers, which would spill at six.
 template <int G, int CH, int VEC, bool ALIGNED, bool BACKWARD, bool WIDE>
 __global__ void __launch_bounds__(kBlockThreads, CH == 4 ? 5 : 6) es_spmm_kernel(const Args a)
 {
