@@ -17,10 +17,11 @@ namespace {
 // block by column.
 //
 // What bounds it: the product, i.e. its gathers.  170 k rows, W = 16 of a mean of 14, F =
-// 128: 126 us (scatter: 406), of which count 11, scan and base 8, fill 15, sort 12.  Larger
-// and denser (233 k rows, W = 64, 14.9 M entries): count 64, fill 140, sort 110 of 900; the
-// fill's records go out 8 bytes at a time (256 walkers: 133 us; 512, with half as many
-// records side by side: 259).
+// 128: 126 us (scatter: 406), of which count 10, scan and base 6, fill 16, sort 12, and the product 83.  Larger
+// and denser (233 k rows, W = 64, 14.9 M entries, F = 64; Bucket / FastRand): count 67 / 82, fill 124 / 244, sort
+// 218 / 209, product 477 / 512 of 900 / 1050.  Beyond every cache (2.45 M rows, W = 64, 58 M entries, F = 128): 254, 417,
+// 1285 and 3373 of 5.4 ms (scatter: 21.8).  The fill's records go out 8 bytes at a time (256 walkers: 133 us; 512, with
+// half as many records side by side: 259).
 // Tried and slower: sums kept in LDS per column block and added to with ds_add_f32,
 // which takes three clocks per lane (170 k rows: 650 us for that pass alone).
 // ---------------------------------------------------------------------------
