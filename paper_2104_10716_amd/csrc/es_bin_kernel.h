@@ -19,7 +19,7 @@ namespace {
 // What bounds it: the product, i.e. its gathers.  170 k rows, W = 16 of a mean of 14, F =
 // 128: 126 us (scatter: 406), of which count 10, scan and base 6, fill 16, sort 12, and the product 83.  Larger
 // and denser (233 k rows, W = 64, 14.9 M entries, F = 64; Bucket / FastRand): count 67 / 82, fill 124 / 244, sort
-// 218 / 209, product 477 / 512 of 900 / 1050.  Beyond every cache (2.45 M rows, W = 64, 58 M entries, F = 128): 254, 417,
+// 218 / 209, product 477 / 512 of 900 / 1050.  Beyond every cache (2.45 M rows, W = 64, 56 M entries, F = 128): 254, 417,
 // 1285 and 3373 of 5.4 ms (scatter: 21.8).  The fill's records go out 8 bytes at a time (256 walkers: 133 us; 512, with
 // half as many records side by side: 259).
 // Tried and slower: sums kept in LDS per column block and added to with ds_add_f32,
@@ -31,7 +31,7 @@ constexpr int kBinRowBits = 22;                       // a record holds the row 
 constexpr int kBinMaxBlocks = 4096;                   // column blocks at most: 16 KB of counters per workgroup
 static_assert(kBinMaxBlocks == (1 << kBinRowBits) >> (32 - kBinRowBits), "the most rows, in blocks of the most columns");
 constexpr int kBinMaxW = 4096;                        // kept entries of a row at most: one workgroup walks them
-constexpr int64_t kBinMinRequests = 1100000;          // requests of the scatter from which on this form is the faster
+constexpr int64_t kBinMinRequests = 1100000;          // requests of the scatter from which on this form is taken (plan_bins)
 constexpr int kBinWalkers = 256;                      // counting / filling workgroups at most
 
 struct BinArgs {
