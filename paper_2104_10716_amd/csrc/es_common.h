@@ -48,7 +48,7 @@ struct Args {
     uint32_t blocks_per_xcd;   // ceil(nblocks / 8); 0: workgroups go round the XCDs in row order (row kernel)
     uint32_t long_blocks;      // leading workgroups that run the long-row part
     // column-partitioned product only
-    const int32_t* cuts;       // [N x kParts]: row r's piece of column range j starts at entry cuts[r][j]
+    const int32_t* cuts;       // [kParts x N]: row r's piece of column range j starts at entry cuts[j][r]
     int32_t part_cols;         // columns per range, ceil(N / kParts)
     int32_t phase;             // 0 .. kParts-1: which row range each XCD serves in this launch
 };

@@ -14,8 +14,8 @@ namespace {
 // differ in length idles the lanes of the short ones.  Here a workgroup takes up
 // to 64 consecutive rows (or the pieces of one column range of those rows), lays
 // their kept entries end to end -- each row padded to a multiple of a block of
-// max(8, E) entries, E = 64 / G edge slots, with zero-valued repeats of its last
-// one -- and stages that run into LDS in bursts of 1536 or 2048 entries (stage 1
+// max(8, E) entries, E = 64 / G edge slots, with absent ones, which touch no memory and
+// multiply nothing -- and stages that run into LDS in bursts of 1536 or 2048 entries (stage 1
 // of Algorithm 1): a table of the burst's blocks first (a binary search per block
 // for its row), then every entry of the burst requested before the first is
 // awaited.  Stage 2: each of the four waves multiplies an equal share of the
@@ -28,15 +28,18 @@ namespace {
 // sums are bit-reproducible.  Row sums leave LDS once, coalesced (plain stores, or
 // load-add-store in the later phases of the column-partitioned product).
 //
-// What bounds it: the L2 misses of the gathers where X is large (7 TB/s of them), and
-// where nearly all gathers hit, the order in which a compute unit's vector cache
-// returns data: a line that misses, be it of the CSR entries, holds back the hits
-// behind it.  Hence the bursts, which put a workgroup's misses on the entries
-// together, and hence no wave-private prefetch.  Dense social-like graph (233 k rows,
-// 113 M entries, F = 64), exact product in column ranges, 82 % L2 hits: 2.59 -> 2.16 ms
-// against the former form (256 entries per wave, requested one tile ahead, a row
-// search per entry); co-purchase-like graph (2.45 M rows, 120 M entries, F = 128), 46 %
-// hits: exact product 6.02 -> 5.68 ms, FastRand W = 64 2.81 -> 2.76 ms.
+// What bounds it: the L2 misses of the gathers where X is large (7.4 TB/s of them). Where
+// nearly all gathers hit, the vector cache, which serves 64 bytes per clock and compute unit, be
+// they one lane's or sixteen lanes': 84 M such accesses per launch of the dense social-like graph's exact product in
+// column ranges (233 k rows, 113 M entries, F = 64), 60 M of them rows of X, in 264 us; with every access a hit
+// still 217 us.  Hence a chunk's entries are loaded in order and permuted on their way into LDS (a permuted load
+// touches three times as many lines), and the cuts lie range by range: 2.17 -> 2.06 ms, 233 k rows of mean 150,
+// F = 128 1628 -> 1548 us.  Lines that miss hold back the hits behind them; the bursts put a workgroup's
+// misses on the entries together (2.59 -> 2.16 ms against 256 entries per wave, requested one tile ahead).
+// Co-purchase-like graph (2.45 M rows, 120 M entries, F = 128), 46 % hits: exact product 5.60 ms, FastRand W = 64 2.76.
+// Tried and slower: entries kept in registers and handed to the slots by DPP, a row's 64 at a time (2.83 ms: short
+// pieces fill a quarter of the lanes), non-temporal loads for rows of X far from the row's own index (9 - 20 % fewer L2
+// misses, 4 - 15 % slower), seven or eight waves per SIMD with bursts of 512 or 1024 (2.26, 2.44 ms).
 // Tried and slower on the former: entries copied into LDS by the load itself (dword
 // copies: 2.9 ms), a pass of 64 entries per row streamed two passes ahead (2.6 ms), 16
 // column ranges (3.2 ms), two batches of gathers in flight per wave (spills or 12 waves).
@@ -55,7 +58,7 @@ struct FlatLds {
     static constexpr int FB = 4 * G;                  // feature columns per block
     static constexpr int ROWS = flat_rows(G, RPS);    // rows of the run
     static constexpr int CAP = RPS == 1 ? 1536 : 2048;   // entries staged in one burst: about the run's mean, six or four workgroups per compute unit
-    int32_t col[CAP];                            // staged column ids, in the order the slots read them
+    uint32_t key[CAP];                           // staged entries' rows of X (FlatRows), in the order the slots read them
     float val[CAP];
     float rowsum[ROWS * FB];                     // [row][FB]
     float head[kWavesPerBlock * FB];                  // per wave: partial sum of a row that began in an earlier wave's share
@@ -125,8 +128,23 @@ struct FlatRow {
     uint32_t len, mul, rot;    // FastRand on a longer row: slot i reads entry (rot + i * mul) mod len; len == 0: entry i
 };
 
+// How a staged entry names its row of X.
+// WIDE == false: by the byte offset of the row, for a buffer load; an absent entry by an offset past the
+// buffer's end, which reads as zero and touches no memory.  WIDE == true (tables of 4 GB and more): by the column id.
+constexpr uint32_t kFlatAbsent = 0xFE000000u;         // + the bytes of one row (< 2^24) does not wrap
+constexpr uint64_t kFlatMaxBytes = kFlatAbsent;       // largest table of the 32-bit form
+constexpr uint32_t kFlatAbsentWide = 0xFFFFFFFFu;
+
+typedef uint32_t uint4_v __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ float4 buffer_row(__amdgpu_buffer_rsrc_t rsrc, uint32_t at)
+{
+    const uint4_v t = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)at, 0, 0);
+    return make_float4(__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w));
+}
+
 // Multiplies the workgroup's run: row j's sum goes to s.rowsum[j][FB] (rows
-// without entries: zeros).  Ends with a barrier.
+// without entries: zeros). Ends with a barrier.
 template <bool ALIGNED, bool WIDE, bool STRIDED, class Lds>
 __device__ __forceinline__ void flat_run(const Args& a, const FlatRow& row, int colblk, Lds& s)
 {
@@ -174,30 +192,34 @@ __device__ __forceinline__ void flat_run(const Args& a, const FlatRow& row, int 
         *reinterpret_cast<float4*>(&s.rowsum[i]) = make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
 
-    // chunk position -> entry of the chunk, in the order the slots read: a slot's four
-    // consecutive steps lie side by side (one 128-bit LDS read)
-    const int c_entry = (((lane >> (LOG_E + 2)) * 4 + (lane & 3)) << LOG_E) + ((lane & (4 * E - 1)) >> 2);
-    const int c_block = c_entry >> LOG_BE;
-    const int c_in = c_entry & (BE - 1);
-    const int32_t* get_col = s.col + e * 4;
+    // A chunk's 64 entries are loaded one per lane, in order, so that a load touches few lines, and stored in
+    // the order in which the slots read them: a slot's four consecutive steps side by side (one 128-bit LDS read).
+    const int c_block = lane >> LOG_BE;
+    const int c_in = lane & (BE - 1);
+    const int c_put = (lane >> (LOG_E + 2) << (LOG_E + 2)) + ((lane & (E - 1)) << 2) + ((lane >> LOG_E) & 3);
+    const uint32_t* get_key = s.key + e * 4;
     const float* get_val = s.val + e * 4;
-    using Stride = std::conditional_t<WIDE, uint64_t, uint32_t>;   // bytes from one row of X to the next: up to 33 bits
-    const Stride stride = (Stride)a.ldx * 4u;
+    const uint64_t stride = (uint64_t)a.ldx * 4u;     // bytes from one row of X to the next: up to 33 bits
     const uint32_t load_at = (uint32_t)cols.off[0] * 4u;
     const char* X = reinterpret_cast<const char*>(a.X);
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.X), 0,
+                                                        (int)(uint32_t)min((uint64_t)a.N * stride, kFlatMaxBytes), 0x00027000);
 
     struct Batch { P x[U]; };
     auto gather = [&](int s0, Batch& bt) {
 #pragma unroll
         for (int q = 0; q < U / 4; ++q) {
-            const int4 col = *reinterpret_cast<const int4*>(get_col + (s0 + 4 * q) * E);
+            const uint4 key = *reinterpret_cast<const uint4*>(get_key + (s0 + 4 * q) * E);
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const uint32_t c = (uint32_t)(&col.x)[u];
-                if constexpr (WIDE)
-                    bt.x[4 * q + u].load(reinterpret_cast<const float*>(X + (c * stride + load_at)));
-                else
-                    bt.x[4 * q + u].load(reinterpret_cast<const float*>(X + (uint32_t)(__umul24(c, stride) + load_at)));
+                const uint32_t k = (&key.x)[u];
+                P& x = bt.x[4 * q + u];
+                if constexpr (WIDE) {
+                    x.zero();
+                    if (k != kFlatAbsentWide) x.load(reinterpret_cast<const float*>(X + (k * stride + load_at)));
+                } else {
+                    x.v = buffer_row(rsrc, k + load_at);
+                }
             }
         }
     };
@@ -230,6 +252,7 @@ __device__ __forceinline__ void flat_run(const Args& a, const FlatRow& row, int 
         for (int q0 = wave; q0 < chunks; q0 += M * kWavesPerBlock) {
             int32_t col[M];
             float val[M];
+            bool there[M];
 #pragma unroll
             for (int i = 0; i < M; ++i) {
                 const int q = min(q0 + i * kWavesPerBlock, chunks - 1);
@@ -249,15 +272,23 @@ __device__ __forceinline__ void flat_run(const Args& a, const FlatRow& row, int 
                     }
                 }
                 const float* v = a.vals ? a.vals + pos : kFlatConst + 1;
-                v = c_in < cnt ? v : kFlatConst;                  // absent entries: zero
+                there[i] = c_in < cnt;
+                v = there[i] ? v : kFlatConst;                    // absent entries: zero
                 col[i] = __builtin_nontemporal_load(a.colidx + pos);
                 val[i] = __builtin_nontemporal_load(v);
             }
 #pragma unroll
             for (int i = 0; i < M; ++i) {
                 const int q = min(q0 + i * kWavesPerBlock, chunks - 1);
-                s.col[q * kWaveSize + lane] = col[i];
-                s.val[q * kWaveSize + lane] = val[i];
+                uint32_t key;
+                if constexpr (WIDE) {
+                    key = there[i] ? (uint32_t)col[i] : kFlatAbsentWide;
+                } else {
+                    key = __umul24((uint32_t)col[i], (uint32_t)stride);
+                    key = there[i] ? key : kFlatAbsent;
+                }
+                s.key[q * kWaveSize + c_put] = key;
+                s.val[q * kWaveSize + c_put] = val[i];
             }
         }
         __syncthreads();
@@ -357,9 +388,8 @@ __device__ __forceinline__ void flat_block(const Args& a, uint32_t vb, int part,
         my_n = a.rowptr[r + 1] - base;
         my_k = kept_count(a.mode, my_n, a.W);
         if constexpr (PART) {
-            const int32_t* cr = a.cuts + r * kParts;
-            const int32_t lo = cr[part];
-            const int32_t hi = (part + 1 < kParts) ? cr[part + 1] : my_n;
+            const int32_t lo = a.cuts[part * a.N + r];
+            const int32_t hi = (part + 1 < kParts) ? a.cuts[(part + 1) * a.N + r] : my_n;
             row.src = base + lo;
             row.k = hi - lo;
             my_store = !ACC || hi > lo;

@@ -19,7 +19,7 @@ namespace {
 // products as in the unpartitioned kernel, added in a fixed order, so results
 // are bit-reproducible.
 //
-// A row's share of range p is the piece [cuts[r][p], cuts[r][p+1]) of its
+// A row's share of range p is the piece [cuts[p][r], cuts[p+1][r]) of its
 // entries, found by binary search for the range bounds (es_cuts_kernel).  The
 // cuts are forced to be non-decreasing inside [0, n], so the eight pieces tile
 // the row whatever order its columns are stored in: every kept entry is
@@ -69,7 +69,7 @@ es_cuts_kernel(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ c
         const int32_t up = __shfl_up(lo, d, kParts);
         if (j >= d) lo = max(lo, up);
     }
-    if (r < N) cuts[r * kParts + j] = lo;
+    if (r < N) cuts[j * N + r] = lo;
 }
 
 // Entries of one row's piece requested ahead of time.
@@ -119,9 +119,8 @@ __device__ __forceinline__ void part_row_block(const Args& a, uint32_t vb, int p
         if (r < a.N) {
             base[i] = a.rowptr[r];
             n[i] = a.rowptr[r + 1] - base[i];
-            const int32_t* cr = a.cuts + r * kParts;
-            lo[i] = cr[part];
-            hi[i] = (part + 1 < kParts) ? cr[part + 1] : n[i];
+            lo[i] = a.cuts[part * a.N + r];
+            hi[i] = (part + 1 < kParts) ? a.cuts[(part + 1) * a.N + r] : n[i];
         }
         const bool strided = fastrand && n[i] > a.W;
         const int piece = hi[i] - lo[i];

@@ -594,7 +594,7 @@ int es_run(const int32_t* rowptr, const int32_t* colidx, const float* vals, cons
     ES_BWD(4, 1) ES_BWD(8, 1) ES_BWD(16, 1) ES_BWD(32, 1) ES_BWD(64, 1) ES_BWD(64, 2) ES_BWD(64, 4)
     // the run kernel's 32-bit form: byte offsets from one 24-bit multiply
     const uint64_t stride_bytes = (uint64_t)ldx * 4u;
-    const bool flat_wide = N > (1 << 24) || stride_bytes >= (1u << 24) || (uint64_t)N * stride_bytes > 0x100000000ull;
+    const bool flat_wide = N > (1 << 24) || stride_bytes >= (1u << 24) || (uint64_t)N * stride_bytes > kFlatMaxBytes;
 #define ES_FLAT(G_, A_)                                                                         \
     if (p.flat && s.G == G_ && s.aligned == A_)                                                 \
         err = flat_wide ? launch_flat<G_, A_, true>(a, grid, p.partition, static_cast<int32_t*>(workspace), st)  \

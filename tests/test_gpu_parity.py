@@ -398,6 +398,44 @@ def test_flattened_kernel_rows_at_tile_boundaries(es, F, lanes):
 
 
 @pytest.mark.parametrize("F,lanes", [(16, 0), (64, 8), (64, 0), (128, 0), (256, 0), (41, 0)])
+@pytest.mark.parametrize("ld", [0, 1 << 22])
+def test_flattened_kernel_absent_entries_multiply_nothing(es, F, lanes, ld):
+    """Infinities in X: a row of Y holds one exactly where the sum of its own kept entries
+    does, whatever the flattened kernel pads the row with (64-bit offsets too: ld = 2^22)."""
+    import torch
+    from gpu_util import DeviceCSR
+    n = 60
+    rng = np.random.default_rng(F + lanes)
+    lengths = rng.permutation(np.concatenate([np.arange(0, 40), rng.integers(1, 20, n - 40)]))
+    cols = [np.sort(rng.choice(n, size=int(L), replace=False)) for L in lengths]
+    rowptr = np.zeros(n + 1, dtype=np.int32)
+    rowptr[1:] = np.cumsum(lengths)
+    colidx = np.concatenate(cols).astype(np.int32)
+    vals = rng.uniform(0.5, 1.5, colidx.size).astype(np.float32)
+    X = rng.uniform(-1, 1, (n, F)).astype(np.float32)
+    X[7], X[31, ::2], X[50, 1::3] = np.inf, -np.inf, np.nan
+    d = DeviceCSR(rowptr, colidx, vals, X)
+    if ld:
+        wide = torch.empty((n - 1) * ld + F, dtype=torch.float32, device="cuda:0").as_strided((n, F), (ld, 1))
+        wide.copy_(d.X)
+        d.X, d.F = wide, F
+    for mode, W in (("full", 0), ("bucket", 9), ("bucket", 13)):
+        ref = np.zeros((n, F))
+        with np.errstate(invalid="ignore"):
+            for r in range(n):
+                for p in range(rowptr[r], rowptr[r + 1] if mode == "full" else min(rowptr[r + 1], rowptr[r] + W)):
+                    ref[r] += float(vals[p]) * X[colidx[p]].astype(np.float64)
+        opts = dict(kernel=2)
+        if lanes:
+            opts["lanes_per_row"] = lanes
+        Y = d.run(W, mode, opts=opts).cpu().numpy()
+        for name, pick in (("nan", np.isnan), ("+inf", np.isposinf), ("-inf", np.isneginf)):
+            assert np.array_equal(pick(Y), pick(ref)), f"{name} F={F} ld={ld} {mode} W={W}"
+        fine = np.isfinite(ref)
+        assert np.abs(Y[fine] - ref[fine]).max() <= 1e-5 * 40      # at most 39 terms of magnitude 1.5
+
+
+@pytest.mark.parametrize("F,lanes", [(16, 0), (64, 8), (64, 0), (128, 0), (256, 0), (41, 0)])
 def test_flattened_kernel_bursts_and_shares(es, F, lanes):
     """The flattened kernel around the sizes a workgroup counts in: bursts of 1536
     and 2048 entries, quarter shares of a burst (a row that ends on, before and
