@@ -2,6 +2,8 @@
 #ifndef ES_SPMM_PULL_KERNEL_H
 #define ES_SPMM_PULL_KERNEL_H
 
+#include <type_traits>
+
 #include "es_tile.h"
 
 namespace {
@@ -105,12 +107,18 @@ __host__ __device__ __forceinline__ bool pull_needs_rows(int32_t mode, uint64_t 
     return (mode == ES_FASTRAND && seed != 0) || norm != ES_NORM_NONE;
 }
 
+constexpr int kPullChunks = 4;                        // chunks of 64 entries requested together
+
 // One wave per output row c, E = 64 / G edge slots.  Stage 1 reads the row's
 // transposed entries 64 at a time, tests them, and packs the kept ones
 // (row of dY as its key, value times the forward row factor) into the LDS tile;
 // stage 2 is the forward kernel's gather.
-template <int G, int CH, int VEC, bool ALIGNED, bool WIDE>
-__global__ void __launch_bounds__(kBlockThreads)
+// MAXC: chunks of 64 entries requested together at most.  With 4 the kernel holds six waves per SIMD (five, four
+// with two and four column chunks per lane, one less where rows of 64 lanes are not aligned, which would spill),
+// which short columns want, as they wait for one round trip after another; long ones rather have 8 chunks in flight
+// (the line is where the pull is launched).
+template <int G, int CH, int VEC, bool ALIGNED, bool WIDE, int MAXC>
+__global__ void __launch_bounds__(kBlockThreads, MAXC == 8 ? 0 : (CH == 1 ? 6 : CH == 2 ? 5 : 4) - (G == 64 && !ALIGNED))
 es_pull_kernel(const Args a, const int32_t* __restrict__ t_ptr, const int32_t* __restrict__ t_row,
                const int32_t* __restrict__ t_idx, const int32_t* __restrict__ t_slot,
                const float* __restrict__ t_vals, const int2* __restrict__ rows)
@@ -144,38 +152,52 @@ es_pull_kernel(const Args a, const int32_t* __restrict__ t_ptr, const int32_t* _
 #pragma unroll
     for (int ch = 0; ch < CH; ++ch) acc[ch].zero();
 
-    // kPullChunks * 64 entries per pass: all their loads are issued before the
-    // first test, so that one pass costs two memory round trips, not sixteen
-    constexpr int kPullChunks = 8;
     // as pull_needs_rows; written out, since through the function the kernel takes up to
     // 4 registers more (56 k rows of mean 6, F = 71: 52.2 us, 51.1 this way)
-    const bool need_rows = (a.mode == ES_FASTRAND && a.seed != 0) || a.norm != ES_NORM_NONE;
+    const bool rotated = a.mode == ES_FASTRAND && a.seed != 0;
+    const bool need_rows = rotated || a.norm != ES_NORM_NONE;
     int fill = 0;
-    for (int j0 = 0; j0 < count; j0 += kPullChunks * kWaveSize) {
-        int32_t r[kPullChunks], pick[kPullChunks];
-        float v[kPullChunks];
-        bool valid[kPullChunks];
+    auto gather = [&]() {
+        wave_lds_fence();
+        consume_tile<G, CH, VEC, ALIGNED, WIDE>(tile, fill, e, E, a.X, a.ldx, cols, acc);
+        wave_lds_fence();
+        fill = 0;
+    };
+    // chunks * 64 entries from j0 on: all their loads are issued before the first test, so
+    // that they cost two memory round trips
+    auto pass = [&](int j0, auto chunks) {
+        constexpr int C = decltype(chunks)::value;
+        int32_t r[C], pick[C];
+        float v[C];
+        bool valid[C];
 #pragma unroll
-        for (int q = 0; q < kPullChunks; ++q) {
+        for (int q = 0; q < C; ++q) {
             const int jj = j0 + q * kWaveSize + lane;
             valid[q] = jj < count;
-            const int64_t j = (int64_t)begin + (valid[q] ? jj : 0);
-            r[q] = t_row[j];
-            v[q] = t_vals[j];
-            pick[q] = a.mode == ES_BUCKET ? t_idx[j] : a.mode == ES_FASTRAND ? t_slot[j] : 0;
-        }
-        int2 info[kPullChunks];
-#pragma unroll
-        for (int q = 0; q < kPullChunks; ++q) info[q] = need_rows ? rows[r[q]] : make_int2(INT32_MAX, 0);
-#pragma unroll
-        for (int q = 0; q < kPullChunks; ++q) {
-            const uint32_t n = (uint32_t)info[q].x;
-            int32_t slot = pick[q];                      // Bucket: entry number; FastRand: slot after rotation
-            if (a.mode == ES_FASTRAND) {
-                slot -= info[q].y;
-                if (slot < 0) slot += (int32_t)n;
+            if (valid[q]) {
+                const int64_t j = (int64_t)begin + jj;
+                r[q] = t_row[j];
+                v[q] = t_vals[j];
+                pick[q] = a.mode == ES_BUCKET ? t_idx[j] : a.mode == ES_FASTRAND ? t_slot[j] : 0;
             }
-            const bool keep = valid[q] && (n <= (uint32_t)a.W || (uint32_t)slot < (uint32_t)a.W);
+        }
+        int2 info[C];
+#pragma unroll
+        for (int q = 0; q < C; ++q) {
+            // without rotation the pick is below n, so it decides alone, and only kept entries need their row
+            if (!rotated) valid[q] = valid[q] && (uint32_t)pick[q] < (uint32_t)a.W;
+            if (need_rows && valid[q]) info[q] = rows[r[q]];
+            else info[q] = make_int2(INT32_MAX, 0);
+        }
+#pragma unroll
+        for (int q = 0; q < C; ++q) {
+            const uint32_t n = (uint32_t)info[q].x;
+            bool keep = valid[q];
+            if (rotated) {
+                int32_t slot = pick[q] - info[q].y;          // slot after rotation
+                if (slot < 0) slot += (int32_t)n;
+                keep = keep && (n <= (uint32_t)a.W || (uint32_t)slot < (uint32_t)a.W);
+            }
             const unsigned long long m = __ballot(keep);
             if (keep) {
                 const int k = kept_count(a.mode, (int)n, a.W);
@@ -184,12 +206,19 @@ es_pull_kernel(const Args a, const int32_t* __restrict__ t_ptr, const int32_t* _
             }
             fill += __popcll(m);
         }
-        if (fill > T - kPullChunks * kWaveSize) {        // the next pass might not fit: gather what is staged
-            wave_lds_fence();
-            consume_tile<G, CH, VEC, ALIGNED, WIDE>(tile, fill, e, E, a.X, a.ldx, cols, acc);
-            wave_lds_fence();
-            fill = 0;
-        }
+    };
+    // One chunk where that holds the rest of the column: an absent one costs its instructions and
+    // branches.  Always 8, at five or six waves / this: 20 k rows of mean 4.5, F = 32: 17.5 / 11.8 us, 170 k of mean 14, F =
+    // 128: 133 / 110, 1 M of mean 50, ids that cluster, Bucket W = 32, F = 64: 999 / 727, 500 k of mean 200, F = 64: 1210 / 1199,
+    // 20 k of mean 300, F = 32: 37.5 / 38.1.
+    for (int j0 = 0; j0 < count;) {
+        const int left = count - j0;
+        const int chunks = MAXC == 8 && left > kPullChunks * kWaveSize ? 8 : left > kWaveSize ? kPullChunks : 1;
+        if (fill > T - chunks * kWaveSize) gather();
+        if (MAXC == 8 && chunks == 8) pass(j0, std::integral_constant<int, MAXC>{});
+        else if (chunks == 1) pass(j0, std::integral_constant<int, 1>{});
+        else pass(j0, std::integral_constant<int, kPullChunks>{});
+        j0 += chunks * kWaveSize;
     }
     wave_lds_fence();
     consume_tile<G, CH, VEC, ALIGNED, WIDE>(tile, fill, e, E, a.X, a.ldx, cols, acc);
@@ -205,6 +234,189 @@ es_pull_kernel(const Args a, const int32_t* __restrict__ t_ptr, const int32_t* _
         for (int ch = 0; ch < CH; ++ch)
             if (cols.ok[ch]) acc[ch].store(y + cols.off[ch], cols.first[ch]);
     }
+}
+
+// ---------------------------------------------------------------------------
+// The same for a rotated FastRand (seed != 0), whose test needs the row's length and
+// rotation.  Looking those up for every stored entry costs a line of the vector cache per lane
+// (233 k rows, 113 M entries: 0.43 ms for the lookups alone, whatever the loads' cache policy), and most
+// entries are dropped by it.  So a persistent workgroup of 16 waves first fills its LDS with four bits of every row's
+// rotation, shift / 2^b mod 16, and an entry is looked up only if its slot can lie in the row's window:
+// slot / 2^b within two steps behind those bits (2^b >= W / 2, so a window touches at most three steps),
+// or slot < W (a window that wraps).  A fifth to a third of the entries pass where rows are much longer than W.
+// The waves deal the columns round; a pass's gathers are under way together with the next one's lookups and the
+// entries after that.  233 k rows of mean 490, F = 64, es_pull_kernel / this: W = 16 911 / 549 us, W = 64 1090 / 968: what
+// is left is the stream of entries (1.36 GB) and the gathers, at 16 waves per compute unit.
+// ---------------------------------------------------------------------------
+constexpr int kPullWaves = 16;
+constexpr int kPullThreads = kPullWaves * kWaveSize;
+constexpr int kPullTile = 64 + kPullChunks * kWaveSize;   // (row, value) slots per wave
+constexpr int kPullLdsBytes = 160 * 1024;
+constexpr int kPullTileBytes = kPullWaves * kPullTile * (int)sizeof(uint2);
+constexpr int64_t kPullFilterRows = (int64_t)(kPullLdsBytes - kPullTileBytes) * 2;   // rows whose bits fit beside the tiles
+
+// log2 of the step: the smallest that is at least W / 2
+__host__ __device__ constexpr int pull_step(uint32_t W)
+{
+    int b = 0;
+    while (b < 30 && (2ull << b) < W) ++b;
+    return b;
+}
+
+// Whether slot i of a row can be kept, from the row's bits.
+__host__ __device__ __forceinline__ bool pull_may_keep(uint32_t slot, uint32_t code, uint32_t W, int b)
+{
+    return (((slot >> b) - code) & 15u) <= 2u || slot < W;
+}
+
+template <int G, int CH, int VEC, bool ALIGNED>
+__global__ void __launch_bounds__(kPullThreads)
+es_pull_filtered_kernel(const Args a, const int32_t* __restrict__ t_ptr, const int32_t* __restrict__ t_row,
+                        const int32_t* __restrict__ t_slot, const float* __restrict__ t_vals,
+                        const int2* __restrict__ rows)
+{
+    extern __shared__ __align__(16) uint32_t pull_lds[];
+    constexpr int LOG_G = ilog2(G);
+    constexpr int E = kWaveSize / G;
+    using P = Pack<VEC, ALIGNED>;
+    using K = RowKey<ALIGNED, false>;
+    uint2* tile = reinterpret_cast<uint2*>(pull_lds) + (threadIdx.x >> 6) * kPullTile;
+    uint32_t* codes = pull_lds + kPullTileBytes / (int)sizeof(uint32_t);
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int e = lane >> LOG_G;
+    const int l = lane & (G - 1);
+    const unsigned long long below_me = (1ull << lane) - 1ull;
+    const uint32_t W = (uint32_t)a.W;
+    const int b = pull_step(W);
+    const int N = (int)a.N;                           // below kPullFilterRows
+
+    for (int w = threadIdx.x; w * 8 < N; w += kPullThreads) {
+        uint32_t word = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            word |= (((uint32_t)rows[min(w * 8 + i, N - 1)].y >> b) & 15u) << (4 * i);
+        codes[w] = word;
+    }
+    __syncthreads();
+
+    LaneCols<G, CH, VEC, ALIGNED> cols;
+    cols.init(blockIdx.y * (G * CH * VEC), l, a.F);
+    P acc[CH];
+#pragma unroll
+    for (int ch = 0; ch < CH; ++ch) acc[ch].zero();
+
+    // entries [at, at + left) of column c are still to be read
+    struct Pass { int c; int32_t at, left; };
+    struct Entries { int32_t row[kPullChunks], slot[kPullChunks]; float val[kPullChunks]; };
+    const int stride = (int)gridDim.x * kPullWaves;
+    const int c0 = wave * (int)gridDim.x + (int)blockIdx.x;      // neighbouring columns go to different workgroups
+    int32_t ends = 0, begins = 0;                     // lane i: the column i strides behind `held`
+    int held = c0 - kWaveSize * stride;
+    auto column = [&](int c) {
+        if (c >= N) return Pass{c, 0, 0};
+        int i = (c - held) / stride;
+        if (i >= kWaveSize) {
+            held = c;
+            i = 0;
+            const int64_t mine = (int64_t)c + (int64_t)lane * stride;
+            begins = mine < N ? t_ptr[mine] : 0;
+            ends = mine < N ? t_ptr[mine + 1] : 0;
+        }
+        const int32_t from = __builtin_amdgcn_readlane(begins, i);
+        return Pass{c, from, __builtin_amdgcn_readlane(ends, i) - from};
+    };
+    auto next = [&](const Pass& p) {
+        if (p.left > kPullChunks * kWaveSize) return Pass{p.c, p.at + kPullChunks * kWaveSize, p.left - kPullChunks * kWaveSize};
+        return column(p.c + stride);
+    };
+    auto request = [&](const Pass& p, Entries& n) {
+#pragma unroll
+        for (int q = 0; q < kPullChunks; ++q) {
+            if (q * kWaveSize + lane < p.left) {
+                const int64_t j = (int64_t)p.at + q * kWaveSize + lane;
+                n.row[q] = t_row[j];
+                n.slot[q] = t_slot[j];
+                n.val[q] = t_vals[j];
+            }
+        }
+    };
+
+    // entries of the pass at hand that can be kept, and their rows' (length, rotation), on their way
+    bool may[kPullChunks];
+    int2 info[kPullChunks];
+    auto look_up = [&](const Pass& p, const Entries& n) {
+#pragma unroll
+        for (int q = 0; q < kPullChunks; ++q) {
+            may[q] = q * kWaveSize + lane < p.left;
+            if (may[q]) {
+                const uint32_t r = (uint32_t)n.row[q];
+                may[q] = pull_may_keep((uint32_t)n.slot[q], codes[r >> 3] >> ((r & 7u) * 4u), W, b);
+                if (may[q]) info[q] = rows[r];
+            }
+        }
+    };
+
+    int fill = 0;
+    Pass now = column(c0);
+    if (now.c >= N) return;
+    Pass then = next(now);
+    // One pass: its kept entries go to the tile; the next pass is looked up, the one after that
+    // requested, and only then are the rows of dY gathered, so that all three are under way together.
+    auto step = [&](Entries& cur, Entries& ahead) {
+#pragma unroll
+        for (int q = 0; q < kPullChunks; ++q) {
+            bool keep = may[q];
+            uint32_t n = 0;
+            if (keep) {
+                n = (uint32_t)info[q].x;
+                int32_t slot = cur.slot[q] - info[q].y;
+                if (slot < 0) slot += (int32_t)n;
+                keep = n <= W || (uint32_t)slot < W;
+            }
+            const unsigned long long m = __ballot(keep);
+            if (keep) {
+                const float w = cur.val[q] * row_factor(a.norm, (int)n, kept_count(ES_FASTRAND, (int)n, a.W));
+                tile[fill + __popcll(m & below_me)] = make_uint2(K::make(cur.row[q], a.stride_units), __float_as_uint(w));
+            }
+            fill += __popcll(m);
+        }
+        const Pass p = now;
+        now = then;
+        if (now.c < N) {
+            look_up(now, ahead);
+            then = next(now);
+            if (then.c < N) request(then, cur);
+        }
+        const bool last = now.c != p.c;
+        if (last || fill > kPullTile - kPullChunks * kWaveSize) {
+            wave_lds_fence();
+            consume_tile<G, CH, VEC, ALIGNED, false>(tile, fill, e, E, a.X, a.ldx, cols, acc);
+            wave_lds_fence();
+            fill = 0;
+        }
+        if (last) {
+#pragma unroll
+            for (int m = G; m < kWaveSize; m <<= 1) {
+#pragma unroll
+                for (int ch = 0; ch < CH; ++ch) acc[ch].add_xor(m);
+            }
+            if (e == 0) {
+                float* y = a.Y + p.c * (int64_t)a.ldy;
+#pragma unroll
+                for (int ch = 0; ch < CH; ++ch)
+                    if (cols.ok[ch]) acc[ch].store(y + cols.off[ch], cols.first[ch]);
+            }
+#pragma unroll
+            for (int ch = 0; ch < CH; ++ch) acc[ch].zero();
+        }
+        return now.c < N;
+    };
+    Entries even, odd;
+    request(now, even);
+    if (then.c < N) request(then, odd);
+    look_up(now, even);
+    while (step(even, odd) && step(odd, even)) {}
 }
 
 }  // namespace

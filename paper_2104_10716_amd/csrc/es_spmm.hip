@@ -57,6 +57,7 @@ namespace {
 // host side
 // ---------------------------------------------------------------------------
 constexpr int kMaxDevices = 64;
+constexpr int kComputeUnits = 256;
 
 // Device address of `scratch` on the current device (every GPU holds its own
 // copy of the array at its own address); looked up once per device.
@@ -612,6 +613,23 @@ int build_transposed(const int32_t* rowptr, const int32_t* colidx, const float* 
                      int64_t nnz, int32_t W, int32_t mode, uint64_t seed, int32_t norm, int32_t* out_ptr,
                      int32_t* out_end, int32_t* out_idx, float* out_vals, int32_t* out_pos, void* stream);
 
+// Whether the pull backward tests entries against the rows' bits in LDS before it looks their rows up
+// (es_pull_filtered_kernel).  That spares most of the lookups, 3.8 ps each, but holds only 16 waves per compute
+// unit, which gather less at a time: columns have to be long and the kept entries' rows of dY few.  Time over
+// that of es_pull_kernel, both on one graph, against mean / (min(W, mean) F):
+//  * 233 k rows of mean 490: 0.48 (W = 16, F = 64): 0.62, 0.24: 0.70, 0.12 (W = 64, F = 64 and W = 128, F = 32): 0.89, 0.06: 1.08;
+//    100 k of mean 300, F = 41, W = 32: 0.83, F = 128: 0.07: 1.03; ids that cluster, 200 k of mean 300: 0.15: 1.06, 0.07: 1.1
+//  * mean 200: 0.20: 0.99, 0.10: 1.17; mean 100: 0.20: 1.2, 0.39: 1.2
+//  * 20 k rows of mean 480 (9.6 M entries) 0.83, of mean 300 (6 M) 1.01, 10 k of mean 300 (3 M) 1.08
+// The passes of es_pull_kernel hold 8 chunks from 128 entries a column on (4 / 8: mean 490, no rotation 717 / 703 us, 200 480 / 459,
+// 150 403 / 397, ids that cluster 396 / 385; 100: 222 / 236, ids that cluster, mean 90: 263 / 265).
+bool pull_filtered(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, uint64_t seed)
+{
+    if (mode != ES_FASTRAND || seed == 0 || N > kPullFilterRows || nnz < 8000000 || nnz < 256 * N) return false;
+    const double mean = (double)nnz / (double)N, kept = mean < W ? mean : W;
+    return mean >= 0.11 * kept * (F % 32 ? F + 31 : F);       // rows that tile no line cost another one (F = 41: 1.07 at 0.15)
+}
+
 // Layout of the binned transposed product's workspace (es_bin_kernel.h); bytes == 0:
 // the scatter is the faster form, or this one does not apply.
 struct BinPlan {
@@ -965,14 +983,31 @@ int es_spmm_backward_pull(const int32_t* rowptr, const int32_t* t_ptr, const int
         if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
     }
     bool launched = false;
+    const bool filtered = !wide && pull_filtered(N, nnz, F, W, mode, seed);
+    const uint32_t filter_lds = (uint32_t)(kPullTileBytes + (N + 7) / 8 * (int64_t)sizeof(uint32_t));
+    const int64_t filter_blocks = (N + kPullWaves - 1) / kPullWaves;
+    const dim3 filter_grid((uint32_t)(filter_blocks < kComputeUnits ? filter_blocks : kComputeUnits), (uint32_t)grid_y);
+    const bool long_columns = nnz >= 128 * N;               // see pull_filtered
+#define ES_PULL_LAUNCH(G_, CH_, V_, A_, C_)                                                          \
+    if (wide)                                                                                        \
+        hipLaunchKernelGGL((es_pull_kernel<G_, CH_, V_, A_, true, C_>), grid, dim3(kBlockThreads), 0, st, a,    \
+                           t_ptr, t_row, t_idx, t_slot, t_vals, rows);                               \
+    else                                                                                             \
+        hipLaunchKernelGGL((es_pull_kernel<G_, CH_, V_, A_, false, C_>), grid, dim3(kBlockThreads), 0, st, a,   \
+                           t_ptr, t_row, t_idx, t_slot, t_vals, rows);
 #define ES_PULL(G_, CH_, V_, A_)                                                                     \
     if (s.G == G_ && s.CH == CH_ && s.vec == V_ && s.aligned == A_) {                                \
-        if (wide)                                                                                    \
-            hipLaunchKernelGGL((es_pull_kernel<G_, CH_, V_, A_, true>), grid, dim3(kBlockThreads), 0, st, a,  \
-                               t_ptr, t_row, t_idx, t_slot, t_vals, rows);                                 \
-        else                                                                                         \
-            hipLaunchKernelGGL((es_pull_kernel<G_, CH_, V_, A_, false>), grid, dim3(kBlockThreads), 0, st, a, \
-                               t_ptr, t_row, t_idx, t_slot, t_vals, rows);                                 \
+        if (filtered) {                                                                              \
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(es_pull_filtered_kernel<G_, CH_, V_, A_>),  \
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kPullLdsBytes) != hipSuccess) \
+                return ES_ERR_LAUNCH;                                                                \
+            hipLaunchKernelGGL((es_pull_filtered_kernel<G_, CH_, V_, A_>), filter_grid, dim3(kPullThreads),   \
+                               filter_lds, st, a, t_ptr, t_row, t_slot, t_vals, rows);               \
+        } else if (long_columns) {                                                                   \
+            ES_PULL_LAUNCH(G_, CH_, V_, A_, 8)                                                       \
+        } else {                                                                                     \
+            ES_PULL_LAUNCH(G_, CH_, V_, A_, 4)                                                       \
+        }                                                                                            \
         launched = true;                                                                             \
     }
     ES_PULL(4, 1, 4, true) ES_PULL(8, 1, 4, true) ES_PULL(16, 1, 4, true) ES_PULL(32, 1, 4, true)
@@ -981,6 +1016,7 @@ int es_spmm_backward_pull(const int32_t* rowptr, const int32_t* t_ptr, const int
     ES_PULL(64, 1, 4, false) ES_PULL(64, 2, 4, false) ES_PULL(64, 4, 4, false)
     ES_PULL(4, 1, 1, false)
 #undef ES_PULL
+#undef ES_PULL_LAUNCH
     if (!launched) return ES_ERR_UNSUPPORTED;
     return hipGetLastError() == hipSuccess ? ES_OK : ES_ERR_LAUNCH;
 }

@@ -734,6 +734,51 @@ def test_backward_pull_row_lengths_that_change_the_multiplier(es):
     check_backward_pull_against_oracle(d, t, 64, "bucket", 0, what="pull multipliers bucket")
 
 
+@pytest.mark.parametrize("F,W", [(16, 1), (16, 3), (32, 8), (41, 4), (3, 64), (16, 65), (3, 90), (260, 2)])
+def test_backward_pull_with_rows_bits_in_lds(es, F, W):
+    """The pull backward where a rotated FastRand's entries are tested against four bits per row first
+    (columns of some 370 entries, 9 M in all): rows of at most W entries, a little longer ones, windows
+    that wrap, rows far longer than sixteen steps; a row count that fills no word and no workgroup, an
+    empty column, and a column longer than several passes."""
+    import torch
+    from gpu_util import DeviceCSR, check_backward_pull_against_oracle
+    N = 24_003
+    rng = np.random.default_rng(F * 1000 + W)
+    lens = rng.choice([0, 1, 2, 3, 4, 8, 63, 64, 65, 66, 99, 101, 128, 200, 400, 700, 1500], size=N).astype(np.int64)
+    lens[rng.choice(N, 60, replace=False)] = 20_000
+    lens[:40] = [W, W + 1, 2 * W, 2 * W + 1, 16 * W] * 8
+    rows = np.repeat(np.arange(N), lens)
+    cols = rng.integers(1, N, rows.size)                           # column 0 stays empty
+    cols[rng.random(rows.size) < 0.0005] = 5                       # a column of some 4000 entries
+    rows = np.concatenate([rows, np.repeat(np.arange(N), 130)])
+    cols = np.concatenate([cols, rng.integers(1, N, N * 130)])
+    order = np.lexsort((cols, rows))
+    rows, cols = rows[order], cols[order]
+    first = np.ones(rows.size, dtype=bool)
+    first[1:] = (rows[1:] != rows[:-1]) | (cols[1:] != cols[:-1])
+    rows, cols = rows[first], cols[first]
+    rowptr = np.zeros(N + 1, dtype=np.int32)
+    rowptr[1:] = np.cumsum(np.bincount(rows, minlength=N))
+    colidx = cols.astype(np.int32)
+    assert colidx.size >= max(8_000_000, 256 * N)
+    vals = rng.standard_normal(colidx.size).astype(np.float32)
+    dY = rng.uniform(-1, 1, (N, F)).astype(np.float32)
+    d = DeviceCSR(rowptr, colidx, vals, dY)
+    t = es.es_spmm_transpose_graph(d.rowptr, d.colidx, d.vals)
+    for seed, norm in ((7, "none"), (2 ** 63 + 5, "rescale")):
+        check_backward_pull_against_oracle(d, t, W, "fastrand", seed, norm, what=f"bits F={F} W={W} seed={seed} {norm}")
+    a, b = (torch.empty((N, F), dtype=torch.float32, device="cuda:0") for _ in range(2))
+    es.es_spmm_backward_pull(d.rowptr, t, d.X, a, W, "fastrand", 7)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        es.es_spmm_backward_pull(d.rowptr, t, d.X, b, W, "fastrand", 7)
+    for _ in range(3):
+        b.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(a, b)
+
+
 def test_backward_pull_full_size(es):
     """Configs 2 and 3 at full size, every element; pull and atomic scatter agree."""
     import torch
