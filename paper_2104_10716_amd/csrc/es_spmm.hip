@@ -308,7 +308,7 @@ size_t part_workspace_bytes(int64_t N)
     return (size_t)N * kParts * sizeof(int32_t);
 }
 
-// Rows from which the flattened kernel serves the column ranges of 16-byte-aligned rows.
+// Rows from which the flattened kernel on 32-column slices serves the column ranges of 16-byte-aligned rows.
 bool part_flat_size(int64_t N) { return (double)N * 32.0 > 4.0e6; }
 
 // Whether to run the column-partitioned product.  It pays when a row's piece inside one
@@ -356,6 +356,28 @@ bool pick_partition(int64_t N, double mean_kept, int32_t mode, int cols_per_bloc
     return mean_kept >= (wide ? 216.0 : 256.0) && reach >= (wide ? 4.5e9 : 4.0e9);
 }
 
+// Whether the exact product of rows that tile whole lines runs sliced on the flattened kernel although X is below
+// 0.3 GB: a slice of X is then of the order of an L2, or a community of its rows is.  32-column slices from 40 k to 140 k rows, where a
+// 64-column one outgrows an L2 (`32`), else 64-column ones (`64`), over whole rows on the row kernel, uniform ids / ids that cluster:
+//  * F = 64, 60 k x 40: `32` 0.86 / 0.87, x 100 0.83 / 0.94, x 130 0.81 / 1.03, 120 k x 100 0.93 / 0.83; 45 k x 100 0.86 / 1.04, 30 k x 40 1.08 / 1.02; 250 k x 40: `64` 1.04 /
+//    0.70, x 100 1.01 / 0.76, 500 k x 100 1.01 / 0.74
+//  * F = 128, 15 k x 100: `64` 0.88 / 1.13, 30 k x 40 0.82 / 0.94, x 100 0.77 / 0.94, x 160 0.76 / 1.00, 45 k x 40: `32` 0.74 / 1.01, x 100 0.68 / 0.95, 120 k x 100
+//    0.84 / 0.80, 250 k x 100: `64` 0.99 / 0.72; short rows: 60 k x 14: `64` 0.95 / 1.11, 120 k 0.96 / 0.97, 150 k 0.96 / 0.88, 500 k 1.00 / 0.76, x 6 1.1 / 1.4
+//  * F = 256, 8 k x 40: `64` 0.88 / 1.09, 15 k x 40 0.81 / 0.92, x 160 0.58 / 1.03, 30 k x 100 0.65 / 0.80, 60 k x 100: `32` 0.64 / 0.83, 250 k x 100: `64` 0.97 / 0.62,
+//    x 14 0.97 / 0.82
+// Longer rows are where column ranges begin (pick_partition).  Rows that tile no line pay for every line twice (F = 100: 1.2 - 1.5),
+// and sampled rows of ids that cluster 1.2 - 2.2 (F = 128).
+// 64-column slices have to tile the row (F = 160, 104 k x 14: 1.18, F = 96, 39 k x 100: 1.12); short rows of uniform ids pay for large tables
+// (F = 128, 515 k x 18, 0.26 GB: 1.02).  Returns the lanes of a slice, 0: none.
+int slice_exact(int64_t N, double mean, int32_t mode, int F, double table)
+{
+    if (mode != ES_FULL || F % 32 != 0 || F < 64 || table < 15.0e6 || table >= 300.0e6) return 0;
+    if (mean >= (F == 64 ? 150.0 : 200.0)) return 0;
+    if (mean >= 32.0 && N >= 40000 && N <= 140000) return 8;
+    if (F % 64 != 0 || mean < (F == 64 && N > 140000 ? 64.0 : N >= 100000 ? 10.0 : 32.0)) return 0;
+    return mean < 32.0 && table >= 250.0e6 ? 0 : 16;
+}
+
 // Launch shape for N >= 1 rows.  `aligned`: F and both row strides are
 // multiples of 4 and both matrices are 16-byte aligned.  `crowded`: see es_run.
 int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool aligned, bool backward,
@@ -393,13 +415,12 @@ int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool a
     // every row short, which the row kernel pays for per row and the flattened
     // kernel does not; so the narrow (32-column) slices go with the flattened
     // kernel.  Both sides, us (profiles/ has the sweeps):
-    //  * partitioned product: the flattened kernel above 125 k rows, where an XCD's share of
-    //    a 64-column slice no longer fits its L2 (row form / this, F = 64: 170 k rows of mean 150
-    //    1149 / 727, 233 k of mean 300 2181 / 1534; it is the faster below that too, 90 k of mean 300 726 /
-    //    640, but multiplies padding by zero, which turns an infinity in X into a NaN; the row
-    //    form does not).  Slices of 32 columns where they tile 128-byte lines, else of 64, which
-    //    fetch fewer lines twice (32 / 64 columns, F = 100: 170 k of mean 150 1970 / 1680, 233 k of mean
-    //    300 5123 / 4501; F = 128, 233 k of mean 300 2910 / 3077).
+    //  * partitioned product: the flattened kernel from 60 k rows on (row form / this, F = 64: 60 k rows of mean 300
+    //    511 / 391, 100 k of mean 400 989 / 688, 170 k of mean 300 1531 / 1024; F = 256, 100 k of mean 400 3665 / 2371).
+    //    Slices of 64 columns, which halve what is paid per piece, of 32 above 125 k rows, where an XCD's share of a
+    //    64-column slice no longer fits its L2 and where 32 tile 128-byte lines (32 / 64 columns, F = 64: 100 k of mean 400 834 /
+    //    688, 170 k of mean 300 1042 / 1024, 233 k of mean 490 2071 / 2365; F = 100: 170 k of mean 150 1970 / 1680, 233 k of
+    //    mean 300 5123 / 4501).
     //  * tables of 0.3 GB and more with F >= 128: 32-column slices on the flattened
     //    kernel, so that the X rows of a community of ids come nearer to an L2.
     //    Whole rows on the row kernel / this, 0.6 GB, F = 128: ids that cluster, mean
@@ -418,9 +439,13 @@ int make_plan(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, bool a
         if (ov.G > 0) slice_G = ov.G;
         else if (ov.G == 0) {
             const double table = (double)N * F * 4.0;
+            const int exact_lanes = slice_exact(N, mean, mode, F, table);
             if (p->partition) {
-                want_flat = flat_allowed && part_flat_size(N);
-                slice_G = want_flat && F % 32 == 0 ? 8 : 16;
+                want_flat = flat_allowed && N >= 60000;
+                slice_G = want_flat && F % 32 == 0 && part_flat_size(N) ? 8 : 16;
+            } else if (flat_allowed && exact_lanes > 0) {
+                want_flat = true;
+                slice_G = exact_lanes;
             } else if (flat_allowed && F >= 128 && table >= 300.0e6) {
                 want_flat = true;
                 slice_G = 8;

@@ -169,6 +169,19 @@ def test_column_range_rule(N, mean, F, aligned, ranges, lanes):
     assert (info["column_ranges"], info["lanes_per_row"]) == (ranges, lanes)
 
 
+@pytest.mark.parametrize("N,mean,F,lanes", [
+    # exact product, whole rows: 32-column slices from 40 k to 140 k rows, else 64-column ones where they tile the row
+    (58_593, 40, 64, 16), (58_594, 40, 64, 8), (58_594, 31, 64, 16), (58_594, 149, 64, 8), (58_594, 150, 64, 16), (140_000, 40, 64, 8),
+    (29_296, 40, 128, 32), (29_297, 40, 128, 16), (39_999, 40, 128, 16), (40_000, 40, 128, 8), (40_000, 199, 128, 8), (40_000, 200, 128, 32),
+    (140_001, 40, 128, 16), (100_000, 31, 128, 16), (100_000, 10, 128, 16), (100_000, 9, 128, 32), (99_999, 31, 128, 32), (488_282, 31, 128, 32),
+    (39_999, 40, 96, 32), (40_000, 40, 96, 8), (140_001, 40, 96, 32), (100_000, 40, 100, 32), (100_000, 40, 48, 16), (500_000, 40, 128, 16)])
+def test_exact_slices_of_middling_tables(N, mean, F, lanes):
+    info = es.es_spmm_launch_info(N, N * mean, F, 0, "full")
+    assert info["column_ranges"] == 1 and info["lanes_per_row"] == lanes
+    assert es.es_spmm_launch_info(N, N * mean, F, 0, "full", opts=dict(kernel=1))["lanes_per_row"] >= 16
+    assert es.es_spmm_launch_info(N, N * mean, F, 0, "full", aligned16=False)["flattened"] == 0
+
+
 def test_flattened_kernel_choice():
     """Without options the flattened kernel runs where narrow column slices pay:
     the partitioned product once a 64-column share outgrows an L2, and tables of
