@@ -14,10 +14,10 @@ namespace {
 // levels, so that no counter lies in global memory: the kept entries by blocks of
 // 2^log_width columns (count per workgroup and block, prefix sums, fill: records of
 // 8 bytes, the row and the column inside the block, value times row factor), then each
-// block by column.
+// block by column.  Where a walker's entries fit its registers one launch does the first level (es_bin_local_kernel).
 //
 // What bounds it: the product, i.e. its gathers.  170 k rows, W = 16 of a mean of 14, F =
-// 128: 126 us (scatter: 406), of which count 10, scan and base 6, fill 16, sort 12, and the product 83.  Larger
+// 128: 110 us (scatter: 406), of which the product 83.  Larger
 // and denser (233 k rows, W = 64, 14.9 M entries, F = 64; Bucket / FastRand): count 67 / 82, fill 124 / 244, sort
 // 218 / 209, product 477 / 512 of 900 / 1050.  Beyond every cache (2.45 M rows, W = 64, 56 M entries, F = 128): 254, 417,
 // 1285 and 3373 of 5.4 ms (scatter: 21.8).  The fill's records go out 8 bytes at a time (256 walkers: 133 us; 512, with
@@ -49,6 +49,125 @@ struct BinArgs {
     int32_t W, mode, norm;
     int32_t log_width, nbins, walkers;
 };
+
+// Inclusive prefix sums over the workgroup's threads; `total` becomes their sum.  Ends with a barrier.
+template <int THREADS>
+__device__ __forceinline__ int32_t block_scan(int32_t v, int32_t* wave_total, int32_t& total)
+{
+    const int lane = threadIdx.x & (kWaveSize - 1);
+    const int wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int d = 1; d < kWaveSize; d <<= 1) {
+        const int32_t up = __shfl_up(v, d, kWaveSize);
+        if (lane >= d) v += up;
+    }
+    if (lane == kWaveSize - 1) wave_total[wave] = v;
+    __syncthreads();
+    int32_t before = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < THREADS / kWaveSize; ++w) {
+        if (w < wave) before += wave_total[w];
+        total += wave_total[w];
+    }
+    __syncthreads();
+    return v + before;
+}
+
+// The first level in one launch, where a walker's kept entries fit its threads' registers (at most
+// kBinLocalRows rows, kBinLocalPer entries per thread): an entry's rank in its column block comes
+// from the counter's atomic, the counters' prefix sums give its place among the walker's own records, and the walker leaves
+// those sums in counts[walker][0 .. nbins].  No launch for counting or prefix sums over walkers is needed: the sort
+// adds up what it needs of the walkers' sums.  Whole product, count / scan / base / fill / sort / gather in place of this / sort /
+// gather: 170 k rows, W = 16 of a mean of 14, F = 128: 121 / 110 us, 60 k rows, W = 60, F = 32: 94 / 82, 10 k rows, W = 250 of a
+// mean of 300, F = 64: 83 / 65.
+constexpr int kBinLocalRows = 1024;
+constexpr int kBinLocalPer = 16;
+__global__ void __launch_bounds__(kBinLocalRows) es_bin_local_kernel(const BinArgs a)
+{
+    extern __shared__ int32_t counter[];              // [nbins + 1]
+    __shared__ int32_t first[kBinLocalRows];
+    __shared__ int32_t src[kBinLocalRows];
+    __shared__ uint32_t len[kBinLocalRows], mul[kBinLocalRows], rot[kBinLocalRows];
+    __shared__ float factor[kBinLocalRows];
+    __shared__ int32_t wave_total[kBinLocalRows / kWaveSize];
+    const int tid = threadIdx.x;
+    for (int b = tid; b <= a.nbins; b += kBinLocalRows) counter[b] = 0;
+    const int64_t r_begin = a.N * blockIdx.x / a.walkers, r_end = a.N * (blockIdx.x + 1) / a.walkers;
+    const int64_t r = r_begin + tid;
+    int32_t k = 0;
+    if (r < r_end) {
+        const int32_t p = a.rowptr[r];
+        const int32_t n = a.rowptr[r + 1] - p;
+        k = kept_count(a.mode, n, a.W);
+        src[tid] = p;
+        const bool strided = a.mode == ES_FASTRAND && n > a.W;
+        len[tid] = strided ? (uint32_t)n : 0u;
+        mul[tid] = strided ? fastrand_multiplier((uint32_t)n) : 0u;
+        rot[tid] = strided ? fastrand_offset(a.seed, r, (uint32_t)n) : 0u;
+        factor[tid] = row_factor(a.norm, n, k);
+    }
+    int32_t total;
+    first[tid] = block_scan<kBinLocalRows>(k, wave_total, total) - k;
+    __syncthreads();
+    // this thread's entries: row and column inside the block, value; block | rank << 12
+    uint32_t key[kBinLocalPer], place[kBinLocalPer];
+    float val[kBinLocalPer];
+#pragma unroll
+    for (int m = 0; m < kBinLocalPer; ++m) {
+        const int32_t i = tid + m * kBinLocalRows;
+        if (i < total) {
+            int q = 0;                                // last row that starts at or before entry i
+#pragma unroll
+            for (int d = kBinLocalRows / 2; d >= 1; d >>= 1) q += first[q + d] <= i ? d : 0;
+            uint32_t entry = (uint32_t)(i - first[q]);
+            const uint32_t n_q = len[q];
+            if (n_q) {                                // Equation 2; W <= 4096, so the product stays below 2^24
+                entry = rot[q] + small_mod(entry * mul[q], n_q);
+                if (entry >= n_q) entry -= n_q;
+            }
+            const int64_t p = (int64_t)src[q] + entry;
+            key[m] = (uint32_t)a.colidx[p];
+            val[m] = (a.vals ? a.vals[p] : 1.0f) * factor[q];
+            place[m] = (uint32_t)q;
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < kBinLocalPer; ++m) {
+        if (tid + m * kBinLocalRows < total) {
+            const uint32_t col = key[m], b = col >> a.log_width;
+            key[m] = (uint32_t)(r_begin + place[m]) | ((col - (b << a.log_width)) << kBinRowBits);
+            place[m] = b | (uint32_t)atomicAdd(&counter[b], 1) << 12;
+        }
+    }
+    __syncthreads();
+    constexpr int PER = kBinMaxBlocks / kBinLocalRows;
+    int32_t mine[PER], sum = 0;
+    const int b0 = tid * PER;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        mine[i] = b0 + i < a.nbins ? counter[b0 + i] : 0;
+        sum += mine[i];
+    }
+    int32_t all;
+    int32_t at = block_scan<kBinLocalRows>(sum, wave_total, all) - sum;
+    int32_t* out = a.counts + (int64_t)blockIdx.x * (a.nbins + 1);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        if (b0 + i < a.nbins) {
+            counter[b0 + i] = at;
+            out[b0 + i] = at;
+        }
+        at += mine[i];
+    }
+    if (tid == 0) out[a.nbins] = all;
+    __syncthreads();
+    uint2* records = a.records + r_begin * a.W;       // the walker's own: at most W per row
+#pragma unroll
+    for (int m = 0; m < kBinLocalPer; ++m)
+        if (tid + m * kBinLocalRows < total)
+            records[counter[place[m] & 0xFFFu] + (int32_t)(place[m] >> 12)] = make_uint2(key[m], __float_as_uint(val[m]));
+}
 
 // Walks the kept entries of this workgroup's rows, 512 rows at a time laid end to
 // end: every thread then takes entries, whatever rows they are of.  FILL == false
@@ -216,27 +335,56 @@ __host__ __device__ constexpr uint32_t bin_record(uint32_t i, int m, uint32_t en
 static_assert(bin_record(INT32_MAX - 1u, kBinSortM - 1, INT32_MAX) == INT32_MAX - 1u && INT32_MAX - 1u + kBinSortStep > INT32_MAX,
               "the last records of the largest graph");
 
-// Sorts column block blockIdx.x by column into the transposed graph.
+// Sorts column block blockIdx.x by column into the transposed graph.  LOCAL: the block's records lie in one
+// piece per walker (es_bin_local_kernel).
+template <bool LOCAL>
 __global__ void __launch_bounds__(kBlockThreads) es_bin_sort_kernel(const BinArgs a)
 {
     constexpr int COLS = 1 << (32 - kBinRowBits);     // columns of a block at most
     constexpr int PER = COLS / kBlockThreads;
     constexpr int M = kBinSortM;
+    static_assert(!LOCAL || kBinWalkers == kBlockThreads, "one thread per walker");
     __shared__ int32_t cursor[COLS];
     __shared__ int32_t wave_total[kWavesPerBlock];
+    __shared__ int32_t piece[LOCAL ? kBinWalkers : 1];                // LOCAL: the walkers' first records of the block,
+    __shared__ int32_t where[LOCAL ? kBinWalkers : 1];                // where walker w's lie, less piece[w]
     const int tid = threadIdx.x;
-    const int lane = tid & (kWaveSize - 1);
-    const int wave = tid >> 6;
     const int64_t c0 = (int64_t)blockIdx.x << a.log_width;
     const int cols = (int)min((int64_t)1 << a.log_width, a.N - c0);
-    const uint32_t begin = (uint32_t)min((int64_t)a.base[blockIdx.x], a.capacity);
-    const uint32_t end = (uint32_t)min((int64_t)a.base[blockIdx.x + 1], a.capacity);
+    uint32_t begin, end;                              // of the block in the transposed graph
+    uint32_t shift = 0;                               // from there to the records' numbers
+    if constexpr (LOCAL) {
+        int32_t from = 0, n = 0;
+        if (tid < a.walkers) {
+            const int32_t* c = a.counts + (int64_t)tid * (a.nbins + 1) + blockIdx.x;
+            from = c[0];
+            n = c[1] - from;
+        }
+        int32_t before, total;                        // records of all blocks before this one, and of this one
+        block_scan<kBlockThreads>(from, wave_total, before);
+        piece[tid] = block_scan<kBlockThreads>(n, wave_total, total) - n;
+        where[tid] = (int32_t)(a.N * tid / a.walkers * a.W) + from - piece[tid];
+        begin = (uint32_t)min((int64_t)before, a.capacity);
+        end = (uint32_t)min((int64_t)before + total, a.capacity);
+        shift = begin;
+    } else {
+        begin = (uint32_t)min((int64_t)a.base[blockIdx.x], a.capacity);
+        end = (uint32_t)min((int64_t)a.base[blockIdx.x + 1], a.capacity);
+    }
+    const auto record_of = [&](uint32_t i) {
+        if constexpr (!LOCAL) return i;
+        const int32_t j = (int32_t)(i - shift);
+        int w = 0;
+#pragma unroll
+        for (int d = kBinWalkers / 2; d >= 1; d >>= 1) w += piece[w + d] <= j ? d : 0;
+        return (uint32_t)(where[w] + j);
+    };
     for (int c = tid; c < COLS; c += kBlockThreads) cursor[c] = 0;
     __syncthreads();
     for (uint32_t i0 = begin + tid; i0 < end; i0 += kBinSortStep) {
         uint32_t key[M];
 #pragma unroll
-        for (int m = 0; m < M; ++m) key[m] = a.records[bin_record(i0, m, end)].x;
+        for (int m = 0; m < M; ++m) key[m] = a.records[record_of(bin_record(i0, m, end))].x;
 #pragma unroll
         for (int m = 0; m < M; ++m)
             if (i0 + m * kBlockThreads < end) atomicAdd(&cursor[key[m] >> kBinRowBits], 1);
@@ -246,16 +394,8 @@ __global__ void __launch_bounds__(kBlockThreads) es_bin_sort_kernel(const BinArg
     int32_t mine = 0;
 #pragma unroll
     for (int i = 0; i < PER; ++i) { count[i] = cursor[tid * PER + i]; mine += count[i]; }
-    int32_t incl = mine;
-#pragma unroll
-    for (int d = 1; d < kWaveSize; d <<= 1) {
-        const int32_t up = __shfl_up(incl, d, kWaveSize);
-        if (lane >= d) incl += up;
-    }
-    if (lane == kWaveSize - 1) wave_total[wave] = incl;
-    __syncthreads();
-    int32_t at = (int32_t)begin + incl - mine;
-    for (int w = 0; w < wave; ++w) at += wave_total[w];
+    int32_t all;
+    int32_t at = (int32_t)begin + block_scan<kBlockThreads>(mine, wave_total, all) - mine;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
         const int c = tid * PER + i;
@@ -268,7 +408,7 @@ __global__ void __launch_bounds__(kBlockThreads) es_bin_sort_kernel(const BinArg
     for (uint32_t i0 = begin + tid; i0 < end; i0 += kBinSortStep) {
         uint2 rec[M];
 #pragma unroll
-        for (int m = 0; m < M; ++m) rec[m] = a.records[bin_record(i0, m, end)];
+        for (int m = 0; m < M; ++m) rec[m] = a.records[record_of(bin_record(i0, m, end))];
 #pragma unroll
         for (int m = 0; m < M; ++m)
             if (i0 + m * kBlockThreads < end) {

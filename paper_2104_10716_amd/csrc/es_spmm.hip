@@ -660,6 +660,7 @@ bool pull_filtered(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, u
 struct BinPlan {
     int64_t capacity;                  // kept entries at most
     int log_width, nbins, walkers;
+    bool local;                        // a walker's entries fit its registers (es_bin_local_kernel)
     size_t records, counts, base, t_ptr, t_row, t_val, bytes;
 };
 
@@ -705,8 +706,10 @@ BinPlan plan_bins(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode)
     p.nbins = (int)((N + ((int64_t)1 << p.log_width) - 1) >> p.log_width);
     p.walkers = (int)((N + kWaveSize - 1) / kWaveSize < kBinWalkers ? (N + kWaveSize - 1) / kWaveSize : kBinWalkers);
     const auto take = [&p](size_t bytes) { const size_t at = p.bytes; p.bytes += (bytes + 255) / 256 * 256; return at; };
-    p.records = take((size_t)p.capacity * sizeof(uint2));
-    p.counts = take((size_t)p.walkers * p.nbins * sizeof(int32_t));
+    const int64_t walker_rows = (N + p.walkers - 1) / p.walkers;
+    p.local = walker_rows <= kBinLocalRows && walker_rows * W <= (int64_t)kBinLocalRows * kBinLocalPer;
+    p.records = take((size_t)(p.local ? N * W : p.capacity) * sizeof(uint2));       // local: W places per row
+    p.counts = take((size_t)p.walkers * (p.nbins + 1) * sizeof(int32_t));
     p.base = take((size_t)(p.nbins + 1) * sizeof(int32_t));
     p.t_ptr = take((size_t)(N + 1) * sizeof(int32_t));
     p.t_row = take((size_t)p.capacity * sizeof(int32_t));
@@ -731,17 +734,25 @@ int run_binned(const int32_t* rowptr, const int32_t* colidx, const float* vals, 
     a.N = N; a.capacity = p.capacity; a.seed = seed; a.W = W; a.mode = mode; a.norm = norm;
     a.log_width = p.log_width; a.nbins = p.nbins; a.walkers = p.walkers;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const uint32_t lds = (uint32_t)p.nbins * sizeof(int32_t);
-    hipLaunchKernelGGL(es_bin_walk_kernel<false>, dim3((uint32_t)p.walkers), dim3(kBinThreads), lds, st, a);
-    if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
-    hipLaunchKernelGGL(es_bin_scan_kernel, dim3((uint32_t)(p.nbins + kWaveSize - 1) / kWaveSize), dim3(kBinScanThreads), 0, st, a);
-    if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
-    hipLaunchKernelGGL(es_bin_base_kernel, dim3(1), dim3(kBinScanThreads), 0, st, a);
-    if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
-    hipLaunchKernelGGL(es_bin_walk_kernel<true>, dim3((uint32_t)p.walkers), dim3(kBinThreads), lds, st, a);
-    if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
-    hipLaunchKernelGGL(es_bin_sort_kernel, dim3((uint32_t)p.nbins), dim3(kBlockThreads), 0, st, a);
-    if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
+    if (p.local) {
+        const uint32_t lds = (uint32_t)(p.nbins + 1) * sizeof(int32_t);
+        hipLaunchKernelGGL(es_bin_local_kernel, dim3((uint32_t)p.walkers), dim3(kBinLocalRows), lds, st, a);
+        if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
+        hipLaunchKernelGGL(es_bin_sort_kernel<true>, dim3((uint32_t)p.nbins), dim3(kBlockThreads), 0, st, a);
+        if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
+    } else {
+        const uint32_t lds = (uint32_t)p.nbins * sizeof(int32_t);
+        hipLaunchKernelGGL(es_bin_walk_kernel<false>, dim3((uint32_t)p.walkers), dim3(kBinThreads), lds, st, a);
+        if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
+        hipLaunchKernelGGL(es_bin_scan_kernel, dim3((uint32_t)(p.nbins + kWaveSize - 1) / kWaveSize), dim3(kBinScanThreads), 0, st, a);
+        if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
+        hipLaunchKernelGGL(es_bin_base_kernel, dim3(1), dim3(kBinScanThreads), 0, st, a);
+        if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
+        hipLaunchKernelGGL(es_bin_walk_kernel<true>, dim3((uint32_t)p.walkers), dim3(kBinThreads), lds, st, a);
+        if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
+        hipLaunchKernelGGL(es_bin_sort_kernel<false>, dim3((uint32_t)p.nbins), dim3(kBlockThreads), 0, st, a);
+        if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
+    }
     return es_run(a.t_ptr, a.t_row, a.t_val, dY, dX, N, p.capacity, F, ldy, ldx, 0, ES_FULL, 0, ES_NORM_NONE, false,
                   &kBinProduct, nullptr, 0, stream, mode == ES_BUCKET ? nnz : 0);
 }

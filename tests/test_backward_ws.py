@@ -89,6 +89,19 @@ def test_backward_through_a_workspace(N, avg, F, ldx, mode, W, seed, norm, extra
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("N,avg,F,ldx,mode,W,seed,norm,extra", [
+    # walkers whose entries fit their registers, at most 1024 rows and 16 entries per thread, and just no longer
+    (16_384, 20.0, 64, None, "fastrand", 256, 3, "mean", dict(long_row=9_000)), (16_384, 20.0, 64, None, "fastrand", 257, 3, "mean", {}),
+    (16_384, 260.0, 20, None, "bucket", 256, 0, "none", {}),                     # every place of a walker taken
+    (262_144, 4.0, 20, None, "bucket", 16, 0, "none", dict(hot=262_143)), (262_145, 4.0, 20, None, "fastrand", 16, 9, "none", {}),
+    (1_000, 200.0, 512, None, "fastrand", 256, 2 ** 63 + 5, "rescale", {}), (65, 60.0, 9_000, None, "bucket", 64, 0, "none", {}),
+    (2_048, 300.0, 160, 164, "fastrand", 257, 7, "none", {}), (40_961, 130.0, 41, 41, "bucket", 120, 0, "inv_degree", {}),
+    (131_073, 40.0, 20, None, "fastrand", 33, 77, "rsqrt", {})])
+def test_backward_through_a_workspace_around_what_a_walker_holds(N, avg, F, ldx, mode, W, seed, norm, extra):
+    test_backward_through_a_workspace(N, avg, F, ldx, mode, W, seed, norm, extra)
+
+
+@pytest.mark.gpu
 def test_backward_workspace_on_streams_in_graphs_and_with_infinities():
     import torch
     from gpu_util import DeviceCSR, check_Y
