@@ -669,13 +669,12 @@ struct BinPlan {
 constexpr es_launch_opts_t kBinProduct = {0, 0, 0, -1, 1};
 
 // Where the lines lie: the scatter moves one 64-byte request per kept entry and 16
-// columns, 20.5 G of them a second; this form takes some 25 us of launches and first
-// round trips, 0.04 us per 1000 kept entries to sort them, and the gather.  us, scatter / this:
-//  * kBinMinRequests, counted on min(nnz, N W) entries.  Rows of one length keep them all and
-//    cross near 0.65 M (F = 20, 14 entries a row: 0.7 M 39 / 37, 1.1 M 57 / 43), power-law rows keep about half
-//    and cross near 1.25 M (F = 20, mean 7, W = 8: 1.12 M 35.6 / 37.2, 1.3 M 39.9 / 39.4; F = 64, mean 13, W = 16:
-//    1.2 M 39 / 32); the line is between the two.  F = 128: 170 k rows, 2.1 M entries at most 406 / 126;
-//    F = 64: 233 k, 14.9 M 2923 / 1048; a column that all rows hold, 20 k to 1 M rows: always this.
+// columns, 20.5 G of them a second; this form takes some 20 us of launches and first
+// round trips, 0.03 us per 1000 kept entries to sort them, and the gather.  us, scatter / this:
+//  * kBinMinRequests, counted on min(nnz, N W) entries, power-law rows keep about half of them (a walker's entries
+//    in registers, 3.4 k to 140 k rows, F = 17 to 256): 0.20 - 0.30 M 13 - 19 / 19 - 25, 0.36 - 0.43 M 17 - 27 / 21 - 36, 0.47 - 0.58 M 18 - 35 / 20 - 38 (0.62 - 1.12
+//    of the time), 0.66 - 0.83 M 30 - 50 / 24 - 29, 0.91 - 1.12 M 30 - 60 / 22 - 54 (0.58 - 1.00).  F = 128: 170 k rows, 2.1 M entries at
+//    most 406 / 110; F = 64: 233 k, 14.9 M 2923 / 1048; a column that all rows hold, 20 k to 1 M rows: always this.
 //  * F <= 16: with one request per entry the sort costs what it saves: 160 k, 2.0 M 60 / 66; 2.4 M rows,
 //    10.5 M 382 / 399; 160 k, 7.6 M 191 / 159.
 //  * rows longer than a line of 128 bytes of which few entries are kept: count and fill wait for
