@@ -331,6 +331,8 @@ bool part_flat_size(int64_t N) { return (double)N * 32.0 > 4.0e6; }
 //    248: 1.10; F = 192: 62 k 177: 0.94, 216: 1.08; F = 256: 31 k 176: 0.90, 244: 1.13, 70 k 180: 1.00, 120 k 179: 0.88,
 //    248: 1.08; F = 300: 62 k 216: 1.09, 120 k 241: 0.99.
 //  * row form on rows of one line: F = 32: 120 k 297: 0.59, 484: 0.76; F = 17: 484: 0.75, F = 31: 297: 0.98, 484: 1.24.
+// From 60 k aligned rows on the flattened kernel serves the rows of the last three (0.6 - 0.8 of the row form's time,
+// make_plan); the lines stay where the row form crosses.
 // Ids that cluster hit on whole rows too and gain less: 0.7 - 0.86 on the flattened kernel, 0.4 - 0.7 on the
 // row form; sizes do not tell them apart.
 bool pick_partition(int64_t N, double mean_kept, int32_t mode, int cols_per_block, int F, bool aligned, bool flat,
