@@ -113,10 +113,11 @@ constexpr int kPullChunks = 4;                        // chunks of 64 entries re
 // transposed entries 64 at a time, tests them, and packs the kept ones
 // (row of dY as its key, value times the forward row factor) into the LDS tile;
 // stage 2 is the forward kernel's gather.
-// MAXC: chunks of 64 entries requested together at most.  With 4 the kernel holds six waves per SIMD (five, four
-// with two and four column chunks per lane, one less where rows of 64 lanes are not aligned, which would spill),
-// which short columns want, as they wait for one round trip after another; long ones rather have 8 chunks in flight
-// (the line is where the pull is launched).
+// MAXC: chunks of 64 entries requested together at most.  Long columns (8) stream: a pass loads all of its chunks without a
+// branch, an absent entry as the column's first.  Short ones (4) wait for one round trip after another: six waves per SIMD
+// (five, four with two and four column chunks per lane, one less where rows of 64 lanes are not aligned, which would spill),
+// one chunk where that holds the column, and only entries that are there are loaded.  The latter on long columns: 50 k rows of
+// mean 300, F = 32, Bucket W = 8: 33.7 us, 44.3 with it.
 template <int G, int CH, int VEC, bool ALIGNED, bool WIDE, int MAXC>
 __global__ void __launch_bounds__(kBlockThreads, MAXC == 8 ? 0 : (CH == 1 ? 6 : CH == 2 ? 5 : 4) - (G == 64 && !ALIGNED))
 es_pull_kernel(const Args a, const int32_t* __restrict__ t_ptr, const int32_t* __restrict__ t_row,
@@ -152,76 +153,125 @@ es_pull_kernel(const Args a, const int32_t* __restrict__ t_ptr, const int32_t* _
 #pragma unroll
     for (int ch = 0; ch < CH; ++ch) acc[ch].zero();
 
-    // as pull_needs_rows; written out, since through the function the kernel takes up to
-    // 4 registers more (56 k rows of mean 6, F = 71: 52.2 us, 51.1 this way)
-    const bool rotated = a.mode == ES_FASTRAND && a.seed != 0;
-    const bool need_rows = rotated || a.norm != ES_NORM_NONE;
-    int fill = 0;
-    auto gather = [&]() {
-        wave_lds_fence();
-        consume_tile<G, CH, VEC, ALIGNED, WIDE>(tile, fill, e, E, a.X, a.ldx, cols, acc);
-        wave_lds_fence();
-        fill = 0;
-    };
-    // chunks * 64 entries from j0 on: all their loads are issued before the first test, so
-    // that they cost two memory round trips
-    auto pass = [&](int j0, auto chunks) {
-        constexpr int C = decltype(chunks)::value;
-        int32_t r[C], pick[C];
-        float v[C];
-        bool valid[C];
+    if constexpr (MAXC == 8) {
+        // MAXC * 64 entries per pass: all their loads are issued before the
+        // first test, so that one pass costs two memory round trips, not sixteen
+        // as pull_needs_rows; written out, since through the function the kernel takes up to
+        // 4 registers more (56 k rows of mean 6, F = 71: 52.2 us, 51.1 this way)
+        const bool need_rows = (a.mode == ES_FASTRAND && a.seed != 0) || a.norm != ES_NORM_NONE;
+        int fill = 0;
+        for (int j0 = 0; j0 < count; j0 += MAXC * kWaveSize) {
+            int32_t r[MAXC], pick[MAXC];
+            float v[MAXC];
+            bool valid[MAXC];
 #pragma unroll
-        for (int q = 0; q < C; ++q) {
-            const int jj = j0 + q * kWaveSize + lane;
-            valid[q] = jj < count;
-            if (valid[q]) {
-                const int64_t j = (int64_t)begin + jj;
+            for (int q = 0; q < MAXC; ++q) {
+                const int jj = j0 + q * kWaveSize + lane;
+                valid[q] = jj < count;
+                const int64_t j = (int64_t)begin + (valid[q] ? jj : 0);
                 r[q] = t_row[j];
                 v[q] = t_vals[j];
                 pick[q] = a.mode == ES_BUCKET ? t_idx[j] : a.mode == ES_FASTRAND ? t_slot[j] : 0;
             }
-        }
-        int2 info[C];
+            int2 info[MAXC];
 #pragma unroll
-        for (int q = 0; q < C; ++q) {
-            // without rotation the pick is below n, so it decides alone, and only kept entries need their row
-            if (!rotated) valid[q] = valid[q] && (uint32_t)pick[q] < (uint32_t)a.W;
-            if (need_rows && valid[q]) info[q] = rows[r[q]];
-            else info[q] = make_int2(INT32_MAX, 0);
-        }
+            for (int q = 0; q < MAXC; ++q) info[q] = need_rows ? rows[r[q]] : make_int2(INT32_MAX, 0);
 #pragma unroll
-        for (int q = 0; q < C; ++q) {
-            const uint32_t n = (uint32_t)info[q].x;
-            bool keep = valid[q];
-            if (rotated) {
-                int32_t slot = pick[q] - info[q].y;          // slot after rotation
-                if (slot < 0) slot += (int32_t)n;
-                keep = keep && (n <= (uint32_t)a.W || (uint32_t)slot < (uint32_t)a.W);
+            for (int q = 0; q < MAXC; ++q) {
+                const uint32_t n = (uint32_t)info[q].x;
+                int32_t slot = pick[q];                      // Bucket: entry number; FastRand: slot after rotation
+                if (a.mode == ES_FASTRAND) {
+                    slot -= info[q].y;
+                    if (slot < 0) slot += (int32_t)n;
+                }
+                const bool keep = valid[q] && (n <= (uint32_t)a.W || (uint32_t)slot < (uint32_t)a.W);
+                const unsigned long long m = __ballot(keep);
+                if (keep) {
+                    const int k = kept_count(a.mode, (int)n, a.W);
+                    const float w = v[q] * row_factor(a.norm, (int)n, k);
+                    tile[fill + __popcll(m & below_me)] = make_uint2(K::make(r[q], a.stride_units), __float_as_uint(w));
+                }
+                fill += __popcll(m);
             }
-            const unsigned long long m = __ballot(keep);
-            if (keep) {
-                const int k = kept_count(a.mode, (int)n, a.W);
-                const float w = v[q] * row_factor(a.norm, (int)n, k);
-                tile[fill + __popcll(m & below_me)] = make_uint2(K::make(r[q], a.stride_units), __float_as_uint(w));
+            if (fill > T - MAXC * kWaveSize) {        // the next pass might not fit: gather what is staged
+                wave_lds_fence();
+                consume_tile<G, CH, VEC, ALIGNED, WIDE>(tile, fill, e, E, a.X, a.ldx, cols, acc);
+                wave_lds_fence();
+                fill = 0;
             }
-            fill += __popcll(m);
         }
-    };
-    // One chunk where that holds the rest of the column: an absent one costs its instructions and
-    // branches.  Always 8, at five or six waves / this: 20 k rows of mean 4.5, F = 32: 17.5 / 11.8 us, 170 k of mean 14, F =
-    // 128: 133 / 110, 1 M of mean 50, ids that cluster, Bucket W = 32, F = 64: 999 / 727, 500 k of mean 200, F = 64: 1210 / 1199,
-    // 20 k of mean 300, F = 32: 37.5 / 38.1.
-    for (int j0 = 0; j0 < count;) {
-        const int left = count - j0;
-        const int chunks = MAXC == 8 && left > kPullChunks * kWaveSize ? 8 : left > kWaveSize ? kPullChunks : 1;
-        if (fill > T - chunks * kWaveSize) gather();
-        if (MAXC == 8 && chunks == 8) pass(j0, std::integral_constant<int, MAXC>{});
-        else if (chunks == 1) pass(j0, std::integral_constant<int, 1>{});
-        else pass(j0, std::integral_constant<int, kPullChunks>{});
-        j0 += chunks * kWaveSize;
+        wave_lds_fence();
+        consume_tile<G, CH, VEC, ALIGNED, WIDE>(tile, fill, e, E, a.X, a.ldx, cols, acc);
+    } else {
+        // as pull_needs_rows; written out, since through the function the kernel takes up to
+        // 4 registers more (56 k rows of mean 6, F = 71: 52.2 us, 51.1 this way)
+        const bool rotated = a.mode == ES_FASTRAND && a.seed != 0;
+        const bool need_rows = rotated || a.norm != ES_NORM_NONE;
+        int fill = 0;
+        auto gather = [&]() {
+            wave_lds_fence();
+            consume_tile<G, CH, VEC, ALIGNED, WIDE>(tile, fill, e, E, a.X, a.ldx, cols, acc);
+            wave_lds_fence();
+            fill = 0;
+        };
+        // chunks * 64 entries from j0 on: all their loads are issued before the first test, so
+        // that they cost two memory round trips
+        auto pass = [&](int j0, auto chunks) {
+            constexpr int C = decltype(chunks)::value;
+            int32_t r[C], pick[C];
+            float v[C];
+            bool valid[C];
+#pragma unroll
+            for (int q = 0; q < C; ++q) {
+                const int jj = j0 + q * kWaveSize + lane;
+                valid[q] = jj < count;
+                if (valid[q]) {
+                    const int64_t j = (int64_t)begin + jj;
+                    r[q] = t_row[j];
+                    v[q] = t_vals[j];
+                    pick[q] = a.mode == ES_BUCKET ? t_idx[j] : a.mode == ES_FASTRAND ? t_slot[j] : 0;
+                }
+            }
+            int2 info[C];
+#pragma unroll
+            for (int q = 0; q < C; ++q) {
+                // without rotation the pick is below n, so it decides alone, and only kept entries need their row
+                if (!rotated) valid[q] = valid[q] && (uint32_t)pick[q] < (uint32_t)a.W;
+                if (need_rows && valid[q]) info[q] = rows[r[q]];
+                else info[q] = make_int2(INT32_MAX, 0);
+            }
+#pragma unroll
+            for (int q = 0; q < C; ++q) {
+                const uint32_t n = (uint32_t)info[q].x;
+                bool keep = valid[q];
+                if (rotated) {
+                    int32_t slot = pick[q] - info[q].y;          // slot after rotation
+                    if (slot < 0) slot += (int32_t)n;
+                    keep = keep && (n <= (uint32_t)a.W || (uint32_t)slot < (uint32_t)a.W);
+                }
+                const unsigned long long m = __ballot(keep);
+                if (keep) {
+                    const int k = kept_count(a.mode, (int)n, a.W);
+                    const float w = v[q] * row_factor(a.norm, (int)n, k);
+                    tile[fill + __popcll(m & below_me)] = make_uint2(K::make(r[q], a.stride_units), __float_as_uint(w));
+                }
+                fill += __popcll(m);
+            }
+        };
+        // One chunk where that holds the rest of the column: an absent one costs its instructions and
+        // branches.  Always 8, at five or six waves / this: 20 k rows of mean 4.5, F = 32: 17.5 / 11.8 us, 170 k of mean 14, F =
+        // 128: 133 / 110, 1 M of mean 50, ids that cluster, Bucket W = 32, F = 64: 999 / 727, 500 k of mean 200, F = 64: 1210 / 1199,
+        // 20 k of mean 300, F = 32: 37.5 / 38.1.
+        for (int j0 = 0; j0 < count;) {
+            const int chunks = count - j0 > kWaveSize ? MAXC : 1;
+            if (fill > T - chunks * kWaveSize) gather();
+            if (chunks == 1) pass(j0, std::integral_constant<int, 1>{});
+            else pass(j0, std::integral_constant<int, MAXC>{});
+            j0 += chunks * kWaveSize;
+        }
+        wave_lds_fence();
+        consume_tile<G, CH, VEC, ALIGNED, WIDE>(tile, fill, e, E, a.X, a.ldx, cols, acc);
     }
-    wave_lds_fence();
-    consume_tile<G, CH, VEC, ALIGNED, WIDE>(tile, fill, e, E, a.X, a.ldx, cols, acc);
 
 #pragma unroll
     for (int m = G; m < kWaveSize; m <<= 1) {

@@ -648,8 +648,8 @@ int build_transposed(const int32_t* rowptr, const int32_t* colidx, const float* 
 //    100 k of mean 300, F = 41, W = 32: 0.83, F = 128: 0.07: 1.03; ids that cluster, 200 k of mean 300: 0.15: 1.06, 0.07: 1.1
 //  * mean 200: 0.20: 0.99, 0.10: 1.17; mean 100: 0.20: 1.2, 0.39: 1.2
 //  * 20 k rows of mean 480 (9.6 M entries) 0.83, of mean 300 (6 M) 1.01, 10 k of mean 300 (3 M) 1.08
-// The passes of es_pull_kernel hold 8 chunks from 128 entries a column on (4 / 8: mean 490, no rotation 717 / 703 us, 200 480 / 459,
-// 150 403 / 397, ids that cluster 396 / 385; 100: 222 / 236, ids that cluster, mean 90: 263 / 265).
+// The passes of es_pull_kernel hold 8 chunks from 96 entries a column on (8 / 4, us: mean 60, W = 8 147 / 133, mean 90, ids that
+// cluster 285 / 263, 110, Bucket W = 8 52.6 / 54.7, 150, W = 8 62.6 / 63.2 and rotated 414 / 403, 300, Bucket W = 8 33.7 / 44.3).
 bool pull_filtered(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, uint64_t seed)
 {
     if (mode != ES_FASTRAND || seed == 0 || N > kPullFilterRows || nnz < 8000000 || nnz < 256 * N) return false;
@@ -1024,7 +1024,7 @@ int es_spmm_backward_pull(const int32_t* rowptr, const int32_t* t_ptr, const int
     const uint32_t filter_lds = (uint32_t)(kPullTileBytes + (N + 7) / 8 * (int64_t)sizeof(uint32_t));
     const int64_t filter_blocks = (N + kPullWaves - 1) / kPullWaves;
     const dim3 filter_grid((uint32_t)(filter_blocks < kComputeUnits ? filter_blocks : kComputeUnits), (uint32_t)grid_y);
-    const bool long_columns = nnz >= 128 * N;               // see pull_filtered
+    const bool long_columns = nnz >= 96 * N;                // see pull_filtered
 #define ES_PULL_LAUNCH(G_, CH_, V_, A_, C_)                                                          \
     if (wide)                                                                                        \
         hipLaunchKernelGGL((es_pull_kernel<G_, CH_, V_, A_, true, C_>), grid, dim3(kBlockThreads), 0, st, a,    \
