@@ -31,7 +31,6 @@ constexpr int kBinRowBits = 22;                       // a record holds the row 
 constexpr int kBinMaxBlocks = 4096;                   // column blocks at most: 16 KB of counters per workgroup
 static_assert(kBinMaxBlocks == (1 << kBinRowBits) >> (32 - kBinRowBits), "the most rows, in blocks of the most columns");
 constexpr int kBinMaxW = 4096;                        // kept entries of a row at most: one workgroup walks them
-constexpr int64_t kBinMinRequests = 700000;           // requests of the scatter from which on this form is taken (plan_bins)
 constexpr int kBinWalkers = 256;                      // counting / filling workgroups at most
 
 struct BinArgs {

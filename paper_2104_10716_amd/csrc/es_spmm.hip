@@ -670,13 +670,31 @@ struct BinPlan {
 // multiplies no absent entries, so infinities in dY come out as from the scatter.
 constexpr es_launch_opts_t kBinProduct = {0, 0, 0, -1, 1};
 
+// Whether the scatter would send so many requests that sorting is the faster.  From 1.1 M on it is, counted on the
+// min(nnz, N W) entries that can be kept; below 0.7 M the two are level or the scatter is ahead.  Between
+// them the line is on the entries that are kept: nearly all of those where nnz and N W are far apart, half of
+// them in power-law rows whose mean is near W, so nnz N W / (nnz + N W) is asked for.  Time of this form over the scatter's, 2.5 k
+// to 700 k rows, W = 1 to 4096, by requests per entry and that estimate:
+//  * 2 (F <= 32): below 0.52 M 0.6 - 1.23 (90 k power-law rows, W = 4 of 4: 0.71 M at most 25.9 / 30.6 us, 62 k, W = 8: 0.88 M
+//    27.7 / 30.6), from there 0.51 - 0.99.  More rows than the walkers' threads (five launches instead of two): 0.98 - 1.145 up
+//    to 1.1 M (350 k rows, 0.70 M: 54.4 / 62.2).
+//  * 3 and 4: below 0.44 M 0.47 - 1.10 (26 k power-law rows, W = 8, F = 49: 0.74 M 25.4 / 28.1), from there 0.38 - 1.01
+//  * 5 and more: from 0.36 M on 0.32 - 0.95
+bool enough_requests(int64_t N, int64_t nnz, int32_t F, int32_t W)
+{
+    const int64_t per_entry = ((int64_t)F + 15) / 16;
+    const double most = (double)(nnz < N * W ? nnz : N * W) * (double)per_entry;
+    if (most >= 1.1e6) return true;
+    if (most < 0.7e6 || (per_entry <= 2 && N > (int64_t)kBinWalkers * kBinLocalRows)) return false;
+    const double stored = (double)nnz, bound = (double)N * (double)W;
+    return stored * bound / (stored + bound) * (double)per_entry >= (per_entry <= 2 ? 0.52e6 : per_entry <= 4 ? 0.44e6 : 0.36e6);
+}
+
 // Where the lines lie: the scatter moves one 64-byte request per kept entry and 16
 // columns, 20.5 G of them a second; this form takes some 20 us of launches and first
 // round trips, 0.03 us per 1000 kept entries to sort them, and the gather.  us, scatter / this:
-//  * kBinMinRequests, counted on min(nnz, N W) entries, power-law rows keep about half of them (a walker's entries
-//    in registers, 3.4 k to 140 k rows, F = 17 to 256): 0.20 - 0.30 M 13 - 19 / 19 - 25, 0.36 - 0.43 M 17 - 27 / 21 - 36, 0.47 - 0.58 M 18 - 35 / 20 - 38 (0.62 - 1.12
-//    of the time), 0.66 - 0.83 M 30 - 50 / 24 - 29, 0.91 - 1.12 M 30 - 60 / 22 - 54 (0.58 - 1.00).  F = 128: 170 k rows, 2.1 M entries at
-//    most 406 / 110; F = 64: 233 k, 14.9 M 2923 / 1048; a column that all rows hold, 20 k to 1 M rows: always this.
+//  * enough requests (enough_requests); F = 128: 170 k rows, 2.1 M entries at most 406 / 110; F = 64: 233 k, 14.9 M
+//    2923 / 1048; a column that all rows hold, 20 k to 1 M rows: always this.
 //  * F <= 16: with one request per entry the sort costs what it saves: 160 k, 2.0 M 60 / 66; 2.4 M rows,
 //    10.5 M 382 / 399; 160 k, 7.6 M 191 / 159.
 //  * rows longer than a line of 128 bytes of which few entries are kept: count and fill wait for
@@ -692,7 +710,7 @@ BinPlan plan_bins(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode)
     if (mode != ES_BUCKET && mode != ES_FASTRAND) return p;    // exact rows have no bound on their length
     if (W < 1 || W > kBinMaxW || F <= 16 || N < 1 || N > (1 << kBinRowBits) || nnz < 1 || nnz > INT32_MAX) return p;
     p.capacity = nnz < N * W ? nnz : N * W;
-    if (p.capacity * ((F + 15) / 16) < kBinMinRequests) return p;
+    if (!enough_requests(N, nnz, F, W)) return p;
     const double mean = (double)nnz / (double)N, row_requests = (double)W * ((F + 15) / 16);
     if (mean > 32.0 && mean > W && row_requests < (mode == ES_FASTRAND ? 5.0 + mean / 25.0 : 1.5 + mean / 46.0)) return p;
     // only where both the gather this form ends in (some million columns are more than its grid covers) and the

@@ -16,6 +16,19 @@ def test_workspace_is_asked_for_only_where_the_form_applies():
     assert ask(2 ** 22, 2 ** 24, 64, 16, "bucket") > 0 and ask(2 ** 22 + 1, 2 ** 24, 64, 16, "bucket") == 0
     assert ask(170_000, 2_370_240, 128, 4096, "bucket") > 0 and ask(170_000, 2_370_240, 128, 4097, "bucket") == 0
     assert ask(19_717, 88_000, 32, 16, "bucket") == 0                           # small: the scatter is the faster form
+    # 0.7 to 1.1 M requests: the line is on the entries that rows of any length law keep (half of min(nnz, N W) where the
+    # two are equal), by requests per entry, and above what two requests per entry repay once there are more rows than threads
+    for F, per_entry, need in ((17, 2, 0.52e6), (32, 2, 0.52e6), (33, 3, 0.44e6), (64, 4, 0.44e6), (65, 5, 0.36e6), (256, 16, 0.36e6)):
+        for N, W in ((1_500, 200), (10_000, 500), (40_000, 4), (90_000, 4), (262_144, 2)):
+            for nnz in [int(x * 1e6 / per_entry) for x in (0.69, 0.71, 0.75, 0.8, 0.9, 1.0, 1.09, 1.11)]:
+                most = min(nnz, N * W) * per_entry
+                kept = nnz * (N * W) / (nnz + N * W) * per_entry
+                taken = most >= 1.1e6 or (most >= 0.7e6 and kept >= need)
+                if nnz <= 32 * N or nnz <= N * W:                              # the rule for long rows has no say
+                    assert (ask(N, nnz, F, W, "bucket") > 0) == taken, (N, nnz, F, W)
+    assert ask(90_000, 360_000, 17, 4, "bucket") == 0 and ask(90_000, 360_000, 65, 4, "bucket") > 0       # 25.9 / 30.6 us at F = 17
+    assert ask(262_145, 500_000, 32, 4, "bucket") == 0 and ask(262_145, 500_000, 33, 4, "bucket") > 0
+    assert ask(262_145, 550_001, 32, 4, "bucket") > 0
     # few entries kept of long rows: requests per row (W times 2 at F = 32) against the mean row
     assert ask(233_000, 233_000 * 300, 32, 8, "fastrand") == 0 and ask(233_000, 233_000 * 300, 32, 9, "fastrand") > 0
     assert ask(233_000, 233_000 * 300, 32, 4, "bucket") == 0 and ask(233_000, 233_000 * 300, 32, 5, "bucket") > 0
