@@ -37,9 +37,10 @@ struct BinArgs {
     const int32_t* rowptr;
     const int32_t* colidx;
     const float* vals;
-    uint2* records;            // [capacity]
-    int32_t* counts;           // [walkers x nbins]: records of walker i in block b, then of all walkers before it
-    int32_t* base;             // [nbins + 1]: first record of block b
+    uint2* records;            // [capacity]; one launch for the first level: a piece for each walker's own
+    int32_t* counts;           // [walkers x nbins]: records of walker i in block b, then of all walkers before it;
+                               // one launch: [walkers x (nbins + 1)]: walker i's records of all blocks before b
+    int32_t* base;             // [nbins + 1]: first record of block b; one launch: [walkers]: first record of walker i
     int32_t* t_ptr;            // [N + 1], t_row and t_val [capacity]: the transposed sampled graph
     int32_t* t_row;
     float* t_val;
@@ -93,6 +94,10 @@ __global__ void __launch_bounds__(kBinLocalRows) es_bin_local_kernel(const BinAr
     const int tid = threadIdx.x;
     for (int b = tid; b <= a.nbins; b += kBinLocalRows) counter[b] = 0;
     const int64_t r_begin = a.N * blockIdx.x / a.walkers, r_end = a.N * (blockIdx.x + 1) / a.walkers;
+    // The walker's own records: what the rows before a row keep is at most what they store and W each, and so
+    // is what the walker's rows keep between the two ends.  (An nnz below rowptr[N] cuts entries off.)
+    const auto piece = [&](int64_t row) { return (int32_t)max((int64_t)0, min(min((int64_t)a.rowptr[row], row * a.W), a.capacity)); };
+    const int32_t own = piece(r_begin), room = max(0, piece(r_end) - own);
     const int64_t r = r_begin + tid;
     int32_t k = 0;
     if (r < r_end) {
@@ -108,6 +113,7 @@ __global__ void __launch_bounds__(kBinLocalRows) es_bin_local_kernel(const BinAr
     }
     int32_t total;
     first[tid] = block_scan<kBinLocalRows>(k, wave_total, total) - k;
+    total = min(total, room);
     __syncthreads();
     // this thread's entries: row and column inside the block, value; block | rank << 12
     uint32_t key[kBinLocalPer], place[kBinLocalPer];
@@ -159,9 +165,12 @@ __global__ void __launch_bounds__(kBinLocalRows) es_bin_local_kernel(const BinAr
         }
         at += mine[i];
     }
-    if (tid == 0) out[a.nbins] = all;
+    if (tid == 0) {
+        out[a.nbins] = all;
+        a.base[blockIdx.x] = own;
+    }
     __syncthreads();
-    uint2* records = a.records + r_begin * a.W;       // the walker's own: at most W per row
+    uint2* records = a.records + own;
 #pragma unroll
     for (int m = 0; m < kBinLocalPer; ++m)
         if (tid + m * kBinLocalRows < total)
@@ -354,6 +363,7 @@ __global__ void __launch_bounds__(kBlockThreads) es_bin_sort_kernel(const BinArg
     uint32_t shift = 0;                               // from there to the records' numbers
     if constexpr (LOCAL) {
         int32_t from = 0, n = 0;
+        const int32_t own = a.base[min(tid, a.walkers - 1)];          // ahead of the counts, a line each: behind them 19.6 us, 18.6 here
         if (tid < a.walkers) {
             const int32_t* c = a.counts + (int64_t)tid * (a.nbins + 1) + blockIdx.x;
             from = c[0];
@@ -362,7 +372,7 @@ __global__ void __launch_bounds__(kBlockThreads) es_bin_sort_kernel(const BinArg
         int32_t before, total;                        // records of all blocks before this one, and of this one
         block_scan<kBlockThreads>(from, wave_total, before);
         piece[tid] = block_scan<kBlockThreads>(n, wave_total, total) - n;
-        where[tid] = (int32_t)(a.N * tid / a.walkers * a.W) + from - piece[tid];
+        where[tid] = own + from - piece[tid];
         begin = (uint32_t)min((int64_t)before, a.capacity);
         end = (uint32_t)min((int64_t)before + total, a.capacity);
         shift = begin;

@@ -727,9 +727,9 @@ BinPlan plan_bins(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode)
     const auto take = [&p](size_t bytes) { const size_t at = p.bytes; p.bytes += (bytes + 255) / 256 * 256; return at; };
     const int64_t walker_rows = (N + p.walkers - 1) / p.walkers;
     p.local = walker_rows <= kBinLocalRows && walker_rows * W <= (int64_t)kBinLocalRows * kBinLocalPer;
-    p.records = take((size_t)(p.local ? N * W : p.capacity) * sizeof(uint2));       // local: W places per row
-    p.counts = take((size_t)p.walkers * (p.nbins + 1) * sizeof(int32_t));
-    p.base = take((size_t)(p.nbins + 1) * sizeof(int32_t));
+    p.records = take((size_t)p.capacity * sizeof(uint2));
+    p.counts = take((size_t)p.walkers * (p.local ? p.nbins + 1 : p.nbins) * sizeof(int32_t));
+    p.base = take((size_t)(p.local ? p.walkers : p.nbins + 1) * sizeof(int32_t));
     p.t_ptr = take((size_t)(N + 1) * sizeof(int32_t));
     p.t_row = take((size_t)p.capacity * sizeof(int32_t));
     p.t_val = take((size_t)p.capacity * sizeof(float));

@@ -40,6 +40,21 @@ def test_workspace_is_asked_for_only_where_the_form_applies():
         assert ask(*bad, "bucket") == 0
 
 
+def test_workspace_grows_with_the_entries_kept():
+    """16 bytes for each of the min(nnz, N W) entries that can be kept, the counters and the column pointers: no more in
+    the one-launch form of the first level, where W may be far above the mean row."""
+    ask = es.es_spmm_backward_workspace_bytes
+    for N, nnz, F, W in ((16_000, 72_000, 256, 256), (16_000, 240_000, 256, 256), (16_384, 16_384 * 300, 64, 256), (170_000, 2_370_240, 128, 16),
+                         (262_144, 262_144 * 5, 32, 16), (1_000, 200_000, 512, 256), (511, 150_000, 256, 200), (65, 4_000, 9_000, 64),
+                         (262_145, 262_145 * 5, 32, 16), (40_000, 400_000, 64, 4_096)):
+        width = 1
+        while width < 1024 and N // (2 * width) >= 1024:
+            width *= 2
+        blocks, walkers = -(-N // width), min(256, -(-N // 64))
+        most = 16 * min(nnz, N * W) + 4 * (walkers * blocks + blocks + 1 + N + 1) + 6 * 255
+        assert 16 * min(nnz, N * W) < ask(N, nnz, F, W, "bucket") <= most, (N, nnz, F, W)
+
+
 def _graph(N, avg, seed, F, ldx=None, hot=None, long_row=0):
     from workloads import random_csr
     rowptr, colidx = random_csr(N, avg, seed, empty_frac=0.05)
@@ -112,6 +127,31 @@ def test_backward_through_a_workspace(N, avg, F, ldx, mode, W, seed, norm, extra
     (131_073, 40.0, 20, None, "fastrand", 33, 77, "rsqrt", {})])
 def test_backward_through_a_workspace_around_what_a_walker_holds(N, avg, F, ldx, mode, W, seed, norm, extra):
     test_backward_through_a_workspace(N, avg, F, ldx, mode, W, seed, norm, extra)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,avg,F,mode,W,more", [
+    (16_384, 4.5, 256, "fastrand", 256, 0), (16_384, 4.5, 256, "fastrand", 256, 977_777),      # rows far shorter than W
+    (30_000, 60.0, 41, "bucket", 16, 0), (30_000, 60.0, 41, "bucket", 16, 5), (262_144, 3.0, 20, "bucket", 5, 0),
+    (16_385, 4.5, 256, "fastrand", 256, 0)])                                                   # more than a walker holds
+def test_backward_workspace_is_not_written_beyond_its_size(N, avg, F, mode, W, more):
+    """A walker's records lie where its rows' entries can at most begin; nnz (the length of colidx) may be more
+    than rowptr[N]."""
+    import torch
+    from gpu_util import DeviceCSR, check_Y
+    import oracle
+    rowptr, colidx, vals, dY = _graph(N, avg, N + F, F, long_row=3_000)
+    nnz = colidx.size + more
+    nbytes = es.es_spmm_backward_workspace_bytes(N, nnz, F, W, mode)
+    assert nbytes > 0
+    d = DeviceCSR(rowptr, colidx, vals, dY)
+    longer, values = (torch.cat([t, t.new_zeros(more)]) for t in (d.colidx, d.vals))
+    whole = torch.full((nbytes // 4 + 4_096,), -7, dtype=torch.int32, device="cuda:0")
+    dX = torch.full((N, F), float("nan"), dtype=torch.float32, device="cuda:0")
+    es.es_spmm_backward_ws(d.rowptr, longer, values, d.X, dX, W, mode, 5, "none", whole[:nbytes // 4])
+    torch.cuda.synchronize()
+    assert bool((whole[nbytes // 4:] == -7).all()) and not bool((whole[:nbytes // 4] == -7).all())
+    check_Y(dX.cpu().numpy(), *oracle.spmm_backward(rowptr, colidx, vals, dY, F, W, mode, 5), f"N={N} W={W} nnz + {more}")
 
 
 @pytest.mark.gpu
