@@ -641,21 +641,26 @@ int build_transposed(const int32_t* rowptr, const int32_t* colidx, const float* 
                      int32_t* out_end, int32_t* out_idx, float* out_vals, int32_t* out_pos, void* stream);
 
 // Whether the pull backward tests entries against the rows' bits in LDS before it looks their rows up
-// (es_pull_filtered_kernel).  That spares most of the lookups, 3.8 ps each, but holds only 16 waves per compute
-// unit, which gather less at a time: columns have to be long and the kept entries' rows of dY few.  Time over
-// that of es_pull_kernel, both on one graph, against mean / (min(W, mean) F):
-//  * 233 k rows of mean 490: 0.48 (W = 16, F = 64): 0.62, 0.24: 0.70, 0.12 (W = 64, F = 64 and W = 128, F = 32): 0.89, 0.06: 1.08;
-//    100 k of mean 300, F = 41, W = 32: 0.83, F = 128: 0.07: 1.03; ids that cluster, 200 k of mean 300: 0.15: 1.06, 0.07: 1.1
-//  * mean 200: 0.20: 0.99, 0.10: 1.17; mean 100: 0.20: 1.2, 0.39: 1.2
-//  * 20 k rows of mean 480 (9.6 M entries) 0.83, of mean 300 (6 M) 1.01, 10 k of mean 300 (3 M) 1.08
-// The passes of es_pull_kernel hold 8 chunks from 96 entries a column on (8 / 4, us: mean 60, W = 8 147 / 133, mean 90, ids that
-// cluster 285 / 263, 110, Bucket W = 8 52.6 / 54.7, 150, W = 8 62.6 / 63.2 and rotated 414 / 403, 300, Bucket W = 8 33.7 / 44.3).
+// (es_pull_filtered_kernel).  That spares most of the lookups, but holds only 16 waves per compute unit, which gather less
+// at a time: columns have to be long, the kept entries' rows of dY few, and the table of lookups beyond an L2's reach
+// also where ids cluster, which sizes do not show.  Time over that of es_pull_kernel, uniform ids / ids that cluster, by
+// `gathered`, the columns of dY a mean row's kept entries gather, as a share of the mean (columns of dX that tile no line cost another one):
+//  * 8 to 50 M entries: 0.61 - 1.06 / 0.81 - 1.36 (40 k rows of mean 310: 1.15 - 1.36, 60 k of 290: 0.96 - 1.36, 100 k of 268: 0.93 - 1.19,
+//    150 k of 264: 0.87 - 1.14), so never: 90 k uniform rows of mean 485 would take 0.61 - 0.9 there
+//  * from 50 M on, mean 257 to 280: 0.75 - 1.1 / 0.82 - 1.13; mean 300 to 350: up to 8 a mean entry 0.8 - 0.9 / 0.78 - 0.98, 8 to 9
+//    0.8 - 0.95 / 0.88 - 1.05; mean 370 and more: up to 9.1 0.61 - 0.95 / 0.73 - 0.98, 9.1 to 12 0.8 - 1.0 / 0.91 - 1.01, beyond 0.85 - 1.09 / 0.96 - 1.14
+//  * F = 3: 0.77 - 1.08, F = 8 0.64 - 1.01, from 16 on at most 0.98 (1328 calls, F up to 1300)
 bool pull_filtered(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, uint64_t seed)
 {
-    if (mode != ES_FASTRAND || seed == 0 || N > kPullFilterRows || nnz < 8000000 || nnz < 256 * N) return false;
-    const double mean = (double)nnz / (double)N, kept = mean < W ? mean : W;
-    return mean >= 0.11 * kept * (F % 32 ? F + 31 : F);       // rows that tile no line cost another one (F = 41: 1.07 at 0.15)
+    if (mode != ES_FASTRAND || seed == 0 || N > kPullFilterRows || F < 8 || nnz < 50000000) return false;
+    const double mean = (double)nnz / (double)N;
+    const double gathered = (mean < W ? mean : W) * (F % 32 ? (double)F + 31.0 : (double)F);
+    return gathered <= 28.0 * (mean - 270.0) && 0.11 * gathered <= mean;
 }
+
+// Entries a column from which the passes of es_pull_kernel hold 8 chunks (8 / 4, us: mean 60, W = 8 147 / 133, mean 90, ids that
+// cluster 285 / 263, 110, Bucket W = 8 52.6 / 54.7, 150, W = 8 62.6 / 63.2 and rotated 414 / 403, 300, Bucket W = 8 33.7 / 44.3).
+constexpr int64_t kPullLongColumn = 96;
 
 // Layout of the binned transposed product's workspace (es_bin_kernel.h); bytes == 0:
 // the scatter is the faster form, or this one does not apply.
@@ -1042,7 +1047,7 @@ int es_spmm_backward_pull(const int32_t* rowptr, const int32_t* t_ptr, const int
     const uint32_t filter_lds = (uint32_t)(kPullTileBytes + (N + 7) / 8 * (int64_t)sizeof(uint32_t));
     const int64_t filter_blocks = (N + kPullWaves - 1) / kPullWaves;
     const dim3 filter_grid((uint32_t)(filter_blocks < kComputeUnits ? filter_blocks : kComputeUnits), (uint32_t)grid_y);
-    const bool long_columns = nnz >= 96 * N;                // see pull_filtered
+    const bool long_columns = nnz >= kPullLongColumn * N;
 #define ES_PULL_LAUNCH(G_, CH_, V_, A_, C_)                                                          \
     if (wide)                                                                                        \
         hipLaunchKernelGGL((es_pull_kernel<G_, CH_, V_, A_, true, C_>), grid, dim3(kBlockThreads), 0, st, a,    \

@@ -734,14 +734,37 @@ def test_backward_pull_row_lengths_that_change_the_multiplier(es):
     check_backward_pull_against_oracle(d, t, 64, "bucket", 0, what="pull multipliers bucket")
 
 
-@pytest.mark.parametrize("F,W", [(16, 1), (16, 3), (32, 8), (41, 4), (3, 64), (16, 65), (3, 90), (260, 2)])
-def test_backward_pull_with_rows_bits_in_lds(es, F, W):
-    """The pull backward where a rotated FastRand's entries are tested against four bits per row first
-    (columns of some 370 entries, 9 M in all): rows of at most W entries, a little longer ones, windows
-    that wrap, rows far longer than sixteen steps; a row count that fills no word and no workgroup, an
-    empty column, and a column longer than several passes."""
+def _pull(es, d, t, dX, W, mode="fastrand", seed=7, norm="none", nnz=None):
+    """es_spmm_backward_pull with an nnz of the caller's: a hint, by which the kernel is chosen."""
     import torch
-    from gpu_util import DeviceCSR, check_backward_pull_against_oracle
+    from paper_2104_10716_amd import binding
+    rc = es.load_library().es_spmm_backward_pull(
+        d.rowptr.data_ptr(), *(t[k].data_ptr() for k in ("t_ptr", "t_row", "t_idx", "t_slot", "t_vals", "t_pinv", "t_rows")),
+        d.X.data_ptr(), dX.data_ptr(), d.N, t["t_row"].numel() if nnz is None else nnz, d.F, d.X.stride(0), dX.stride(0), W,
+        binding.MODES[mode], seed, binding.NORMS[norm], torch.cuda.current_stream().cuda_stream or None)
+    assert rc == 0
+
+
+def _kernels(call):
+    """Names of this library's kernels that `call` launches."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    return " ".join(e.name for e in p.events() if "es_" in e.name)
+
+
+@pytest.mark.parametrize("F,W", [(16, 1), (16, 3), (32, 8), (41, 4), (3, 64), (16, 65), (3, 90), (260, 2), (131, 5), (255, 33), (512, 2),
+                                 (700, 3), (1030, 1)])
+def test_backward_pull_with_rows_bits_in_lds(es, F, W):
+    """The pull backward where a rotated FastRand's entries are tested against four bits per row first:
+    rows of at most W entries, a little longer ones, windows that wrap, rows far longer than sixteen steps; a row
+    count that fills no word and no workgroup, an empty column, and a column longer than several passes; rows of 64 lanes
+    that are not aligned, two and four column chunks per lane, a second column block."""
+    import torch
+    import oracle
+    from gpu_util import DeviceCSR, check_Y
     N = 24_003
     rng = np.random.default_rng(F * 1000 + W)
     lens = rng.choice([0, 1, 2, 3, 4, 8, 63, 64, 65, 66, 99, 101, 128, 200, 400, 700, 1500], size=N).astype(np.int64)
@@ -749,34 +772,85 @@ def test_backward_pull_with_rows_bits_in_lds(es, F, W):
     lens[:40] = [W, W + 1, 2 * W, 2 * W + 1, 16 * W] * 8
     rows = np.repeat(np.arange(N), lens)
     cols = rng.integers(1, N, rows.size)                           # column 0 stays empty
-    cols[rng.random(rows.size) < 0.0005] = 5                       # a column of some 4000 entries
-    rows = np.concatenate([rows, np.repeat(np.arange(N), 130)])
-    cols = np.concatenate([cols, rng.integers(1, N, N * 130)])
-    order = np.lexsort((cols, rows))
-    rows, cols = rows[order], cols[order]
-    first = np.ones(rows.size, dtype=bool)
-    first[1:] = (rows[1:] != rows[:-1]) | (cols[1:] != cols[:-1])
-    rows, cols = rows[first], cols[first]
+    cols[rng.random(rows.size) < 0.0005] = 5                       # a column of some 2000 entries
+    key = np.unique(rows * N + cols)
     rowptr = np.zeros(N + 1, dtype=np.int32)
-    rowptr[1:] = np.cumsum(np.bincount(rows, minlength=N))
-    colidx = cols.astype(np.int32)
-    assert colidx.size >= max(8_000_000, 256 * N)
+    rowptr[1:] = np.cumsum(np.bincount(key // N, minlength=N))
+    colidx = (key % N).astype(np.int32)
+    kept = np.diff(rowptr)
+    in_column = np.bincount(colidx, minlength=N)
+    assert (kept <= W).any() and (kept > 16 * W).any() and in_column[0] == 0 and in_column[5] > 1_000
     vals = rng.standard_normal(colidx.size).astype(np.float32)
     dY = rng.uniform(-1, 1, (N, F)).astype(np.float32)
     d = DeviceCSR(rowptr, colidx, vals, dY)
     t = es.es_spmm_transpose_graph(d.rowptr, d.colidx, d.vals)
-    for seed, norm in ((7, "none"), (2 ** 63 + 5, "rescale")):
-        check_backward_pull_against_oracle(d, t, W, "fastrand", seed, norm, what=f"bits F={F} W={W} seed={seed} {norm}")
-    a, b = (torch.empty((N, F), dtype=torch.float32, device="cuda:0") for _ in range(2))
-    es.es_spmm_backward_pull(d.rowptr, t, d.X, a, W, "fastrand", 7)
+    a, b = (torch.full((N, F), float("nan"), dtype=torch.float32, device="cuda:0") for _ in range(2))
+    hint = 2_000_000_000 if F >= 8 else None                       # the widths below stay with es_pull_kernel
+    taken = _kernels(lambda: _pull(es, d, t, a, W, nnz=hint))
+    assert ("es_pull_filtered_kernel" in taken) == (F >= 8), taken
+    for seed, norm in ((2 ** 63 + 5, "rescale"), (7, "none")):
+        a.fill_(float("nan"))
+        _pull(es, d, t, a, W, seed=seed, norm=norm, nnz=hint)
+        torch.cuda.synchronize()
+        ref, den = oracle.spmm_backward(rowptr, colidx, vals, dY, F, W, "fastrand", seed, norm=norm)
+        check_Y(a.cpu().numpy(), ref, den, f"bits F={F} W={W} seed={seed} {norm}")
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
-        es.es_spmm_backward_pull(d.rowptr, t, d.X, b, W, "fastrand", 7)
+        _pull(es, d, t, b, W, nnz=hint)
     for _ in range(3):
         b.fill_(float("nan"))
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("N", [1, 3, 8, 17, 4_097])
+def test_backward_pull_with_rows_bits_in_lds_on_few_rows(es, N):
+    import torch
+    import oracle
+    from gpu_util import DeviceCSR, check_Y
+    F, W = 20, 2
+    rng = np.random.default_rng(N)
+    key = np.unique(np.repeat(np.arange(N), 9) * N + rng.integers(0, N, 9 * N))
+    rowptr = np.zeros(N + 1, dtype=np.int32)
+    rowptr[1:] = np.cumsum(np.bincount(key // N, minlength=N))
+    colidx = (key % N).astype(np.int32)
+    vals = rng.standard_normal(colidx.size).astype(np.float32)
+    dY = rng.uniform(-1, 1, (N, F)).astype(np.float32)
+    d = DeviceCSR(rowptr, colidx, vals, dY)
+    t = es.es_spmm_transpose_graph(d.rowptr, d.colidx, d.vals)
+    dX = torch.full((N, F), float("nan"), dtype=torch.float32, device="cuda:0")
+    _pull(es, d, t, dX, W, nnz=2_000_000_000)
+    torch.cuda.synchronize()
+    check_Y(dX.cpu().numpy(), *oracle.spmm_backward(rowptr, colidx, vals, dY, F, W, "fastrand", 7), f"bits N={N}")
+
+
+@pytest.mark.parametrize("N,nnz,F,W,mode,seed,filtered", [
+    (233_000, 113_000_000, 64, 64, "fastrand", 7, True), (233_000, 113_000_000, 64, 64, "fastrand", 0, False),
+    (233_000, 113_000_000, 64, 64, "bucket", 7, False),
+    # 50 M entries; fewer were 1.05 to 1.36 times as slow where ids cluster
+    (150_000, 50_000_000, 64, 16, "fastrand", 7, True), (150_000, 49_999_999, 64, 16, "fastrand", 7, False),
+    (40_000, 12_400_000, 16, 20, "fastrand", 7, False), (100_000, 33_900_000, 32, 16, "fastrand", 7, False),
+    # gathered columns: 28 a mean entry above 270, and the mean over 0.11
+    (200_000, 60_000_000, 16, 17, "fastrand", 7, True), (200_000, 60_000_000, 16, 18, "fastrand", 7, False),
+    (200_000, 56_000_000, 64, 16, "fastrand", 7, False),
+    (244_000, 244_000 * 490, 64, 69, "fastrand", 7, True), (244_000, 244_000 * 490, 64, 70, "fastrand", 7, False),
+    (244_000, 244_000 * 490, 41, 61, "fastrand", 7, True), (244_000, 244_000 * 490, 41, 62, "fastrand", 7, False),
+    (150_000, 70_000_000, 8, 16, "fastrand", 7, True), (150_000, 70_000_000, 7, 16, "fastrand", 7, False),
+    # rows whose bits fit
+    (245_760, 110_000_000, 32, 16, "fastrand", 7, True), (245_761, 110_000_000, 32, 16, "fastrand", 7, False)])
+def test_backward_pull_filter_rule(es, N, nnz, F, W, mode, seed, filtered):
+    """Where the entries are tested against the rows' bits: by sizes alone, so an almost empty graph shows it."""
+    import torch
+    from gpu_util import DeviceCSR
+    rowptr = np.zeros(N + 1, dtype=np.int32)
+    rowptr[1:] = np.minimum(np.arange(1, N + 1), 100)
+    d = DeviceCSR(rowptr, np.arange(100, dtype=np.int32), np.ones(100, dtype=np.float32), np.ones((N, F), dtype=np.float32))
+    t = es.es_spmm_transpose_graph(d.rowptr, d.colidx, d.vals)
+    dX = torch.full((N, F), float("nan"), dtype=torch.float32, device="cuda:0")
+    taken = _kernels(lambda: _pull(es, d, t, dX, W, mode, seed, nnz=nnz))
+    assert ("es_pull_filtered_kernel" in taken) == filtered and ("es_pull_kernel" in taken) != filtered, taken
+    assert bool((dX[:100] == 1).all()) and not bool(dX[100:].any())
 
 
 def test_backward_pull_full_size(es):
