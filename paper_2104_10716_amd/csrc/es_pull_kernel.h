@@ -115,11 +115,12 @@ constexpr int kPullChunks = 4;                        // chunks of 64 entries re
 // stage 2 is the forward kernel's gather.
 // MAXC: chunks of 64 entries requested together at most.  Long columns (8) stream: a pass loads all of its chunks without a
 // branch, an absent entry as the column's first.  Short ones (4) wait for one round trip after another: six waves per SIMD
-// (five, four with two and four column chunks per lane, one less where rows of 64 lanes are not aligned, which would spill),
+// (five, four with two and four column chunks per lane, one less where rows of 64 lanes are not aligned or
+// the keys of fewer lanes have 64 bits, which would spill),
 // one chunk where that holds the column, and only entries that are there are loaded.  The latter on long columns: 50 k rows of
 // mean 300, F = 32, Bucket W = 8: 33.7 us, 44.3 with it.
 template <int G, int CH, int VEC, bool ALIGNED, bool WIDE, int MAXC>
-__global__ void __launch_bounds__(kBlockThreads, MAXC == 8 ? 0 : (CH == 1 ? 6 : CH == 2 ? 5 : 4) - (G == 64 && !ALIGNED))
+__global__ void __launch_bounds__(kBlockThreads, MAXC == 8 ? 0 : (CH == 1 ? 6 : CH == 2 ? 5 : 4) - (G == 64 && !ALIGNED) - (G < 64 && WIDE))
 es_pull_kernel(const Args a, const int32_t* __restrict__ t_ptr, const int32_t* __restrict__ t_row,
                const int32_t* __restrict__ t_idx, const int32_t* __restrict__ t_slot,
                const float* __restrict__ t_vals, const int2* __restrict__ rows)
