@@ -115,12 +115,21 @@ constexpr int kPullChunks = 4;                        // chunks of 64 entries re
 // stage 2 is the forward kernel's gather.
 // MAXC: chunks of 64 entries requested together at most.  Long columns (8) stream: a pass loads all of its chunks without a
 // branch, an absent entry as the column's first.  Short ones (4) wait for one round trip after another: six waves per SIMD
-// (five, four with two and four column chunks per lane, one less where rows of 64 lanes are not aligned or
-// the keys of fewer lanes have 64 bits, which would spill),
-// one chunk where that holds the column, and only entries that are there are loaded.  The latter on long columns: 50 k rows of
-// mean 300, F = 32, Bucket W = 8: 33.7 us, 44.3 with it.
+// (five with 64-bit keys, five to three on 64 lanes, below which the form spills, and a spill costs 1.1 to 1.6 times
+// the time), one chunk where that holds the column, and only entries that are there are loaded.  The latter on long columns: 50 k
+// rows of mean 300, F = 32, Bucket W = 8: 33.7 us, 44.3 with it.
+// The two are written out, for one body with both needs 80 to 128 registers where the streaming form of 64 lanes has 72.
+// Always 8 / the short form, mean of less than 96 entries, over 17 graphs of 3 k to 1 M rows: 4 to 32 lanes, F = 3 to 128, 0.59 - 1.03 of
+// the time (uniform ids of mean 20, F = 100: the 1.03); 20 k rows of mean 4.5, F = 32: 17.5 / 11.8 us, 170 k of mean 14, F =
+// 128: 133 / 110, 1 M of mean 50, ids that cluster, Bucket W = 32, F = 64: 999 / 727.  64 lanes have fewer waves for it: rows that are
+// not aligned, rotated, 0.84 - 1.02 (F = 131 to 701), four chunks per lane 0.95 - 1.01; else 0.93 - 1.06 (F = 131, 170 k of mean 14, no
+// rotation 117.5 / 123.4, 40 k of mean 90, ids that cluster 41.1 / 43.8), aligned 0.95 - 1.06 (F = 256, 170 k of mean 14: 174.9 / 180.6), so
+// those stream.
+template <int G, int CH, bool ALIGNED>
+__host__ __device__ constexpr bool pull_short_form(bool rotated) { return G < 64 || (!ALIGNED && (rotated || CH == 4)); }
+
 template <int G, int CH, int VEC, bool ALIGNED, bool WIDE, int MAXC>
-__global__ void __launch_bounds__(kBlockThreads, MAXC == 8 ? 0 : (CH == 1 ? 6 : CH == 2 ? 5 : 4) - (G == 64 && !ALIGNED) - (G < 64 && WIDE))
+__global__ void __launch_bounds__(kBlockThreads, MAXC == 8 ? 0 : G < 64 ? 6 - WIDE : CH == 1 ? 5 : CH == 2 ? 4 : 3)
 es_pull_kernel(const Args a, const int32_t* __restrict__ t_ptr, const int32_t* __restrict__ t_row,
                const int32_t* __restrict__ t_idx, const int32_t* __restrict__ t_slot,
                const float* __restrict__ t_vals, const int2* __restrict__ rows)
@@ -157,8 +166,6 @@ es_pull_kernel(const Args a, const int32_t* __restrict__ t_ptr, const int32_t* _
     if constexpr (MAXC == 8) {
         // MAXC * 64 entries per pass: all their loads are issued before the
         // first test, so that one pass costs two memory round trips, not sixteen
-        // as pull_needs_rows; written out, since through the function the kernel takes up to
-        // 4 registers more (56 k rows of mean 6, F = 71: 52.2 us, 51.1 this way)
         const bool need_rows = (a.mode == ES_FASTRAND && a.seed != 0) || a.norm != ES_NORM_NONE;
         int fill = 0;
         for (int j0 = 0; j0 < count; j0 += MAXC * kWaveSize) {
@@ -259,10 +266,7 @@ es_pull_kernel(const Args a, const int32_t* __restrict__ t_ptr, const int32_t* _
                 fill += __popcll(m);
             }
         };
-        // One chunk where that holds the rest of the column: an absent one costs its instructions and
-        // branches.  Always 8, at five or six waves / this: 20 k rows of mean 4.5, F = 32: 17.5 / 11.8 us, 170 k of mean 14, F =
-        // 128: 133 / 110, 1 M of mean 50, ids that cluster, Bucket W = 32, F = 64: 999 / 727, 500 k of mean 200, F = 64: 1210 / 1199,
-        // 20 k of mean 300, F = 32: 37.5 / 38.1.
+        // one chunk where that holds the rest of the column: an absent one costs its instructions and branches
         for (int j0 = 0; j0 < count;) {
             const int chunks = count - j0 > kWaveSize ? MAXC : 1;
             if (fill > T - chunks * kWaveSize) gather();

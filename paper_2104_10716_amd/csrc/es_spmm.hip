@@ -642,14 +642,15 @@ int build_transposed(const int32_t* rowptr, const int32_t* colidx, const float* 
 
 // Whether the pull backward tests entries against the rows' bits in LDS before it looks their rows up
 // (es_pull_filtered_kernel).  That spares most of the lookups, but holds only 16 waves per compute unit, which gather less
-// at a time: columns have to be long, the kept entries' rows of dY few, and the table of lookups beyond an L2's reach
-// also where ids cluster, which sizes do not show.  Time over that of es_pull_kernel, uniform ids / ids that cluster, by
-// `gathered`, the columns of dY a mean row's kept entries gather, as a share of the mean (columns of dX that tile no line cost another one):
-//  * 8 to 50 M entries: 0.61 - 1.06 / 0.81 - 1.36 (40 k rows of mean 310: 1.15 - 1.36, 60 k of 290: 0.96 - 1.36, 100 k of 268: 0.93 - 1.19,
-//    150 k of 264: 0.87 - 1.14), so never: 90 k uniform rows of mean 485 would take 0.61 - 0.9 there
-//  * from 50 M on, mean 257 to 280: 0.75 - 1.1 / 0.82 - 1.13; mean 300 to 350: up to 8 a mean entry 0.8 - 0.9 / 0.78 - 0.98, 8 to 9
-//    0.8 - 0.95 / 0.88 - 1.05; mean 370 and more: up to 9.1 0.61 - 0.95 / 0.73 - 0.98, 9.1 to 12 0.8 - 1.0 / 0.91 - 1.01, beyond 0.85 - 1.09 / 0.96 - 1.14
-//  * F = 3: 0.77 - 1.08, F = 8 0.64 - 1.01, from 16 on at most 0.98 (1328 calls, F up to 1300)
+// at a time: columns have to be long, the columns of dY that a mean row's kept entries gather (`gathered`; rows that tile no line
+// cost another one) few, and the lookups' table beyond what an L2 serves also where ids cluster, which sizes do not
+// show.  Time over that of es_pull_kernel, uniform ids / ids that cluster, 0.11 gathered <= mean unless said:
+//  * 8 to 50 M entries: 0.61 - 1.06 / 0.85 - 1.38 (40 k rows of mean 310: 1.15 - 1.36, 60 k of 290: 0.96 - 1.36, 100 k of 268: 0.93 - 1.19,
+//    150 k of 264: 0.87 - 1.14), so never, though 90 k uniform rows of mean 485 would take 0.61 - 0.84
+//  * from 50 M on, mean 257 to 280: 0.73 - 0.99 / 0.81 - 1.05, 281 to 300: 0.77 - 0.96 / 0.80 - 1.01; 300 to 370, ids that cluster, gathered up to 6
+//    a mean entry 0.76 - 1.00, 6 to 9.1 0.81 - 1.05; 370 and more 0.61 - 0.95 / 0.73 - 1.00; gathered 9.1 to 12 a mean entry 0.80 - 1.11 / 0.87 - 1.12
+//    whatever the mean, more 0.83 - 1.14 / 0.96 - 1.14
+//  * F = 3: 0.77 - 1.08; where the lines below hold, F = 8: 0.64 - 1.01, F = 16 to 1300 0.61 - 0.98 (1344 calls)
 bool pull_filtered(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, uint64_t seed)
 {
     if (mode != ES_FASTRAND || seed == 0 || N > kPullFilterRows || F < 8 || nnz < 50000000) return false;
@@ -661,6 +662,50 @@ bool pull_filtered(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, u
 // Entries a column from which the passes of es_pull_kernel hold 8 chunks (8 / 4, us: mean 60, W = 8 147 / 133, mean 90, ids that
 // cluster 285 / 263, 110, Bucket W = 8 52.6 / 54.7, 150, W = 8 62.6 / 63.2 and rotated 414 / 403, 300, Bucket W = 8 33.7 / 44.3).
 constexpr int64_t kPullLongColumn = 96;
+
+struct PullGraph {
+    const int32_t *ptr, *row, *idx, *slot;
+    const float* vals;
+    const int2* rows;                  // this call's (length, rotation) per row of A
+};
+
+template <int G, int CH, int VEC, bool ALIGNED, int MAXC>
+void launch_pull_passes(const Args& a, const PullGraph& t, dim3 grid, bool wide, hipStream_t st)
+{
+    if (wide)
+        hipLaunchKernelGGL((es_pull_kernel<G, CH, VEC, ALIGNED, true, MAXC>), grid, dim3(kBlockThreads), 0, st, a, t.ptr,
+                           t.row, t.idx, t.slot, t.vals, t.rows);
+    else
+        hipLaunchKernelGGL((es_pull_kernel<G, CH, VEC, ALIGNED, false, MAXC>), grid, dim3(kBlockThreads), 0, st, a, t.ptr,
+                           t.row, t.idx, t.slot, t.vals, t.rows);
+}
+
+template <int G, int CH, int VEC, bool ALIGNED>
+hipError_t launch_pull(const Args& a, const PullGraph& t, dim3 grid, bool wide, bool filtered, bool long_columns,
+                       hipStream_t st)
+{
+    if constexpr (VEC == 4) {                              // rows of fewer than 4 columns are never filtered
+        if (filtered) {
+            const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(es_pull_filtered_kernel<G, CH, VEC, ALIGNED>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, kPullLdsBytes);
+            if (err != hipSuccess) return err;
+            const uint32_t lds = (uint32_t)(kPullTileBytes + (a.N + 7) / 8 * (int64_t)sizeof(uint32_t));
+            const int64_t blocks = (a.N + kPullWaves - 1) / kPullWaves;
+            const dim3 fgrid((uint32_t)(blocks < kComputeUnits ? blocks : kComputeUnits), grid.y);
+            hipLaunchKernelGGL((es_pull_filtered_kernel<G, CH, VEC, ALIGNED>), fgrid, dim3(kPullThreads), lds, st, a, t.ptr,
+                               t.row, t.slot, t.vals, t.rows);
+            return hipGetLastError();
+        }
+    }
+    if constexpr (pull_short_form<G, CH, ALIGNED>(true)) {
+        if (!long_columns && pull_short_form<G, CH, ALIGNED>(a.mode == ES_FASTRAND && a.seed != 0)) {
+            launch_pull_passes<G, CH, VEC, ALIGNED, kPullChunks>(a, t, grid, wide, st);
+            return hipGetLastError();
+        }
+    }
+    launch_pull_passes<G, CH, VEC, ALIGNED, 8>(a, t, grid, wide, st);
+    return hipGetLastError();
+}
 
 // Layout of the binned transposed product's workspace (es_bin_kernel.h); bytes == 0:
 // the scatter is the faster form, or this one does not apply.
@@ -1042,43 +1087,20 @@ int es_spmm_backward_pull(const int32_t* rowptr, const int32_t* t_ptr, const int
                            mode, seed, a.W, rows);
         if (hipGetLastError() != hipSuccess) return ES_ERR_LAUNCH;
     }
-    bool launched = false;
+    const PullGraph t = {t_ptr, t_row, t_idx, t_slot, t_vals, rows};
     const bool filtered = !wide && pull_filtered(N, nnz, F, W, mode, seed);
-    const uint32_t filter_lds = (uint32_t)(kPullTileBytes + (N + 7) / 8 * (int64_t)sizeof(uint32_t));
-    const int64_t filter_blocks = (N + kPullWaves - 1) / kPullWaves;
-    const dim3 filter_grid((uint32_t)(filter_blocks < kComputeUnits ? filter_blocks : kComputeUnits), (uint32_t)grid_y);
     const bool long_columns = nnz >= kPullLongColumn * N;
-#define ES_PULL_LAUNCH(G_, CH_, V_, A_, C_)                                                          \
-    if (wide)                                                                                        \
-        hipLaunchKernelGGL((es_pull_kernel<G_, CH_, V_, A_, true, C_>), grid, dim3(kBlockThreads), 0, st, a,    \
-                           t_ptr, t_row, t_idx, t_slot, t_vals, rows);                               \
-    else                                                                                             \
-        hipLaunchKernelGGL((es_pull_kernel<G_, CH_, V_, A_, false, C_>), grid, dim3(kBlockThreads), 0, st, a,   \
-                           t_ptr, t_row, t_idx, t_slot, t_vals, rows);
-#define ES_PULL(G_, CH_, V_, A_)                                                                     \
-    if (s.G == G_ && s.CH == CH_ && s.vec == V_ && s.aligned == A_) {                                \
-        if (filtered) {                                                                              \
-            if (hipFuncSetAttribute(reinterpret_cast<const void*>(es_pull_filtered_kernel<G_, CH_, V_, A_>),  \
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kPullLdsBytes) != hipSuccess) \
-                return ES_ERR_LAUNCH;                                                                \
-            hipLaunchKernelGGL((es_pull_filtered_kernel<G_, CH_, V_, A_>), filter_grid, dim3(kPullThreads),   \
-                               filter_lds, st, a, t_ptr, t_row, t_slot, t_vals, rows);               \
-        } else if (long_columns) {                                                                   \
-            ES_PULL_LAUNCH(G_, CH_, V_, A_, 8)                                                       \
-        } else {                                                                                     \
-            ES_PULL_LAUNCH(G_, CH_, V_, A_, 4)                                                       \
-        }                                                                                            \
-        launched = true;                                                                             \
-    }
+    hipError_t err = hipErrorInvalidValue;
+#define ES_PULL(G_, CH_, V_, A_)                                         \
+    if (s.G == G_ && s.CH == CH_ && s.vec == V_ && s.aligned == A_)      \
+        err = launch_pull<G_, CH_, V_, A_>(a, t, grid, wide, filtered, long_columns, st);
     ES_PULL(4, 1, 4, true) ES_PULL(8, 1, 4, true) ES_PULL(16, 1, 4, true) ES_PULL(32, 1, 4, true)
     ES_PULL(64, 1, 4, true) ES_PULL(64, 2, 4, true) ES_PULL(64, 4, 4, true)
     ES_PULL(4, 1, 4, false) ES_PULL(8, 1, 4, false) ES_PULL(16, 1, 4, false) ES_PULL(32, 1, 4, false)
     ES_PULL(64, 1, 4, false) ES_PULL(64, 2, 4, false) ES_PULL(64, 4, 4, false)
     ES_PULL(4, 1, 1, false)
 #undef ES_PULL
-#undef ES_PULL_LAUNCH
-    if (!launched) return ES_ERR_UNSUPPORTED;
-    return hipGetLastError() == hipSuccess ? ES_OK : ES_ERR_LAUNCH;
+    return err == hipSuccess ? ES_OK : ES_ERR_LAUNCH;
 }
 
 }  // extern "C"

@@ -804,6 +804,28 @@ def test_backward_pull_with_rows_bits_in_lds(es, F, W):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("F,ldx,rotated,unrotated", [
+    # chunks requested together where columns are short: 64 lanes stream (8) unless the short form has the waves for it
+    (16, 16, 4, 4), (41, 41, 4, 4), (127, 127, 4, 4), (128, 128, 4, 4), (131, 131, 4, 8), (256, 256, 8, 8), (256, 257, 4, 8), (301, 301, 4, 8),
+    (512, 512, 8, 8), (701, 701, 4, 4), (1000, 1000, 8, 8)])
+def test_backward_pull_passes(es, F, ldx, rotated, unrotated):
+    """Both forms of the pull's passes, by the mean column (96 entries) and the rows' alignment, against the oracle."""
+    import torch
+    import oracle
+    from gpu_util import DeviceCSR, check_Y
+    rowptr, colidx, vals, dY = _random_graph(700, 40.0, seed=F, F=F, ldx=ldx)
+    d = DeviceCSR(rowptr, colidx, vals, dY, F=F)
+    t = es.es_spmm_transpose_graph(d.rowptr, d.colidx, d.vals)
+    dX = torch.empty((d.N, F), dtype=torch.float32, device="cuda:0")
+    for mode, seed, short in (("fastrand", 7, rotated), ("fastrand", 0, unrotated), ("bucket", 7, unrotated)):
+        ref, den = oracle.spmm_backward(rowptr, colidx, vals, dY, F, 9, mode, seed, norm="mean")
+        for nnz, chunks in ((96 * d.N - 1, short), (96 * d.N, 8)):
+            dX.fill_(float("nan"))
+            taken = _kernels(lambda: _pull(es, d, t, dX, 9, mode, seed, "mean", nnz=nnz))
+            assert f", {chunks}>" in taken.split("es_pull_kernel")[1], (F, mode, seed, nnz, taken)
+            check_Y(dX.cpu().numpy(), ref, den, f"passes F={F} {mode} seed={seed} nnz={nnz}")
+
+
 @pytest.mark.parametrize("N", [1, 3, 8, 17, 4_097])
 def test_backward_pull_with_rows_bits_in_lds_on_few_rows(es, N):
     import torch
