@@ -361,12 +361,16 @@ bool pick_partition(int64_t N, double mean_kept, int32_t mode, int cols_per_bloc
 // Whether the exact product of rows that tile whole lines runs sliced on the flattened kernel although X is below
 // 0.3 GB: a slice of X is then of the order of an L2, or a community of its rows is.  32-column slices from 40 k to 140 k rows, where a
 // 64-column one outgrows an L2 (`32`), else 64-column ones (`64`), over whole rows on the row kernel, uniform ids / ids that cluster:
-//  * F = 64, 60 k x 40: `32` 0.86 / 0.87, x 100 0.83 / 0.94, x 130 0.81 / 1.03, 120 k x 100 0.93 / 0.83; 45 k x 100 0.86 / 1.04, 30 k x 40 1.08 / 1.02; 250 k x 40: `64` 1.04 /
-//    0.70, x 100 1.01 / 0.76, 500 k x 100 1.01 / 0.74
-//  * F = 128, 15 k x 100: `64` 0.88 / 1.13, 30 k x 40 0.82 / 0.94, x 100 0.77 / 0.94, x 160 0.76 / 1.00, 45 k x 40: `32` 0.74 / 1.01, x 100 0.68 / 0.95, 120 k x 100
-//    0.84 / 0.80, 250 k x 100: `64` 0.99 / 0.72; short rows: 60 k x 14: `64` 0.95 / 1.11, 120 k 0.96 / 0.97, 150 k 0.96 / 0.88, 500 k 1.00 / 0.76, x 6 1.1 / 1.4
-//  * F = 256, 8 k x 40: `64` 0.88 / 1.09, 15 k x 40 0.81 / 0.92, x 160 0.58 / 1.03, 30 k x 100 0.65 / 0.80, 60 k x 100: `32` 0.64 / 0.83, 250 k x 100: `64` 0.97 / 0.62,
-//    x 14 0.97 / 0.82
+//  * F = 96, 41 k - 140 k x 33 - 190: `32` 0.70 - 0.97 / 0.73 - 1.01
+//  * F = 128, 15 k x 100: `64` 0.88 / 1.13, 30 k x 40 - 190: 0.78 - 0.86 / 0.92 - 1.00, 41 k - 140 k x 33 - 190: `32` 0.65 - 0.93 / 0.77 - 1.01, 140 k - 600 k: `64`
+//    0.96 - 1.01 / 0.70 - 0.78; short rows, 60 k x 14: `64` 0.95 / 1.11, 100 k - 450 k x 11 - 29: 0.92 - 1.04 / 0.71 - 1.00, 500 k x 6 1.1 / 1.4
+//  * F = 160 and 256 to 512, 15 k - 40 k x 33 - 190: `64` 0.51 - 0.82 / 0.71 - 0.98, 41 k - 140 k: `32` 0.56 - 0.93 / 0.66 - 0.91, more: `64` 0.88 - 0.98 / 0.55 - 0.78;
+//    100 k and more x 11 - 29: `64` 0.85 - 0.96 / 0.61 - 0.93
+//  * F = 64 and 192, whose rows the row kernel gathers best, gain nothing from `64` on uniform ids beyond 100 k rows (1.00 - 1.08 / 0.63 - 0.90), so
+//    `32` there up to 200 k rows: 100 k - 140 k x 16 - 130 0.85 - 0.98 / 0.74 - 1.01, 155 k - 200 k x 16 - 130 0.93 - 1.01 / 0.73 - 0.90; beyond, F = 64 x 80 and more `64`
+//    0.99 - 1.02 / 0.70 - 0.77 (x 66: 1.04), F = 192 x 64 and more up to 0.2 GB `32` 0.99 - 1.02 / 0.71 - 0.77 (`64`
+//    1.02 - 1.04 / 0.63 - 0.67; x 40 - 50 `32` 1.00 - 1.05; 0.23 GB 1.03 / 0.71)
+//    F = 64, 59 k x 140: 0.82 / 1.03
 // Longer rows are where column ranges begin (pick_partition).  Rows that tile no line pay for every line twice (F = 100: 1.2 - 1.5),
 // and sampled rows of ids that cluster 1.2 - 2.2 (F = 128).
 // 64-column slices have to tile the row (F = 160, 104 k x 14: 1.18, F = 96, 39 k x 100: 1.12); short rows of uniform ids pay for large tables
@@ -375,8 +379,13 @@ int slice_exact(int64_t N, double mean, int32_t mode, int F, double table)
 {
     if (mode != ES_FULL || F % 32 != 0 || F < 64 || table < 15.0e6 || table >= 300.0e6) return 0;
     if (mean >= (F == 64 ? 150.0 : 200.0)) return 0;
-    if (mean >= 32.0 && N >= 40000 && N <= 140000) return 8;
-    if (F % 64 != 0 || mean < (F == 64 && N > 140000 ? 64.0 : N >= 100000 ? 10.0 : 32.0)) return 0;
+    const bool narrow_gain = F == 64 || F == 192;
+    if (N >= 40000 && N <= (narrow_gain ? 200000 : 140000) && mean >= (narrow_gain && N >= 100000 ? 16.0 : 32.0)) return 8;
+    if (narrow_gain && N >= 100000) {
+        if (N <= 200000) return 0;
+        return F == 64 ? (mean >= 80.0 ? 16 : 0) : (mean >= 64.0 && table < 200.0e6 ? 8 : 0);
+    }
+    if (F % 64 != 0 || mean < (N >= 100000 ? 10.0 : 32.0)) return 0;
     return mean < 32.0 && table >= 250.0e6 ? 0 : 16;
 }
 

@@ -182,6 +182,20 @@ def test_exact_slices_of_middling_tables(N, mean, F, lanes):
     assert es.es_spmm_launch_info(N, N * mean, F, 0, "full", aligned16=False)["flattened"] == 0
 
 
+@pytest.mark.parametrize("N,mean,F,lanes,flattened", [
+    # F = 64 takes 16 lanes on the row kernel and in 64-column slices alike: which of the two runs is asked for too
+    (58_593, 40, 64, 16, 0), (58_594, 31, 64, 16, 0), (58_594, 32, 64, 8, 1), (58_594, 150, 64, 16, 0), (99_999, 31, 64, 16, 0),
+    (100_000, 15, 64, 16, 0), (100_000, 16, 64, 8, 1), (200_000, 15, 64, 16, 0), (200_000, 16, 64, 8, 1), (200_000, 127, 64, 8, 1),
+    (200_001, 63, 64, 16, 0), (200_001, 64, 64, 16, 0), (200_001, 79, 64, 16, 0), (200_001, 80, 64, 16, 1),
+    (39_999, 32, 192, 16, 1), (40_000, 32, 192, 8, 1), (99_999, 31, 192, 64, 0), (100_000, 15, 192, 64, 0), (100_000, 16, 192, 8, 1),
+    (200_000, 16, 192, 8, 1), (200_001, 63, 192, 64, 0), (200_001, 64, 192, 8, 1), (260_416, 64, 192, 8, 1), (260_417, 64, 192, 64, 0),
+    (29_296, 40, 128, 32, 0), (29_297, 40, 128, 16, 1), (40_000, 40, 128, 8, 1), (140_001, 40, 128, 16, 1), (100_000, 9, 128, 32, 0),
+    (99_999, 31, 256, 64, 0), (100_000, 10, 256, 16, 1), (140_001, 40, 320, 16, 1), (140_001, 40, 96, 32, 0)])
+def test_exact_slices_and_the_kernel_that_runs_them(N, mean, F, lanes, flattened):
+    info = es.es_spmm_launch_info(N, N * mean, F, 0, "full")
+    assert (info["column_ranges"], info["lanes_per_row"], info["flattened"]) == (1, lanes, flattened)
+
+
 def test_flattened_kernel_choice():
     """Without options the flattened kernel runs where narrow column slices pay:
     the partitioned product once a 64-column share outgrows an L2, and tables of
