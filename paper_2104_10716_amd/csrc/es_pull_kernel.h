@@ -115,21 +115,28 @@ constexpr int kPullChunks = 4;                        // chunks of 64 entries re
 // stage 2 is the forward kernel's gather.
 // MAXC: chunks of 64 entries requested together at most.  Long columns (8) stream: a pass loads all of its chunks without a
 // branch, an absent entry as the column's first.  Short ones (4) wait for one round trip after another: six waves per SIMD
-// (five with 64-bit keys, five to three on 64 lanes, below which the form spills, and a spill costs 1.1 to 1.6 times
-// the time), one chunk where that holds the column, and only entries that are there are loaded.  The latter on long columns: 50 k
-// rows of mean 300, F = 32, Bucket W = 8: 33.7 us, 44.3 with it.
+// (five with 64-bit keys, five to three where a lane holds several chunks of columns, below which the form spills, and a spill costs 1.1 to 1.6
+// times the time), one chunk where that holds the column, and only entries that are there are loaded.  The latter on long columns:
+// 50 k rows of mean 300, F = 32, Bucket W = 8: 33.7 us, 44.3 with it.
 // The two are written out, for one body with both needs 80 to 128 registers where the streaming form of 64 lanes has 72.
-// Always 8 / the short form, mean of less than 96 entries, over 17 graphs of 3 k to 1 M rows: 4 to 32 lanes, F = 3 to 128, 0.59 - 1.03 of
-// the time (uniform ids of mean 20, F = 100: the 1.03); 20 k rows of mean 4.5, F = 32: 17.5 / 11.8 us, 170 k of mean 14, F =
-// 128: 133 / 110, 1 M of mean 50, ids that cluster, Bucket W = 32, F = 64: 999 / 727.  64 lanes have fewer waves for it: rows that are
-// not aligned, rotated, 0.84 - 1.02 (F = 131 to 701), four chunks per lane 0.95 - 1.01; else 0.93 - 1.06 (F = 131, 170 k of mean 14, no
-// rotation 117.5 / 123.4, 40 k of mean 90, ids that cluster 41.1 / 43.8), aligned 0.95 - 1.06 (F = 256, 170 k of mean 14: 174.9 / 180.6), so
-// those stream.
+// Time over that of always 8, mean of less than 96 entries, 60 graphs of 3 k to 1 M rows: 4 to 16 lanes (F up to 64), the column's number in a
+// scalar register, 0.57 - 1.03 (in a vector register, with six waves where this has seven, 0.59 - 1.07: 235 k rows of mean 82, F = 20, W = 22
+// 149 / 159 us); 20 k rows of mean 4.5, F = 32: 17.5 / 11.8 us, 170 k of mean 14, F = 128: 133 / 110, 1 M of mean 50, ids that cluster, Bucket W = 32,
+// F = 64: 999 / 727.  32 lanes, the number in a vector register: 0.76 - 1.04, uniform ids of mean 20 and more 0.93 - 1.04 (a seventh wave would cost them
+// 1 - 2 % of L2 hits).  64 lanes:
+//  * not aligned, one chunk of columns per lane, the number in a scalar register (76 vector registers; 98 without, 0.79 - 1.07): 0.76 - 1.02
+//  * aligned, one chunk: rows looked up for the kept entries alone, or a mean of at most 12: ids that cluster 0.79 - 0.99, uniform ones 0.79 -
+//    1.06 (F = 200 to 256, mean 8 to 30); else 0.93 - 1.04: those stream
+//  * more chunks, aligned: mean of at most 12, 0.83 - 1.00, else 0.95 - 1.06: those stream; not aligned, four 0.95 - 1.01, two rotated 0.93 - 1.01, not
+//    rotated 0.93 - 1.09: those stream
 template <int G, int CH, bool ALIGNED>
-__host__ __device__ constexpr bool pull_short_form(bool rotated) { return G < 64 || (!ALIGNED && (rotated || CH == 4)); }
+__host__ __device__ constexpr bool pull_short_form(bool rotated, bool rows, bool few)
+{
+    return G < 64 || (ALIGNED ? few || (CH == 1 && rows) : CH != 2 || rotated);
+}
 
 template <int G, int CH, int VEC, bool ALIGNED, bool WIDE, int MAXC>
-__global__ void __launch_bounds__(kBlockThreads, MAXC == 8 ? 0 : G < 64 ? 6 - WIDE : CH == 1 ? 5 : CH == 2 ? 4 : 3)
+__global__ void __launch_bounds__(kBlockThreads, MAXC == 8 ? 0 : G < 64 ? 6 - WIDE : (CH == 1 ? 6 : CH == 2 ? 5 : 4) - (CH > 1 && !ALIGNED))
 es_pull_kernel(const Args a, const int32_t* __restrict__ t_ptr, const int32_t* __restrict__ t_row,
                const int32_t* __restrict__ t_idx, const int32_t* __restrict__ t_slot,
                const float* __restrict__ t_vals, const int2* __restrict__ rows)
@@ -146,7 +153,8 @@ es_pull_kernel(const Args a, const int32_t* __restrict__ t_ptr, const int32_t* _
     const uint32_t vb = blockIdx.x;
     if (vb >= a.nblocks) return;
     const int lane = threadIdx.x & (kWaveSize - 1);
-    const int wave = threadIdx.x >> 6;
+    int wave = threadIdx.x >> 6;
+    if constexpr (MAXC != 8 && (G <= 16 || (G == 64 && CH == 1 && !ALIGNED))) wave = __builtin_amdgcn_readfirstlane(wave);
     const int e = lane >> LOG_G;
     const int l = lane & (G - 1);
     uint2* tile = lds + wave * kWaveTileStride;

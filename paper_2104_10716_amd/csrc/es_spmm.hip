@@ -655,16 +655,19 @@ int build_transposed(const int32_t* rowptr, const int32_t* colidx, const float* 
 // cost another one) few, and the lookups' table beyond what an L2 serves also where ids cluster, which sizes do not
 // show.  Time over that of es_pull_kernel, uniform ids / ids that cluster, 0.11 gathered <= mean unless said:
 //  * 8 to 50 M entries: 0.61 - 1.06 / 0.85 - 1.38 (40 k rows of mean 310: 1.15 - 1.36, 60 k of 290: 0.96 - 1.36, 100 k of 268: 0.93 - 1.19,
-//    150 k of 264: 0.87 - 1.14), so never, though 90 k uniform rows of mean 485 would take 0.61 - 0.84
+//    150 k of 264: 0.87 - 1.14)
 //  * from 50 M on, mean 257 to 280: 0.73 - 0.99 / 0.81 - 1.05, 281 to 300: 0.77 - 0.96 / 0.80 - 1.01; 300 to 370, ids that cluster, gathered up to 6
 //    a mean entry 0.76 - 1.00, 6 to 9.1 0.81 - 1.05; 370 and more 0.61 - 0.95 / 0.73 - 1.00; gathered 9.1 to 12 a mean entry 0.80 - 1.11 / 0.87 - 1.12
 //    whatever the mean, more 0.83 - 1.14 / 0.96 - 1.14
-//  * F = 3: 0.77 - 1.08; where the lines below hold, F = 8: 0.64 - 1.01, F = 16 to 1300 0.61 - 0.98 (1344 calls)
+//  * fewer entries where the mean row is 400 and more, gathered at most 6 a mean entry: 70 k to 110 k rows 0.58 - 0.84 / 0.71 - 1.00 (the ids in 10, 24, 40 or 64
+//    blocks); 60 k up to 1.02, 40 k up to 1.17
+//  * F = 3: 0.77 - 1.08; where the lines below hold, F = 8: 0.64 - 1.01, F = 16 to 1300 0.58 - 1.00 (1600 calls)
 bool pull_filtered(int64_t N, int64_t nnz, int32_t F, int32_t W, int32_t mode, uint64_t seed)
 {
-    if (mode != ES_FASTRAND || seed == 0 || N > kPullFilterRows || F < 8 || nnz < 50000000) return false;
+    if (mode != ES_FASTRAND || seed == 0 || N > kPullFilterRows || F < 8) return false;
     const double mean = (double)nnz / (double)N;
     const double gathered = (mean < W ? mean : W) * (F % 32 ? (double)F + 31.0 : (double)F);
+    if (nnz < 50000000) return N >= 70000 && mean >= 400.0 && gathered <= 6.0 * mean;
     return gathered <= 28.0 * (mean - 270.0) && 0.11 * gathered <= mean;
 }
 
@@ -690,8 +693,7 @@ void launch_pull_passes(const Args& a, const PullGraph& t, dim3 grid, bool wide,
 }
 
 template <int G, int CH, int VEC, bool ALIGNED>
-hipError_t launch_pull(const Args& a, const PullGraph& t, dim3 grid, bool wide, bool filtered, bool long_columns,
-                       hipStream_t st)
+hipError_t launch_pull(const Args& a, const PullGraph& t, dim3 grid, int64_t nnz, bool wide, bool filtered, hipStream_t st)
 {
     if constexpr (VEC == 4) {                              // rows of fewer than 4 columns are never filtered
         if (filtered) {
@@ -706,13 +708,12 @@ hipError_t launch_pull(const Args& a, const PullGraph& t, dim3 grid, bool wide, 
             return hipGetLastError();
         }
     }
-    if constexpr (pull_short_form<G, CH, ALIGNED>(true)) {
-        if (!long_columns && pull_short_form<G, CH, ALIGNED>(a.mode == ES_FASTRAND && a.seed != 0)) {
-            launch_pull_passes<G, CH, VEC, ALIGNED, kPullChunks>(a, t, grid, wide, st);
-            return hipGetLastError();
-        }
-    }
-    launch_pull_passes<G, CH, VEC, ALIGNED, 8>(a, t, grid, wide, st);
+    const bool rotated = a.mode == ES_FASTRAND && a.seed != 0;
+    if (nnz < kPullLongColumn * a.N &&
+        pull_short_form<G, CH, ALIGNED>(rotated, pull_needs_rows(a.mode, a.seed, a.norm), nnz <= 12 * a.N))
+        launch_pull_passes<G, CH, VEC, ALIGNED, kPullChunks>(a, t, grid, wide, st);
+    else
+        launch_pull_passes<G, CH, VEC, ALIGNED, 8>(a, t, grid, wide, st);
     return hipGetLastError();
 }
 
@@ -1098,11 +1099,10 @@ int es_spmm_backward_pull(const int32_t* rowptr, const int32_t* t_ptr, const int
     }
     const PullGraph t = {t_ptr, t_row, t_idx, t_slot, t_vals, rows};
     const bool filtered = !wide && pull_filtered(N, nnz, F, W, mode, seed);
-    const bool long_columns = nnz >= kPullLongColumn * N;
     hipError_t err = hipErrorInvalidValue;
 #define ES_PULL(G_, CH_, V_, A_)                                         \
     if (s.G == G_ && s.CH == CH_ && s.vec == V_ && s.aligned == A_)      \
-        err = launch_pull<G_, CH_, V_, A_>(a, t, grid, wide, filtered, long_columns, st);
+        err = launch_pull<G_, CH_, V_, A_>(a, t, grid, nnz, wide, filtered, st);
     ES_PULL(4, 1, 4, true) ES_PULL(8, 1, 4, true) ES_PULL(16, 1, 4, true) ES_PULL(32, 1, 4, true)
     ES_PULL(64, 1, 4, true) ES_PULL(64, 2, 4, true) ES_PULL(64, 4, 4, true)
     ES_PULL(4, 1, 4, false) ES_PULL(8, 1, 4, false) ES_PULL(16, 1, 4, false) ES_PULL(32, 1, 4, false)

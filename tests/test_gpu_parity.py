@@ -806,7 +806,7 @@ def test_backward_pull_with_rows_bits_in_lds(es, F, W):
 
 @pytest.mark.parametrize("F,ldx,rotated,unrotated", [
     # chunks requested together where columns are short: 64 lanes stream (8) unless the short form has the waves for it
-    (16, 16, 4, 4), (41, 41, 4, 4), (127, 127, 4, 4), (128, 128, 4, 4), (131, 131, 4, 8), (256, 256, 8, 8), (256, 257, 4, 8), (301, 301, 4, 8),
+    (16, 16, 4, 4), (41, 41, 4, 4), (127, 127, 4, 4), (128, 128, 4, 4), (131, 131, 4, 4), (256, 256, 4, 8), (256, 257, 4, 4), (301, 301, 4, 8),
     (512, 512, 8, 8), (701, 701, 4, 4), (1000, 1000, 8, 8)])
 def test_backward_pull_passes(es, F, ldx, rotated, unrotated):
     """Both forms of the pull's passes, by the mean column (96 entries) and the rows' alignment, against the oracle."""
@@ -817,11 +817,12 @@ def test_backward_pull_passes(es, F, ldx, rotated, unrotated):
     d = DeviceCSR(rowptr, colidx, vals, dY, F=F)
     t = es.es_spmm_transpose_graph(d.rowptr, d.colidx, d.vals)
     dX = torch.empty((d.N, F), dtype=torch.float32, device="cuda:0")
-    for mode, seed, short in (("fastrand", 7, rotated), ("fastrand", 0, unrotated), ("bucket", 7, unrotated)):
-        ref, den = oracle.spmm_backward(rowptr, colidx, vals, dY, F, 9, mode, seed, norm="mean")
-        for nnz, chunks in ((96 * d.N - 1, short), (96 * d.N, 8)):
+    for mode, seed, norm, short in (("fastrand", 7, "mean", rotated), ("fastrand", 0, "none", unrotated), ("bucket", 7, "none", unrotated),
+                                    ("bucket", 0, "mean", 4 if ldx == 256 else unrotated)):      # row factors are looked up too
+        ref, den = oracle.spmm_backward(rowptr, colidx, vals, dY, F, 9, mode, seed, norm=norm)
+        for nnz, chunks in ((12 * d.N, 8 if F == 301 and short == 8 else 4), (12 * d.N + 1, short), (96 * d.N - 1, short), (96 * d.N, 8)):
             dX.fill_(float("nan"))
-            taken = _kernels(lambda: _pull(es, d, t, dX, 9, mode, seed, "mean", nnz=nnz))
+            taken = _kernels(lambda: _pull(es, d, t, dX, 9, mode, seed, norm, nnz=nnz))
             assert f", {chunks}>" in taken.split("es_pull_kernel")[1], (F, mode, seed, nnz, taken)
             check_Y(dX.cpu().numpy(), ref, den, f"passes F={F} {mode} seed={seed} nnz={nnz}")
 
@@ -853,6 +854,8 @@ def test_backward_pull_with_rows_bits_in_lds_on_few_rows(es, N):
     # 50 M entries; fewer were 1.05 to 1.36 times as slow where ids cluster
     (150_000, 50_000_000, 64, 16, "fastrand", 7, True), (150_000, 49_999_999, 64, 16, "fastrand", 7, False),
     (40_000, 12_400_000, 16, 20, "fastrand", 7, False), (100_000, 33_900_000, 32, 16, "fastrand", 7, False),
+    (70_000, 28_000_000, 64, 37, "fastrand", 7, True), (70_000, 28_000_000, 64, 38, "fastrand", 7, False),
+    (70_000, 27_999_999, 64, 16, "fastrand", 7, False), (69_999, 30_000_000, 64, 16, "fastrand", 7, False),
     # gathered columns: 28 a mean entry above 270, and the mean over 0.11
     (200_000, 60_000_000, 16, 17, "fastrand", 7, True), (200_000, 60_000_000, 16, 18, "fastrand", 7, False),
     (200_000, 56_000_000, 64, 16, "fastrand", 7, False),
