@@ -435,6 +435,44 @@ def test_flattened_kernel_absent_entries_multiply_nothing(es, F, lanes, ld):
         assert np.abs(Y[fine] - ref[fine]).max() <= 1e-5 * 40      # at most 39 terms of magnitude 1.5
 
 
+@pytest.mark.parametrize("F,lanes", [(16, 0), (64, 8), (128, 0), (41, 0)])
+@pytest.mark.parametrize("n,ld", [(60, 0), (508, 1 << 21), (509, 1 << 21)])
+def test_flattened_kernel_strided_rows_and_offsets_up_to_4_gb(es, F, lanes, n, ld):
+    """FastRand's strided entries beside absent ones, with infinities in X; 508 rows 8 MiB apart are the largest table that is
+    addressed by 32-bit byte offsets (4.26 GB, most of them beyond 2 GiB), one more takes the 64-bit form."""
+    import torch
+    import oracle
+    from gpu_util import DeviceCSR
+    rng = np.random.default_rng(F + lanes + n)
+    lengths = rng.permutation(np.concatenate([np.arange(0, 40), rng.integers(1, 50, n - 40)]))
+    cols = [np.sort(rng.choice(n, size=int(L), replace=False)) for L in lengths]
+    rowptr = np.zeros(n + 1, dtype=np.int32)
+    rowptr[1:] = np.cumsum(lengths)
+    colidx = np.concatenate(cols).astype(np.int32)
+    assert (colidx >= 0.95 * n).any()
+    vals = rng.uniform(0.5, 1.5, colidx.size).astype(np.float32)
+    X = rng.uniform(-1, 1, (n, F)).astype(np.float32)
+    X[7], X[31, ::2], X[n - 1, 1::3], X[0, 3] = np.inf, -np.inf, np.nan, np.inf
+    d = DeviceCSR(rowptr, colidx, vals, X)
+    if ld:
+        wide = torch.empty((n - 1) * ld + F, dtype=torch.float32, device="cuda:0").as_strided((n, F), (ld, 1))
+        wide.copy_(d.X)
+        d.X, d.F = wide, F
+    for mode, W, seed in (("full", 0, 0), ("bucket", 9, 0), ("fastrand", 9, 0), ("fastrand", 13, 2 ** 63 + 5)):
+        ref = np.zeros((n, F))
+        kept = (np.stack([np.arange(rowptr[-1]), np.repeat(np.arange(n), lengths)], axis=1).tolist() if mode == "full" else
+                [(q, r) for r, row in enumerate(oracle.kept(rowptr, W, mode, seed)[0].reshape(n, W)) for q in row if q >= 0])
+        with np.errstate(invalid="ignore"):
+            for q, r in kept:
+                ref[r] += float(vals[q]) * X[colidx[q]].astype(np.float64)
+        opts = dict(kernel=2, **(dict(lanes_per_row=lanes) if lanes else {}))
+        Y = d.run(W, mode, seed, opts=opts).cpu().numpy()
+        for name, pick in (("nan", np.isnan), ("+inf", np.isposinf), ("-inf", np.isneginf)):
+            assert np.array_equal(pick(Y), pick(ref)), f"{name} F={F} n={n} {mode} W={W} seed={seed}"
+        fine = np.isfinite(ref)
+        assert np.abs(Y[fine] - ref[fine]).max() <= 1e-5 * 50      # at most 49 terms of magnitude 1.5
+
+
 @pytest.mark.parametrize("F,lanes", [(16, 0), (64, 8), (64, 0), (128, 0), (256, 0), (41, 0)])
 def test_flattened_kernel_bursts_and_shares(es, F, lanes):
     """The flattened kernel around the sizes a workgroup counts in: bursts of 1536
