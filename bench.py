@@ -742,12 +742,16 @@ def backward_table(dw, dev, cases):
         idx, val = idx[:kept], val[:kept]
         t_pull = _time_fn(lambda: es.es_spmm(ptr, idx, val, dw.X, dX, 0, "full", F=dw.F))
         t_inv = _time_fn(lambda: es.es_spmm_backward_pull(dw.rowptr, tg, dw.X, dX, W, mode, 0, F=dw.F))
+        t_seed = (_time_fn(lambda: es.es_spmm_backward_pull(dw.rowptr, tg, dw.X, dX, W, mode, 7, F=dw.F))
+                  if mode == "fastrand" else None)             # a rotation per row, as in training
         out["rows"].append({"mode": mode, "W": W, "forward_ms": round(t_fwd, 4),
                             "backward_pull_ms": round(t_inv, 4),
+                            "backward_pull_seeded_ms": None if t_seed is None else round(t_seed, 4),
                             "backward_ms": round(t_bwd, 4), "backward_atomic_ms": round(t_atomic, 4),
                             "sampled_transpose_build_ms": round(t_build, 4),
                             "full_product_on_sampled_transpose_ms": round(t_pull, 4)})
-        log(f"  backward {mode:8s} W={W:3d}: pull over the transposed graph {t_inv:.3f} ms | through a workspace "
+        seeded = "" if t_seed is None else f" (seed 7: {t_seed:.3f} ms)"
+        log(f"  backward {mode:8s} W={W:3d}: pull over the transposed graph {t_inv:.3f} ms{seeded} | through a workspace "
             f"{t_bwd:.3f} ms | atomic scatter {t_atomic:.3f} ms | sampled transpose build {t_build:.3f} ms + product on "
             f"it {t_pull:.3f} ms | "
             f"forward {t_fwd:.3f} ms")

@@ -2,8 +2,6 @@
 #ifndef ES_SPMM_FLAT_KERNEL_H
 #define ES_SPMM_FLAT_KERNEL_H
 
-#include <type_traits>
-
 #include "es_fused_kernel.h"
 
 namespace {
@@ -40,9 +38,11 @@ namespace {
 // Tried and slower: entries kept in registers and handed to the slots by DPP, a row's 64 at a time (2.83 ms: short
 // pieces fill a quarter of the lanes), non-temporal loads for rows of X far from the row's own index (9 - 20 % fewer L2
 // misses, 4 - 15 % slower), seven or eight waves per SIMD with bursts of 512 or 1024 (2.26, 2.44 ms).
-// Tried and slower on the former: entries copied into LDS by the load itself (dword
+// Tried and slower on the form with permuted loads (2.17 ms): entries copied into LDS by the load itself (dword
 // copies: 2.9 ms), a pass of 64 entries per row streamed two passes ahead (2.6 ms), 16
 // column ranges (3.2 ms), two batches of gathers in flight per wave (spills or 12 waves).
+// The 64-bit form branches round absent entries' gathers; over permuted loads that multiplied padding: 0.985 - 1.005 of the
+// time (1.1 to 2.45 M rows, F = 128 to 448 at row stride 1024, exact and sampled: 2.45 M, F = 128 7302 / 7301, FastRand W = 64 3564 / 3533 us).
 // ---------------------------------------------------------------------------
 constexpr int kFlatMaxRows = 64;                      // rows of a workgroup's run at most: one per lane
 constexpr int kFlatBlockMin = 8;                      // smallest unit a row is padded to
@@ -58,7 +58,7 @@ struct FlatLds {
     static constexpr int FB = 4 * G;                  // feature columns per block
     static constexpr int ROWS = flat_rows(G, RPS);    // rows of the run
     static constexpr int CAP = RPS == 1 ? 1536 : 2048;   // entries staged in one burst: about the run's mean, six or four workgroups per compute unit
-    uint32_t key[CAP];                           // staged entries' rows of X (FlatRows), in the order the slots read them
+    uint32_t key[CAP];                           // staged entries' rows of X (kFlatAbsent), in the order the slots read them
     float val[CAP];
     float rowsum[ROWS * FB];                     // [row][FB]
     float head[kWavesPerBlock * FB];                  // per wave: partial sum of a row that began in an earlier wave's share
