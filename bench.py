@@ -372,6 +372,7 @@ def calibrate_gather(dev):
     import torch
     import paper_2104_10716_amd as es
     deg = 64
+    whole = dict(lanes_per_row=-1, kernel=1)           # whole rows at a time, whatever the rule would slice
     out = []
     g = torch.Generator(device=dev)
     g.manual_seed(99)
@@ -389,7 +390,7 @@ def calibrate_gather(dev):
                     owner = (torch.arange(N, device=dev) // share).clamp(max=7).repeat_interleave(deg)
                     cols = owner * share + cols % share
                 cols = cols.to(torch.int32)
-                t = _time_fn(lambda: es.es_spmm(rowptr, cols, None, X, Y, 0, "full"), reps=5, warm=2)
+                t = _time_fn(lambda: es.es_spmm_ex(rowptr, cols, None, X, Y, 0, "full", opts=whole), reps=5, warm=2)
                 row[kind + "_GBps"] = round(algorithmic_bytes(N, N * deg, F) / (t * 1e6), 1)
                 del cols
             out.append(row)
