@@ -94,10 +94,6 @@ __global__ void __launch_bounds__(kBinLocalRows) es_bin_local_kernel(const BinAr
     const int tid = threadIdx.x;
     for (int b = tid; b <= a.nbins; b += kBinLocalRows) counter[b] = 0;
     const int64_t r_begin = a.N * blockIdx.x / a.walkers, r_end = a.N * (blockIdx.x + 1) / a.walkers;
-    // The walker's own records: what the rows before a row keep is at most what they store and W each, and so
-    // is what the walker's rows keep between the two ends.  (An nnz below rowptr[N] cuts entries off.)
-    const auto piece = [&](int64_t row) { return (int32_t)max((int64_t)0, min(min((int64_t)a.rowptr[row], row * a.W), a.capacity)); };
-    const int32_t own = piece(r_begin), room = max(0, piece(r_end) - own);
     const int64_t r = r_begin + tid;
     int32_t k = 0;
     if (r < r_end) {
@@ -113,8 +109,11 @@ __global__ void __launch_bounds__(kBinLocalRows) es_bin_local_kernel(const BinAr
     }
     int32_t total;
     first[tid] = block_scan<kBinLocalRows>(k, wave_total, total) - k;
-    total = min(total, room);
     __syncthreads();
+    // The walker's own records begin where those of the rows before it can end at most, rowptr[r] or W for each of
+    // them, and end where the next walker's begin.  (An nnz below rowptr[N] cuts entries off.)
+    const int32_t own = (int32_t)max((int64_t)0, min(min((int64_t)src[0], r_begin * a.W), a.capacity));
+    total = (int32_t)min((int64_t)total, a.capacity - own);
     // this thread's entries: row and column inside the block, value; block | rank << 12
     uint32_t key[kBinLocalPer], place[kBinLocalPer];
     float val[kBinLocalPer];
