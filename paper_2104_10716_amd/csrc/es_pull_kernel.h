@@ -122,8 +122,8 @@ constexpr int kPullChunks = 4;                        // chunks of 64 entries re
 // Time over that of always 8, mean of less than 96 entries, 60 graphs of 3 k to 1 M rows: 4 to 16 lanes (F up to 64), the column's number in a
 // scalar register, 0.57 - 1.03 (in a vector register, with six waves where this has seven, 0.59 - 1.07: 235 k rows of mean 82, F = 20, W = 22
 // 149 / 159 us); 20 k rows of mean 4.5, F = 32: 17.5 / 11.8 us, 170 k of mean 14, F = 128: 133 / 110, 1 M of mean 50, ids that cluster, Bucket W = 32,
-// F = 64: 999 / 727.  32 lanes, the number in a vector register: 0.76 - 1.04, uniform ids of mean 20 and more 0.93 - 1.04 (a seventh wave would cost them
-// 1 - 2 % of L2 hits).  64 lanes:
+// F = 64: 999 / 727.  32 lanes, the number in a vector register: 0.76 - 1.05, uniform ids of mean 20 and more 0.93 - 1.05 (in a scalar one, with seven waves,
+// up to 2 % more of them).  64 lanes:
 //  * not aligned, one chunk of columns per lane, the number in a scalar register (76 vector registers; 98 without, 0.79 - 1.07): 0.76 - 1.02
 //  * aligned, one chunk: rows looked up for the kept entries alone, or a mean of at most 12: ids that cluster 0.79 - 0.99, uniform ones 0.79 -
 //    1.06 (F = 200 to 256, mean 8 to 30); else 0.93 - 1.04: those stream
